@@ -13,6 +13,7 @@ typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
 // Operand-to-lane maps on a 64-lane wave (lane = 16*g + c for the 16-wide shapes).
@@ -93,6 +94,36 @@ __device__ __forceinline__ half8 load8_clamp(const half_t* __restrict__ row, int
     return r;
 }
 
+// Border windows.  Eight pixels from column xs on, part of them outside the row, are loaded from the
+// nearest column that keeps the load inside (xs - d) and moved afterwards, in registers: one 16-byte
+// load where a pixel-by-pixel load with clamped columns takes eight.  Element i becomes element
+// min(i + d, 7) of the loaded run, d >= 0 (what lies past the last pixel repeats it) ...
+__device__ __forceinline__ half8 shift_in_from_right(half8 v, int d) {
+    u32x4 a = __builtin_bit_cast(u32x4, v);
+    const uint32_t t = (a[3] & 0xffff0000u) | (a[3] >> 16);
+    const u32x4 s8 = {t, t, t, t}, s4 = {a[2], a[3], t, t};
+    a = d >= 8 ? s8 : (d & 4) ? s4 : a;
+    const u32x4 s2 = {a[1], a[2], a[3], t};
+    a = (d & 2) && d < 8 ? s2 : a;
+    const u32x4 s1 = {__builtin_amdgcn_alignbit(a[1], a[0], 16), __builtin_amdgcn_alignbit(a[2], a[1], 16),
+                      __builtin_amdgcn_alignbit(a[3], a[2], 16), t};
+    a = (d & 1) && d < 8 ? s1 : a;
+    return __builtin_bit_cast(half8, a);
+}
+// ... or element max(i - d, 0) (what lies left of pixel 0 repeats it).
+__device__ __forceinline__ half8 shift_in_from_left(half8 v, int d) {
+    u32x4 a = __builtin_bit_cast(u32x4, v);
+    const uint32_t t = (a[0] << 16) | (a[0] & 0xffffu);
+    const u32x4 s8 = {t, t, t, t}, s4 = {t, t, a[0], a[1]};
+    a = d >= 8 ? s8 : (d & 4) ? s4 : a;
+    const u32x4 s2 = {t, a[0], a[1], a[2]};
+    a = (d & 2) && d < 8 ? s2 : a;
+    const u32x4 s1 = {t, __builtin_amdgcn_alignbit(a[1], a[0], 16), __builtin_amdgcn_alignbit(a[2], a[1], 16),
+                      __builtin_amdgcn_alignbit(a[3], a[2], 16)};
+    a = (d & 1) && d < 8 ? s1 : a;
+    return __builtin_bit_cast(half8, a);
+}
+
 // Four consecutive pixels row[xs .. xs+3], clamped like load8_clamp.
 __device__ __forceinline__ half4 load4_clamp(const half_t* __restrict__ row, int xs, int W) {
     if (xs >= 0 && xs + 4 <= W) {
@@ -170,6 +201,45 @@ __device__ __forceinline__ void store_rows_via_lds(float* patch, float* dst, uin
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
+}
+
+// LDS traffic inside one wave: what the wave wrote is there for its own lanes (LDS serves one wave's
+// instructions in order); only the compiler has to be kept from reordering.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// store_rows_via_lds for a tile group at the image border: only rows < rows and columns < cols are
+// stored, still as runs of one row per 4 NW lanes.
+template <int NW, bool STREAM>
+__device__ __forceinline__ void store_rows_via_lds_masked(float* patch, float* dst, int64_t pitch_elems,
+                                                          const floatx4 (&acc)[NW], int lane, int rows, int cols) {
+    const int c = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int w = 0; w < NW; ++w)
+        *reinterpret_cast<floatx4*>(patch + c * RowPatch<NW>::kPitch + 16 * w + 4 * g) = acc[w];
+    wave_lds_fence();
+    constexpr int kLanesPerRow = 4 * NW, kRowsPerPass = 64 / kLanesPerRow;
+    const int rr = lane / kLanesPerRow, x = 4 * (lane - rr * kLanesPerRow);
+#pragma unroll
+    for (int s = 0; s < 16 / kRowsPerPass; ++s) {
+        const int row = s * kRowsPerPass + rr;
+        const floatx4 v = *reinterpret_cast<const floatx4*>(patch + row * RowPatch<NW>::kPitch + x);
+        if (row < rows) {
+            float* q = dst + (int64_t)row * pitch_elems + x;
+            if (x + 4 <= cols) {
+                if (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<floatx4_u*>(q));
+                else *reinterpret_cast<floatx4_u*>(q) = v;
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (x + i < cols) q[i] = v[i];
+            }
+        }
+    }
+    wave_lds_fence();
 }
 
 // Workgroups are handed to the 8 XCDs (each with its own L2) round-robin by workgroup id.

@@ -1,47 +1,27 @@
-// hb_pyr_level: one Laplacian-pyramid level (2x down, 2x up, residual) as four chained
-// products with strided-Toeplitz and two-phase coefficient matrices (Sec. V-B), and its
-// vector-ALU twin.
+// hb_pyr_level: one Laplacian-pyramid level (2x down, 2x up, residual) with strided-Toeplitz and
+// two-phase coefficient matrices (Sec. V-B), and its vector-ALU twin.
 //
-// MFMA formulation.  w = [1,4,6,4,1]/16.  Every pass contracts over the index that the
-// previous accumulator holds per lane, so the whole chain stays in registers:
-//   1 down, x   T1[y][n]  = sum_k P[y][k]  * Adx[k][n]    Adx[k][n] = w[k - 2n]        (A_down)
-//   2 down, y   D'[n][m]  = sum_k T1[k][n] * Ady[k][m]    Ady[k][m] = w[k - 2m]
-//   3 up,   x   U1[m][x]  = sum_k D[m][k]  * Aux[k][x]    Aux[k][x] = K_phase(k - x/2, x%2)
-//   4 up,   y   U'[x][y]  = sum_k U1[k][x] * Auy[k][y]    Auy[k][y] = K_phase(k - y/2, y%2)
-// with K_phase the two phases of 2w: even outputs (1,6,1)/8 on D[q-1..q+1], odd outputs
-// (1,1)/2 on D[q..q+1].  The phases are interleaved by the coefficient matrix itself
-// (column x of Aux belongs to phase x%2), so pass 4 ends with four consecutive output
-// columns of one row per lane and the residual in - U leaves with 16-byte stores.
+// MFMA formulation.  w = [1,4,6,4,1]/16.  Per axis the level is two linear maps, A_down(n, u) = w[u - 2n + 2]
+// and the phase matrix A_up(x, n) (even outputs (1,6,1)/8 on D[q-1..q+1], odd outputs (1,1)/2 on
+// D[q..q+1]), so what is subtracted from the image is
+//     U = C_y * in * C_x^T,   C = A_up * A_down,
+// a band matrix of two alternating rows, [1,4,12,28,38,28,12,4,1]/128 and [1,4,7,8,7,4,1]/32, whose entries
+// are exact in fp16.  The border rules (pixel index clamped in A_down, D index clamped in A_up) only change
+// the entries of the first three and the last four rows of C, which stay multiples of 1/128.  So a level is
+// ONE pair of chained Toeplitz products per 16 x 16 output tile, as in hb_sepblur, instead of four:
+//   row pass      T1[y][n] = sum_k P[y][k] * C_x[n][k]        P = 32 pixels of a row from x0 - 8 on
+//   column pass   R'[n][m] = in'[n][m] - sum_k T1h[k][n] * C_y[m][k]    k = 32 image rows from y0 - 8 on
+// The original pixels reach the column pass through the same registers: a 0/1 selection product copies
+// them into accumulator layout (exactly), and a second one, with the rows shifted by the window's 8,
+// seeds the accumulator.  The coarser level, when it is wanted, shares both passes' operands: 32 pixels
+// give 8 D columns of a 16-column tile, two tiles (and two row steps) fill one D tile.
 //
-// Geometry.  A wave owns a strip of NS blocks of 32 output columns and walks down in steps
-// of 32 output rows.  D tiles (16 x 16) lie on a grid shifted against the outputs so that the
-// K = 32 window of an up pass (two adjacent D tiles) covers the 18 values that 32 outputs need:
-// NS + 1 column tiles per strip, one extra row tile per task.  A D tile needs 35 image
-// rows/columns: a K = 32 plus a K = 16 product over three image row tiles / a 48-pixel window.
-//
-// Interior tasks (pyr_fast_task) shift the D grid by 7: image tiles then start 16 rows / columns
-// before the outputs, so an image row tile holds exactly the rows of one 16-row output tile.  The
-// loaded operand fragments are parked in a wave-private LDS ring and come back, three tiles
-// later, as the B operand of a 0/1 selection product that seeds the accumulator of the last
-// pass with the original pixels: the residual in - U then needs no second read of the image
-// and no separate subtraction (the up-x pass stores -U1).  Image tiles are requested three
-// tiles ahead into a register ring (the loop is unrolled over the ring, so no copy waits on a
-// load in flight).
-//
-// At the image border (pyr_task) the up passes clamp the D index; there the coefficient
-// fragments are rebuilt from absolute indices (taps that clamp onto the same D sample
-// add up), which also makes out-of-range D tiles (computed from clamped pixels) inert.
-#include <type_traits>
-
+// Geometry.  A wave owns 64 columns x 16 NS rows and requests every pixel it needs before its first
+// product (NS + 1 row tiles): it lives for one memory round trip plus its arithmetic, and what keeps the
+// memory busy is the number of such waves.  Windows that reach over the image border load from an address
+// moved inside the row; what lies outside has weight zero.
 #include "hb_device.hpp"
 #include "hb_host.hpp"
-
-#ifndef HB_PYR_NS
-#define HB_PYR_NS 2           // 32-column output blocks per wave strip
-#endif
-#ifndef HB_PYR_WAVES
-#define HB_PYR_WAVES 5400     // aim for about this many interior wave tasks per launch
-#endif
 
 namespace hb {
 
@@ -51,481 +31,242 @@ struct PyrArgs {
     half_t* down;      // may be null
     int H, W, Hd, Wd;
     int64_t in_pitch, res_pitch, down_pitch;
-    // Task list of one launch (wave tasks).  Row steps are 32 output rows high.
-    // Border tasks come first, each one 32-column block wide (the general path): the row steps above
-    // r0 and from r1 on, one step per task, over all nblk blocks; then the blocks left of the interior
-    // (nbl of them) and right of it (from block bR on) over the row steps [r0, r1) in chunks of
-    // kPyrBorderSteps.  Interior tasks follow: nci strips of 32*NS columns starting at column 32*nbl,
-    // each cut into nseg segments of `steps` row steps out of [r0, r1).
-    int nblk, rowsteps;
-    int nbl, bR, nci, r0, r1;
-    int steps, nseg, nchunk;
-    int ntop, nbot, nborder;
-
-    __host__ __device__ int count() const { return nborder + nci * nseg; }
+    int nct, ntasks;   // 64-column strips; strips x segments of 16 NS rows
 };
-constexpr int kPyrBorderSteps = 4;
 
-__device__ __forceinline__ half_t w5(int t) {
-    // [1,4,6,4,1]/16, zero outside
-    const float v = (t == 0 || t == 4) ? 0.0625f : (t == 1 || t == 3) ? 0.25f : (t == 2) ? 0.375f : 0.f;
-    return (half_t)v;
+// Rows of C and of A_down as zero-padded runs, in 1/128: entry kPyrPad + t is the weight of pixel x + t (of pixel
+// 2n + t for A_down), of pixel t at the left / top border, of pixel n - 1 + t at the right / bottom one.  A
+// fragment is eight (or twice four) consecutive entries of the row that its output column selects.
+constexpr int kPyrPad = 40, kPyrRow = 96;
+constexpr int kPyrStd = 0, kPyrLeft = 2, kPyrRight = 5, kPyrDown = 9, kPyrDownLeft = 10, kPyrDownRight = 11, kPyrRows = 12;
+struct PyrTable { uint16_t v[kPyrRows * kPyrRow]; };
+
+// fp16 bits of v / 128, 0 <= v <= 128
+constexpr uint16_t pyr_half_bits(int v) {
+    if (v == 0) return 0;
+    int k = 0;
+    while ((v >> (k + 1)) != 0) ++k;
+    return (uint16_t)(((k - 7 + 15) << 10) | ((v << (10 - k)) & 0x3ff));
 }
-// Weight of D[q + delta] in output 2q + phase (gain 2 per axis).
-__device__ __forceinline__ float upw(int phase, int delta) {
-    if (phase) return (delta == 0 || delta == 1) ? 0.5f : 0.f;
-    return (delta == 0) ? 0.75f : (delta == -1 || delta == 1) ? 0.125f : 0.f;
-}
-// Weight of D[dabs] in output xabs when the D index is clamped to [0, n-1]: the plain phase weight,
-// plus, on the first and last D sample, the weights of the neighbours that clamp onto it.
-__device__ __forceinline__ float upw_clamped(int dabs, int xabs, int n) {
-    const int q = xabs >> 1, ph = xabs & 1;
-    float s = (dabs >= 0 && dabs < n) ? upw(ph, dabs - q) : 0.f;
-    if (dabs == 0 || dabs == n - 1) {
-#pragma unroll
-        for (int delta = -1; delta <= 1; ++delta) {
-            const int d = q + delta;
-            if ((dabs == 0 && d < 0) || (dabs == n - 1 && d > n - 1)) s += upw(ph, delta);
-        }
+// 16 * weight of pixel u in D sample n (pixel index clamped to [0, len - 1])
+constexpr int pyr_down_weight(int n, int u, int len) {
+    constexpr int w[5] = {1, 4, 6, 4, 1};
+    int s = 0;
+    for (int t = 0; t < 5; ++t) {
+        int q = 2 * n + t - 2;
+        q = q < 0 ? 0 : (q > len - 1 ? len - 1 : q);
+        if (q == u) s += w[t];
     }
     return s;
 }
-
-// Sum of the taps t < j of [1,4,6,4,1]/16.
-__device__ __forceinline__ float w5_prefix(int j) {
-    return j <= 0 ? 0.f : j == 1 ? 0.0625f : j == 2 ? 0.3125f : j == 3 ? 0.6875f : j == 4 ? 0.9375f : 1.f;
-}
-// Weight of pixel u in D sample n when the pixel index 2n + t - 2 (t = 0..4) is clamped to [0, len-1]:
-// the plain tap, plus, on the first and last pixel, the taps that clamp onto it.
-__device__ __forceinline__ half_t down_tap_clamped(int n, int u, int len) {
-    float s = (u >= 0 && u < len) ? (float)w5(u - 2 * n + 2) : 0.f;
-    if (u == 0) s += w5_prefix(2 - 2 * n);                         // taps with 2n + t - 2 < 0
-    if (u == len - 1) s += 1.f - w5_prefix(len + 2 - 2 * n);       // taps with 2n + t - 2 > len - 1
-    return (half_t)s;                                     // multiples of 1/16 up to 1: exact
-}
-
-// B fragment of an up pass for the K = 32 window starting at D index d0 and the 16 outputs
-// starting at x0abs (lane c = output, chained slot order), D extent n.
-__device__ __forceinline__ half8 up_fragment_clamped(int d0, int x0abs, int n, int c, int g) {
-    half8 r;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) r[i] = (half_t)upw_clamped(d0 + krow32(g, i), x0abs + c, n);
-    return r;
-}
-
-// Row-direction coefficient fragments of the border path (B operands; lane c = D row).
-struct PyrCoef {
-    half8 dy32;        // A_down, slots = rows 0..31 of the window (chained order)
-    half8 d16;         // A_down for rows 32..35, in slots 8g + (0..3); zero in 8g + (4..7)
-};
-
-// One border task: a strip of NS blocks, nsteps output steps, anywhere in the image (D grid shift 8).
-template <int NS, bool STREAM>
-__device__ __forceinline__ void pyr_task(const PyrArgs& p, const PyrCoef& k, int X0, int R0, int nsteps, int c, int g) {
-    constexpr int NT = NS + 1;                            // D column tiles per strip
-    const int Dx0 = X0 / 2 - 8;                           // first D column of tile 0
-    const int M0 = R0 / 2 - 8;                            // first D row of row tile 0
-    const int px0 = 2 * Dx0 - 2;                          // first pixel of tile 0's window
-    const int y00 = 2 * M0 - 2;                           // first image row of image tile 0
-    const half4 z4 = half4{0, 0, 0, 0};
-
-    half4 T1[3][NT];                                      // row-filtered image tiles r-2, r-1, r
-    half4 U1[2][NS][2];                                   // up-x results of D row tiles q-1, q
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) T1[a][t] = z4;
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int t = 0; t < NS; ++t)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) U1[a][t][h] = z4;
-
-    // per D column tile, a pixel window moved inside the row and A_down fragments with the
-    // column clamp folded in
-    int wsx[NT];
-    half8 fdx32[NT], fdx16[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        wsx[t] = clampi(px0 + 32 * t, 0, p.W - 48);
-        const int n = Dx0 + 16 * t + c;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            fdx32[t][i] = down_tap_clamped(n, wsx[t] + 8 * g + i, p.W);
-            fdx16[t][i] = (i < 4) ? down_tap_clamped(n, wsx[t] + 32 + 4 * g + i, p.W) : (half_t)0;
-        }
+// 128 * weight of pixel u in output x of U (D index clamped as well)
+constexpr int pyr_weight(int x, int u, int len) {
+    constexpr int up[2][3] = {{1, 6, 1}, {0, 4, 4}};
+    int s = 0;
+    for (int d = -1; d <= 1; ++d) {
+        int n = (x >> 1) + d;
+        n = n < 0 ? 0 : (n > len / 2 - 1 ? len / 2 - 1 : n);
+        s += up[x & 1][d + 1] * pyr_down_weight(n, u, len);
     }
-
-    half8 fux[NS][2];                                     // up-x fragments with the D column clamp folded in
-#pragma unroll
-    for (int t = 0; t < NS; ++t)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) fux[t][h] = up_fragment_clamped(Dx0 + 16 * t, X0 + 32 * t + 16 * h, p.Wd, c, g);
-
-    half8 win32[NT], nxt32[NT];
-    half4 win16[NT], nxt16[NT];
-    auto load_rows = [&](int r, half8 (&a32)[NT], half4 (&a16)[NT]) {
-        const half_t* row = p.in + (int64_t)clampi(y00 + 16 * r + c, 0, p.H - 1) * p.in_pitch;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            a32[t] = *reinterpret_cast<const half8_u*>(row + wsx[t] + 8 * g);
-            a16[t] = *reinterpret_cast<const half4_u*>(row + wsx[t] + 32 + 4 * g);
+    return s;
+}
+constexpr PyrTable pyr_make_table() {
+    constexpr int L = 64;                                 // any length whose two borders do not meet
+    PyrTable t{};
+    for (int u = 0; u < L; ++u) {
+        for (int e = 0; e < 2; ++e) {                     // outputs 32 and 33: away from both borders
+            const int w = pyr_weight(L / 2 + e, u, L), o = u - (L / 2 + e) + kPyrPad;
+            if (w) t.v[(kPyrStd + e) * kPyrRow + o] = pyr_half_bits(w);
         }
-    };
-
-    const int ntiles = 2 * nsteps + 3;                    // image row tiles of this task
-    load_rows(0, win32, win16);
-    for (int r = 0; r < ntiles; ++r) {
-        if (r + 1 < ntiles) load_rows(r + 1, nxt32, nxt16);   // next row tile in flight during the products
-        // pass 1: this image row tile, all D column tiles
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            T1[0][t] = T1[1][t];
-            T1[1][t] = T1[2][t];
-            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-            acc = mfma16x16x32(win32[t], fdx32[t], acc);
-            acc = mfma16x16x32(join(win16[t], z4), fdx16[t], acc);
-            T1[2][t] = to_half4(acc);
-        }
-        if ((r & 1) == 0 && r >= 2) {
-            const int q = r / 2 - 1;                      // D row tile completed by image tiles 2q .. 2q+2
-            // pass 2: D tile (lane c = D row, four D columns)
-            half4 D[NT];
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-                acc = mfma16x16x32(join(T1[0][t], T1[1][t]), k.dy32, acc);
-                acc = mfma16x16x32(join(T1[2][t], z4), k.d16, acc);
-                D[t] = to_half4(acc);
-            }
-            if (p.down) {
-                // each task writes the D samples under its own outputs
-                const int m = M0 + 16 * q + c;
-                if (m >= R0 / 2 && m < min(R0 / 2 + 16 * nsteps, p.Hd)) {
-                    half_t* drow = p.down + (int64_t)m * p.down_pitch;
-#pragma unroll
-                    for (int t = 0; t < NT; ++t)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const int n = Dx0 + 16 * t + 4 * g + v;
-                            if (n >= X0 / 2 && n < min(X0 / 2 + 16 * NS, p.Wd)) drow[n] = D[t][v];
-                        }
-                }
-            }
-            // pass 3: up along x (lane c = output column, four D rows)
-#pragma unroll
-            for (int t = 0; t < NS; ++t)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    U1[0][t][h] = U1[1][t][h];
-                    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-                    acc = mfma16x16x32(join(D[t], D[t + 1]), fux[t][h], acc);
-                    U1[1][t][h] = to_half4(acc);
-                }
-            if (q >= 1) {
-                // pass 4: up along y for output rows R0 + 32 (q-1) + (0..31), then the residual
-                const int Rq = R0 + 32 * (q - 1);
-#pragma unroll
-                for (int h2 = 0; h2 < 2; ++h2) {
-                    const half8 b = up_fragment_clamped(M0 + 16 * (q - 1), Rq + 16 * h2, p.Hd, c, g);
-                    const int yo = Rq + 16 * h2 + c;
-                    const half_t* irow = p.in + (int64_t)min(yo, p.H - 1) * p.in_pitch;
-                    float* orow = p.res + (int64_t)yo * p.res_pitch;
-#pragma unroll
-                    for (int t = 0; t < NS; ++t)
-#pragma unroll
-                        for (int h = 0; h < 2; ++h) {
-                            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-                            acc = mfma16x16x32(join(U1[0][t][h], U1[1][t][h]), b, acc);
-                            const int xo = X0 + 32 * t + 16 * h + 4 * g;
-                            if (yo < p.H && xo < p.W) {
-                                const half4 px = load4_clamp(irow, xo, p.W);
-                                floatx4 rv = {(float)px[0] - acc[0], (float)px[1] - acc[1],
-                                              (float)px[2] - acc[2], (float)px[3] - acc[3]};
-                                store4_mask(orow, xo, p.W, rv);
-                            }
-                        }
-                }
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            win32[t] = nxt32[t];
-            win16[t] = nxt16[t];
-        }
+        for (int x = 0; x < 3; ++x)
+            if (u < kPyrRow - kPyrPad) t.v[(kPyrLeft + x) * kPyrRow + u + kPyrPad] = pyr_half_bits(pyr_weight(x, u, L));
+        for (int d = 0; d < 4; ++d)
+            if (u - (L - 1) + kPyrPad >= 0)
+                t.v[(kPyrRight + d) * kPyrRow + u - (L - 1) + kPyrPad] = pyr_half_bits(pyr_weight(L - 1 - d, u, L));
+        const int dw = pyr_down_weight(L / 4, u, L), dl = pyr_down_weight(0, u, L), dr = pyr_down_weight(L / 2 - 1, u, L);
+        if (dw) t.v[kPyrDown * kPyrRow + u - L / 2 + kPyrPad] = pyr_half_bits(8 * dw);
+        if (dl) t.v[kPyrDownLeft * kPyrRow + u + kPyrPad] = pyr_half_bits(8 * dl);
+        if (dr) t.v[kPyrDownRight * kPyrRow + u - (L - 1) + kPyrPad] = pyr_half_bits(8 * dr);
     }
+    return t;
+}
+__device__ const PyrTable kPyrTable = pyr_make_table();
+// Borders that do not meet: row 2 of C reads pixel 6, row n - 4 reads pixel n - 8 and up.
+constexpr int kPyrMinSide = 8;
+
+// Entry of the table from which the weights of pixels u, u + 1, ... in output x (of an axis of n) run.
+__device__ __forceinline__ const uint16_t* pyr_run(int x, int u, int n) {
+    const bool left = x <= 2, right = x >= n - 4 && x < n;
+    const int row = left ? kPyrLeft + x : right ? kPyrRight + (n - 1 - x) : kPyrStd + (x & 1);
+    const int off = left ? u : right ? u - (n - 1) : u - x;
+    return kPyrTable.v + row * kPyrRow + kPyrPad + off;
+}
+// ... and in D sample m
+__device__ __forceinline__ const uint16_t* pyr_down_run(int m, int u, int n) {
+    const bool left = m == 0, right = m == n / 2 - 1;
+    const int row = left ? kPyrDownLeft : right ? kPyrDownRight : kPyrDown;
+    const int off = left ? u : right ? u - (n - 1) : u - 2 * m;
+    return kPyrTable.v + row * kPyrRow + kPyrPad + off;
+}
+__device__ __forceinline__ half8 pyr_natural(const uint16_t* run) { return *reinterpret_cast<const half8_u*>(run); }
+// chained slot order: slots 8g + 0..3 and 8g + 4..7 are 16 rows apart
+__device__ __forceinline__ half8 pyr_chained(const uint16_t* run) {
+    return join(*reinterpret_cast<const half4_u*>(run), *reinterpret_cast<const half4_u*>(run + 16));
+}
+__device__ __forceinline__ half8 pyr_negated(half8 v) {
+    u32x4 b = __builtin_bit_cast(u32x4, v);
+    b ^= 0x80008000u;
+    return __builtin_bit_cast(half8, b);
 }
 
-// ---------------------------------------------------------------------------
-// Interior tasks.
-//
-// Coefficient fragments of the interior path (D grid shift 7, image column tiles of 32 pixels
-// starting 16 left of the strip).  The two halves of a chained K = 32 operand live in one
-// register quadruple that is filled alternately (tile r goes to half r % 2), so every second
-// use sees the halves in swapped order and takes the fragment built for that order: no
-// register is ever copied to line operands up.
-struct PyrFastCoef {
-    half8 dxa, dxb;    // A_down over image column tiles j and j + 1 (slot = pixel)
-    half8 dy32;        // A_down over image row tiles r-2 | r-1 (chained slot order)
-    half8 dy16;        // A_down for rows 32..35 in slots 8g + (0..3), zero in 8g + (4..7)
-    half8 up[2];       // phase matrix of the first / second 16 outputs, operand halves (older | newer)
-    half8 upsw[2];     // same for halves (newer | older)
-    half8 sel[2];      // 0/1 selection (A operand): output column m <- tile pixel 16 + m / pixel m
-};
+// 16-column tiles per strip.  Two: 122 registers, four waves per SIMD (8192 x 8192 with the coarser level
+// 96 us, 4096 x 4096 22.3); four (256-byte runs, 196 registers, two waves) 99 / 24.0.
+constexpr int kPyrNW = 2;
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-constexpr int kBufFlags = 0x00020000;                     // raw buffer, 32-bit data format
-
-__device__ __forceinline__ half4 lo4(half8 v) { return __builtin_shufflevector(v, v, 0, 1, 2, 3); }
-__device__ __forceinline__ half4 hi4(half8 v) { return __builtin_shufflevector(v, v, 4, 5, 6, 7); }
-
-constexpr int kPyrStashTile = 1024;                       // bytes per parked fragment: 64 lanes x 16
-template <int NS>
-struct PyrStash { static constexpr int kSlot = (NS + 1) * kPyrStashTile, kBytes = 3 * kSlot; };
-
-// One interior task: a strip of NS blocks, nsteps (even) output steps, no image border in reach.
-// Image row tile r holds rows R0 - 16 + 16 r + (0..15); image column tile j holds pixels
-// X0 - 16 + 32 j + (0..31).  Tile loads are buffer loads: a wave-uniform descriptor of the
-// task's footprint, one per-lane offset for the whole task, the row tile as scalar offset.
-template <int NS, bool STREAM, bool DOWN>
-__device__ __forceinline__ void pyr_fast_task(const PyrArgs& p, const PyrFastCoef& k, float* patch, char* stash,
-                                              int X0, int R0, int nsteps, int lane) {
-    constexpr int NT = NS + 1;                            // D column tiles per strip
-    constexpr int NC = NS + 2;                            // image column tiles per strip
-    constexpr int NB = 4;                                 // register ring of image row tiles (3 ahead)
-    constexpr int NW = 2 * NS;                            // 16-column output tiles per row tile
+// One task: 16 NW columns x 16 NS rows from (x0, Y0).  INSIDE: every window and every output column of the
+// strip lies inside the image (rows may still reach over the top and bottom).
+template <int NS, int NW, bool INSIDE, bool STREAM, bool DOWN>
+__device__ __forceinline__ void pyr_task(const PyrArgs& p, float* patch, int x0, int Y0, int lane) {
+    constexpr int NV = NW / 2, NL = NS + 1;
     const int c = lane & 15, g = lane >> 4;
-    const int Dx0 = X0 / 2 - 7, M0 = R0 / 2 - 7;          // first D column / row of tile 0
+    const half8 z8 = {0, 0, 0, 0, 0, 0, 0, 0};
+    const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
 
-    // descriptors end with the image: an access past the last pixel would return zero / be dropped
-    const int64_t in_left = ((int64_t)(p.H - 1 - (R0 - 16)) * p.in_pitch + (p.W - (X0 - 16))) * 2;
-    const int64_t out_left = ((int64_t)(p.H - 1 - R0) * p.res_pitch + (p.W - X0)) * 4;
-    const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<half_t*>(p.in + (int64_t)(R0 - 16) * p.in_pitch + (X0 - 16)), 0,
-        (int)(in_left < 0x7fffffff ? in_left : 0x7fffffff), kBufFlags);
-    const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(
-        p.res + (int64_t)R0 * p.res_pitch + X0, 0, (int)(out_left < 0x7fffffff ? out_left : 0x7fffffff), kBufFlags);
-    const uint32_t ivoff = (uint32_t)c * (uint32_t)p.in_pitch * 2u + 16u * g;
-    // The last image column tile only feeds its first three pixels into a product (A_down of the last
-    // D column); all four lanes of a row read its first eight pixels, so that a strip touches no
-    // pixel beyond 24 past its last output.
-    const uint32_t ivoff_last = (uint32_t)c * (uint32_t)p.in_pitch * 2u + 64u * (NC - 1);
-    const uint32_t itile = 32u * (uint32_t)p.in_pitch;    // bytes per image row tile
-    const uint32_t ovoff = ((uint32_t)g * (uint32_t)p.res_pitch + 4u * c) * 4u;
-    const uint32_t orow4 = 16u * (uint32_t)p.res_pitch;   // bytes per four output rows
-    const int ntiles = 2 * nsteps + 3;
-
-    half8 W[NB][NC];                                      // image row tiles in flight / in use
-    half8 TP[2][NT];                                      // row-filtered tiles: TP[a] = tiles (4i+2a | 4i+2a+1)
-    half8 UP[NS][2];                                      // -(up-x results) of D row tiles (even q | odd q)
+    half8 px[NL][NW];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int q = 0; q < NL; ++q) {
+        const half_t* row = p.in + (int64_t)clampi(Y0 - 8 + 16 * q + c, 0, p.H - 1) * p.in_pitch;
 #pragma unroll
-        for (int t = 0; t < NT; ++t) TP[a][t] = half8{0, 0, 0, 0, 0, 0, 0, 0};   // (finite: zero weights meet these)
-#pragma unroll
-    for (int t = 0; t < NS; ++t)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) UP[t][h] = half8{0, 0, 0, 0, 0, 0, 0, 0};
-
-    auto load_tile = [&](int r, half8 (&w)[NC]) {
-        const uint32_t soff = (uint32_t)min(r, ntiles - 1) * itile;   // past the end: the last tile again
-#pragma unroll
-        for (int j = 0; j < NC - 1; ++j)
-            w[j] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(rin, ivoff + 64u * j, soff, 0));
-        w[NC - 1] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(rin, ivoff_last, soff, 0));
-    };
-    int sslot = 0;                                        // stash slot of the current tile: r % 3
-    char* const mystash = stash + 16 * lane;
-
-    // One image row tile.  S = r % 4 (compile time): ring slot of the tile, half of TP it fills.
-    auto tile = [&](auto Stag, int r, __amdgpu_buffer_rsrc_t rdst) {
-        constexpr int S = decltype(Stag)::value;
-        // (no instruction may move between tiles: a product hoisted from a later tile would wait for
-        // loads that are meant to stay in flight)
-        __builtin_amdgcn_sched_barrier(0);
-        load_tile(r + 3, W[(S + 3) % NB]);
-        const half8 (&w)[NC] = W[S];
-        // pass 1: down along x, all D column tiles
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-            acc = mfma16x16x32(w[t], k.dxa, acc);
-            acc = mfma16x16x32(w[t + 1], k.dxb, acc);
-            const half4 h = to_half4(acc);
-            TP[S >> 1][t] = (S & 1) ? join(lo4(TP[S >> 1][t]), h) : join(h, hi4(TP[S >> 1][t]));
+        for (int w = 0; w < NW; ++w) {
+            const int xs = x0 - 8 + 16 * w + 8 * g;
+            px[q][w] = *reinterpret_cast<const half8_u*>(row + (INSIDE ? xs : clampi(xs, 0, p.W - 8)));
         }
-        if constexpr ((S & 1) == 0) {
-            const int q = r / 2 - 1;                      // D row tile completed by image tiles r-2 .. r
-            constexpr int QO = (S == 0);                  // q is odd for S = 0, even for S = 2
-            // pass 2: down along y (lane c = D row, four D columns)
-            half4 D[NT];
+    }
+    // coefficients only now: a wave that waited for them first would put a memory round trip in front of
+    // its pixel requests
+    __builtin_amdgcn_sched_barrier(0);
+    // Weights of tile w for the row pass, and for the D columns 16 v + c under the strip: tile 2v gives those of the
+    // lanes c < 8, tile 2v + 1 the others (away from the borders the same numbers, eight lanes on).  Away from the
+    // borders every tile has the same weights: column 32 stands for any.
+    constexpr int NF = INSIDE ? 1 : NW;
+    half8 bx[NF], bd[NF];
 #pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-                acc = mfma16x16x32(TP[(S >> 1) ^ 1][t], k.dy32, acc);
-                acc = mfma16x16x32(TP[S >> 1][t], k.dy16, acc);   // upper half: older rows, zero weights
-                D[t] = to_half4(acc);
+    for (int w = 0; w < NF; ++w) {
+        const int xt = INSIDE ? 32 : x0 + 16 * w, n = INSIDE ? 1 << 20 : p.W;
+        bx[w] = pyr_natural(pyr_run(xt + c, xt - 8 + 8 * g, n));
+        if (DOWN) bd[w] = pyr_natural(pyr_down_run(xt / 2 + (c & 7), xt - 8 + 8 * g, n));
+    }
+    half8 selx, sely;                                     // pixels 8 .. 23 of the window; rows 8 .. 23 of it
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        selx[i] = (half_t)(8 * g + i == c + 8 ? 1.f : 0.f);
+        sely[i] = (half_t)(krow32(g, i) == c + 8 ? 1.f : 0.f);
+    }
+    // column-pass weights of row step R; of D, a step has eight rows, so two steps share a tile of 16
+    auto column_weights = [&](int R, int n) { return pyr_negated(pyr_chained(pyr_run(R + c, R - 8 + 4 * g, n))); };
+    auto down_column_weights = [&](int R, int n) { return pyr_chained(pyr_down_run(R / 2 + (c & 7), R - 8 + 4 * g, n)); };
+    auto half_lanes = [&](half8 f, int u) { return (c >= 8) == (bool)u ? f : z8; };
+    const bool edge = Y0 == 0 || Y0 + 16 * NS + 4 > p.H;  // uniform
+    const half8 by0 = column_weights(32, 1 << 20);
+    half8 bm0;
+    if (DOWN) bm0 = down_column_weights(32, 1 << 20);
+
+    half4 T[2][NW], X[2][NW], Td[2][NV];                  // row tiles q - 1 and q: row-filtered, copied, D columns
+    floatx4 D[NV];
+#pragma unroll
+    for (int q = 0; q < NL; ++q) {
+        __builtin_amdgcn_sched_barrier(0);                // row tile by row tile: keeps few results live at a time
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            if (!INSIDE) {
+                const int xs = x0 - 8 + 16 * w + 8 * g;
+                px[q][w] = shift_in_from_right(px[q][w], xs - clampi(xs, 0, p.W - 8));
             }
-            if constexpr (DOWN) {
-                // each task writes the D samples under its own outputs
-                const int m = M0 + 16 * q + c;
-                if (m >= R0 / 2 && m < R0 / 2 + 16 * nsteps) {
-                    half_t* drow = p.down + (int64_t)m * p.down_pitch;
+            T[q & 1][w] = to_half4(mfma16x16x32(px[q][w], bx[INSIDE ? 0 : w], zero));
+            X[q & 1][w] = to_half4(mfma16x16x32(px[q][w], selx, zero));
+        }
+        if (DOWN) {
 #pragma unroll
-                    for (int t = 0; t < NT; ++t)
+            for (int v = 0; v < NV; ++v) {
+                floatx4 d = mfma16x16x32(px[q][2 * v], half_lanes(bd[INSIDE ? 0 : 2 * v], 0), zero);
+                d = mfma16x16x32(px[q][2 * v + 1], half_lanes(bd[INSIDE ? 0 : 2 * v + 1], 1), d);
+                Td[q & 1][v] = to_half4(d);
+            }
+        }
+        if (q == 0) continue;
+        const int s = q - 1, R = Y0 + 16 * s;             // output rows R .. R + 15, window rows R - 8 .. R + 23
+        if (R >= p.H) break;                              // uniform
+        half8 by = by0, bm;
+        if (DOWN) bm = bm0;
+        if (edge && (R == 0 || R + 20 > p.H)) {           // uniform
+            by = column_weights(R, p.H);
+            if (DOWN) bm = down_column_weights(R, p.H);
+        }
+        floatx4 acc[NW];
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const int n = Dx0 + 16 * t + 4 * g + v;
-                            if (n >= X0 / 2 && n < X0 / 2 + 16 * NS) drow[n] = D[t][v];
+        for (int w = 0; w < NW; ++w) {
+            acc[w] = mfma16x16x32(join(X[s & 1][w], X[q & 1][w]), sely, zero);
+            acc[w] = mfma16x16x32(join(T[s & 1][w], T[q & 1][w]), by, acc[w]);
+        }
+        if (INSIDE && R + 16 <= p.H)
+            store_rows_via_lds<NW, STREAM>(patch, p.res + (int64_t)R * p.res_pitch + x0, (uint32_t)p.res_pitch, acc, lane);
+        else
+            store_rows_via_lds_masked<NW, STREAM>(patch, p.res + (int64_t)R * p.res_pitch + x0, p.res_pitch, acc, lane, p.H - R, p.W - x0);
+        if (DOWN) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+                D[v] = mfma16x16x32(join(Td[s & 1][v], Td[q & 1][v]), half_lanes(bm, s & 1), (s & 1) ? D[v] : zero);
+            if ((s & 1) || R + 16 >= p.H) {
+                // D rows m0 + lane column, m0 that of the pair's first step; 16 bytes per lane, 32 NV bytes
+                // of a row together.  Plain stores: the next level reads them
+                const int m0 = (R - 16 * (s & 1)) / 2;
+                half_t* const dp = reinterpret_cast<half_t*>(patch);
+                constexpr int kPitch = 16 * NV + 8, kLanes = 2 * NV;
+#pragma unroll
+                for (int v = 0; v < NV; ++v) *reinterpret_cast<half4*>(dp + c * kPitch + 16 * v + 4 * g) = to_half4(D[v]);
+                wave_lds_fence();
+                const int dr = lane / kLanes, n = 8 * (lane - kLanes * dr);
+                if (NV == 2 || dr < 16) {
+                    const half8 dv = *reinterpret_cast<const half8*>(dp + dr * kPitch + n);
+                    half_t* const dst = p.down + (int64_t)(m0 + dr) * p.down_pitch + x0 / 2 + n;
+                    const int rows = min(p.Hd - m0, (s & 1) ? 16 : 8), cols = p.Wd - x0 / 2 - n;
+                    if (dr < rows) {
+                        if (INSIDE || cols >= 8) {
+                            *reinterpret_cast<half8_u*>(dst) = dv;
+                        } else {
+#pragma unroll
+                            for (int i = 0; i < 8; ++i)
+                                if (i < cols) dst[i] = dv[i];
                         }
-                }
-            }
-            // pass 3: up along x (lane c = output column, four D rows), sign flipped
-#pragma unroll
-            for (int t = 0; t < NS; ++t) {
-                const half8 dd = join(D[t], D[t + 1]);
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-                    acc = mfma16x16x32(dd, k.up[h], acc);
-                    const half4 u = to_half4(-acc);
-                    UP[t][h] = QO ? join(lo4(UP[t][h]), u) : join(u, hi4(UP[t][h]));
-                }
-            }
-            {
-                // pass 4: parked pixels (tiles r-3, r-2) minus up along y, output rows 32 (q-1) + (0..31)
-#pragma unroll
-                for (int h2 = 0; h2 < 2; ++h2) {
-                    const int sl = (sslot + h2 >= 3) ? sslot + h2 - 3 : sslot + h2;
-                    const char* park = mystash + sl * PyrStash<NS>::kSlot;
-                    half8 px[NT];
-#pragma unroll
-                    for (int j = 0; j < NT; ++j) px[j] = *reinterpret_cast<const half8*>(park + j * kPyrStashTile);
-                    const half8 b = QO ? k.up[h2] : k.upsw[h2];
-                    floatx4 rv[NW];
-#pragma unroll
-                    for (int t = 0; t < NS; ++t)
-#pragma unroll
-                        for (int h = 0; h < 2; ++h) {
-                            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-                            acc = mfma16x16x32(k.sel[h], px[t + h], acc);
-                            acc = mfma16x16x32(UP[t][h], b, acc);
-                            rv[2 * t + h] = acc;
-                        }
-                    // rows through the wave-private patch: 256-byte runs of one row per 16 lanes
-#pragma unroll
-                    for (int w2 = 0; w2 < NW; ++w2)
-                        *reinterpret_cast<floatx4*>(patch + c * RowPatch<NW>::kPitch + 16 * w2 + 4 * g) = rv[w2];
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                    const uint32_t so = (uint32_t)(8 * (q - 1) + 4 * h2) * orow4;
-#pragma unroll
-                    for (int s4 = 0; s4 < 4; ++s4) {
-                        const floatx4 v = *reinterpret_cast<const floatx4*>(patch + (4 * s4 + g) * RowPatch<NW>::kPitch + 4 * c);
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rdst, ovoff,
-                                                               so + (uint32_t)s4 * orow4, STREAM ? 2 : 0);
                     }
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
                 }
+                wave_lds_fence();
             }
         }
-        // park this tile's fragments that lie under the outputs (read back three tiles later)
-        {
-            char* park = mystash + sslot * PyrStash<NS>::kSlot;
-#pragma unroll
-            for (int j = 0; j < NT; ++j) *reinterpret_cast<half8*>(park + j * kPyrStashTile) = w[j];
-            sslot = (sslot == 2) ? 0 : sslot + 1;
-        }
-    };
-    using I0 = std::integral_constant<int, 0>;
-    using I1 = std::integral_constant<int, 1>;
-    using I2 = std::integral_constant<int, 2>;
-    using I3 = std::integral_constant<int, 3>;
-
-    // Tiles run in rounds of four (ring slots 0..3); slots 0 and 2 complete a D row tile and store the
-    // 32 output rows above it.  The first round has nothing to store yet: its stores go through a
-    // descriptor of zero length, which the hardware drops.  Every round thereby issues the same
-    // sequence of memory instructions, and so does the start-up below (loads, eight dropped stores,
-    // loads): the compiler's counted waits then leave three tiles in flight instead of falling back
-    // to the shortest path through the code.
-    const __amdgpu_buffer_rsrc_t rnull = __builtin_amdgcn_make_buffer_rsrc(p.res, 0, 0, kBufFlags);
-    load_tile(0, W[0]);
-    load_tile(1, W[1]);
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-        __builtin_amdgcn_raw_buffer_store_b128(u32x4{0u, 0u, 0u, 0u}, rnull, ovoff, 0, 0);
-    load_tile(2, W[2]);
-    for (int r = 0; r < ntiles; r += 4) {                 // tiles 0 .. 2 nsteps + 2, one spare at the end
-        const __amdgpu_buffer_rsrc_t rdst = (r == 0) ? rnull : rout;
-        tile(I0{}, r, rdst);
-        tile(I1{}, r + 1, rdst);
-        tile(I2{}, r + 2, rdst);
-        tile(I3{}, r + 3, rdst);
     }
 }
 
-template <bool STREAM, bool DOWN>
-__global__ void __launch_bounds__(256, 2) pyr_mfma_kernel(PyrArgs p) {
-    constexpr int NS = HB_PYR_NS;
+template <int NS, bool STREAM, bool DOWN>
+__global__ void __launch_bounds__(256, 4) pyr_mfma_kernel(PyrArgs p) {
+    __shared__ __attribute__((aligned(16))) float s_patch[4][RowPatch<kPyrNW>::kFloats];
     const int lane = threadIdx.x & 63;
-    const int c = lane & 15, g = lane >> 4;
-
-    __shared__ __attribute__((aligned(16))) float s_patch[4][RowPatch<2 * NS>::kFloats];
-    __shared__ __attribute__((aligned(16))) char s_stash[4][PyrStash<NS>::kBytes];
-
-    // (of every 32 workgroups an XCD takes four neighbours: the waves in flight still sweep down the
-    // image as one band, and neighbouring strips meet in one L2.  8192 x 8192: 91.4 us, plain launch
-    // order 93.9, one contiguous eighth of the tasks per XCD, i.e. eight separate bands, 97)
-    const int wgpos = xcd_blocked(blockIdx.x, gridDim.x, 4);
-    const int wave = __builtin_amdgcn_readfirstlane(wgpos * 4 + (threadIdx.x >> 6));
-    const int nwaves = (gridDim.x * blockDim.x) >> 6;
-    const int ntasks = p.count();
-    for (int task = wave; task < ntasks; task += nwaves) {
-        if (task >= p.nborder) {
-            PyrFastCoef k;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                k.dxa[i] = w5(8 * g + i - 2 * c);
-                k.dxb[i] = w5(32 + 8 * g + i - 2 * c);
-                k.dy32[i] = w5(krow32(g, i) - 2 * c);
-                k.dy16[i] = (i < 4) ? w5(32 + 4 * g + i - 2 * c) : (half_t)0;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    k.up[h][i] = (half_t)upw(c & 1, krow32(g, i) - 7 - 8 * h - (c >> 1));
-                    k.upsw[h][i] = (half_t)upw(c & 1, krow32(g, i ^ 4) - 7 - 8 * h - (c >> 1));
-                }
-                k.sel[0][i] = (half_t)((8 * g + i == 16 + c) ? 1.f : 0.f);
-                k.sel[1][i] = (half_t)((8 * g + i == c) ? 1.f : 0.f);
-            }
-            const int id = task - p.nborder;
-            const int seg = id / p.nci, ct = id - seg * p.nci;
-            const int rs = p.r0 + seg * p.steps;
-            pyr_fast_task<NS, STREAM, DOWN>(p, k, s_patch[threadIdx.x >> 6], s_stash[threadIdx.x >> 6],
-                                            32 * (p.nbl + NS * ct), 32 * rs, min(p.steps, p.r1 - rs), lane);
-        } else {
-            PyrCoef k;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                k.dy32[i] = w5(krow32(g, i) - 2 * c);
-                k.d16[i] = (i < 4) ? w5(32 + 4 * g + i - 2 * c) : (half_t)0;
-            }
-            int rs, blk, nst = 1;                         // one 32-column block, nst row steps
-            if (task < p.ntop) {
-                rs = task / p.nblk, blk = task - rs * p.nblk;
-            } else if (task < p.ntop + p.nbot) {
-                const int id = task - p.ntop;
-                rs = id / p.nblk, blk = id - rs * p.nblk, rs += p.r1;
-            } else {
-                const int id = task - p.ntop - p.nbot;
-                const int bi = id / p.nchunk, ch = id - bi * p.nchunk;
-                blk = bi < p.nbl ? bi : p.bR + (bi - p.nbl);
-                rs = p.r0 + kPyrBorderSteps * ch;
-                nst = min(kPyrBorderSteps, p.r1 - rs);
-            }
-            pyr_task<1, STREAM>(p, k, 32 * blk, 32 * rs, nst, c, g);
+    // of every 32 workgroups an XCD takes four neighbours: the chip sweeps through the image in launch
+    // order and neighbouring tasks meet in one L2
+    const int task = __builtin_amdgcn_readfirstlane(xcd_blocked(blockIdx.x, gridDim.x, 4) * 4 + (threadIdx.x >> 6));
+    if (task >= p.ntasks) return;
+    const int seg = task / p.nct, ct = task - seg * p.nct;
+    const int x0 = 16 * kPyrNW * ct, Y0 = 16 * NS * seg;
+    float* patch = s_patch[threadIdx.x >> 6];
+    if (x0 > 0 && x0 + 16 * kPyrNW + 8 <= p.W) {
+        pyr_task<NS, kPyrNW, true, STREAM, DOWN>(p, patch, x0, Y0, lane);
+    } else {
+        // border strips two row steps at a time: with weights per tile the whole task's registers would cost every
+        // strip a wave per SIMD
+#pragma unroll 1
+        for (int y = Y0; y < min(Y0 + 16 * NS, p.H); y += 32) {
+            int l = lane;                                 // nothing lane-dependent is kept from turn to turn
+            asm volatile("" : "+v"(l));
+            pyr_task<2, kPyrNW, false, STREAM, DOWN>(p, patch, x0, y, l);
         }
     }
 }
@@ -625,38 +366,19 @@ static hb_status pyr_prepare(PyrArgs& a, const hb_half* in, float* res, hb_half*
     a.in_pitch = in_pitch;
     a.res_pitch = res_pitch;
     a.down_pitch = down_pitch;
-    constexpr int SW = 32 * HB_PYR_NS;                    // interior strip width
-    a.nblk = ceil_div(W, 32);
-    a.rowsteps = ceil_div(H, 32);
-    // interior: a task reads pixels from 16 before its first output to 32 past its last one (24 along
-    // x), in both directions; then no up pass reads a clamped D index either.  One border block on
-    // the left; on the right whatever the strips leave.
-    a.nbl = 1;
-    a.nci = (W - 32 - 32 >= SW) ? (W - 32 - 32) / SW : 0;
-    a.bR = a.nbl + HB_PYR_NS * a.nci;
-    a.r0 = 1;
-    a.r1 = (H - 64 >= 0) ? (H - 64) / 32 + 1 : 0;        // last interior step e: 32 e + 32 + 32 <= H
-    if ((a.r1 - a.r0) & 1) --a.r1;                        // interior tasks take two row steps per round
-    // a task's footprint must stay below 2 GiB from its first row (32-bit buffer offsets)
-    const int64_t rowbytes = in_pitch * 2 > res_pitch * 4 ? in_pitch * 2 : res_pitch * 4;
-    const int64_t maxrows = (((int64_t)1 << 31) - 1) / rowbytes;
-    // the interior path reads with 16-byte buffer loads: rows must start on 4-byte boundaries
-    const bool dword_rows = (in_pitch % 2 == 0) && (reinterpret_cast<uintptr_t>(in) % 4 == 0);
-    if (!dword_rows || maxrows < 2 * 32 + 64 || a.nci <= 0 || a.r1 <= a.r0) {   // no interior: everything is "top"
-        a.nci = 0;
-        a.nbl = a.bR = a.nblk;
-        a.r0 = a.r1 = a.rowsteps;
-    }
-    const int nr = a.r1 - a.r0;
-    int steps = 2 * (int)(((int64_t)nr * a.nci + 2 * HB_PYR_WAVES - 1) / (2 * HB_PYR_WAVES));
-    if ((int64_t)32 * steps + 64 > maxrows) steps = (int)((maxrows - 64) / 64) * 2;
-    a.steps = steps < 2 ? 2 : steps;
-    a.nseg = a.nci > 0 ? ceil_div(nr, a.steps) : 0;
-    a.nchunk = ceil_div(nr, kPyrBorderSteps);
-    a.ntop = a.r0 * a.nblk;
-    a.nbot = (a.rowsteps - a.r1) * a.nblk;
-    a.nborder = a.ntop + a.nbot + (nr > 0 ? (a.nbl + a.nblk - a.bR) * a.nchunk : 0);
+    a.nct = a.ntasks = 0;
     return HB_OK;
+}
+
+template <int NS>
+static hb_status pyr_launch(PyrArgs& a, hipStream_t st) {
+    const int64_t ntasks = (int64_t)a.nct * ceil_div(a.H, 16 * NS);
+    if (ntasks > 0x7fffffff - 4) return HB_ERR_UNSUPPORTED;
+    a.ntasks = (int)ntasks;
+    const dim3 grid((unsigned)((ntasks + 3) / 4));
+    if (a.down) hipLaunchKernelGGL((pyr_mfma_kernel<NS, true, true>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((pyr_mfma_kernel<NS, true, false>), grid, dim3(256), 0, st, a);
+    return launch_status();
 }
 
 }  // namespace hb
@@ -672,19 +394,15 @@ extern "C" hb_status hb_pyr_level(const hb_half* in, float* residual, hb_half* d
     PyrArgs a;
     hb_status s = pyr_prepare(a, in, residual, down_or_null, H, W, in_pitch, res_pitch, down_pitch);
     if (s != HB_OK) return s;
-    if (W < 48)   // narrower than one pixel window of the matrix formulation: vector-ALU kernel
+    if (W < kPyrMinSide || H < kPyrMinSide)   // the two borders' rows of C meet: vector-ALU kernel
         return hb_pyr_level_valu(in, residual, down_or_null, H, W, in_pitch, res_pitch, down_pitch, stream);
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    const dim3 grid(min(ceil_div(a.count(), 4), kMaxStreamBlocks));
-    const bool stream_stores = (int64_t)H * W * 4 <= kStreamStoreMaxBytes;
-    if (a.down) {
-        if (stream_stores) hipLaunchKernelGGL((pyr_mfma_kernel<true, true>), grid, dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((pyr_mfma_kernel<false, true>), grid, dim3(256), 0, st, a);
-    } else {
-        if (stream_stores) hipLaunchKernelGGL((pyr_mfma_kernel<true, false>), grid, dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((pyr_mfma_kernel<false, false>), grid, dim3(256), 0, st, a);
-    }
-    return launch_status();
+    a.nct = ceil_div(W, 16 * kPyrNW);
+    // Long tasks re-read fewer rows (NS + 1 row tiles for NS), short ones fill the chip and end together: NS = 4 /
+    // NS = 2 measured 96 / 111 us on 8192 x 8192 (32768 long tasks), 22.3 / 25.3 on 4096 x 4096 (8192), 18.2 / 16.1
+    // on 3002 x 2710 (3995), the same on 2048 x 2048 (2048).
+    if ((int64_t)a.nct * ceil_div(H, 64) >= 24 * num_cu()) return pyr_launch<4>(a, st);
+    return pyr_launch<2>(a, st);
 }
 
 extern "C" hb_status hb_pyr_level_valu(const hb_half* in, float* residual, hb_half* down_or_null,

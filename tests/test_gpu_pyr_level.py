@@ -77,6 +77,17 @@ def test_pyr_benchmark_width_slab(orc, fn):
     assert_close(res.cpu().numpy(), orc.pyr_level(img), fn)
 
 
+@pytest.mark.parametrize("H,W", [(8, 8), (8, 74), (10, 40), (72, 8), (14, 18), (16, 104), (36, 36), (66, 74), (34, 2056), (1030, 46)])
+def test_pyr_border_rows_and_columns_of_the_composite_matrix(orc, H, W):
+    """Sizes around the ends of the 32 x 32 and 32 x 64 tasks and of the windows (8 pixels before a tile, 8 after),
+    down to the smallest image whose two borders do not meet; tolerance as everywhere: one fp16 rounding of the
+    row-filtered pixels, at most 2^-12 of a value below 1."""
+    _, res, down, _, _ = out = run("hb_pyr_level", H, W, True, pitch_extra=3)
+    ref, dref = orc.pyr_level(out[0], want_down=True)
+    assert_close(res, ref, f"residual {H}x{W}")
+    assert_close(down.astype(np.float64), dref, f"down {H}x{W}")
+
+
 @pytest.mark.parametrize("want_down", [False, True])
 def test_pyr_full_benchmark_size_sampled_bands(orc, want_down):
     """The benchmark's 8192 x 8192 launch (long interior tasks, many rounds of the tile ring), checked on
