@@ -1,7 +1,7 @@
 // hb_sepblur: separable 2-D blur as two chained Toeplitz products per tile
 // (Sec. V-A), and its vector-ALU twin.
 //
-// MFMA formulation.  A wave owns a strip of HB_SEP_TILES 16-column tiles and walks
+// MFMA formulation.  A wave owns a strip of HB_SEP_TILES 16-column tiles and goes
 // down it in steps of 16 rows.
 //   row pass     T1[m][n] = sum_k P[m][k] * Bx[k][n]     m = image row, n = column, k = pixel
 //                P = the 32*NKX pixels from x0 - ax - e on (e = ax & 1: even, dword-aligned
@@ -22,18 +22,14 @@
 // consecutive tiles and produces one new tile.  Rows outside the image repeat the
 // edge row: clamping the image row index at the load is the same as clamping the
 // index of the row-filtered intermediate, because the row pass treats rows
-// independently.  The pixels of the next row tile are requested before the current
-// one is multiplied, so a wave always has one tile of loads in flight.
+// independently.
 #include "hb_device.hpp"
 #include "hb_host.hpp"
+#include <algorithm>
 
 #ifndef HB_SEP_TILES
 #define HB_SEP_TILES 2        // 16-column tiles per wave strip
 #endif
-#ifndef HB_SEP_WAVES
-#define HB_SEP_WAVES 4096     // at most this many wave tasks per launch: one resident round, no straggler round
-#endif
-
 
 namespace hb {
 
@@ -43,136 +39,13 @@ struct SepArgs {
     int H, W;
     int64_t in_pitch, out_pitch;
     int Tx, ax, Ty, ay;
-    int steps;         // 16-row steps per task
-    TaskGrid grid;     // strips x row segments
+    int nct, nseg;     // strips (of 128 columns for the marching kernel) x segments
+    int steps;         // 16-row steps per segment
+    int c0, c1;        // strips whose windows and tiles lie inside the row
     Taps tx, ty;
-    FoldTables foldx;
 };
 
 __device__ __forceinline__ half_t sep_tap(uint16_t b) { return __builtin_bit_cast(half_t, b); }
-
-// One task: a strip of NW tiles, nsteps output steps.  XIN = every window of the strip
-// lies inside the row and every tile is full: plain Toeplitz fragment, no store mask.
-// Otherwise each tile's window is moved inside the row and the column clamp is folded
-// into a per-tile hi + lo fragment.
-template <int NKX, int NT, int NW, bool XIN, bool STREAM>
-__device__ __forceinline__ void sep_task(const SepArgs& p, const FoldTables& fold, float* patch,
-                                         const half8 (&coefx)[NKX],
-                                         const half8 (&coefy)[(NT + 1) / 2],
-                                         int x0, int Y0, int nsteps, int xw, int c, int g) {
-    constexpr int NK = (NT + 1) / 2;
-    const int ntiles = nsteps + NT - 1;
-
-    // border strips: per-tile window start (absolute pixel, inside the row) and folded fragments
-    int wsh[NW];
-    half8 fh[XIN ? 1 : NW][NKX], fl[XIN ? 1 : NW][NKX];
-    if (!XIN) {
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const int xt = x0 + 16 * w;
-            const int ws = clampi(xt - xw, 0, p.W - 32 * NKX);
-            wsh[w] = ws;
-#pragma unroll
-            for (int kk = 0; kk < NKX; ++kk) {
-                if (ws == xt - xw && xt + 16 <= p.W) {
-                    fh[w][kk] = coefx[kk];
-                    fl[w][kk] = half8{0, 0, 0, 0, 0, 0, 0, 0};
-                } else if (xt < p.W) {
-                    folded_fragment(fold, p.Tx, p.ax, p.W, xt, ws, kk, c, g, fh[w][kk], fl[w][kk]);
-                } else {
-                    fh[w][kk] = fl[w][kk] = half8{0, 0, 0, 0, 0, 0, 0, 0};
-                }
-            }
-        }
-    }
-    const half_t* src = p.in + (x0 - xw);                 // uniform; lanes add row * pitch + 8g
-    float* dst = p.out + x0;
-
-    half4 hist[NT][NW];                                   // row-filtered tiles q .. q+NT-1
-#pragma unroll
-    for (int q = 0; q < NT; ++q)
-#pragma unroll
-        for (int w = 0; w < NW; ++w) hist[q][w] = half4{0, 0, 0, 0};
-
-    auto load_tile = [&](int q, half8 (&dstw)[NW][NKX]) {
-        // tile q covers image rows Y0 - ay + 16 q + (0..15), clamped to the image
-        const int yr = clampi(Y0 - p.ay + 16 * q + c, 0, p.H - 1);
-        if (XIN) {
-            const uint32_t off = ((uint32_t)yr * (uint32_t)p.in_pitch + 8u * g) * 2u;
-#pragma unroll
-            for (int w = 0; w < NW; ++w)
-#pragma unroll
-                for (int kk = 0; kk < NKX; ++kk) dstw[w][kk] = ldg8(src, off + 2u * (16u * w + 32u * kk));
-        } else {
-            const half_t* row = p.in + (int64_t)yr * p.in_pitch + 8 * g;
-#pragma unroll
-            for (int w = 0; w < NW; ++w)
-#pragma unroll
-                for (int kk = 0; kk < NKX; ++kk)
-                    dstw[w][kk] = *reinterpret_cast<const half8_u*>(row + wsh[w] + 32 * kk);
-        }
-    };
-
-    half8 cur[NW][NKX], nxt[NW][NKX];
-    load_tile(0, cur);
-    for (int q = 0; q < ntiles; ++q) {
-        if (q + 1 < ntiles) load_tile(q + 1, nxt);        // next row tile in flight while this one is multiplied
-#pragma unroll
-        for (int u = 0; u < NT - 1; ++u)
-#pragma unroll
-            for (int w = 0; w < NW; ++w) hist[u][w] = hist[u + 1][w];
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kk = 0; kk < NKX; ++kk) {
-                if (XIN) {
-                    acc = mfma16x16x32(cur[w][kk], coefx[kk], acc);
-                } else {
-                    acc = mfma16x16x32(cur[w][kk], fh[w][kk], acc);
-                    acc = mfma16x16x32(cur[w][kk], fl[w][kk], acc);
-                }
-            }
-            hist[NT - 1][w] = to_half4(acc);
-        }
-        const int s = q - (NT - 1);                       // output step completed by this tile
-        if (s >= 0) {
-            const int yo = Y0 + 16 * s + c;
-            floatx4 acc[NW];
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                acc[w] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int j = 0; j < NK; ++j) {
-                    const half4 lo = hist[2 * j][w];
-                    const half4 hi = (2 * j + 1 < NT) ? hist[2 * j + 1][w] : half4{0, 0, 0, 0};
-                    acc[w] = mfma16x16x32(join(lo, hi), coefy[j], acc[w]);
-                }
-            }
-            if (XIN) {
-                if (Y0 + 16 * s + 16 <= p.H) {
-                    store_rows_via_lds<NW, STREAM>(patch, dst + (int64_t)(Y0 + 16 * s) * p.out_pitch,
-                                                   (uint32_t)p.out_pitch, acc, (g << 4) | c);
-                } else if (yo < p.H) {
-                    const uint32_t off = ((uint32_t)yo * (uint32_t)p.out_pitch + 4u * g) * 4u;
-#pragma unroll
-                    for (int w = 0; w < NW; ++w) stg4<STREAM>(dst, off + 64u * w, acc[w]);
-                }
-            } else if (yo < p.H) {
-                float* orow = p.out + (int64_t)yo * p.out_pitch;
-#pragma unroll
-                for (int w = 0; w < NW; ++w) {
-                    const int xo = x0 + 16 * w + 4 * g;
-                    if (xo < p.W) store4_mask(orow, xo, p.W, acc[w]);
-                }
-            }
-        }
-#pragma unroll
-        for (int w = 0; w < NW; ++w)
-#pragma unroll
-            for (int kk = 0; kk < NKX; ++kk) cur[w][kk] = nxt[w][kk];
-    }
-}
 
 // Coefficient fragments, read from the tap tables in the kernel arguments: coefx[kk] = B operand of the
 // row pass, Bx[32 kk + 8g + i][c]; coefy[j] = B operand of the column pass in the chained slot order.
@@ -187,43 +60,53 @@ __device__ __forceinline__ void sep_fragments(const SepArgs& p, int c, int g, ha
         for (int i = 0; i < 8; ++i) coefy[j][i] = tap_at(p.ty.tab, 32 * j + krow32(g, i) - c);
 }
 
-// Short task for the common case (one window per tile, up to three row tiles under an output tile):
-// a strip of NW tiles x NS output steps whose NS + NT - 1 row tiles are ALL requested before the
-// first product.  A wave then lives for one memory round trip plus its arithmetic, and what keeps
+// One window per tile (up to 17 taps along x).  A wave requests ALL its row tiles before the
+// first product.  It then lives for one memory round trip plus its arithmetic, and what keeps
 // the memory system busy is the number of such waves in flight (the dispatcher refills as they
 // leave) rather than a chain of dependent steps inside one long-lived wave, each waiting for the
-// one tile it has in flight.  Interior strips only (plain fragment, full tiles); rows are clamped
-// per lane and rows beyond the image are not stored.
-template <int NT, int NS, bool STREAM>
-__device__ __forceinline__ void sep_task_short(const SepArgs& p, float* patch,
-                                               int x0, int Y0, int xw, int c, int g) {
+// one tile it has in flight.  INSIDE: every window of the strip lies inside the row and every tile is full.
+// The other strips load what reaches over the row's ends from an address moved inside and shift it into
+// place in registers, which is the column clamp itself (with the clamp folded into per-tile coefficients
+// instead, whose tables every lane gathered from the kernel arguments, a border strip took 15 us whatever the
+// image size).  Rows are clamped per lane and rows beyond the image are not stored.
+template <int NT, int NS, bool INSIDE>
+__device__ __forceinline__ void sep_task(const SepArgs& p, float* patch, int x0, int Y0, int xw, int lane) {
     constexpr int NW = HB_SEP_TILES, NL = NS + NT - 1, NK = (NT + 1) / 2;
-    const half_t* src = p.in + (x0 - xw);                 // uniform; lanes add row * pitch + 8g
-    float* dst = p.out + x0;
+    const int c = lane & 15, g = lane >> 4;
+    const half_t* src = p.in + (INSIDE ? x0 - xw : 0);    // uniform; lanes add row * pitch + 8g
     half8 px[NL][NW];
 #pragma unroll
     for (int q = 0; q < NL; ++q) {
         const int yr = clampi(Y0 - p.ay + 16 * q + c, 0, p.H - 1);
-        const uint32_t off = ((uint32_t)yr * (uint32_t)p.in_pitch + 8u * g) * 2u;
+        const uint32_t off = (uint32_t)yr * (uint32_t)p.in_pitch * 2u;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) px[q][w] = ldg8(src, off + 32u * w);
+        for (int w = 0; w < NW; ++w) {
+            const int xs = 16 * w + 8 * g;
+            px[q][w] = ldg8(src, off + 2u * (uint32_t)(INSIDE ? xs : clampi(x0 - xw + xs, 0, p.W - 8)));
+        }
     }
     // The tap tables are read only now: a wave that waited for them first would put a memory round
     // trip in front of its pixel requests.
     __builtin_amdgcn_sched_barrier(0);
-    half8 coefx1[1], coefy[NK];
-    sep_fragments<1, NK>(p, c, g, coefx1, coefy);
-    const half8 coefx = coefx1[0];
+    half8 coefx[1], coefy[NK];
+    sep_fragments<1, NK>(p, c, g, coefx, coefy);
     half4 h[NL][NW];                                      // row-filtered tiles, rounded to fp16
 #pragma unroll
     for (int q = 0; q < NL; ++q) {
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
+            half8 v = px[q][w];
+            if (!INSIDE) {
+                const int xs = x0 - xw + 16 * w + 8 * g;
+                v = shift_in_from_right(v, max(xs - (p.W - 8), 0));
+                v = shift_in_from_left(v, max(-xs, 0));
+            }
             const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-            h[q][w] = to_half4(mfma16x16x32(px[q][w], coefx, zero));
+            h[q][w] = to_half4(mfma16x16x32(v, coefx[0], zero));
         }
         if (q < NT - 1) continue;
-        const int s = q - (NT - 1);                       // output step completed by this tile
+        const int s = q - (NT - 1), R = Y0 + 16 * s;      // output step completed by this tile
+        if (R >= p.H) break;                              // uniform
         floatx4 acc[NW];
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
@@ -235,59 +118,147 @@ __device__ __forceinline__ void sep_task_short(const SepArgs& p, float* patch,
                 acc[w] = mfma16x16x32(join(lo, hi), coefy[j], acc[w]);
             }
         }
-        if (Y0 + 16 * s + 16 <= p.H) {
-            store_rows_via_lds<NW, STREAM>(patch, dst + (int64_t)(Y0 + 16 * s) * p.out_pitch,
-                                           (uint32_t)p.out_pitch, acc, (g << 4) | c);
-        } else {
-            const int yo = Y0 + 16 * s + c;
-            if (yo < p.H) {
-                const uint32_t off = ((uint32_t)yo * (uint32_t)p.out_pitch + 4u * g) * 4u;
+        float* const dst = p.out + (int64_t)R * p.out_pitch + x0;
+        if (INSIDE && R + 16 <= p.H) store_rows_via_lds<NW, true>(patch, dst, (uint32_t)p.out_pitch, acc, lane);
+        else store_rows_via_lds_masked<NW, true>(patch, dst, p.out_pitch, acc, lane, p.H - R, p.W - x0);
+    }
+}
+constexpr int kSepMinWidth = 8;               // of an image for those loads
+
+template <int NT, int NS>
+__global__ void __launch_bounds__(256) sepblur_mfma_kernel(SepArgs p) {
+    __shared__ __attribute__((aligned(16))) float s_patch[4][RowPatch<HB_SEP_TILES>::kFloats];
+    const int lane = threadIdx.x & 63;
+    const int xw = p.ax + (p.ax & 1);         // window start, left of the tile
+    // of every 32 workgroups an XCD takes four neighbours (measured on 4096 x 4096 / 8192 x 8192: this
+    // order 24.1 / 84.7 us, one contiguous eighth of the tasks per XCD 24.2 / 97.7, plain order 26.4 / 87.3)
+    const int task = __builtin_amdgcn_readfirstlane(xcd_blocked(blockIdx.x, gridDim.x, 4) * 4 + (threadIdx.x >> 6));
+    if (task >= p.nct * p.nseg) return;
+    const int seg = task / p.nct, ct = task - seg * p.nct;
+    const int x0 = 16 * HB_SEP_TILES * ct, Y0 = 16 * NS * seg;
+    float* patch = s_patch[threadIdx.x >> 6];
+    if (ct >= p.c0 && ct < p.c1) sep_task<NT, NS, true>(p, patch, x0, Y0, xw, lane);
+    else sep_task<NT, NS, false>(p, patch, x0, Y0, xw, lane);
+}
+
+// Two or three windows per tile (18 to 64 taps along x).  Straight from memory every pixel would be requested
+// NKX times along x, by loads that touch 16 rows each; here a workgroup of four strips marches down 128
+// columns, the pixels under them pass through LDS (two row tiles, clamped when they are requested; row pitch an
+// odd multiple of 16 bytes: conflict-free), and the windows are LDS reads.  Three row tiles are in flight
+// in registers; NT filtered ones are kept.  128 registers, four workgroups per compute unit (three: 29 us
+// instead of 19 at 4096 x 4096, 31 taps).  4096 x 4096 with 31 / 64 taps 28.2 / 41.7 -> 19.0 / 22.3 us, a copy of the
+// same bytes 18.3; all its pixels staged before the first product, four workgroups of 64 rows deep, 34.6 / 53.
+constexpr int kSepMarchCols = 4 * 16 * HB_SEP_TILES;
+constexpr int kSepAhead = 3;
+template <int NKX>
+struct SepMarch {
+    static constexpr int kChunks = (kSepMarchCols - 16 + 32 * NKX) / 8;   // of 8 pixels, per row
+    static constexpr int kPitch = 8 * (kChunks | 1);
+};
+// LDS written by this workgroup is there for all of it; loads from memory stay in flight (the compiler puts a
+// wait for everything in front of a barrier it emits).
+__device__ __forceinline__ void sep_lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+template <int NKX, int NT, bool FULL>
+__device__ __forceinline__ void sep_march(const SepArgs& p, half_t* s_px, float* patch, int x0, int Y0, int nsteps, int lane, int wv) {
+    using S = SepMarch<NKX>;
+    constexpr int NW = HB_SEP_TILES, NK = (NT + 1) / 2, kPieces = (16 * S::kChunks + 255) / 256;
+    const int c = lane & 15, g = lane >> 4, tid = threadIdx.x;
+    const int xw = x0 - p.ax - (p.ax & 1);                // first pixel staged
+    const half_t* const src = p.in + (FULL ? xw : 0);
+    const int ntiles = nsteps + NT - 1;
+    int prow[kPieces], pcol[kPieces];
 #pragma unroll
-                for (int w = 0; w < NW; ++w) stg4<STREAM>(dst, off + 64u * w, acc[w]);
-            }
+    for (int u = 0; u < kPieces; ++u) {
+        const int i = min(tid + 256 * u, 16 * S::kChunks - 1);        // the last threads repeat the last piece
+        prow[u] = i / S::kChunks;
+        pcol[u] = 8 * (i - prow[u] * S::kChunks);
+    }
+    auto load_tile = [&](int q, half8 (&v)[kPieces]) {
+#pragma unroll
+        for (int u = 0; u < kPieces; ++u) {
+            const int yr = clampi(Y0 - p.ay + 16 * min(q, ntiles - 1) + prow[u], 0, p.H - 1);
+            const uint32_t off = (uint32_t)yr * (uint32_t)p.in_pitch + (uint32_t)(FULL ? pcol[u] : clampi(xw + pcol[u], 0, p.W - 8));
+            v[u] = ldg8(src, 2u * off);
         }
+    };
+    half8 ahead[kSepAhead][kPieces];
+#pragma unroll
+    for (int d = 0; d < kSepAhead; ++d) load_tile(d, ahead[d]);
+    half8 coefx[NKX], coefy[NK];
+    sep_fragments<NKX, NK>(p, c, g, coefx, coefy);
+    half4 h[NT][NW];                                      // row-filtered tiles q - NT + 1 .. q, rounded to fp16
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int w = 0; w < NW; ++w) h[t][w] = half4{0, 0, 0, 0};
+    auto tile = [&](int q) {
+        half_t* const buf = s_px + (q & 1) * 16 * S::kPitch;
+#pragma unroll
+        for (int u = 0; u < kPieces; ++u) {
+            half8 v = ahead[0][u];
+            if (!FULL) {                                  // see sep_task
+                v = shift_in_from_right(v, max(xw + pcol[u] - (p.W - 8), 0));
+                v = shift_in_from_left(v, max(-xw - pcol[u], 0));
+            }
+            *reinterpret_cast<half8*>(buf + prow[u] * S::kPitch + pcol[u]) = v;
+        }
+#pragma unroll
+        for (int d = 0; d + 1 < kSepAhead; ++d)
+#pragma unroll
+            for (int u = 0; u < kPieces; ++u) ahead[d][u] = ahead[d + 1][u];
+        load_tile(q + kSepAhead, ahead[kSepAhead - 1]);
+        sep_lds_barrier();                                // also: nobody reads the other buffer any more
+#pragma unroll
+        for (int t = 0; t + 1 < NT; ++t)
+#pragma unroll
+            for (int w = 0; w < NW; ++w) h[t][w] = h[t + 1][w];
+        const half_t* const px = buf + c * S::kPitch + 16 * NW * wv + 8 * g;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kk = 0; kk < NKX; ++kk)
+                acc = mfma16x16x32(*reinterpret_cast<const half8*>(px + 16 * w + 32 * kk), coefx[kk], acc);
+            h[NT - 1][w] = to_half4(acc);
+        }
+    };
+#pragma unroll
+    for (int q = 0; q < NT - 1; ++q) tile(q);
+#pragma unroll 1
+    for (int s = 0; s < nsteps; ++s) {
+        tile(s + NT - 1);
+        const int R = Y0 + 16 * s;
+        floatx4 acc[NW];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            acc[w] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < NK; ++j)
+                acc[w] = mfma16x16x32(join(h[2 * j][w], 2 * j + 1 < NT ? h[2 * j + 1 < NT ? 2 * j + 1 : 0][w] : half4{0, 0, 0, 0}), coefy[j], acc[w]);
+        }
+        const int x = x0 + 16 * NW * wv;
+        float* const dst = p.out + (int64_t)R * p.out_pitch + x;
+        if (FULL) store_rows_via_lds<NW, true>(patch, dst, (uint32_t)p.out_pitch, acc, lane);
+        else if (x < p.W) store_rows_via_lds_masked<NW, true>(patch, dst, p.out_pitch, acc, lane, p.H - R, p.W - x);
     }
 }
 
-// Short tasks come in two lengths: 8 output steps while that still leaves the image in one resident
-// round of waves (4096 x 4096: 4096 waves; measured 24 us against 27 us with 4 steps), else 4 steps
-// (8192 x 8192: 98 us against 107 us).  NS = 0 selects the walking task.
-constexpr bool sep_short_ok(int nkx, int nt) { return nkx == 1 && nt <= 3; }
-constexpr int kSepOneRoundWaves = 4608;
-
-template <int NKX, int NT, bool STREAM, int NS = 0>
-__global__ void __launch_bounds__(256) sepblur_mfma_kernel(SepArgs p) {
-    constexpr int NK = (NT + 1) / 2;          // K = 32 chunks of the column pass
-    constexpr int NW = HB_SEP_TILES;
+template <int NKX, int NT>
+__global__ void __launch_bounds__(256, 4) sepblur_march_mfma_kernel(SepArgs p) {
+    using S = SepMarch<NKX>;
+    __shared__ __attribute__((aligned(16))) half_t s_px[2 * 16 * S::kPitch];
     __shared__ __attribute__((aligned(16))) float s_patch[4][RowPatch<HB_SEP_TILES>::kFloats];
-
-    const int lane = threadIdx.x & 63;
-    const int c = lane & 15, g = lane >> 4;
-
-    const int e = p.ax & 1;
-    const int xw = p.ax + e;                  // window start, left of the tile
-    // of every 32 workgroups an XCD takes four neighbours (measured on 4096 x 4096 / 8192 x 8192: this
-    // order 24.1 / 84.7 us, one contiguous eighth of the tasks per XCD 24.2 / 97.7, plain order 26.4 / 87.3)
-    const int wgpos = xcd_blocked(blockIdx.x, gridDim.x, 4);
-    const int wave = __builtin_amdgcn_readfirstlane(wgpos * 4 + (threadIdx.x >> 6));
-    const int nwaves = (gridDim.x * blockDim.x) >> 6;
-    const int ntasks = p.grid.count();
-    for (int task = wave; task < ntasks; task += nwaves) {
-        const int seg = task / p.grid.nct, ct = task - seg * p.grid.nct;
-        const int x0 = 16 * NW * ct;
-        const int Y0 = seg * p.steps * 16;
-        const int nsteps = min(p.steps, (p.H - Y0 + 15) / 16);
-        if constexpr (NS > 0) {
-            if (p.grid.interior(seg, ct)) {   // builds its fragments itself, AFTER its pixel loads are on their way
-                sep_task_short<NT, NS, STREAM>(p, s_patch[threadIdx.x >> 6], x0, Y0, xw, c, g);
-                continue;
-            }
-        }
-        half8 coefx[NKX], coefy[NK];
-        sep_fragments<NKX, NK>(p, c, g, coefx, coefy);
-        if (p.grid.interior(seg, ct)) sep_task<NKX, NT, NW, true, STREAM>(p, p.foldx, s_patch[threadIdx.x >> 6], coefx, coefy, x0, Y0, nsteps, xw, c, g);
-        else sep_task<NKX, NT, NW, false, STREAM>(p, p.foldx, s_patch[threadIdx.x >> 6], coefx, coefy, x0, Y0, nsteps, xw, c, g);
-    }
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int task = xcd_blocked(blockIdx.x, gridDim.x, 4);
+    const int seg = task / p.nct, ct = task - seg * p.nct;
+    const int x0 = kSepMarchCols * ct, Y0 = 16 * p.steps * seg;
+    const int nsteps = min(p.steps, (p.H - Y0 + 15) / 16);
+    const int xw = x0 - p.ax - (p.ax & 1);
+    if (xw >= 0 && xw + 8 * S::kChunks <= p.W && Y0 + 16 * nsteps <= p.H)
+        sep_march<NKX, NT, true>(p, s_px, s_patch[wv], x0, Y0, nsteps, lane, wv);
+    else
+        sep_march<NKX, NT, false>(p, s_px, s_patch[wv], x0, Y0, nsteps, lane, wv);
 }
 
 // ---------------------------------------------------------------------------
@@ -400,57 +371,48 @@ static hb_status sep_prepare(SepArgs& a, const hb_half* in, float* out, int H, i
     a.ax = ax;
     a.Ty = nty;
     a.ay = ay;
-    const int nct = ceil_div(W, 16 * HB_SEP_TILES);
-    const int rowsteps = ceil_div(H, 16);
-    // enough tasks to fill the chip, few enough that the (NT-1)-tile warm-up stays small; the short
-    // tasks of the common case have a fixed length
-    const int nkx0 = ceil_div(15 + ntx + (ax & 1), 32);
-    int steps = (int)(((int64_t)rowsteps * nct + HB_SEP_WAVES - 1) / HB_SEP_WAVES);
-    steps = steps < 1 ? 1 : steps;
-    if (sep_short_ok(nkx0, (nty + 30) / 16))
-        steps = (int64_t)ceil_div(rowsteps, 8) * nct <= kSepOneRoundWaves ? 8 : 4;
-    a.steps = steps;
-    a.grid.nct = nct;
-    a.grid.nseg = ceil_div(rowsteps, steps);
-    // a strip is interior when all its windows lie inside the row and its tiles are full;
-    // rows are clamped per lane in both kernels
-    const int xw = ax + (ax & 1);
-    const int nkx = ceil_div(15 + ntx + (ax & 1), 32);
-    const int after = 16 * (HB_SEP_TILES - 1) - xw + 32 * nkx;
-    interior_range(nct, 16 * HB_SEP_TILES, xw, after > 16 * HB_SEP_TILES ? after : 16 * HB_SEP_TILES, W,
-                   a.grid.c0, a.grid.c1);
-    a.grid.s0 = 0;
-    a.grid.s1 = a.grid.c1 > a.grid.c0 ? a.grid.nseg : 0;
+    a.nct = a.nseg = a.steps = a.c0 = a.c1 = 0;
     a.tx = pack_taps(tx, ntx);
     a.ty = pack_taps(ty, nty);
-    a.foldx = pack_fold_tables(tx, ntx);
     return HB_OK;
 }
 
-template <int NKX, int NT, bool STREAM>
-static void sep_launch2(hipStream_t st, const SepArgs& a) {
-    const dim3 grid(min(ceil_div(a.grid.count(), 4), kMaxStreamBlocks));
-    if constexpr (sep_short_ok(NKX, NT)) {
-        if (a.steps == 8) hipLaunchKernelGGL((sepblur_mfma_kernel<NKX, NT, STREAM, 8>), grid, dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((sepblur_mfma_kernel<NKX, NT, STREAM, 4>), grid, dim3(256), 0, st, a);
-    } else {
-        hipLaunchKernelGGL((sepblur_mfma_kernel<NKX, NT, STREAM, 0>), grid, dim3(256), 0, st, a);
-    }
+template <class K>
+static hb_status sep_launch(K kernel, hipStream_t st, SepArgs& a, int ns, int cols, int per_wg) {
+    a.nct = ceil_div(a.W, cols);
+    a.steps = ns;
+    a.nseg = ceil_div(a.H, 16 * ns);
+    const int64_t tasks = (int64_t)a.nct * a.nseg;
+    if (tasks > 0x7fffffff) return HB_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((tasks + per_wg - 1) / per_wg)), dim3(256), 0, st, a);
+    return launch_status();
 }
-template <int NKX, bool STREAM>
-static void sep_launch_nt(int nt, hipStream_t st, const SepArgs& a) {
-    switch (nt) {
-        case 1: sep_launch2<NKX, 1, STREAM>(st, a); break;
-        case 2: sep_launch2<NKX, 2, STREAM>(st, a); break;
-        case 3: sep_launch2<NKX, 3, STREAM>(st, a); break;
-        case 4: sep_launch2<NKX, 4, STREAM>(st, a); break;
-        default: sep_launch2<NKX, 5, STREAM>(st, a); break;
+// One window per tile: 8 output steps per task while that leaves the image in one resident round of waves
+// (4096 x 4096: 4096 waves) and for the filters whose NT - 1 extra row tiles weigh most, else 4
+// (8192 x 4096, 16 taps: 33.3 us against 34.0).
+constexpr int kSepOneRoundWaves = 4608;
+template <int NT>
+static hb_status sep_launch_one_window(hipStream_t st, SepArgs& a) {
+    // a strip is interior when all its windows lie inside the row and its tiles are full
+    constexpr int cols = 16 * HB_SEP_TILES;
+    const int xw = a.ax + (a.ax & 1), nct = ceil_div(a.W, cols);
+    const int after = cols - 16 - xw + 32;
+    interior_range(nct, cols, xw, after > cols ? after : cols, a.W, a.c0, a.c1);
+    if constexpr (NT <= 3) {
+        if ((int64_t)ceil_div(a.H, 128) * nct > kSepOneRoundWaves)
+            return sep_launch(sepblur_mfma_kernel<NT, 4>, st, a, 4, cols, 4);
     }
+    return sep_launch(sepblur_mfma_kernel<NT, 8>, st, a, 8, cols, 4);
 }
-template <int NKX>
-static void sep_launch(bool stream_stores, int nt, hipStream_t st, const SepArgs& a) {
-    if (stream_stores) sep_launch_nt<NKX, true>(nt, st, a);
-    else sep_launch_nt<NKX, false>(nt, st, a);
+template <int NT>
+static hb_status sep_launch_nt(int nkx, hipStream_t st, SepArgs& a) {
+    if (nkx == 1) return sep_launch_one_window<NT>(st, a);
+    // four workgroups per compute unit are resident; segments beyond 8 steps only cost balance (8192 x 4096, 48
+    // taps: 36 us with 8 steps, 42 with the 16 that four workgroups per unit would give)
+    const int64_t rowsteps = ceil_div(a.H, 16), nct = ceil_div(a.W, kSepMarchCols), want = 4 * num_cu();
+    const int steps = (int)std::min<int64_t>((rowsteps * nct + want - 1) / want, 8);
+    if (nkx == 2) return sep_launch(sepblur_march_mfma_kernel<2, NT>, st, a, steps, kSepMarchCols, 1);
+    return sep_launch(sepblur_march_mfma_kernel<3, NT>, st, a, steps, kSepMarchCols, 1);
 }
 
 }  // namespace hb
@@ -469,20 +431,18 @@ extern "C" hb_status hb_sepblur(const hb_half* in, float* out, int H, int W,
     hb_status s = sep_prepare(a, in, out, H, W, in_pitch, out_pitch, taps_x_host, ntaps_x, anchor_x,
                               taps_y_host, ntaps_y, anchor_y);
     if (s != HB_OK) return s;
-    const int nkx = ceil_div(15 + ntaps_x + (anchor_x & 1), 32);
-    if (W < 32 * nkx)   // narrower than one window of the matrix formulation: vector-ALU kernel
+    const int nkx = ceil_div(15 + ntaps_x + (anchor_x & 1), 32);          // 1 .. 3
+    if (W < kSepMinWidth)
         return hb_sepblur_valu(in, out, H, W, in_pitch, out_pitch, taps_x_host, ntaps_x, anchor_x,
                                taps_y_host, ntaps_y, anchor_y, stream);
-    const int nt = (ntaps_y + 30) / 16;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    const bool ss = (int64_t)H * W * 4 <= kStreamStoreMaxBytes;
-    switch (nkx) {
-        case 1: sep_launch<1>(ss, nt, st, a); break;
-        case 2: sep_launch<2>(ss, nt, st, a); break;
-        case 3: sep_launch<3>(ss, nt, st, a); break;
-        default: return HB_ERR_UNSUPPORTED;
+    switch ((ntaps_y + 30) / 16) {
+        case 1: return sep_launch_nt<1>(nkx, st, a);
+        case 2: return sep_launch_nt<2>(nkx, st, a);
+        case 3: return sep_launch_nt<3>(nkx, st, a);
+        case 4: return sep_launch_nt<4>(nkx, st, a);
+        default: return sep_launch_nt<5>(nkx, st, a);
     }
-    return launch_status();
 }
 
 extern "C" hb_status hb_sepblur_valu(const hb_half* in, float* out, int H, int W,

@@ -48,6 +48,16 @@ def test_sepblur_matches_oracle(orc, fn, H, W, Tx, ax, Ty, ay):
     assert_close(got, orc.sepblur(img, tx, ax, ty, ay), f"{fn} {H}x{W}")
 
 
+@pytest.mark.parametrize("Tx,ax,Ty,ay", [(17, 16, 31, 0), (16, 1, 50, 20), (18, 0, 17, 8), (31, 30, 33, 32), (49, 24, 64, 31),
+                                         (64, 63, 2, 1)])
+@pytest.mark.parametrize("H,W", [(15, 7), (40, 8), (1, 33), (145, 127), (128, 129), (37, 160)])
+def test_sepblur_windows_over_both_row_ends(orc, H, W, Tx, ax, Ty, ay):
+    """Images about as wide as a window, a strip or a workgroup's 128 columns, every filter length's kernel."""
+    img, tx, ty, got, obuf = run("hb_sepblur", H, W, Tx, ax, Ty, ay, pitch_extra=1)
+    assert_close(got, orc.sepblur(img, tx, ax, ty, ay), f"{H}x{W}")
+    assert np.all(obuf[:, W:] == 7.0), "wrote past the row end"
+
+
 @pytest.mark.parametrize("fn", ["hb_sepblur", "hb_sepblur_valu"])
 @pytest.mark.parametrize("extra", [8, 3])
 def test_sepblur_pitched_layouts(orc, fn, extra):
