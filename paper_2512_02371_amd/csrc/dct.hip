@@ -7,13 +7,17 @@
 // The paper keeps the blend as a second launch; here the matrix-unit path blends inside the same
 // kernel (a workgroup owns a patch of the output and accumulates its tiles in LDS), which saves
 // writing and re-reading 1 KB per tile; the vector-ALU twin keeps the two-launch structure with the
-// tiles in the workspace.  The products run on the matrix units in
-// fp32 (v_mfma_f32_16x16x4_f32, four instructions per product): DCT coefficients reach 16 times the
-// pixel range, so fp16 intermediates would cost about 1e-3 of absolute accuracy per rounding, and the
-// products are far too small for the precision to matter for speed.  A product leaves its result
-// with a lane owning four ROWS of one column while the next product needs that matrix as an operand
-// indexed the other way round, so each of the three hand-overs goes through a wave-private 16 x 17
-// LDS tile.
+// tiles in the workspace.  What the products hand on stays fp32: DCT coefficients reach 16 times the
+// pixel range, so fp16 intermediates would cost about 1e-3 of absolute accuracy per rounding.
+//
+// Every product contracts over the ROW index of what the one before left in its accumulators (lane
+// (c, g) holds rows 4g + j of column c), with the accumulators as the A operand: instruction j of the
+// next product (K = 4) takes register j as it is, if slot g of its B operand stands for row 4g + j.  The
+// result's rows are the old columns, so the next product contracts over the other axis:
+//     Q[r][v] = sum_x P[r][x] E[v][x]     Y[v][u] = sum_r Q[r][v] E[u][r]        (E[u][i] = D[u][i] w[i])
+//     R[u][x] = sum_v Y[v][u] E[v][x]     rec[x][r] = sum_u R[u][x] E[u][r]
+// No transpose and no LDS between the four, and rec ends with four consecutive pixels of a row per lane.
+// The windows are part of E.
 #include <math.h>
 
 #include "hb_device.hpp"
@@ -33,6 +37,7 @@ struct DctArgs {
     float threshold;
     float d[256];                             // D[u][i], orthonormal DCT-II, row-major
     float w[16];                              // sine window
+    float e[256];                             // E[u][i] = D[u][i] w[i]
 };
 
 __device__ __forceinline__ void dct_wave_sync() {
@@ -63,28 +68,29 @@ __device__ __forceinline__ void dct_tile_origin(const DctArgs& p, int64_t t, int
 // back.  Tiles overlap their neighbours at stride 8, tiles at stride 16 do not: the tiles are taken in
 // four rounds by the parity of their (row, column) index, within a round the waves add to disjoint
 // pixels with plain loads and stores, and the order of the four additions into a pixel is fixed.
-constexpr int kDfPatch = 64;
-constexpr int kDfPitch = kDfPatch + 4;        // rows 4 apart fall into different banks
+//
+// What bounds it: the fp32 products, 12 x 32 cycles a tile and SIMD (the first product, whose pixels are
+// fp16, is one K = 32 product with E as fp16 hi + lo parts instead of four more), 1.27x for the rim tiles
+// of 64 x 64 patches.  3 x 1024 x 1024: 33.0 -> 23.8 us against four fp32 products with an LDS transpose between
+// each two; 61 tiles a SIMD x 400 cycles of products are 12 us of it.
 constexpr int kDfWaves = 8;
-constexpr int kDfRegion = kDfPatch + 16;      // pixels under the tiles of a patch, per axis
-constexpr int kDfPxPitch = kDfRegion + 8;     // 88 halves: 16 consecutive rows fall into 16 different banks
+template <int PATCH>
+struct DfGeom {
+    static constexpr int kPitch = PATCH + 4;              // 16 rows of a tile: 16-byte pieces in different banks
+    static constexpr int kRegion = PATCH + 16;            // pixels under the tiles of a patch, per axis
+    static constexpr int kPxPitch = kRegion + 8;
+};
+constexpr float kDfScale = 1024.f;                        // of the first product's E: keeps its low part a normal fp16 number
 
+template <int PATCH>
 __global__ void __launch_bounds__(64 * kDfWaves) dct_fused_mfma_kernel(DctArgs p) {
-    __shared__ float s_tile[kDfWaves][16 * kDctPitch];
-    __shared__ __attribute__((aligned(16))) float s_acc[kDfPatch * kDfPitch];
-    __shared__ __attribute__((aligned(16))) half_t s_px[kDfRegion * kDfPxPitch];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    using G = DfGeom<PATCH>;
+    __shared__ __attribute__((aligned(16))) float s_acc[PATCH * G::kPitch];
+    __shared__ __attribute__((aligned(16))) half_t s_px[G::kRegion * G::kPxPitch];
+    __shared__ float s_w2[16];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 15, g = lane >> 4;
-    float* tile = s_tile[wv];
-    float dlk[4], dkl[4], win[4], wout[4];
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-        dlk[kk] = p.d[c * 16 + 4 * kk + g];
-        dkl[kk] = p.d[(4 * kk + g) * 16 + c];
-        win[kk] = p.w[c] * p.w[4 * kk + g];
-        wout[kk] = p.w[4 * g + kk] * p.w[c];
-    }
-    const int npx = (p.W + kDfPatch - 1) / kDfPatch, npy = (p.H + kDfPatch - 1) / kDfPatch;
+    const int npx = (p.W + PATCH - 1) / PATCH, npy = (p.H + PATCH - 1) / PATCH;
     // every XCD takes one contiguous run of the patches: the 8-pixel rims that neighbouring patches share
     // (whole 128-byte lines in memory) are fetched into one L2 once (measured reads 1.05x the image
     // instead of 2.9x)
@@ -92,101 +98,85 @@ __global__ void __launch_bounds__(64 * kDfWaves) dct_fused_mfma_kernel(DctArgs p
     const int pc = wg % npx;
     wg /= npx;
     const int pr = wg % npy, plane = wg / npy;
-    const int py0 = kDfPatch * pr, px0 = kDfPatch * pc;
-    for (int i = threadIdx.x; i < kDfPatch * kDfPitch; i += 64 * kDfWaves) s_acc[i] = 0.f;
-    // the pixels under every tile of the patch: rows py0 - 8 .. py0 + 71, columns px0 - 8 .. px0 + 71
+    const int py0 = PATCH * pr, px0 = PATCH * pc;
+    // the pixels under every tile of the patch: rows py0 - 8 .. py0 + PATCH + 7, columns px0 - 8 .. px0 + PATCH + 7
     // (what lies outside the image is under no tile and is never read)
     {
         const half_t* plane_px = p.in + (int64_t)plane * p.in_plane;
-        for (int i = threadIdx.x; i < kDfRegion * (kDfRegion / 8); i += 64 * kDfWaves) {
-            const int r = i / (kDfRegion / 8), ch = i - r * (kDfRegion / 8);
+        for (int i = threadIdx.x; i < G::kRegion * (G::kRegion / 8); i += 64 * kDfWaves) {
+            const int r = i / (G::kRegion / 8), ch = i - r * (G::kRegion / 8);
             const int y = py0 - 8 + r, x = px0 - 8 + 8 * ch;
             if (y >= 0 && y < p.H && x >= 0 && x < p.W)       // W is a multiple of 8: whole chunks
-                *reinterpret_cast<half8*>(&s_px[r * kDfPxPitch + 8 * ch]) =
+                *reinterpret_cast<half8*>(&s_px[r * G::kPxPitch + 8 * ch]) =
                     *reinterpret_cast<const half8_u*>(plane_px + (int64_t)y * p.in_pitch + x);
         }
     }
+    for (int i = threadIdx.x; i < PATCH * G::kPitch / 4; i += 64 * kDfWaves)
+        *reinterpret_cast<floatx4*>(&s_acc[4 * i]) = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (threadIdx.x < 16) s_w2[threadIdx.x] = p.w[threadIdx.x] * p.w[threadIdx.x];
+    half8 e1;                                 // E[c][4g + j] as hi (slots 0..3) and lo (4..7): the slots share a pixel
+    float ef[4], eb[4];                       // E[c][4g + j] (undoing the scale of the first product), E[4g + j][c]
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float v = kDfScale * p.e[c * 16 + 4 * g + j];
+        e1[j] = (half_t)v;
+        e1[4 + j] = (half_t)(v - (float)e1[j]);
+        ef[j] = (1.f / kDfScale) * p.e[c * 16 + 4 * g + j];
+        eb[j] = p.e[(4 * g + j) * 16 + c];
+    }
+    const float cut0 = c == 0 && g == 0 ? -1.f : p.threshold;   // the DC bin always stays
+    const int lane_px = (c + 8 - py0) * G::kPxPitch + 4 * g + 8 - px0, lane_acc = (c - py0) * G::kPitch + 4 * g - px0;
     // tiles (ty, tx), origin (8 ty, 8 tx), that overlap the patch
-    const int ty_lo = max(py0 / 8 - 1, 0), ty_hi = min(py0 / 8 + kDfPatch / 8 - 1, p.nty - 1);
-    const int tx_lo = max(px0 / 8 - 1, 0), tx_hi = min(px0 / 8 + kDfPatch / 8 - 1, p.ntx - 1);
+    const int ty_lo = max(py0 / 8 - 1, 0), ty_hi = min(py0 / 8 + PATCH / 8 - 1, p.nty - 1);
+    const int tx_lo = max(px0 / 8 - 1, 0), tx_hi = min(px0 / 8 + PATCH / 8 - 1, p.ntx - 1);
     __syncthreads();
     for (int round = 0; round < 4; ++round) {
         const int ty0 = ty_lo + ((ty_lo ^ (round >> 1)) & 1), tx0 = tx_lo + ((tx_lo ^ round) & 1);
         const int ny = ty0 <= ty_hi ? (ty_hi - ty0) / 2 + 1 : 0, nx = tx0 <= tx_hi ? (tx_hi - tx0) / 2 + 1 : 0;
+        const int inv = nx > 0 ? 65536 / nx + 1 : 0;      // i / nx = i * inv >> 16 for the few tiles of a round
         for (int i = wv; i < ny * nx; i += kDfWaves) {
-            const int ty = ty0 + 2 * (i / nx), tx = tx0 + 2 * (i % nx);
-            // lane (c = row, g) reads pixels (row, 4 kk + g)
-            const half_t* src = &s_px[(8 * ty - py0 + 8 + c) * kDfPxPitch + 8 * tx - px0 + 8 + g];
-            float px[4];
+            const int row = (i * inv) >> 16;
+            const int ty = ty0 + 2 * row, tx = tx0 + 2 * (i - row * nx);
+            // lane (c = row, g) reads pixels (row, 4g .. 4g + 3)
+            const half4 px = *reinterpret_cast<const half4*>(&s_px[lane_px + 8 * (ty * G::kPxPitch + tx)]);
+            const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+            const floatx4 q = mfma16x16x32(join(px, px), e1, zero);
+            floatx4 y = zero;
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) px[kk] = (float)src[4 * kk] * win[kk];
-            // Q = T D^T
-            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) acc = mfma16x16x4f32(px[kk], dlk[kk], acc);
-            dct_put(tile, acc, c, g);
-            dct_wave_sync();
-            // Y = D Q
-            float b[4];
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) b[kk] = tile[(4 * kk + g) * kDctPitch + c];
-            acc = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) acc = mfma16x16x4f32(dlk[kk], b[kk], acc);
-            // coring: lane (c = v, g) holds Y[4g + j][v]; the DC bin always stays
+            for (int j = 0; j < 4; ++j) y = mfma16x16x4f32(q[j], ef[j], y);
+            // coring: lane (c = u, g) holds bins (u, v = 4g + j)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if (fabsf(acc[j]) < p.threshold && !(c == 0 && g == 0 && j == 0)) acc[j] = 0.f;
-            dct_wave_sync();
-            dct_put(tile, acc, c, g);
-            dct_wave_sync();
-            // R = D^T Y
+                if (fabsf(y[j]) < (j == 0 ? cut0 : p.threshold)) y[j] = 0.f;
+            floatx4 r = zero, rec = zero;
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) b[kk] = tile[(4 * kk + g) * kDctPitch + c];
-            acc = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int j = 3; j >= 0; --j) r = mfma16x16x4f32(y[j], eb[j], r);     // the large low bins last
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) acc = mfma16x16x4f32(dkl[kk], b[kk], acc);
-            dct_wave_sync();
-            dct_put(tile, acc, c, g);
-            dct_wave_sync();
-            // rec = R D
-            float a[4];
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) a[kk] = tile[c * kDctPitch + 4 * kk + g];
-            acc = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) acc = mfma16x16x4f32(a[kk], dkl[kk], acc);
-            dct_wave_sync();
-            // lane (c = col, g) holds rec[4g + j][col]: window again, add the part inside the patch
-            const int xx = 8 * tx + c - px0;
-            if (xx >= 0 && xx < kDfPatch) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int yy = 8 * ty + 4 * g + j - py0;
-                    if (yy >= 0 && yy < kDfPatch) s_acc[yy * kDfPitch + xx] += acc[j] * wout[j];
-                }
+            for (int j = 3; j >= 0; --j) rec = mfma16x16x4f32(r[j], eb[j], rec);
+            // lane (c = row, g) holds pixels 4g .. 4g + 3 of its row: add the part inside the patch
+            const uint32_t xx = 8 * tx - px0 + 4 * g, yy = 8 * ty - py0 + c;
+            if (xx < PATCH && yy < PATCH) {
+                floatx4* const dst = reinterpret_cast<floatx4*>(&s_acc[lane_acc + 8 * (ty * G::kPitch + tx)]);
+                *dst = *dst + rec;
             }
         }
         __syncthreads();
     }
     // out = sum of the windowed reconstructions / sum of the squared windows of the tiles covering the pixel
     // (the tiles covering a pixel are a product set, so the denominator is a product of two 1-D sums)
-    for (int idx = threadIdx.x; idx < kDfPatch * (kDfPatch / 4); idx += 64 * kDfWaves) {
-        const int r = idx / (kDfPatch / 4), q4 = idx - r * (kDfPatch / 4);
+    auto covered = [&](int z, int n) {                    // z / 8 - 1 and z / 8: the tiles over pixel z of an axis of n tiles
+        const int t = z >> 3, i = z & 7;
+        return (t >= 1 ? s_w2[i + 8] : 0.f) + (t < n ? s_w2[i] : 0.f);
+    };
+    for (int idx = threadIdx.x; idx < PATCH * (PATCH / 4); idx += 64 * kDfWaves) {
+        const int r = idx / (PATCH / 4), q4 = idx - r * (PATCH / 4);
         const int y = py0 + r, x = px0 + 4 * q4;
         if (y >= p.H || x >= p.W) continue;
-        float dy = 0.f;
-        for (int ty = y / 8 - 1; ty <= y / 8; ++ty)
-            if (ty >= 0 && ty < p.nty) dy += p.w[y - 8 * ty] * p.w[y - 8 * ty];
-        const floatx4 v = *reinterpret_cast<const floatx4*>(&s_acc[r * kDfPitch + 4 * q4]);
+        const float dy = covered(y, p.nty);
+        const floatx4 v = *reinterpret_cast<const floatx4*>(&s_acc[r * G::kPitch + 4 * q4]);
         floatx4 o;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            float dx = 0.f;
-            for (int tx = (x + q) / 8 - 1; tx <= (x + q) / 8; ++tx)
-                if (tx >= 0 && tx < p.ntx) dx += p.w[x + q - 8 * tx] * p.w[x + q - 8 * tx];
-            o[q] = v[q] / (dy * dx);
-        }
+        for (int q = 0; q < 4; ++q) o[q] = v[q] / (dy * covered(x + q, p.ntx));
         *reinterpret_cast<floatx4_u*>(p.out + (int64_t)plane * p.out_plane + (int64_t)y * p.out_pitch + x) = o;
     }
 }
@@ -309,6 +299,9 @@ static hb_status dct_run(bool valu, const hb_half* in, float* out, int C, int H,
         for (int i = 0; i < 16; ++i)
             a.d[u * 16 + i] = (float)(u == 0 ? 0.25 : sqrt(2.0 / 16.0) * cos(pi * (2.0 * i + 1.0) * u / 32.0));
     for (int i = 0; i < 16; ++i) a.w[i] = (float)sin(pi * (i + 0.5) / 16.0);
+    for (int u = 0; u < 16; ++u)
+        for (int i = 0; i < 16; ++i)
+            a.e[u * 16 + i] = (float)((u == 0 ? 0.25 : sqrt(2.0 / 16.0) * cos(pi * (2.0 * i + 1.0) * u / 32.0)) * sin(pi * (i + 0.5) / 16.0));
 
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     const int64_t ntiles = (int64_t)C * a.nty * a.ntx;
@@ -316,9 +309,15 @@ static hb_status dct_run(bool valu, const hb_half* in, float* out, int C, int H,
     const unsigned blocks = (unsigned)(wgs < 4096 ? wgs : 4096);     // waves stride over the tiles
     if (!valu) {
         // one launch: tiles and blend fused, the workspace stays unused
-        const int64_t patches = (int64_t)C * ceil_div(H, kDfPatch) * ceil_div(W, kDfPatch);
+        // 32 x 32 patches (1.56x the products) while the larger ones would leave compute units idle (512 x 512:
+        // below the host's launch rate of 12.6 us, 17.0 with one workgroup of 64 x 64 on every fourth unit)
+        const int64_t patches = (int64_t)C * ceil_div(H, 64) * ceil_div(W, 64);
+        const int64_t small = (int64_t)C * ceil_div(H, 32) * ceil_div(W, 32);
         if (patches > 0x7fffffff) return HB_ERR_UNSUPPORTED;
-        hipLaunchKernelGGL(dct_fused_mfma_kernel, dim3((unsigned)patches), dim3(64 * kDfWaves), 0, st, a);
+        if (patches < num_cu())
+            hipLaunchKernelGGL(dct_fused_mfma_kernel<32>, dim3((unsigned)small), dim3(64 * kDfWaves), 0, st, a);
+        else
+            hipLaunchKernelGGL(dct_fused_mfma_kernel<64>, dim3((unsigned)patches), dim3(64 * kDfWaves), 0, st, a);
         return launch_status();
     }
     hipLaunchKernelGGL(dct_transform_valu_kernel, dim3(blocks), dim3(64 * kDctWaves), 0, st, a);

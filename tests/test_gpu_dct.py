@@ -96,6 +96,8 @@ def check(orc, got, img, threshold, what, max_masked=0.5):
     (2, 128, 72, 0.2),        # strong coring: most of the noise bins go
     (1, 24, 40, 1000.0),      # only DC survives
     (1, 200, 136, 0.03),
+    (5, 512, 512, 0.05),      # 320 patches of 64 x 64: the larger patch
+    (4, 520, 456, 0.05),      # 288, the last ones of a row and a column in part outside
 ])
 def test_dct_denoise_matches_oracle(orc, fn, C, H, W, thr):
     img = noisy_image(9800 + H + W, C, H, W)
