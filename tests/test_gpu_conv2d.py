@@ -24,6 +24,12 @@ CASES = [
     (16, 64, 16, 16, 7, 7),       # exactly one strip wide: border kernel only
     (48, 128, 16, 16, 7, 7),      # two strips wide
     (31, 1100, 31, 29, 11, 20),
+    (130, 9, 16, 32, 0, 31),      # narrower than a window
+    (129, 65, 17, 18, 16, 0),     # one past the workgroup tile in both directions
+    (127, 63, 32, 17, 1, 16),
+    (5, 65537, 4, 32, 3, 30),     # 513 tiles of 128 x 128: the wider tile
+    (3, 65700, 32, 3, 31, 1),
+    (3, 65600, 1, 1, 0, 0),
 ]
 
 

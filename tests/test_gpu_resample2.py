@@ -24,6 +24,9 @@ DOWN_CASES = [
     (5, 9, 32, 32, 16, 16),       # image smaller than the kernel
     (33, 128, 16, 16, 7, 7),      # exactly one strip of outputs
     (47, 2300, 31, 29, 11, 20),
+    (258, 7, 9, 5, 4, 2),         # narrower than eight pixels
+    (257, 65, 18, 32, 0, 17),     # one past the workgroup tile
+    (259, 70001, 3, 4, 1, 2),     # more tiles than workgroups
 ]
 
 UP_CASES = [
@@ -39,6 +42,9 @@ UP_CASES = [
     (3, 5, 32, 32, 8, 8),         # image smaller than the kernel
     (16, 32, 16, 16, 3, 3),       # exactly one strip
     (31, 550, 30, 28, 5, 10),
+    (65, 7, 8, 18, 3, 8),         # narrower than eight pixels
+    (65, 33, 32, 20, 15, 9),      # one past the workgroup tile
+    (130, 30001, 4, 6, 1, 2),     # more tiles than workgroups
 ]
 
 
