@@ -71,7 +71,7 @@ typedef void *hb_stream;      /* hipStream_t */
 #define HB_MAX_TAPS 64          /* per axis, hb_sepblur */
 #define HB_MAX_TAPS_FIR1D 256   /* hb_fir1d: the large-tap regime of Sec. V-A */
 #define HB_MAX_TAPS_CONV2D 32   /* per axis, hb_conv2d, hb_down2, hb_up2 */
-#define HB_RESIZE_MAX_SPAN 512   /* hb_resize: largest band; input samples of a group handled per round */
+#define HB_RESIZE_MAX_SPAN 512   /* hb_resize: largest band */
 
 /* Human-readable name of a status code (static storage). */
 const char *hb_status_string(hb_status s);
@@ -172,8 +172,9 @@ hb_status hb_sepblur_valu(const hb_half *in, float *out, int H, int W,
  * known width; groups of 16 rows are treated as one dense block):
  *     out[c][yo][xo] = sum_{i < band_y} sum_{j < band_x} coef_y[yo * band_y + i] * coef_x[xo * band_x + j]
  *                      * in[c][clampH(start_y[yo] + i)][clampW(start_x[xo] + j)]
- * The horizontal pass runs first; its result is rounded to fp16 and kept, transposed,
- * in `workspace`.  in: C planes of H x W fp16 (row pitch in_pitch, plane stride in_plane,
+ * The horizontal pass runs first; its result is rounded to fp16 (hb_resize keeps it on the chip
+ * and leaves the workspace untouched unless W < 8; the twin keeps it there, transposed.  Both
+ * check the workspace the same way.)  in: C planes of H x W fp16 (row pitch in_pitch, plane stride in_plane,
  * in elements); out: C planes of Ho x Wo fp32 (out_pitch, out_plane).
  * start_y / start_x: Ho / Wo int32; coef_y / coef_x: Ho x band_y / Wo x band_x fp16,
  * row-major.  All four are DEVICE pointers, read by the kernels on `stream`.
@@ -181,8 +182,8 @@ hb_status hb_sepblur_valu(const hb_half *in, float *out, int H, int W,
  * 256-byte aligned; contents undefined on exit; concurrent calls need their own.
  * 1 <= band <= HB_RESIZE_MAX_SPAN.  Every read is clamped into the image whatever
  * the matrices hold, and any starts are computed correctly: an aligned group of 16
- * outputs whose rows together span more than HB_RESIZE_MAX_SPAN input samples is
- * processed in several rounds of that many samples (slower, same result).
+ * outputs whose rows together span more than a few hundred input samples is
+ * processed in several rounds (slower, same result).
  */
 size_t hb_resize_workspace_size(int C, int H, int Wo);
 hb_status hb_resize(const hb_half *in, float *out, void *workspace, size_t workspace_bytes,

@@ -97,28 +97,30 @@ __device__ __forceinline__ half8 load8_clamp(const half_t* __restrict__ row, int
 // Border windows.  Eight pixels from column xs on, part of them outside the row, are loaded from the
 // nearest column that keeps the load inside (xs - d) and moved afterwards, in registers: one 16-byte
 // load where a pixel-by-pixel load with clamped columns takes eight.  Element i becomes element
-// min(i + d, 7) of the loaded run, d >= 0 (what lies past the last pixel repeats it) ...
+// min(i + d, 7) of the loaded run, d >= 0 (what lies past the last pixel repeats it, or is zero) ...
+template <bool ZERO = false>
 __device__ __forceinline__ half8 shift_in_from_right(half8 v, int d) {
     u32x4 a = __builtin_bit_cast(u32x4, v);
-    const uint32_t t = (a[3] & 0xffff0000u) | (a[3] >> 16);
+    const uint32_t t = ZERO ? 0u : (a[3] & 0xffff0000u) | (a[3] >> 16);
     const u32x4 s8 = {t, t, t, t}, s4 = {a[2], a[3], t, t};
     a = d >= 8 ? s8 : (d & 4) ? s4 : a;
     const u32x4 s2 = {a[1], a[2], a[3], t};
     a = (d & 2) && d < 8 ? s2 : a;
     const u32x4 s1 = {__builtin_amdgcn_alignbit(a[1], a[0], 16), __builtin_amdgcn_alignbit(a[2], a[1], 16),
-                      __builtin_amdgcn_alignbit(a[3], a[2], 16), t};
+                      __builtin_amdgcn_alignbit(a[3], a[2], 16), ZERO ? a[3] >> 16 : t};
     a = (d & 1) && d < 8 ? s1 : a;
     return __builtin_bit_cast(half8, a);
 }
-// ... or element max(i - d, 0) (what lies left of pixel 0 repeats it).
+// ... or element max(i - d, 0) (what lies left of pixel 0 repeats it, or is zero).
+template <bool ZERO = false>
 __device__ __forceinline__ half8 shift_in_from_left(half8 v, int d) {
     u32x4 a = __builtin_bit_cast(u32x4, v);
-    const uint32_t t = (a[0] << 16) | (a[0] & 0xffffu);
+    const uint32_t t = ZERO ? 0u : (a[0] << 16) | (a[0] & 0xffffu);
     const u32x4 s8 = {t, t, t, t}, s4 = {t, t, a[0], a[1]};
     a = d >= 8 ? s8 : (d & 4) ? s4 : a;
     const u32x4 s2 = {t, a[0], a[1], a[2]};
     a = (d & 2) && d < 8 ? s2 : a;
-    const u32x4 s1 = {t, __builtin_amdgcn_alignbit(a[1], a[0], 16), __builtin_amdgcn_alignbit(a[2], a[1], 16),
+    const u32x4 s1 = {ZERO ? a[0] << 16 : t, __builtin_amdgcn_alignbit(a[1], a[0], 16), __builtin_amdgcn_alignbit(a[2], a[1], 16),
                       __builtin_amdgcn_alignbit(a[3], a[2], 16)};
     a = (d & 1) && d < 8 ? s1 : a;
     return __builtin_bit_cast(half8, a);

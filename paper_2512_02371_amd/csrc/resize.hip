@@ -9,12 +9,11 @@
 // times that block is NK products of the usual kind: the image operand is 8 consecutive samples of
 // one row per lane, straight from memory.
 //
-// One kernel does both axes.  It contracts over the memory-contiguous index of its input and writes
-// its result TRANSPOSED, Z[o][r] = sum_j X[r][start[o] + j] coef[o][j]: the horizontal pass turns the
-// image into T^T[xo][y] (rounded to fp16, kept in the workspace), so the vertical pass finds its
-// contraction index y contiguous again and its transposed result is the output in its natural
-// orientation.  The accumulators leave with a lane owning four consecutive r of one o, which is four
-// consecutive elements of a row of Z.
+// Both passes run in one launch.  A wave owns 16 output columns x 16 GY output rows: it applies the
+// horizontal matrix to 16 input rows at a time and leaves the result, rounded to fp16, TRANSPOSED in its piece of
+// LDS, T[xo][y], where the vertical pass finds its contraction index y contiguous: out^T = T * coef_y^T ends with
+// a lane owning four consecutive columns of a row.  (The vector-ALU twin keeps two launches with T in the
+// workspace.)
 #include <math.h>
 
 #include "hb_device.hpp"
@@ -22,10 +21,7 @@
 
 namespace hb {
 
-constexpr int kRzTiles = 4;                   // 16-row tiles of X per wave (64 rows r)
-constexpr int kRzWaves = 2;                   // waves per workgroup: 2 strips of 64 rows, one group of 16 outputs (measured: 1, 4, 8 are slower)
-constexpr int kRzMaxChunks = HB_RESIZE_MAX_SPAN / 32;
-
+// One pass of the vector-ALU twin.
 struct BandArgs {
     const half_t* x;                          // [planes][rows][len], row pitch x_pitch, plane stride x_plane
     void* z;                                  // [planes][nout][rows] transposed result, fp16 or fp32
@@ -33,165 +29,205 @@ struct BandArgs {
     const half_t* coef;                       // device: nout x band coefficients
     int rows, len, nout, band, planes;
     int64_t x_pitch, x_plane, z_pitch, z_plane;
-    int ngroups, nruns;                       // groups of 16 outputs; runs of kRzWaves strips per plane
+    int ngroups;                              // groups of 16 outputs
 };
 
-// Sixteen rows of 64 floats from the accumulators (lane (c, g): row c, columns 16 w + 4 g ..) to
-// fp16 rows in memory, through the wave's LDS patch so that a row leaves as one 128-byte run.
-template <int NW>
-__device__ __forceinline__ void rz_store_rows_half(float* patch, half_t* dst, uint32_t pitch_elems,
-                                                   const floatx4 (&acc)[NW], int lane) {
-    const int c = lane & 15, g = lane >> 4;
+struct ResizeArgs {
+    const half_t* in;
+    float* out;
+    const int *start_x, *start_y;
+    const half_t *coef_x, *coef_y;
+    int C, H, W, Ho, Wo, band_x, band_y;
+    int64_t in_pitch, in_plane, out_pitch, out_plane;
+    int ngx, ngy;                             // workgroups across and down
+};
+
+constexpr int kRzChunks = 12;                 // chunks of 32 columns whose coefficients are kept in LDS
+constexpr int kRzMinWidth = 8;                // of an image
+// A workgroup's waves own the same columns, either one below the other, each with its own T, or (SHARED, for
+// outputs too small to fill the chip that way) all the same 16 rows: the input rows are dealt among them.
+template <bool SHARED>
+struct RzGeom {
+    static constexpr int kWaves = SHARED ? 8 : 4;
+    static constexpr int kRows = SHARED ? 512 : 160;      // input rows whose horizontal results T holds at a time
+    static constexpr int kPitch = kRows + 40;             // halves per xo: 32 rows beyond, and an odd multiple of 16 bytes
+};
+
+// Coefficients t .. t + 7 of row o of an n x band matrix, zero outside [0, band).  The neighbouring rows' entries
+// that the load covers are masked; only at the two ends of the matrix is it moved and shifted back.
+__device__ __forceinline__ half8 rz_coef8(const half_t* m, int n, int band, int o, int t) {
+    const int64_t end = (int64_t)n * band - 8, want = (int64_t)o * band + t;
+    if (end < 0) {                                        // uniform: fewer than eight entries in all
+        half8 f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w)
-        *reinterpret_cast<floatx4*>(patch + c * RowPatch<NW>::kPitch + 16 * w + 4 * g) = acc[w];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    constexpr int kLanesPerRow = 4 * NW, kRowsPerPass = 64 / kLanesPerRow;
-    const int rr = lane / kLanesPerRow, xq = lane - rr * kLanesPerRow;
-#pragma unroll
-    for (int s = 0; s < 16 / kRowsPerPass; ++s) {
-        const int row = s * kRowsPerPass + rr;
-        const floatx4 v = *reinterpret_cast<const floatx4*>(patch + row * RowPatch<NW>::kPitch + 4 * xq);
-        const half4 h = {(half_t)v[0], (half_t)v[1], (half_t)v[2], (half_t)v[3]};
-        *reinterpret_cast<half4_u*>(dst + (size_t)row * pitch_elems + 4 * xq) = h;
+        for (int i = 0; i < 8; ++i) f[i] = t + i >= 0 && t + i < band ? m[(int64_t)o * band + t + i] : (half_t)0;
+        return f;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    const int64_t at = want < 0 ? 0 : want > end ? end : want;
+    half8 v = *reinterpret_cast<const half8_u*>(m + at);
+    if (at != want) {
+        const int d = (int)(want - at);
+        v = d > 0 ? shift_in_from_right<true>(v, d) : shift_in_from_left<true>(v, -d);
+    }
+    u32x4 b = __builtin_bit_cast(u32x4, v);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        b[j] &= ((uint32_t)(t + 2 * j) < (uint32_t)band ? 0xffffu : 0u) | ((uint32_t)(t + 2 * j + 1) < (uint32_t)band ? 0xffff0000u : 0u);
+    return __builtin_bit_cast(half8, b);
 }
-
-template <bool OUT_HALF>
-__global__ void __launch_bounds__(64 * kRzWaves) band_mfma_kernel(BandArgs p) {
-    constexpr int NW = kRzTiles;
-    // The coefficient block and, once the products are done, the waves' store patches share one piece
-    // of LDS: with both resident a compute unit held too few workgroups to cover the grid in one round.
-    constexpr int kFragBytes = kRzMaxChunks * 64 * 16, kPatchBytes = kRzWaves * RowPatch<NW>::kFloats * 4;
-    __shared__ __attribute__((aligned(16))) char s_mem[kFragBytes > kPatchBytes ? kFragBytes : kPatchBytes];
-    half8* s_frag = reinterpret_cast<half8*>(s_mem);
-    float* s_patch = reinterpret_cast<float*>(s_mem);
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wv = tid >> 6;
-    const int c = lane & 15, g = lane >> 4;
-    // neighbouring groups read neighbouring pieces of the same rows: walk them back to back inside one XCD
-    int wg = xcd_contiguous(blockIdx.x, gridDim.x);
-    const int grp = wg % p.ngroups;
-    wg /= p.ngroups;
-    const int run = wg % p.nruns, plane = wg / p.nruns;
-    const int o0 = 16 * grp;
-
-    // geometry of the group: first sample (even) and number of 32-sample chunks.  Lane column c
-    // reads the start of output o0 + c; the minimum and maximum over the 16 columns come from four
-    // butterfly steps inside each row of 16 lanes, so every lane ends up with the same numbers.
-    // A start below -band (above len - 1) reads nothing but the first (last) sample, and so does
-    // -band (len - 1): clamping it there changes no result and bounds the span by the image.
-    const int o = o0 + c;
-    const bool live = o < p.nout;
-    const int st = live ? clampi(p.start[o], -p.band, p.len - 1) : 0;
-    int lo = live ? st : 0x7fffffff, hi = live ? st + p.band : -0x7fffffff;
+// Smallest lo and largest hi over the 16 lanes of a row.
+__device__ __forceinline__ void rz_extent(int& lo, int& hi) {
 #pragma unroll
     for (int off = 1; off < 16; off <<= 1) {
         lo = min(lo, __shfl_xor(lo, off, 64));
         hi = max(hi, __shfl_xor(hi, off, 64));
     }
-    const int first = lo & ~1, nk_all = (hi - first + 31) / 32;
+}
 
-    const int r0 = 64 * (kRzWaves * run + wv);            // this wave's strip of rows
-    const bool active = r0 < p.rows;
-    const half_t* xpl = p.x + (size_t)plane * p.x_plane;
-    const uint32_t rowbytes = (uint32_t)p.x_pitch * 2u;
-    uint32_t rowoff[NW];
-#pragma unroll
-    for (int w = 0; w < NW; ++w) rowoff[w] = (uint32_t)min(r0 + 16 * w + c, p.rows - 1) * rowbytes;
+// What bounds it: a wave's chain of dependent round trips (starts -> pixels and coefficients -> vertical products ->
+// stores) where waves are few, and its instructions (the geometry of a group is 600 of them) where they are many: GY
+// groups of rows per wave share them and the rows that neighbouring groups both need.  As two launches with T in
+// memory: 3 x 2048 x 2048 -> 450 27.7 -> 19.4 us, 4096 x 4096 -> 2048 36 -> 27, -> 256 39 -> 20.
+template <int GY, bool SHARED>
+__global__ void __launch_bounds__(64 * RzGeom<SHARED>::kWaves, 4) resize_mfma_kernel(ResizeArgs p) {
+    constexpr int kWaves = RzGeom<SHARED>::kWaves, kRows = RzGeom<SHARED>::kRows, kPitch = RzGeom<SHARED>::kPitch;
+    __shared__ __attribute__((aligned(16))) half8 s_frag[kRzChunks * 64];
+    __shared__ __attribute__((aligned(16))) half_t s_rows[(SHARED ? 1 : kWaves) * 16 * kPitch];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c = lane & 15, g = lane >> 4;
+    // workgroups side by side read overlapping pieces of the same rows: walk them back to back inside one XCD
+    int wg = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int gx = wg % p.ngx;
+    wg /= p.ngx;
+    const int gy = wg % p.ngy, plane = wg / p.ngy;
 
-    auto load_chunk = [&](int kk, half8 (&d)[NW]) {
-        const int xs = first + 32 * kk;                   // uniform
-        if (xs >= 0 && xs + 32 <= p.len) {
+    // Columns: the aligned group of 16 outputs shares its first sample (even) and number of 32-sample chunks.  A
+    // start below -band (above len - 1) reads nothing but the first (last) sample, and so does
+    // -band (len - 1): clamping it there changes no result and bounds the span by the image.
+    const int xo = min(16 * gx + c, p.Wo - 1);            // lanes beyond Wo repeat the last output and store nothing
+    const int sx = clampi(p.start_x[xo], -p.band_x, p.W - 1);
+    // Rows: lane c + 16 q holds the start of output row c of the wave's group q
+    const int yo0 = 16 * GY * (SHARED ? gy : kWaves * gy + wv);
+    const int sy = clampi(p.start_y[min(yo0 + (lane & (16 * GY - 1)), p.Ho - 1)], -p.band_y, p.H - 1);
+    int xlo = sx, xhi = sx + p.band_x;
+    rz_extent(xlo, xhi);
+    xlo = __builtin_amdgcn_readfirstlane(xlo) & ~1;
+    const int nk = (__builtin_amdgcn_readfirstlane(xhi) - xlo + 31) / 32;
+    int glo = sy, ghi = sy + p.band_y;                    // of the lane's group of 16 rows
+    rz_extent(glo, ghi);
+    int ylo = glo, yhi = ghi;
 #pragma unroll
-            for (int w = 0; w < NW; ++w) d[w] = ldg8(xpl, rowoff[w] + 2u * (uint32_t)(xs + 8 * g));
-        } else {
+    for (int off = 16; off < 16 * GY; off <<= 1) {
+        ylo = min(ylo, __shfl_xor(ylo, off, 64));
+        yhi = max(yhi, __shfl_xor(yhi, off, 64));
+    }
+    ylo = __builtin_amdgcn_readfirstlane(ylo);
+    yhi = __builtin_amdgcn_readfirstlane(yhi);
+
+    // coefficient blocks, B-operand layout: lane (c = o, g) holds coef[o][first + 32 kk + 8g + i - start[o]]
+    auto frag_x = [&](int kk) { return rz_coef8(p.coef_x, p.Wo, p.band_x, xo, xlo + 32 * kk + 8 * g - sx); };
+    for (int kk = wv; kk < min(nk, kRzChunks); kk += kWaves) s_frag[kk * 64 + lane] = frag_x(kk);
+
+    const half_t* const px = p.in + (int64_t)plane * p.in_plane;
+    half_t* const rows = s_rows + (SHARED ? 0 : wv * 16 * kPitch);        // T
+    floatx4 out[GY];
 #pragma unroll
-            for (int w = 0; w < NW; ++w)
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const int x = clampi(xs + 8 * g + i, 0, p.len - 1);
-                    d[w][i] = *reinterpret_cast<const half_t*>(reinterpret_cast<const char*>(xpl) + (rowoff[w] + 2u * (uint32_t)x));
-                }
-        }
+    for (int q = 0; q < GY; ++q) out[q] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto load = [&](int y, int kk) {                      // chunk kk of row y
+        const uint32_t row = (uint32_t)clampi(y, 0, p.H - 1) * (uint32_t)p.in_pitch;
+        const int xs = xlo + 32 * kk, x = xs + 8 * g;
+        if (xs >= 0 && xs + 32 <= p.W) return ldg8(px, 2u * (row + (uint32_t)x));     // uniform
+        // requested inside the row, then shifted into place
+        const half8 v = ldg8(px, 2u * (row + (uint32_t)clampi(x, 0, p.W - 8)));
+        return shift_in_from_left(shift_in_from_right(v, max(x - (p.W - 8), 0)), max(-x, 0));
     };
-    floatx4 acc[NW];
-#pragma unroll
-    for (int w = 0; w < NW; ++w) acc[w] = floatx4{0.f, 0.f, 0.f, 0.f};
-    half8 bufa[NW], bufb[NW];
-    // The coefficient block holds kRzMaxChunks chunks; a group that spans more (a very large factor,
-    // or starts that jump inside the group) takes several rounds of block + products.
-    for (int base = 0; base < nk_all; base += kRzMaxChunks) {
-        const int nk = min(nk_all - base, kRzMaxChunks);
-        if (base) __syncthreads();                        // every wave is done with the previous block
-        // the first window chunk is requested before the coefficient block is built
-        if (active) load_chunk(base, bufa);
+    auto rows_ready = [&]() {
+        if (SHARED) __syncthreads();
+        else wave_lds_fence();
+    };
+    const int t_first = SHARED ? wv : 0, t_step = SHARED ? kWaves : 1;    // row tiles of this wave
+    __syncthreads();
+    if (yo0 >= p.Ho) return;                              // SHARED: no such workgroup
 
-        // coefficient block, B-operand layout: lane (c = o, g) holds B[8g + i][o] = coef[o][first + 32 kk + 8g + i - start[o]];
-        // wave wv builds chunks wv, wv + kRzWaves, ...
-        for (int kk = wv; kk < nk; kk += kRzWaves) {
-            half8 f;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) f[i] = (half_t)0;
-            if (live) {
-                const int t0 = first + 32 * (base + kk) + 8 * g - st;
-                const half_t* row = p.coef + (size_t)o * p.band;
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    if (t0 + i >= 0 && t0 + i < p.band) f[i] = row[t0 + i];
-            }
-            s_frag[kk * 64 + lane] = f;
-        }
-        __syncthreads();
-
-        // two window buffers used alternately: the next chunk is in flight while this one is multiplied
-        auto use_chunk = [&](int kk, const half8 (&d)[NW]) {
-            const half8 f = s_frag[kk * 64 + lane];
-#pragma unroll
-            for (int w = 0; w < NW; ++w) acc[w] = mfma16x16x32(d[w], f, acc[w]);
+#pragma unroll 1
+    for (int base = ylo; base < yhi; base += kRows) {
+        // T of rows base .. base + rows - 1; a chunk of the vertical pass that starts before base + kRows may reach
+        // 32 rows further, real ones or, after the last, zeros
+        const bool last = yhi - base <= kRows;
+        const int tiles = last ? (yhi - base + 15) / 16 : (kRows + 32) / 16;
+        rows_ready();                                     // the previous rows are read
+        if (last && (!SHARED || wv == 0)) *reinterpret_cast<half8*>(rows + c * kPitch + 16 * tiles + 8 * g) = half8{};
+        // D[m = y][n = xo]: lane (c = xo, g) holds rows 4g .. 4g + 3
+        auto keep = [&](int t, const floatx4& acc) {
+            *reinterpret_cast<half4*>(rows + c * kPitch + 16 * t + 4 * g) = to_half4(acc);
         };
-        for (int kk = 0; active && kk < nk; kk += 2) {
-            if (kk + 1 < nk) load_chunk(base + kk + 1, bufb);
-            use_chunk(kk, bufa);
-            if (kk + 1 >= nk) break;
-            if (kk + 2 < nk) load_chunk(base + kk + 2, bufa);
-            use_chunk(kk + 1, bufb);
+        if (nk <= kRzChunks) {
+            // up to four chunks of a tile are one piece of work; the next piece is requested before the current one
+            // is multiplied
+            auto request = [&](int t, int k0, half8 (&d)[4]) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (k0 + k < nk) d[k] = load(base + 16 * t + c, k0 + k);          // uniform
+            };
+            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+            half8 cur[4], nxt[4];
+            int t = t_first, k0 = 0;
+            if (t < tiles) request(t, 0, cur);
+#pragma unroll 1
+            while (t < tiles) {
+                const bool end = k0 + 4 >= nk;
+                const int t1 = end ? t + t_step : t, k1 = end ? 0 : k0 + 4;
+                if (t1 < tiles) request(t1, k1, nxt);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (k0 + k < nk) acc = mfma16x16x32(cur[k], s_frag[(k0 + k) * 64 + lane], acc);
+                if (end) {
+                    keep(t, acc);
+                    acc = floatx4{0.f, 0.f, 0.f, 0.f};
+                }
+                t = t1;
+                k0 = k1;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) cur[k] = nxt[k];
+            }
+        } else {                                          // spans of more than 384 columns: no room for the block
+#pragma unroll 1
+            for (int t = t_first; t < tiles; t += t_step) {
+                floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                for (int kk = 0; kk < nk; ++kk) acc = mfma16x16x32(load(base + 16 * t + c, kk), frag_x(kk), acc);
+                keep(t, acc);
+            }
+        }
+        rows_ready();
+        if (SHARED && wv != 0) continue;
+#pragma unroll
+        for (int q = 0; q < GY; ++q) {
+            const int vsy = __shfl(sy, 16 * q + c, 64), vo = min(yo0 + 16 * q + c, p.Ho - 1);
+            const int first = ylo + ((__builtin_amdgcn_readlane(glo, 16 * q) - ylo) & ~7);   // 16-byte pieces of T
+            const int hi = __builtin_amdgcn_readlane(ghi, 16 * q);
+            // chunks that start in this round, four coefficient loads at a time
+            const int k_first = max(base - first + 31, 0) / 32, k_end = min(hi - first + 31, base + kRows - first + 31) / 32;
+#pragma unroll 1
+            for (int k0 = k_first; k0 < k_end; k0 += 4) {
+                half8 f[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (k0 + k < k_end) f[k] = rz_coef8(p.coef_y, p.Ho, p.band_y, vo, first + 32 * (k0 + k) + 8 * g - vsy);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (k0 + k < k_end)
+                        out[q] = mfma16x16x32(*reinterpret_cast<const half8*>(rows + c * kPitch + first + 32 * (k0 + k) - base + 8 * g), f[k], out[q]);
+            }
         }
     }
-    __syncthreads();                                      // every wave is done with the coefficient block
-    if (!active) return;
-
-    // D[m = r][n = o]: lane (c = o, g) holds rows r0 + 16 w + 4 g .. + 3 = four consecutive elements of Z's row o
-    float* patch = s_patch + wv * RowPatch<NW>::kFloats;
-    const bool whole = o0 + 16 <= p.nout && r0 + 64 <= p.rows;
-    if (OUT_HALF) {
-        half_t* z = reinterpret_cast<half_t*>(p.z) + (size_t)plane * p.z_plane;
-        if (whole) {
-            rz_store_rows_half<NW>(patch, z + (size_t)o0 * p.z_pitch + r0, (uint32_t)p.z_pitch, acc, lane);
-        } else if (o0 + c < p.nout) {
-            half_t* row = z + (size_t)(o0 + c) * p.z_pitch;
+    if (SHARED && wv != 0) return;
+    // D[m = xo][n = yo]: lane (c = yo, g) holds columns 4g .. 4g + 3 of its row
 #pragma unroll
-            for (int w = 0; w < NW; ++w)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int r = r0 + 16 * w + 4 * g + j;
-                    if (r < p.rows) row[r] = (half_t)acc[w][j];
-                }
-        }
-    } else {
-        float* z = reinterpret_cast<float*>(p.z) + (size_t)plane * p.z_plane;
-        if (whole) {
-            store_rows_via_lds<NW, true>(patch, z + (size_t)o0 * p.z_pitch + r0, (uint32_t)p.z_pitch, acc, lane);
-        } else if (o0 + c < p.nout) {
-            float* row = z + (size_t)(o0 + c) * p.z_pitch;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) store4_mask(row, r0 + 16 * w + 4 * g, p.rows, acc[w]);
-        }
+    for (int q = 0; q < GY; ++q) {
+        const int yo = yo0 + 16 * q + c, x = 16 * gx + 4 * g;
+        if (yo < p.Ho && x < p.Wo)
+            store4_mask(p.out + (int64_t)plane * p.out_plane + (int64_t)yo * p.out_pitch, x, p.Wo, out[q]);
     }
 }
 
@@ -283,6 +319,45 @@ static hb_status resize_run(bool valu, const hb_half* in, float* out, void* work
     if (!workspace || workspace_bytes < need || !aligned_to(workspace, 256)) return HB_ERR_WORKSPACE;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
 
+    if (!valu && W >= kRzMinWidth) {
+        ResizeArgs r;
+        r.in = reinterpret_cast<const half_t*>(in);
+        r.out = out;
+        r.start_x = start_x;
+        r.start_y = start_y;
+        r.coef_x = reinterpret_cast<const half_t*>(coef_x);
+        r.coef_y = reinterpret_cast<const half_t*>(coef_y);
+        r.C = C;
+        r.H = H;
+        r.W = W;
+        r.Ho = Ho;
+        r.Wo = Wo;
+        r.band_x = band_x;
+        r.band_y = band_y;
+        r.in_pitch = in_pitch;
+        r.in_plane = in_plane;
+        r.out_pitch = out_pitch;
+        r.out_plane = out_plane;
+        r.ngx = ceil_div(Wo, 16);
+        // Groups of 16 output rows per wave: more share more, while the rows they need fit the wave's LDS and the
+        // chip keeps two waves per SIMD (2048 x 2048 from 4096 x 4096: 34 / 29 / 27 us with 1 / 2 / 4; 450 x 450 x 3 from
+        // 2048 x 2048: 19 / 29 / 37).  Under one wave per SIMD the waves of a workgroup share one group (256 x 256 from
+        // 4096 x 4096: 20 us against 92).
+        const int groups = ceil_div(Ho, 16);
+        const int64_t waves = (int64_t)C * r.ngx * groups;
+        auto good = [&](int q) { return waves >= 8 * q * num_cu() && 16.0 * q * H / Ho + band_y <= RzGeom<false>::kRows; };
+        const int gq = waves < 4 * num_cu() ? 0 : good(4) ? 4 : good(2) ? 2 : 1;
+        r.ngy = gq ? ceil_div(groups, gq * RzGeom<false>::kWaves) : groups;
+        const int64_t blocks = (int64_t)C * r.ngx * r.ngy;
+        if (blocks > 0x7fffffff) return HB_ERR_UNSUPPORTED;
+        const dim3 grid((unsigned)blocks), block(64 * RzGeom<false>::kWaves);
+        if (gq == 4) hipLaunchKernelGGL((resize_mfma_kernel<4, false>), grid, block, 0, st, r);
+        else if (gq == 2) hipLaunchKernelGGL((resize_mfma_kernel<2, false>), grid, block, 0, st, r);
+        else if (gq == 1) hipLaunchKernelGGL((resize_mfma_kernel<1, false>), grid, block, 0, st, r);
+        else hipLaunchKernelGGL((resize_mfma_kernel<1, true>), grid, dim3(64 * RzGeom<true>::kWaves), 0, st, r);
+        return launch_status();
+    }
+
     BandArgs a;
     // horizontal: image rows y, contraction over x, result T^T[xo][y] in fp16
     a.x = reinterpret_cast<const half_t*>(in);
@@ -315,18 +390,10 @@ static hb_status resize_run(bool valu, const hb_half* in, float* out, void* work
     b.z_plane = out_plane;
     for (BandArgs* q : {&a, &b}) {
         q->ngroups = ceil_div(q->nout, 16);
-        q->nruns = ceil_div(q->rows, 64 * kRzWaves);
-        if (valu) {
-            const int64_t blocks = (int64_t)q->planes * q->ngroups * ceil_div(q->rows, 64);
-            if (blocks > 0x7fffffff) return HB_ERR_UNSUPPORTED;
-            if (q == &a) hipLaunchKernelGGL(band_valu_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, st, *q);
-            else hipLaunchKernelGGL(band_valu_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, st, *q);
-        } else {
-            const int64_t blocks = (int64_t)q->planes * q->ngroups * q->nruns;
-            if (blocks > 0x7fffffff) return HB_ERR_UNSUPPORTED;
-            if (q == &a) hipLaunchKernelGGL(band_mfma_kernel<true>, dim3((unsigned)blocks), dim3(64 * kRzWaves), 0, st, *q);
-            else hipLaunchKernelGGL(band_mfma_kernel<false>, dim3((unsigned)blocks), dim3(64 * kRzWaves), 0, st, *q);
-        }
+        const int64_t blocks = (int64_t)q->planes * q->ngroups * ceil_div(q->rows, 64);
+        if (blocks > 0x7fffffff) return HB_ERR_UNSUPPORTED;
+        if (q == &a) hipLaunchKernelGGL(band_valu_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, st, *q);
+        else hipLaunchKernelGGL(band_valu_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, st, *q);
         const hb_status s = launch_status();
         if (s != HB_OK) return s;
     }

@@ -94,6 +94,29 @@ def test_resize_starts_far_apart_and_far_outside(orc, fn):
     assert_close(got[0], orc.band_resize(img[0], sy, cy, sx, cx), fn)
 
 
+@pytest.mark.parametrize("C,H,W,Ho,Wo,by,bx,reach", [
+    (1, 40, 7, 33, 40, 5, 3, 30),            # narrower than eight pixels
+    (1, 900, 8, 40, 20, 400, 2, 900),        # fewer than eight samples of a row; rows in several rounds
+    (2, 260, 1200, 17, 33, 3, 500, 700),     # spans of more than 384 columns
+    (1, 300, 500, 135, 2090, 9, 12, 250),    # one group of rows per wave, rows in several rounds
+    (1, 150, 900, 131, 8330, 20, 7, 60),     # two
+    (1, 250, 700, 230, 9610, 30, 8, 20),     # four
+])
+def test_resize_random_starts_over_the_work_splits(orc, C, H, W, Ho, Wo, by, bx, reach):
+    """Starts scattered around a ramp, some outside the image, over the sizes where the split of the work changes."""
+    img = synth.uniform01_f16(9500 + H, (C, H, W))
+    def matrix(seed, n, band, n_in):
+        k = (synth.random_kernel2d_f16(seed, n, band).view(np.float16).astype(np.float64) * n).astype(np.float16).view(np.uint16)
+        h = synth.hash_u64(seed + 1, 0, n)
+        return (np.arange(n) * n_in // n + (h % np.uint64(reach)).astype(np.int64) - reach // 2).astype(np.int32), k
+    sy, cy = matrix(9510 + Ho, Ho, by, H)
+    sx, cx = matrix(9520 + Wo, Wo, bx, W)
+    got, obuf = run("hb_resize", img, sy, cy, sx, cx, pitch_extra=3)
+    for c in range(C):
+        assert_close(got[c], orc.band_resize(img[c], sy, cy, sx, cx), f"plane {c}")
+    assert np.all(obuf[:, :, Wo:] == 7.0) and np.all(obuf[:, Ho:, :] == 7.0), "wrote outside the output planes"
+
+
 @pytest.mark.parametrize("fn", ["hb_resize", "hb_resize_valu"])
 def test_resize_pitched_planes(orc, fn):
     from paper_2512_02371_amd import hb
