@@ -9,9 +9,10 @@
 // product T * X^T (K = 32) per half of the outputs, and the recursion survives only as the
 // propagation of a two-number state (Y_{t-1}, Y_{t-2}) from block to block: the state after a block
 // is M32 * (state before) + (last two local outputs), M32 the 32nd power of the companion matrix.
-// Three launches, like the summed-area table: (1) local products, end state of every 512-sample
-// tile; (2) scan of the tile states along the signal; (3) local products again, block states from
-// the true tile state, outputs = local outputs + response of the block's initial state.
+// Two launches: (1) local products, the end state of every run of 512-sample tiles as if it started from zero;
+// (2) the true state before a run from the end states of the runs before it, local products again, block states
+// from the true tile state, outputs = local outputs + response of the block's initial state.  (The vector-ALU twin
+// keeps a launch of its own for the scan of the tile states in between.)
 //
 // The impulse response is not an fp16 number: T is split into a rounded part and the rounded
 // remainder (two products), which leaves a relative coefficient error of about 2^-22.
@@ -34,6 +35,8 @@ struct IirArgs {
     float* start;                             // [C][ntiles][2] true state before each tile
     float m32[4], m512[4], mwave[4];          // state maps over a block, a tile, a wave's tiles in the scan (row-major 2x2)
     float mpow[6][4];                         // ... and over 2^j lanes' tiles, j = 0..5
+    int nruns, run;                           // matrix kernels: runs of `run` tiles per channel, one wave each
+    float rpow[7][4];                         // state map over 2^j runs, j = 0..6
     float bpow[4][4];                         // state map over 2^j blocks, j = 0..3 (in-tile scan)
     float bsel[16][4];                        // state map over b blocks, b = 0..15
     float ca[kIirBlock], cb[kIirBlock];       // response of output i to the initial state (Y_-1, Y_-2)
@@ -107,28 +110,83 @@ __device__ __forceinline__ State2 iir_scan_blocks(const IirArgs& p, const floatx
     return v;
 }
 
-// 1  end state of every tile started from zero
-__global__ void __launch_bounds__(256) iir2_state_mfma_kernel(IirArgs p) {
-    const int lane = threadIdx.x & 63;
-    const half8 fhi = iir_fragment(p.thi, 1, lane), flo = iir_fragment(p.tlo, 1, lane);
-    const int64_t total = (int64_t)p.C * p.ntiles, nwaves = (int64_t)gridDim.x * 4;
-    // waves stride over the tiles: the fragments above are built once per wave
-    for (int64_t w = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6; w < total; w += nwaves) {
-        const int ch = (int)(w / p.ntiles), tile = (int)(w - (int64_t)ch * p.ntiles);
-        const half8 x = iir_load_tile(p.in + (int64_t)ch * p.in_pitch, (int64_t)tile * kIirTile, p.T, lane);
-        floatx4 d1 = {0.f, 0.f, 0.f, 0.f};
-        d1 = mfma16x16x32(fhi, x, d1);
-        d1 = mfma16x16x32(flo, x, d1);
-        const State2 s = iir_scan_blocks(p, d1, lane);        // lane column 15: the state after the last block
-        if (lane == 15) {
-            float* e = p.end + 2 * w;
-            e[0] = s.a;
-            e[1] = s.b;
+// A wave walks over the tiles of its run four at a time; the next four are requested before the current ones are
+// used.  use(i, x) takes tile i of the run.
+constexpr int kIirAhead = 4;
+template <class Use>
+__device__ __forceinline__ void iir_walk(const half_t* sig, int64_t t0, int64_t T, int n, int lane, const half8 (&first)[kIirAhead], Use use) {
+    half8 cur[kIirAhead], nxt[kIirAhead];
+#pragma unroll
+    for (int u = 0; u < kIirAhead; ++u) cur[u] = first[u];
+#pragma unroll 1
+    for (int i = 0; i < n; i += kIirAhead) {
+        if (i + kIirAhead < n) {
+#pragma unroll
+            for (int u = 0; u < kIirAhead; ++u) nxt[u] = iir_load_tile(sig, t0 + (int64_t)(i + kIirAhead + u) * kIirTile, T, lane);
         }
+#pragma unroll
+        for (int u = 0; u < kIirAhead; ++u)
+            if (i + u < n) use(i + u, cur[u]);
+#pragma unroll
+        for (int u = 0; u < kIirAhead; ++u) cur[u] = nxt[u];
     }
 }
 
-// 2  true state before every tile: one workgroup of 16 waves per channel, a lane owns `chunk`
+// 1  end state of every run started from zero
+__global__ void __launch_bounds__(256) iir2_state_mfma_kernel(IirArgs p) {
+    const int lane = threadIdx.x & 63;
+    const int64_t w = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
+    if (w >= (int64_t)p.C * p.nruns) return;
+    const int ch = (int)(w / p.nruns), run = (int)(w - (int64_t)ch * p.nruns);
+    const int tile0 = run * p.run, n = min(p.run, p.ntiles - tile0);
+    const half_t* const sig = p.in + (int64_t)ch * p.in_pitch;
+    const int64_t t0 = (int64_t)tile0 * kIirTile;
+    half8 first[kIirAhead];
+#pragma unroll
+    for (int u = 0; u < kIirAhead; ++u) first[u] = iir_load_tile(sig, t0 + (int64_t)u * kIirTile, p.T, lane);
+    const half8 fhi = iir_fragment(p.thi, 1, lane), flo = iir_fragment(p.tlo, 1, lane);
+    State2 s{0.f, 0.f};                                   // lane column 15: the state after the tile
+    iir_walk(sig, t0, p.T, n, lane, first, [&](int, const half8& x) {
+        floatx4 d1 = {0.f, 0.f, 0.f, 0.f};
+        d1 = mfma16x16x32(fhi, x, d1);
+        d1 = mfma16x16x32(flo, x, d1);
+        const State2 e = iir_scan_blocks(p, d1, lane);
+        s = iir_step(p.m512, s, e.a, e.b);
+    });
+    if (lane == 15) {
+        p.end[2 * w] = s.a;
+        p.end[2 * w + 1] = s.b;
+    }
+}
+
+// The true state before run r of a channel, the same in every lane: the sum over k < r of M^k end[r - 1 - k], M the
+// state map over a run.  Lane l sums k = l, l + 64, ... (coalesced loads, eight in flight), and the lanes are folded
+// in six steps.  At most 1024 runs: two rounds of loads.
+constexpr int kIirMaxRuns = 1024;
+__device__ __forceinline__ State2 iir_state_before(const IirArgs& p, const float* end, int r, int lane) {
+    State2 s{0.f, 0.f};
+    for (int i0 = (r + 63) / 64; i0 > 0; i0 -= 8) {       // uniform
+        float ea[8], eb[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int j = r - 1 - lane - 64 * (i0 - 1 - u);
+            const bool live = i0 - 1 - u >= 0 && j >= 0;
+            ea[u] = live ? end[2 * j] : 0.f;
+            eb[u] = live ? end[2 * j + 1] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (i0 - 1 - u >= 0) s = iir_step(p.rpow[6], s, ea[u], eb[u]);
+    }
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+        const float ha = __shfl_down(s.a, 1 << j, 64), hb = __shfl_down(s.b, 1 << j, 64);
+        s = iir_step(p.rpow[j], State2{ha, hb}, s.a, s.b);
+    }
+    return State2{__shfl(s.a, 0, 64), __shfl(s.b, 0, 64)};
+}
+
+// The twin's scan, the true state before every tile: one workgroup of 16 waves per channel, a lane owns `chunk`
 // consecutive tiles.  Lanes are scanned in doubling steps, waves chained serially; only the last
 // lanes may own fewer tiles, and nothing depends on what follows them.
 constexpr int kIirScanWaves = 16;
@@ -214,11 +272,23 @@ __global__ void __launch_bounds__(64 * kIirScanWaves) iir2_scan_kernel(IirArgs p
     iir_scan_tiles(p, e, st, lo, hi, mine);
 }
 
-// 3  outputs
+// 2  outputs.  A wave holds its run's first tiles before it sums the states, and carries the state from tile to tile:
+// 2 x 2^21 samples 9 us behind 4 us of the launch before it, where the scan of 8192 tile states by one workgroup
+// per channel was another 9 (20.4 -> 13.4 us, the host's rate for two launches; 8 x 2^20 20.4 -> 16.0, a copy of the
+// bytes 9).
 __global__ void __launch_bounds__(256) iir2_apply_mfma_kernel(IirArgs p) {
     __shared__ __attribute__((aligned(16))) float s_patch[4 * RowPatch<2>::kFloats];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int c = lane & 15, g = lane >> 4;
+    const int64_t w = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
+    if (w >= (int64_t)p.C * p.nruns) return;
+    const int ch = (int)(w / p.nruns), run = (int)(w - (int64_t)ch * p.nruns);
+    const int tile0 = run * p.run, n = min(p.run, p.ntiles - tile0);
+    const half_t* const sig = p.in + (int64_t)ch * p.in_pitch;
+    const int64_t t0 = (int64_t)tile0 * kIirTile;
+    half8 first[kIirAhead];
+#pragma unroll
+    for (int u = 0; u < kIirAhead; ++u) first[u] = iir_load_tile(sig, t0 + (int64_t)u * kIirTile, p.T, lane);
     half8 fhi[2], flo[2];
     float ra[2][4], rb[2][4];                 // response of the lane's outputs i = 16 hh + 4 g + j to the block's state
 #pragma unroll
@@ -234,12 +304,8 @@ __global__ void __launch_bounds__(256) iir2_apply_mfma_kernel(IirArgs p) {
     float bsel[4];                            // state map over the c blocks before the lane's block
 #pragma unroll
     for (int i = 0; i < 4; ++i) bsel[i] = p.bsel[c][i];
-    const int64_t total = (int64_t)p.C * p.ntiles, nwaves = (int64_t)gridDim.x * 4;
-    // waves stride over the tiles: fragments and responses above are built once per wave
-    for (int64_t w = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6; w < total; w += nwaves) {
-        const int ch = (int)(w / p.ntiles), tile = (int)(w - (int64_t)ch * p.ntiles);
-        const int64_t t0 = (int64_t)tile * kIirTile;
-        const half8 x = iir_load_tile(p.in + (int64_t)ch * p.in_pitch, t0, p.T, lane);
+    State2 start = iir_state_before(p, p.end + 2 * (int64_t)ch * p.nruns, run, lane);
+    iir_walk(sig, t0, p.T, n, lane, first, [&](int i, const half8& x) {
         floatx4 d[2];
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
@@ -248,16 +314,17 @@ __global__ void __launch_bounds__(256) iir2_apply_mfma_kernel(IirArgs p) {
             d[hh] = mfma16x16x32(flo[hh], x, d[hh]);
         }
         // state before block c = (tile state carried across c blocks) + (blocks 0 .. c-1 from zero)
-        const float* st = p.start + 2 * w;
         const State2 incl = iir_scan_blocks(p, d[1], lane);
-        const State2 mine = iir_step(bsel, State2{st[0], st[1]}, iir_row_shr<1>(incl.a), iir_row_shr<1>(incl.b));
+        const State2 mine = iir_step(bsel, start, iir_row_shr<1>(incl.a), iir_row_shr<1>(incl.b));
+        start = iir_step(p.m512, start, __shfl(incl.a, 15, 64), __shfl(incl.b, 15, 64));
         // lane (c = block, g) holds outputs i = 16 hh + 4 g + j of its block: add the response to the block's state
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
             for (int j = 0; j < 4; ++j) d[hh][j] += ra[hh][j] * mine.a + rb[hh][j] * mine.b;
-        float* dst = p.out + (int64_t)ch * p.out_pitch + t0;
-        if (t0 + kIirTile <= p.T) {
+        const int64_t t = t0 + (int64_t)i * kIirTile;
+        float* dst = p.out + (int64_t)ch * p.out_pitch + t;
+        if (t + kIirTile <= p.T) {
             // the tile is 16 rows (blocks) of 32 consecutive samples
             store_rows_via_lds<2, true>(s_patch + wv * RowPatch<2>::kFloats, dst, kIirBlock, d, lane);
         } else {
@@ -265,14 +332,14 @@ __global__ void __launch_bounds__(256) iir2_apply_mfma_kernel(IirArgs p) {
             for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const int i = 32 * c + 16 * hh + 4 * g + j;
-                    if (t0 + i < p.T) dst[i] = d[hh][j];
+                    const int k = 32 * c + 16 * hh + 4 * g + j;
+                    if (t + k < p.T) dst[k] = d[hh][j];
                 }
         }
-    }
+    });
 }
 
-// Vector-ALU twin of launches 1 and 3: a lane owns one block of 32 samples and runs the recursion
+// Vector-ALU twin of both launches: a lane owns one block of 32 samples and runs the recursion
 // itself; a wave covers four tiles.  WRITE = false: end states of the tiles started from zero;
 // WRITE = true: outputs, every block started from its true state.
 template <bool WRITE>
@@ -449,16 +516,28 @@ static hb_status iir2_run(bool valu, const hb_half* in, float* out, int C, int64
         }
     }
 
+    // Runs: as short as leaves at most 1024 of them per channel (the sum over them stays cheap) and one
+    // resident round of waves in all.  Longer runs than one tile only where there are 64 of them: the powers of
+    // the map that are formed then span no more than the signal, whose growth the gain check bounds.
+    a.run = 1;
+    while (a.ntiles > (int64_t)kIirMaxRuns * a.run || ((int64_t)C * a.ntiles > (int64_t)16 * num_cu() * a.run && a.ntiles >= (int64_t)128 * a.run)) a.run *= 2;
+    a.nruns = (a.ntiles + a.run - 1) / a.run;
+    for (int j = 0; j < 7; ++j) {
+        const Mat2 rp = mat2_pow(m512, (int64_t)a.run << j);
+        for (int i = 0; i < 4; ++i) a.rpow[j][i] = (float)rp.v[i];
+    }
+
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    const int64_t waves = (int64_t)C * (valu ? (a.ntiles + 3) / 4 : a.ntiles);
-    int64_t wgs = (waves + 3) / 4;
-    if (!valu && wgs > 8 * num_cu()) wgs = 8 * num_cu();          // the matrix kernels' waves stride over the tiles
-    const unsigned blocks = (unsigned)wgs;
-    if (valu) hipLaunchKernelGGL(iir2_blocks_valu_kernel<false>, dim3(blocks), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL(iir2_state_mfma_kernel, dim3(blocks), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(iir2_scan_kernel, dim3(C), dim3(64 * kIirScanWaves), 0, st, a);
-    if (valu) hipLaunchKernelGGL(iir2_blocks_valu_kernel<true>, dim3(blocks), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL(iir2_apply_mfma_kernel, dim3(blocks), dim3(256), 0, st, a);
+    const int64_t waves = (int64_t)C * (valu ? (a.ntiles + 3) / 4 : a.nruns);
+    const dim3 grid((unsigned)((waves + 3) / 4));
+    if (valu) {
+        hipLaunchKernelGGL(iir2_blocks_valu_kernel<false>, grid, dim3(256), 0, st, a);
+        hipLaunchKernelGGL(iir2_scan_kernel, dim3(C), dim3(64 * kIirScanWaves), 0, st, a);
+        hipLaunchKernelGGL(iir2_blocks_valu_kernel<true>, grid, dim3(256), 0, st, a);
+    } else {
+        if (a.nruns > 1) hipLaunchKernelGGL(iir2_state_mfma_kernel, grid, dim3(256), 0, st, a);
+        hipLaunchKernelGGL(iir2_apply_mfma_kernel, grid, dim3(256), 0, st, a);
+    }
     return launch_status();
 }
 

@@ -54,6 +54,16 @@ def test_iir2_matches_oracle(orc, fn, alpha, beta, C, T):
     assert_close(got, ref, f"{fn} {C}x{T} ({alpha}, {beta})")
 
 
+@pytest.mark.parametrize("C,T", [(1, 65 * 512 + 1), (1, 1025 * 512), (40, 129 * 512 + 7), (70, 300 * 512 - 3)])
+@pytest.mark.parametrize("alpha,beta", [(1.6, -0.8), (1.9, -0.9025)])
+def test_iir2_runs_of_tiles(orc, C, T, alpha, beta):
+    """More than one load round of run states, and runs of two and four tiles with a short last one."""
+    sig = synth.uniform_pm1_f16(9700 + C, (C, T))
+    got, _ = run("hb_iir2", sig, alpha, beta)
+    for c in {0, C // 2, C - 1}:
+        assert_close(got[c:c + 1], orc.iir2(sig[c:c + 1], float(np.float32(alpha)), float(np.float32(beta))), f"channel {c}")
+
+
 @pytest.mark.parametrize("fn", ["hb_iir2", "hb_iir2_valu"])
 def test_iir2_pitched_rows(orc, fn):
     sig = synth.uniform_pm1_f16(9600, (2, 3000))
