@@ -17,6 +17,7 @@
 // with A[m][k] = taps[k - m - e] (zero outside the taps): A_K itself, built once per
 // wave from a zero-padded tap table.  In D' a lane owns four consecutive output
 // columns of one row, so the result leaves with one 16-byte store per lane.
+#include <algorithm>
 #include <utility>
 
 #include "hb_device.hpp"
@@ -24,20 +25,6 @@
 
 #ifndef HB_FIR_TILES
 #define HB_FIR_TILES 4        // 16-column tiles per wave strip
-#endif
-#ifndef HB_FIR_WAVES
-#define HB_FIR_WAVES (1 << 20) // wave tasks per launch before a task takes more than one 16-row step;
-                              // rows are independent here, so short-lived waves stream best
-#endif
-
-#ifndef HB_FIR_WALK_WAVES
-#define HB_FIR_WALK_WAVES 4096 // the walk of long filters: aim for about this many wave tasks per launch ...
-#endif
-#ifndef HB_FIR_WALK_MIN_NK
-#define HB_FIR_WALK_MIN_NK 2    // windows per tile from which the walk is used
-#endif
-#ifndef HB_FIR_WALK_MIN_TURNS
-#define HB_FIR_WALK_MIN_TURNS 2 // ... but no run shorter than this many turns of the accumulator ring (2 NK tiles each)
 #endif
 
 namespace hb {
@@ -60,129 +47,63 @@ struct FirArgs {
     int64_t in_pitch, out_pitch;
     int T, anchor;
     int nct;             // strips per row group
-    int steps;           // 16-row steps per task
-    int ntasks;          // strips x row segments
+    int ntasks;          // strips x row groups
     int ntiles, run_tiles, nruns, wtasks;   // the walk of long filters: tiles per row, per run, runs per row group, tasks
     TapsT<HB_MAX_TAPS_FIR1D> taps;
-    FoldTablesT<HB_MAX_TAPS_FIR1D> fold;
 };
 
-// Tiles per wave strip of the one-window kernel (it is written for any NK, but filters with two or
-// more windows per tile take the walk further down).
-constexpr int fir_tiles(int) { return HB_FIR_TILES; }
-
-__device__ __forceinline__ half_t tap_from_bits(uint16_t b) {
-    return __builtin_bit_cast(half_t, b);
+constexpr int kFirMinWidth = 8;               // of an image for those loads
+// Eight pixels from column xs on of the row at byte offset rowoff, requested from an address inside the row
+// (W >= 8); fir_clamped() shifts what reaches over the row's ends into place, which is the column clamp.
+__device__ __forceinline__ half8 fir_request(const FirArgs& p, uint32_t rowoff, int xs) {
+    return ldg8(p.in, rowoff + 2u * (uint32_t)clampi(xs, 0, p.W - 8));
+}
+__device__ __forceinline__ half8 fir_clamped(const FirArgs& p, half8 v, int xs) {
+    return shift_in_from_left(shift_in_from_right(v, max(xs - (p.W - 8), 0)), max(-xs, 0));
 }
 
-// A wave owns a strip of HB_FIR_TILES tiles and walks down it in steps of 16 rows; the pixels of
-// the next step are requested before the current step is multiplied.
-template <int NK, bool STREAM>
+// One window per tile (up to 17 taps): nothing to share between tiles or steps.  A wave takes HB_FIR_TILES tiles of one
+// 16-row group, all requested up front, and leaves.  A strip at the image's border shifts its pixels into place in
+// registers (with the clamp folded into per-tile coefficients from tables in the kernel arguments the 256 x 256 launch
+// took 5.0 us, now 3.8; 4096 x 4096 20.7 -> 19.0, a copy 18.3).
 __global__ void __launch_bounds__(256) fir1d_mfma_kernel(FirArgs p) {
-    constexpr int NW = fir_tiles(NK);
+    constexpr int NW = HB_FIR_TILES;
     __shared__ __attribute__((aligned(16))) float s_patch[4][RowPatch<NW>::kFloats];
-
     const int lane = threadIdx.x & 63;
     const int c = lane & 15, g = lane >> 4;
-
-    // Toeplitz fragments, A-operand layout: lane (c, g) holds A[c][32kk + 8g + i] = taps[32kk + 8g + i - c - e].
     const int e = p.anchor & 1;
     const int aw = p.anchor + e;              // window start, left of the tile
-    // (read from the tap table in the kernel arguments AFTER the first pixel loads are on their way: a
-    // wave that waited for the table first would put a memory round trip in front of its pixel requests)
-    auto fragments = [&](half8 (&coef)[NK]) {
-#pragma unroll
-        for (int kk = 0; kk < NK; ++kk) coef[kk] = tap_run(p.taps.tab, 32 * kk + 8 * g - c - e);
-    };
-    const int wmax = p.W - 32 * NK;           // last window start that stays inside the row
-
     // (tasks in plain launch order: with one contiguous eighth of the tasks per XCD this kernel measured
     // 10 % slower on tall images, 100 against 89 us on 262144 x 256; groups of 2 to 8 neighbours per XCD
     // measured within 2 % of the plain order there)
-    const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-    const int nwaves = (gridDim.x * blockDim.x) >> 6;
-    for (int task = wave; task < p.ntasks; task += nwaves) {
-        const int seg = task / p.nct, ct = task - seg * p.nct;
-        const int x0 = 16 * NW * ct;
-        const int Y0 = seg * p.steps * 16;
-        const int nsteps = min(p.steps, (p.H - Y0 + 15) / 16);
-        const bool xin = (x0 - aw >= 0) && (x0 + 16 * (NW - 1) - aw + 32 * NK <= p.W) && (x0 + 16 * NW <= p.W);
-        if (xin) {
-            // strip inside the row: uniform bases, 32-bit lane offsets, coalesced row stores
-            const half_t* src = p.in + (x0 - aw);
-            float* dst = p.out + x0;
-            half8 cur[NW][NK], nxt[NW][NK];
-            auto load_step = [&](int q, half8 (&d)[NW][NK]) {
-                const int yr = min(Y0 + 16 * q + c, p.H - 1);
-                const uint32_t off = ((uint32_t)yr * (uint32_t)p.in_pitch + 8u * g) * 2u;
+    const int task = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    if (task >= p.ntasks) return;
+    const int rg = task / p.nct, ct = task - rg * p.nct;
+    const int x0 = 16 * NW * ct, y0 = 16 * rg;
+    const bool inside = x0 >= aw && x0 + 16 * (NW - 1) - aw + 32 <= p.W && x0 + 16 * NW <= p.W;   // uniform
+    const uint32_t rowoff = (uint32_t)min(y0 + c, p.H - 1) * (uint32_t)p.in_pitch * 2u;
+    half8 px[NW];
 #pragma unroll
-                for (int w = 0; w < NW; ++w)
+    for (int w = 0; w < NW; ++w) px[w] = fir_request(p, rowoff, x0 - aw + 16 * w + 8 * g);
+    // The Toeplitz fragment, A-operand layout: lane (c, g) holds A[c][8g + i] = taps[8g + i - c - e], read from the tap
+    // table in the kernel arguments only now: a wave that waited for the table first would put a memory round
+    // trip in front of its pixel requests.
+    __builtin_amdgcn_sched_barrier(0);
+    const half8 coef = tap_run(p.taps.tab, 8 * g - c - e);
+    if (!inside) {
 #pragma unroll
-                    for (int kk = 0; kk < NK; ++kk) d[w][kk] = ldg8(src, off + 2u * (16u * w + 32u * kk));
-            };
-            load_step(0, cur);
-            __builtin_amdgcn_sched_barrier(0);
-            half8 coef[NK];
-            fragments(coef);
-            for (int q = 0; q < nsteps; ++q) {
-                if (q + 1 < nsteps) load_step(q + 1, nxt);
-                floatx4 acc[NW];
-#pragma unroll
-                for (int w = 0; w < NW; ++w) {
-                    acc[w] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int kk = 0; kk < NK; ++kk) acc[w] = mfma16x16x32(coef[kk], cur[w][kk], acc[w]);
-                }
-                const int y0 = Y0 + 16 * q;
-                if (y0 + 16 <= p.H) {
-                    store_rows_via_lds<NW, STREAM>(s_patch[threadIdx.x >> 6], dst + (int64_t)y0 * p.out_pitch,
-                                                   (uint32_t)p.out_pitch, acc, lane);
-                } else if (y0 + c < p.H) {
-                    const uint32_t off = ((uint32_t)(y0 + c) * (uint32_t)p.out_pitch + 4u * g) * 4u;
-#pragma unroll
-                    for (int w = 0; w < NW; ++w) stg4<STREAM>(dst, off + 64u * w, acc[w]);
-                }
-#pragma unroll
-                for (int w = 0; w < NW; ++w)
-#pragma unroll
-                    for (int kk = 0; kk < NK; ++kk) cur[w][kk] = nxt[w][kk];
-            }
-        } else {
-            // border strip, tile by tile: the window is moved inside the row and the clamp is
-            // folded into the fragment; rows past the image repeat the last one
-            half8 coef[NK];
-            fragments(coef);
-#pragma unroll 1
-            for (int w = 0; w < NW; ++w) {
-                const int xt = x0 + 16 * w;
-                if (xt >= p.W) break;
-                const int ws = clampi(xt - aw, 0, wmax);
-                const bool plain = (ws == xt - aw) && (xt + 16 <= p.W);
-                half8 hi[NK], lo[NK];
-#pragma unroll
-                for (int kk = 0; kk < NK; ++kk) {
-                    if (plain) {
-                        hi[kk] = coef[kk];
-                        lo[kk] = half8{0, 0, 0, 0, 0, 0, 0, 0};
-                    } else {
-                        folded_fragment(p.fold, p.T, p.anchor, p.W, xt, ws, kk, c, g, hi[kk], lo[kk]);
-                    }
-                }
-                for (int q = 0; q < nsteps; ++q) {
-                    const int y = Y0 + 16 * q + c;
-                    const half_t* row = p.in + (int64_t)min(y, p.H - 1) * p.in_pitch;
-                    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int kk = 0; kk < NK; ++kk) {
-                        const half8 px = *reinterpret_cast<const half8_u*>(row + ws + 32 * kk + 8 * g);
-                        acc = mfma16x16x32(hi[kk], px, acc);
-                        acc = mfma16x16x32(lo[kk], px, acc);
-                    }
-                    if (y < p.H) store4_mask(p.out + (int64_t)y * p.out_pitch, xt + 4 * g, p.W, acc);
-                }
-            }
-        }
+        for (int w = 0; w < NW; ++w) px[w] = fir_clamped(p, px[w], x0 - aw + 16 * w + 8 * g);
     }
+    floatx4 acc[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+        acc[w] = mfma16x16x32(coef, px[w], zero);
+    }
+    float* const dst = p.out + (int64_t)y0 * p.out_pitch + x0;
+    float* const patch = s_patch[threadIdx.x >> 6];
+    if (inside && y0 + 16 <= p.H) store_rows_via_lds<NW, true>(patch, dst, (uint32_t)p.out_pitch, acc, lane);
+    else store_rows_via_lds_masked<NW, true>(patch, dst, p.out_pitch, acc, lane, p.H - y0, p.W - x0);
 }
 
 // ---------------------------------------------------------------------------
@@ -197,15 +118,15 @@ __global__ void __launch_bounds__(256) fir1d_mfma_kernel(FirArgs p) {
 // accumulators, indexed at compile time: the walk is unrolled over one turn of the ring); a tile is
 // complete 2 NK - 2 steps after its first window, and completed tiles leave in pairs through the LDS
 // patch as 128-byte runs.  A pixel is requested twice (windows of 32 at a stride of 16) instead of
-// 2 NK times.  Windows that reach over the row ends are loaded pixel by pixel with the column
-// clamped: the Toeplitz matrix is indexed by window position, so the border rule needs nothing else.
+// 2 NK times.  Windows that reach over the row ends are shifted into place when they are used:
+// the Toeplitz matrix is indexed by window position, so the border rule needs nothing else.
 // Runs start 2 NK - 2 windows early (products into accumulators of tiles left of the run are
 // computed and dropped), the price of cutting a row into several tasks.
 // Waves per workgroup of the walk: the longest filters (few, long-lived waves of 100+ registers) run
 // best as single-wave workgroups, the shorter ones four to a workgroup (measured).
 constexpr int fir_walk_waves(int nk) { return nk >= 7 ? 1 : 4; }
 
-template <int NK, bool STREAM>
+template <int NK>
 __global__ void __launch_bounds__(64 * fir_walk_waves(NK)) fir1d_walk_kernel(FirArgs p) {
     constexpr int R = 2 * NK;
     constexpr int WV = fir_walk_waves(NK);
@@ -230,19 +151,10 @@ __global__ void __launch_bounds__(64 * fir_walk_waves(NK)) fir1d_walk_kernel(Fir
     float* patch = s_patch[threadIdx.x >> 6];
     const bool rows16 = y0 + 16 <= p.H;
 
-    auto load_window = [&](int u) {
-        const int xs = 16 * (t0 + u) - aw;                // uniform
-        half8 v;
-        if (xs >= 0 && xs + 32 <= p.W) {
-            v = ldg8(p.in, rowoff + 2u * (uint32_t)(xs + 8 * g));
-        } else {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int x = clampi(xs + 8 * g + i, 0, p.W - 1);
-                v[i] = *reinterpret_cast<const half_t*>(reinterpret_cast<const char*>(p.in) + (rowoff + 2u * (uint32_t)x));
-            }
-        }
-        return v;
+    auto load_window = [&](int u) { return fir_request(p, rowoff, 16 * (t0 + u) - aw + 8 * g); };
+    auto window_inside = [&](int u) {                     // uniform
+        const int xs = 16 * (t0 + u) - aw;
+        return xs >= 0 && xs + 32 <= p.W;
     };
     floatx4 done[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
     // the pair of tiles tb, tb + 1 (tb even, relative to the run), completed in the two steps before
@@ -250,7 +162,7 @@ __global__ void __launch_bounds__(64 * fir_walk_waves(NK)) fir1d_walk_kernel(Fir
         if (tb < 0 || tb >= L) return;
         const int x = 16 * (t0 + tb);
         if (rows16 && x + 32 <= p.W) {
-            store_rows_via_lds<2, STREAM>(patch, p.out + (int64_t)y0 * p.out_pitch + x, (uint32_t)p.out_pitch, done, lane);
+            store_rows_via_lds<2, true>(patch, p.out + (int64_t)y0 * p.out_pitch + x, (uint32_t)p.out_pitch, done, lane);
         } else if (y0 + c < p.H) {
             float* row = p.out + (int64_t)(y0 + c) * p.out_pitch;
             store4_mask(row, x + 4 * g, p.W, done[0]);
@@ -273,6 +185,7 @@ __global__ void __launch_bounds__(64 * fir_walk_waves(NK)) fir1d_walk_kernel(Fir
         const int u = ub + S;
         if (S % 2 == 0) store_pair(u - R);                // before the loads: loads and stores share one counter
         if (u < nsteps) {
+            if (!window_inside(u)) win[S % NK] = fir_clamped(p, win[S % NK], 16 * (t0 + u) - aw + 8 * g);
             auto product = [&](auto kc) {
                 constexpr int KK = decltype(kc)::value, slot = ((S - 2 * KK) % R + R) % R;
                 acc[slot] = mfma16x16x32(coef[KK], win[S % NK], acc[slot]);
@@ -366,26 +279,21 @@ static hb_status fir1d_prepare(FirArgs& a, const hb_half* in, float* out, int H,
     a.out_pitch = out_pitch;
     a.T = ntaps;
     a.anchor = anchor;
-    const int nk = ceil_div(15 + ntaps + (anchor & 1), 32);
-    a.nct = ceil_div(W, 16 * fir_tiles(nk));
     const int rowsteps = ceil_div(H, 16);
-    const int64_t waves = HB_FIR_WAVES;
-    int steps = (int)(((int64_t)rowsteps * a.nct + waves - 1) / waves);
-    a.steps = steps < 1 ? 1 : steps;
-    a.ntasks = ceil_div(rowsteps, a.steps) * a.nct;
-    // the walk of long filters: runs of an even number of tiles, at least a few turns of the ring long
+    a.nct = ceil_div(W, 16 * HB_FIR_TILES);
+    if ((int64_t)rowsteps * a.nct > 0x7fffffff / 2) return HB_ERR_UNSUPPORTED;
+    a.ntasks = rowsteps * a.nct;
+    // The walk of long filters: runs of an even number of tiles, two waves per SIMD in all.  More of them only walk more
+    // windows ahead of their run (4096 x 4096, 128 / 256 taps: 20.6 / 25.6 us, with four waves per SIMD 25.8 / 32.0), fewer
+    // leave the chip idle (24.7 / 27.7 with one; 512 x 512 with 256 taps 15 us with one run per row group, 10 so).
     a.ntiles = ceil_div(W, 16);
-    const int want_runs = ceil_div(HB_FIR_WALK_WAVES, rowsteps);
-    int max_runs = a.ntiles / (HB_FIR_WALK_MIN_TURNS * 2 * nk);
-    if (max_runs < 1) max_runs = 1;
-    const int runs = want_runs < max_runs ? want_runs : max_runs;
+    const int runs = std::max(1, std::min(8 * num_cu() / rowsteps, a.ntiles / 4));
     a.run_tiles = (ceil_div(a.ntiles, runs) + 1) & ~1;
     a.nruns = ceil_div(a.ntiles, a.run_tiles);
     const int64_t wtasks = (int64_t)rowsteps * a.nruns;
     if (wtasks > 0x7fffffff / 4) return HB_ERR_UNSUPPORTED;
     a.wtasks = (int)wtasks;
     a.taps = pack_taps<HB_MAX_TAPS_FIR1D>(taps_host, ntaps);
-    a.fold = pack_fold_tables<HB_MAX_TAPS_FIR1D>(taps_host, ntaps);
     return HB_OK;
 }
 
@@ -405,30 +313,22 @@ extern "C" hb_status hb_fir1d(const hb_half* in, float* out, int H, int W,
     // a 16-column tile reads the 16 + ntaps - 1 pixels from x0 - anchor on (one more when the
     // window is moved to an even pixel): NK windows of 32
     const int nk = ceil_div(15 + ntaps + (anchor & 1), 32);
-    if (W < 32 * nk)   // narrower than one window of the matrix formulation: vector-ALU kernel
+    if (W < kFirMinWidth)
         return hb_fir1d_valu(in, out, H, W, in_pitch, out_pitch, taps_host, ntaps, anchor, stream);
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    const bool ss = (int64_t)H * W * 4 <= kStreamStoreMaxBytes;
-    if (nk >= HB_FIR_WALK_MIN_NK) {   // long filters: the walk along the row, every window loaded once
 #define HB_FIR_WALK(N)                                                                            \
-    case N: {                                                                                     \
-        const dim3 wgrid(ceil_div(a.wtasks, fir_walk_waves(N))), wblock(64 * fir_walk_waves(N));  \
-        if (ss) hipLaunchKernelGGL((fir1d_walk_kernel<N, true>), wgrid, wblock, 0, st, a);        \
-        else hipLaunchKernelGGL((fir1d_walk_kernel<N, false>), wgrid, wblock, 0, st, a);          \
-        break;                                                                                    \
+    case N:                                                                                       \
+        hipLaunchKernelGGL(fir1d_walk_kernel<N>, dim3(ceil_div(a.wtasks, fir_walk_waves(N))),     \
+                           dim3(64 * fir_walk_waves(N)), 0, st, a);                               \
+        break;
+    switch (nk) {
+        // one window per tile: nothing to share between tiles, every wave takes one strip of tiles
+        case 1: hipLaunchKernelGGL(fir1d_mfma_kernel, dim3(ceil_div(a.ntasks, 4)), dim3(256), 0, st, a); break;
+        // long filters: the walk along the row, every window loaded once
+        HB_FIR_WALK(2) HB_FIR_WALK(3) HB_FIR_WALK(4) HB_FIR_WALK(5) HB_FIR_WALK(6) HB_FIR_WALK(7) HB_FIR_WALK(8) HB_FIR_WALK(9)
+        default: return HB_ERR_UNSUPPORTED;
     }
-        switch (nk) {
-            HB_FIR_WALK(2) HB_FIR_WALK(3) HB_FIR_WALK(4) HB_FIR_WALK(5) HB_FIR_WALK(6) HB_FIR_WALK(7) HB_FIR_WALK(8) HB_FIR_WALK(9)
-            default: return HB_ERR_UNSUPPORTED;
-        }
 #undef HB_FIR_WALK
-        return launch_status();
-    }
-    // one window per tile: nothing to share between tiles, every wave takes one strip of tiles
-    const int blocks = min(ceil_div(a.ntasks, 4), kMaxStreamBlocks);
-    const dim3 grid(blocks), block(256);
-    if (ss) hipLaunchKernelGGL((fir1d_mfma_kernel<1, true>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((fir1d_mfma_kernel<1, false>), grid, block, 0, st, a);
     return launch_status();
 }
 

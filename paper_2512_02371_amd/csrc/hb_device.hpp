@@ -57,14 +57,6 @@ __device__ __forceinline__ floatx16 mfma32x32x16(half8 a, half8 b, floatx16 c) {
 // 8g + i of a chained K = 32 operand stands for.
 __device__ __forceinline__ int krow32(int g, int i) { return 16 * (i >> 2) + 4 * g + (i & 3); }
 
-// Two D fragments (rows 0..15 and 16..31 of a window), rounded to fp16 (RNE), as
-// one K = 32 operand in the slot order of krow32.
-__device__ __forceinline__ half8 chain2(floatx4 lo, floatx4 hi) {
-    half8 r;
-    r[0] = (half_t)lo[0]; r[1] = (half_t)lo[1]; r[2] = (half_t)lo[2]; r[3] = (half_t)lo[3];
-    r[4] = (half_t)hi[0]; r[5] = (half_t)hi[1]; r[6] = (half_t)hi[2]; r[7] = (half_t)hi[3];
-    return r;
-}
 __device__ __forceinline__ half4 to_half4(floatx4 v) {
     half4 r;
     r[0] = (half_t)v[0]; r[1] = (half_t)v[1]; r[2] = (half_t)v[2]; r[3] = (half_t)v[3];
@@ -126,17 +118,6 @@ __device__ __forceinline__ half8 shift_in_from_left(half8 v, int d) {
     return __builtin_bit_cast(half8, a);
 }
 
-// Four consecutive pixels row[xs .. xs+3], clamped like load8_clamp.
-__device__ __forceinline__ half4 load4_clamp(const half_t* __restrict__ row, int xs, int W) {
-    if (xs >= 0 && xs + 4 <= W) {
-        return *reinterpret_cast<const half4_u*>(row + xs);
-    }
-    half4 r;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) r[i] = row[clampi(xs + i, 0, W - 1)];
-    return r;
-}
-
 // Store four consecutive floats at row[x .. x+3], dropping columns >= W.
 __device__ __forceinline__ void store4_mask(float* __restrict__ row, int x, int W, floatx4 v) {
     if (x + 4 <= W) {
@@ -152,9 +133,6 @@ __device__ __forceinline__ void store4_mask(float* __restrict__ row, int x, int 
 // hardware addresses with a scalar base register and one vector offset register.
 __device__ __forceinline__ half8 ldg8(const half_t* base, uint32_t byte_off) {
     return *reinterpret_cast<const half8_u*>(reinterpret_cast<const char*>(base) + byte_off);
-}
-__device__ __forceinline__ half4 ldg4(const half_t* base, uint32_t byte_off) {
-    return *reinterpret_cast<const half4_u*>(reinterpret_cast<const char*>(base) + byte_off);
 }
 // Output stores.  STREAM = true marks the lines non-temporal (written once, not read back by the
 // kernel).  With the coalesced row stores below, streaming stores measured faster at every output
@@ -275,45 +253,6 @@ __device__ __forceinline__ half8 tap_run(const uint16_t* tab, int t0) {
 }
 __device__ __forceinline__ half_t tap_at(const uint16_t* tab, int t) {
     return __builtin_bit_cast(half_t, tab[kTapPad + t]);
-}
-
-// ---------------------------------------------------------------------------
-// Clamp-to-edge folded into the coefficient matrix.
-//
-// Clamping the input index is linear in the pixels: every tap that would read left of
-// pixel 0 reads pixel 0 instead, so its weight moves onto the matrix row of pixel 0 (and
-// likewise for the last pixel).  A border tile therefore keeps the in-bounds, aligned
-// 16-byte window loads of an interior tile (the window is shifted to lie inside the row)
-// and only swaps the Toeplitz fragment for a folded one built from absolute indices.
-// Sums of fp16 taps are not fp16 numbers, so a folded fragment is carried as hi + lo
-// (two products), which keeps the border as accurate as the interior.
-//
-// Tables (FoldTablesT, filled on the host): kf[t] = taps as fp32, pfx[i] = sum of taps t < i.
-// Weight of pixel u in output x: sum of taps[t] over t with clamp(x + t - anchor, 0, n-1) == u.
-template <class FT>
-__device__ __forceinline__ float folded_tap(const FT& ft, int ntaps, int anchor, int n, int x, int u) {
-    float v = 0.f;
-    const int t = u - x + anchor;
-    if (t >= 0 && t < ntaps) v = ft.kf[t];
-    if (u == 0) v += ft.pfx[clampi(anchor - x, 0, ntaps)];                 // taps that read left of 0
-    if (u == n - 1) {
-        const int t0 = clampi(n - x + anchor, 0, ntaps);                   // first tap that reads past n-1
-        v += ft.pfx[ntaps] - ft.pfx[t0];
-    }
-    return v;
-}
-// Folded fragment (natural slot order: slot 8g + i = window pixel 32*kk + 8g + i) for the 16
-// outputs xbase + c and the window starting at absolute pixel ws.
-template <class FT>
-__device__ __forceinline__ void folded_fragment(const FT& ft, int ntaps, int anchor, int n,
-                                                int xbase, int ws, int kk, int c, int g,
-                                                half8& hi, half8& lo) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const float v = folded_tap(ft, ntaps, anchor, n, xbase + c, ws + 32 * kk + 8 * g + i);
-        hi[i] = (half_t)v;
-        lo[i] = (half_t)(v - (float)hi[i]);
-    }
 }
 
 }  // namespace hb

@@ -15,38 +15,14 @@ namespace hb {
 
 // Filter taps as they travel inside the kernel arguments: a zero-padded fp16 table (entry
 // kTapPad + t holds taps[t] for 0 <= t < ntaps and zero for every other t in
-// [-kTapPad, MAXT + 48)), from which a Toeplitz fragment is eight consecutive entries,
-// and, for the border tiles, the taps and their running sums in fp32.  MAXT is the largest tap
-// count of the entry point (hb_fir1d: 256, hb_sepblur: 64 per axis).
+// [-kTapPad, MAXT + 48)), from which a Toeplitz fragment is eight consecutive entries.
+// MAXT is the largest tap count of the entry point (hb_fir1d: 256, hb_sepblur: 64 per axis).
 constexpr int kTapPad = 16;
 template <int MAXT>
 struct TapsT {
     uint16_t tab[kTapPad + MAXT + 48];
 };
-template <int MAXT>
-struct FoldTablesT {
-    float kf[MAXT];          // taps as fp32, zero beyond ntaps
-    float pfx[MAXT + 1];     // pfx[i] = sum of taps t < i
-};
 using Taps = TapsT<HB_MAX_TAPS>;
-using FoldTables = FoldTablesT<HB_MAX_TAPS>;
-
-// Streaming kernels launch one short-lived wave per task (the dispatcher keeps the memory
-// pipes fed best that way); beyond this many 256-thread workgroups every wave walks a
-// strided list of tasks instead.  The number of compute units (MI355X: 256, 4 SIMDs each) is
-// read from the device, see num_cu().
-constexpr int kMaxStreamBlocks = 1 << 20;
-
-// Tasks form an nct x nseg grid.  Those in the rectangle [c0, c1) x [s0, s1) touch no image
-// border and take a lean code path (plain loads, unmasked stores); the others take a
-// border-aware path that is written for small register use rather than speed, so that it
-// does not lower the occupancy of the kernel that holds both.
-struct TaskGrid {
-    int nct, nseg;
-    int c0, c1, s0, s1;
-    __host__ __device__ int count() const { return nct * nseg; }
-    __device__ bool interior(int seg, int ct) const { return ct >= c0 && ct < c1 && seg >= s0 && seg < s1; }
-};
 
 // Interior range [lo, hi) of the n task indices t whose footprint
 // [t*step - before, t*step + after) lies inside [0, extent); lo = hi = 0 when empty.
@@ -130,21 +106,6 @@ inline TapsT<MAXT> pack_taps(const hb_half* taps, int ntaps) {
     return t;
 }
 
-template <int MAXT = HB_MAX_TAPS>
-inline FoldTablesT<MAXT> pack_fold_tables(const hb_half* taps, int ntaps) {
-    FoldTablesT<MAXT> ft;
-    memset(&ft, 0, sizeof(ft));
-    float run = 0.f;
-    for (int i = 0; i <= MAXT; ++i) {
-        ft.pfx[i] = run;
-        if (i < ntaps) {
-            ft.kf[i] = half_bits_to_float(taps[i]);
-            run += ft.kf[i];
-        }
-    }
-    return ft;
-}
-
 inline hb_status launch_status() { return hipGetLastError() == hipSuccess ? HB_OK : HB_ERR_HIP; }
 
 // Raises a kernel's dynamic LDS limit to `bytes`.  The runtime call costs about ten microseconds of
@@ -183,7 +144,6 @@ inline int num_cu() {
     return n > 0 ? n : 256;
 }
 
-inline int floor_div(int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b); }
 inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 }  // namespace hb

@@ -45,8 +45,6 @@ struct SepArgs {
     Taps tx, ty;
 };
 
-__device__ __forceinline__ half_t sep_tap(uint16_t b) { return __builtin_bit_cast(half_t, b); }
-
 // Coefficient fragments, read from the tap tables in the kernel arguments: coefx[kk] = B operand of the
 // row pass, Bx[32 kk + 8g + i][c]; coefy[j] = B operand of the column pass in the chained slot order.
 template <int NKX, int NK>

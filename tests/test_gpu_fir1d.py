@@ -27,7 +27,13 @@ CASES = [
     (48, 1200, 256, 127),    # maximum taps
     (17, 600, 256, 255),     # rightmost anchor
     (17, 600, 256, 0),
-    (9, 250, 256, 100),      # narrower than one window: falls to the vector-ALU kernel
+    (9, 250, 256, 100),      # narrower than one window
+    (20, 7, 33, 3),          # narrower than eight pixels: falls to the vector-ALU kernel
+    (17, 8, 17, 16),
+    (18, 9, 256, 0),         # every window reaches over both ends of the row
+    (3, 65, 16, 15),         # one pixel past a strip
+    (2100, 90, 200, 3),      # one run of six tiles per row group
+    (31, 4100, 40, 39),      # many runs of four tiles, the last one short
 ]
 
 
