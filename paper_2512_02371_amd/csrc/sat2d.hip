@@ -45,20 +45,21 @@ struct SatArgs {
     float* es;             // [nb][ns]  exclusive scan of tot over segments
 };
 
-// Eight pixels row[xs .. xs+7], zero where the row or the column is outside the image.
+// Eight pixels row[xs .. xs+7], zero where the row or the column is outside the image: one load from an address
+// inside, shifted into place (eight predicated ones per lane made the ragged tiles the last to arrive at the
+// grid-wide wait: 1079 x 1917 19.2 us, now 17.4).
 __device__ __forceinline__ half8 load8_zero(const half_t* in, int64_t pitch, int y, int xs, int H, int W) {
+    const half_t* row = in + (int64_t)min(y, H - 1) * pitch;
     half8 r = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (y < H) {
-        const half_t* row = in + (int64_t)y * pitch;
-        if (xs + 8 <= W) {
-            r = *reinterpret_cast<const half8_u*>(row + xs);
-        } else {
+    if (W >= 8) {
+        r = *reinterpret_cast<const half8_u*>(row + min(xs, W - 8));
+        r = shift_in_from_right<true>(r, max(xs - (W - 8), 0));
+    } else {
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (xs + i < W) r[i] = row[xs + i];
-        }
+        for (int i = 0; i < 8; ++i)
+            if (xs + i < W) r[i] = row[xs + i];
     }
-    return r;
+    return y < H ? r : half8{0, 0, 0, 0, 0, 0, 0, 0};
 }
 
 __device__ __forceinline__ half8 ones8() { return half8{1, 1, 1, 1, 1, 1, 1, 1}; }
@@ -192,6 +193,10 @@ __global__ void __launch_bounds__(256) sat_scan_kernel(SatArgs p) {
 
 // ---------------------------------------------------------------------------
 // 3  apply
+// every lane of a 16-lane row receives lane 15's value
+__device__ __forceinline__ float dpp_row_last(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x15f, 0xf, 0xf, true));   // row_newbcast:15
+}
 __device__ __forceinline__ float dpp_row_shr(float v, int n) {
     // lane i of each 16-lane row receives lane i - n of the same row, 0 where there is none
     int r;
@@ -288,21 +293,14 @@ __global__ void __launch_bounds__(256) sat_apply_mfma_kernel(SatArgs p) {
                 x += dpp_row_shr(x, 8);
                 x += ccar[t][v];
                 acc[t][v] = x;
-                ccar[t][v] = __shfl(x, (lane & 48) | 15, 64);         // value of the last row = next column carry
+                ccar[t][v] = dpp_row_last(x);             // value of the last row = next column carry
             }
         if (full) {
             store_rows_via_lds<4, STREAM>(s_patch[threadIdx.x >> 6], p.out + (int64_t)(y0 + 16 * rt) * p.out_pitch + x0,
                                           (uint32_t)p.out_pitch, acc, lane);
-        } else {
-            const int y = y0 + 16 * rt + c;
-            if (y < p.H) {
-                float* orow = p.out + (int64_t)y * p.out_pitch;
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const int xo = x0 + 16 * t + 4 * g;
-                    if (xo < p.W) store4_mask(orow, xo, p.W, acc[t]);
-                }
-            }
+        } else if (y0 + 16 * rt < p.H) {
+            store_rows_via_lds_masked<4, STREAM>(s_patch[threadIdx.x >> 6], p.out + (int64_t)(y0 + 16 * rt) * p.out_pitch + x0,
+                                                 p.out_pitch, acc, lane, p.H - y0 - 16 * rt, p.W - x0);
         }
     }
 }
@@ -471,7 +469,7 @@ __device__ __forceinline__ void sat_fused_local(const SatFusedArgs& p, SatFusedL
                 x += dpp_row_shr(x, 8);
                 x += ccar[t][v];
                 Lt[rt][t][v] = x;
-                ccar[t][v] = __shfl(x, (lane & 48) | 15, 64);         // value of the last row = next column carry
+                ccar[t][v] = dpp_row_last(x);             // value of the last row = next column carry
             }
         if (g == 3) L.lastcol[ts][tb][16 * rt + c] = Lt[rt][3][3];    // column 63 of row 16 rt + c
     }
@@ -575,16 +573,9 @@ __device__ __forceinline__ void sat_fused_finish(const SatFusedArgs& p, SatFused
         if (full) {
             store_rows_via_lds<4, STREAM>(L.patch[wv], p.out + (int64_t)(y0 + 16 * rt) * p.out_pitch + x0,
                                           (uint32_t)p.out_pitch, acc, lane);
-        } else {
-            const int y = y0 + 16 * rt + c;
-            if (y < p.H) {
-                float* orow = p.out + (int64_t)y * p.out_pitch;
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const int xo = x0 + 16 * t + 4 * g;
-                    if (xo < p.W) store4_mask(orow, xo, p.W, acc[t]);
-                }
-            }
+        } else if (y0 + 16 * rt < p.H) {
+            store_rows_via_lds_masked<4, STREAM>(L.patch[wv], p.out + (int64_t)(y0 + 16 * rt) * p.out_pitch + x0, p.out_pitch,
+                                                 acc, lane, p.H - y0 - 16 * rt, p.W - x0);
         }
     }
 }
@@ -928,7 +919,9 @@ static int sat_fused_capacity(int t) {
 }
 
 static hb_status sat_launch_mfma(const SatArgs& a, void* ws, hipStream_t st) {
-    const bool stream_stores = (int64_t)a.H * a.W * 4 <= kStreamStoreMaxBytes;
+    // Rows whose 16-byte pieces are misaligned leave through the L2, which puts the lines that two pieces share together
+    // (4095 x 4093 38.5 us, streamed 49), unless the output fits the memory-side cache (2047 x 2045 20.8, streamed 19.0).
+    const bool stream_stores = (a.out_pitch % 4 == 0 && aligned_to(a.out, 16)) || (int64_t)a.H * a.W * 4 <= (32 << 20);
     const int t = sat_fused_shape(a.H, a.W);
     if (t) {
         SatFusedArgs f;
