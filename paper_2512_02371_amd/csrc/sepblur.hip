@@ -402,13 +402,20 @@ static hb_status sep_launch_one_window(hipStream_t st, SepArgs& a) {
     }
     return sep_launch(sepblur_mfma_kernel<NT, 8>, st, a, 8, cols, 4);
 }
+// The march also serves the short filters where rows of the output start inside 128-byte lines: the runs of its four
+// strips meet in one L2, the lone 128-byte runs of the kernel above do not (16 taps, 4095 x 4095 44 -> 31 us,
+// 1079 x 1917 13 -> 7.7).
 template <int NT>
 static hb_status sep_launch_nt(int nkx, hipStream_t st, SepArgs& a) {
-    if (nkx == 1) return sep_launch_one_window<NT>(st, a);
+    const bool lines = a.out_pitch % 32 == 0 && aligned_to(a.out, 128);
+    if (nkx == 1 && (lines || NT > 3)) return sep_launch_one_window<NT>(st, a);
     // four workgroups per compute unit are resident; segments beyond 8 steps only cost balance (8192 x 4096, 48
     // taps: 36 us with 8 steps, 42 with the 16 that four workgroups per unit would give)
     const int64_t rowsteps = ceil_div(a.H, 16), nct = ceil_div(a.W, kSepMarchCols), want = 4 * num_cu();
     const int steps = (int)std::min<int64_t>((rowsteps * nct + want - 1) / want, 8);
+    if constexpr (NT <= 3) {
+        if (nkx == 1) return sep_launch(sepblur_march_mfma_kernel<1, NT>, st, a, steps, kSepMarchCols, 1);
+    }
     if (nkx == 2) return sep_launch(sepblur_march_mfma_kernel<2, NT>, st, a, steps, kSepMarchCols, 1);
     return sep_launch(sepblur_march_mfma_kernel<3, NT>, st, a, steps, kSepMarchCols, 1);
 }
