@@ -96,7 +96,7 @@ static hb_status conv2d_prepare(T2Args& a, const hb_half* in, float* out, int H,
     memcpy(a.taps, taps_host, sizeof(uint16_t) * (size_t)kh * (size_t)kw);
     a.Ho = H;
     a.Wo = W;
-    a.ncol = a.nrow = a.ntiles = a.per_wg = a.steps = a.srows = a.rows = 0;
+    a.ncol = a.nrow = a.ntiles = a.per_wg = a.stream = a.steps = a.srows = a.rows = 0;
     return HB_OK;
 }
 
