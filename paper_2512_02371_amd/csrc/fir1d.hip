@@ -48,6 +48,7 @@ struct FirArgs {
     int T, anchor;
     int nct;             // strips per row group
     int ntasks;          // strips x row groups
+    int lines;           // every row of the output starts a 128-byte line
     int ntiles, run_tiles, nruns, wtasks;   // the walk of long filters: tiles per row, per run, runs per row group, tasks
     TapsT<HB_MAX_TAPS_FIR1D> taps;
 };
@@ -130,7 +131,7 @@ template <int NK>
 __global__ void __launch_bounds__(64 * fir_walk_waves(NK)) fir1d_walk_kernel(FirArgs p) {
     constexpr int R = 2 * NK;
     constexpr int WV = fir_walk_waves(NK);
-    __shared__ __attribute__((aligned(16))) float s_patch[WV][RowPatch<2>::kFloats];
+    __shared__ __attribute__((aligned(16))) float s_patch[WV][RowPatch<4>::kFloats];
     const int lane = threadIdx.x & 63;
     const int c = lane & 15, g = lane >> 4;
     const int e = p.anchor & 1;
@@ -157,11 +158,47 @@ __global__ void __launch_bounds__(64 * fir_walk_waves(NK)) fir1d_walk_kernel(Fir
         return xs >= 0 && xs + 32 <= p.W;
     };
     floatx4 done[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
+    // Rows that start inside a 128-byte line: columns 32 k + o .. 32 k + o + 31 of the run are a line of the row, o its
+    // first column's distance to the next line.  The patch keeps the last two pairs, and with pair k the line that ends in
+    // it leaves, whole: pairs stored as they are would write two parts of a line (100 taps, 4095 x 4095 63 us
+    // so, 38 by lines; 4096 x 4100 46, 23.6).
+    const int limit = min(16 * L, p.W - 16 * t0);         // columns of the run
+    int o[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const int64_t at = (int64_t)(reinterpret_cast<uintptr_t>(p.out) / 4) + (int64_t)(y0 + 8 * s + (lane >> 3)) * p.out_pitch + 16 * t0;
+        o[s] = (int)(-at & 31);
+    }
+    auto store_line = [&](int k) {                        // the one that ends in pair k
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int row = 8 * s + (lane >> 3), col = 32 * (k - 1) + o[s] + 4 * (lane & 7);
+            floatx4 v;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = patch[row * RowPatch<4>::kPitch + ((col + i) & 63)];
+            if (y0 + row >= p.H) continue;
+            float* const q = p.out + (int64_t)(y0 + row) * p.out_pitch + 16 * t0 + col;
+            if (col >= 0 && col + 4 <= limit) {
+                __builtin_nontemporal_store(v, reinterpret_cast<floatx4_u*>(q));
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (col + i >= 0 && col + i < limit) q[i] = v[i];
+            }
+        }
+        wave_lds_fence();
+    };
     // the pair of tiles tb, tb + 1 (tb even, relative to the run), completed in the two steps before
     auto store_pair = [&](int tb) {
         if (tb < 0 || tb >= L) return;
         const int x = 16 * (t0 + tb);
-        if (rows16 && x + 32 <= p.W) {
+        if (!p.lines) {                                   // uniform
+#pragma unroll
+            for (int w = 0; w < 2; ++w)
+                *reinterpret_cast<floatx4*>(patch + c * RowPatch<4>::kPitch + ((16 * (tb + w)) & 63) + 4 * g) = done[w];
+            wave_lds_fence();
+            store_line(tb / 2);
+        } else if (rows16 && x + 32 <= p.W) {
             store_rows_via_lds<2, true>(patch, p.out + (int64_t)y0 * p.out_pitch + x, (uint32_t)p.out_pitch, done, lane);
         } else if (y0 + c < p.H) {
             float* row = p.out + (int64_t)(y0 + c) * p.out_pitch;
@@ -200,6 +237,7 @@ __global__ void __launch_bounds__(64 * fir_walk_waves(NK)) fir1d_walk_kernel(Fir
 #pragma unroll 1
     for (ub = 0; ub < nsteps; ub += R) unrolled_steps<R>(step);
     store_pair(ub - R);
+    if (!p.lines) store_line((L + 1) / 2);                // what is left of the last line
 }
 
 // Vector-ALU twin: a 16 x 128 tile is staged in LDS as fp32 with its halo, the column index clamped
@@ -277,6 +315,7 @@ static hb_status fir1d_prepare(FirArgs& a, const hb_half* in, float* out, int H,
     a.W = W;
     a.in_pitch = in_pitch;
     a.out_pitch = out_pitch;
+    a.lines = out_pitch % 32 == 0 && aligned_to(out, 128);
     a.T = ntaps;
     a.anchor = anchor;
     const int rowsteps = ceil_div(H, 16);

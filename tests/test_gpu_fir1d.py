@@ -61,6 +61,15 @@ def test_fir1d_matches_oracle(orc, fn, H, W, T, a):
     assert_close(got, orc.fir1d(img, taps, a), f"{fn} {H}x{W} T={T} a={a}")
 
 
+@pytest.mark.parametrize("extra", [1, 4, 7, 20])
+@pytest.mark.parametrize("H,W,T,a", [(19, 500, 40, 20), (40, 31, 100, 3), (17, 130, 256, 255), (5, 1040, 64, 0)])
+def test_fir1d_long_filters_with_rows_inside_lines(orc, H, W, T, a, extra):
+    """Row pitches that move the rows' starts through a 128-byte line, runs that end inside one."""
+    img, taps, got, obuf = run("hb_fir1d", H, W, T, a, pitch_extra=extra)
+    assert_close(got, orc.fir1d(img, taps, a), f"{H}x{W} T={T} pitch+{extra}")
+    assert np.all(obuf[:, W:] == 7.0), "wrote past the row end"
+
+
 @pytest.mark.parametrize("fn", ["hb_fir1d", "hb_fir1d_valu"])
 @pytest.mark.parametrize("extra,offset", [(8, 0), (3, 0), (5, 1), (12, 8)])
 def test_fir1d_pitched_and_misaligned_layouts(orc, fn, extra, offset):
