@@ -26,7 +26,9 @@
  *    `anchor` shifts the window, tap r reads x + r - anchor; anchor = 0 is the
  *    paper's formula verbatim.  Output has the size of the input; out-of-range
  *    reads clamp the INPUT index to the edge (zero padding for hb_conv3x3).
- *  - Arithmetic: fp16 operands, fp32 accumulation on the matrix units.
+ *  - Arithmetic: fp16 operands, fp32 accumulation on the matrix units.  A window of the
+ *    matrix formulation is a little wider than the filter, with zero coefficients there: a
+ *    non-finite sample makes NaN of every output whose window holds it.
  *  - `stream` is a hipStream_t (passed as void* so that this header needs no HIP
  *    include).  All work is enqueued on it; no call synchronises, allocates, frees
  *    or keeps a pointer.  Input and output buffers must not overlap.
