@@ -340,12 +340,13 @@ hb_status hb_conv3x3_valu(const hb_half *in_nhwc, const hb_half *w_hwio, hb_half
  * 2x downsample as a product with A_down(x, y) = K(y - 2x), 2x upsample as a
  * two-phase filter K_phase(x, dx) = K(2x + dx) whose phases are interleaved before
  * the store):
- *     D[m][n]  = sum_{i,j=-2..2} w[i] w[j] in[clampH(2m+i)][clampW(2n+j)]      (H/2 x W/2)
+ *     D[m][n]  = sum_{i,j=-2..2} w[i] w[j] in[clampH(2m+i)][clampW(2n+j)]      (H/2 x W/2, fp16 on chip)
  *     per axis:  U[2n] = (D[c(n-1)] + 6 D[n] + D[c(n+1)]) / 8,  U[2n+1] = (D[n] + D[c(n+1)]) / 2
  *                (c clamps the D index to its extent), along x then along y
  *     residual = in - U                                                        (H x W, fp32)
- * (hb_pyr_level applies down and up as one matrix per axis and rounds the row-filtered
- * pixels to fp16 once; the twin rounds D to fp16.)
+ * U is formed from the fp16 D, so that residual + U(down) gives the input back: exactly up to
+ * fp32 sums with the twin, within 2^-11 of the largest pixel with hb_pyr_level, which also rounds
+ * the row-filtered pixels and U along x to fp16 (images narrower than 48 pixels run the twin).
  * H and W must be even.  `down_or_null`, when not null, receives D rounded to fp16
  * (H/2 x W/2, pitch down_pitch); pass NULL (and any pitch) to skip it.
  */

@@ -109,3 +109,64 @@ def test_pyr_full_benchmark_size_sampled_bands(orc, want_down):
         if want_down:
             got = down[(lo + a) // 2:(lo + b) // 2].cpu().numpy().astype(np.float64)
             assert_close(got, dref[a // 2:b // 2], f"down rows {(lo + a) // 2}..{(lo + b) // 2}")
+
+
+def _up(d):
+    """U of the definition, in float64, from a coarser level d."""
+    def axis0(d):
+        e = np.concatenate([d[:1], d, d[-1:]])
+        u = np.empty((2 * d.shape[0], d.shape[1]))
+        u[0::2] = (e[:-2] + 6 * e[1:-1] + e[2:]) / 8
+        u[1::2] = (e[1:-1] + e[2:]) / 2
+        return u
+    return axis0(axis0(d.T).T)
+
+
+def _down_axis0(p):
+    e = np.concatenate([p[:1], p[:1], p, p[-1:], p[-1:]])
+    n = p.shape[0] // 2
+    return sum(w * e[i:i + 2 * n:2] for i, w in enumerate((0.0625, 0.25, 0.375, 0.25, 0.0625)))
+
+
+ROUND_TRIP_SIZES = [(2, 48), (6, 50), (64, 64), (34, 70), (130, 300), (96, 104), (66, 202), (30, 1026), (1030, 88)]
+
+
+@pytest.mark.parametrize("smooth", [False, True])
+@pytest.mark.parametrize("fn", ["hb_pyr_level", "hb_pyr_level_valu"])
+@pytest.mark.parametrize("H,W", ROUND_TRIP_SIZES + [(16, 46), (20, 8)])
+def test_pyr_residual_belongs_to_the_coarser_level(fn, H, W, smooth):
+    """residual + up(down) is the input: up to fp32 sums (three of numbers below 1: 3 * 2^-23) for the twin and for
+    narrow images, up to the rounding of U along x otherwise (below 1: half of 2^-11, passed on with weights that add up
+    to 1)."""
+    import torch
+    from paper_2512_02371_amd import hb
+    img = synth.uniform01_f16(5800 + H + W, (H, W)).view(np.float16)
+    if smooth:
+        y, x = np.mgrid[0:H, 0:W]
+        img = (0.5 + 0.45 * np.sin(y / 9.0) * np.cos(x / 13.0)).astype(np.float16)
+    d_in = torch.from_numpy(img).to("cuda:0")
+    res = torch.empty((H, W), dtype=torch.float32, device="cuda:0")
+    down = torch.empty((H // 2, W // 2), dtype=torch.float16, device="cuda:0")
+    getattr(hb, fn)(d_in, res, down)
+    back = res.cpu().numpy().astype(np.float64) + _up(down.cpu().numpy().astype(np.float64))
+    bound = 3 * 2.0 ** -23 + (2.0 ** -12 if fn == "hb_pyr_level" and W >= 48 else 0.0)
+    assert np.abs(back - img.astype(np.float64)).max() <= bound
+
+
+@pytest.mark.parametrize("H,W", ROUND_TRIP_SIZES)
+def test_pyr_rounds_where_the_definition_of_the_stage_says(H, W):
+    """The row-filtered pixels, D and U along x are fp16, every sum is fp32.  On the 2^-11 grid the sums are exact, so
+    the roundings alone decide the results."""
+    _, res, down, _, _ = out = run("hb_pyr_level", H, W, True)
+    img = out[0].view(np.float16).astype(np.float64)
+    f16 = lambda a: a.astype(np.float16).astype(np.float64)
+    d = f16(_down_axis0(f16(_down_axis0(img.T).T)))
+    e = np.concatenate([d[:, :1], d, d[:, -1:]], axis=1)
+    u1 = np.empty((H // 2, W))
+    u1[:, 0::2], u1[:, 1::2] = (e[:, :-2] + 6 * e[:, 1:-1] + e[:, 2:]) / 8, (e[:, 1:-1] + e[:, 2:]) / 2
+    u1 = f16(u1)
+    e = np.concatenate([u1[:1], u1, u1[-1:]])
+    u = np.empty((H, W))
+    u[0::2], u[1::2] = (e[:-2] + 6 * e[1:-1] + e[2:]) / 8, (e[1:-1] + e[2:]) / 2
+    assert np.array_equal(down.astype(np.float64), d)
+    assert np.abs(res - (img - u)).max() <= 2.0 ** -23
