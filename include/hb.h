@@ -175,8 +175,8 @@ hb_status hb_sepblur_valu(const hb_half *in, float *out, int H, int W,
  *     out[c][yo][xo] = sum_{i < band_y} sum_{j < band_x} coef_y[yo * band_y + i] * coef_x[xo * band_x + j]
  *                      * in[c][clampH(start_y[yo] + i)][clampW(start_x[xo] + j)]
  * The horizontal pass runs first; its result is rounded to fp16 (hb_resize keeps it on the chip
- * and leaves the workspace untouched unless W < 8; the twin keeps it there, transposed.  Both
- * check the workspace the same way.)  in: C planes of H x W fp16 (row pitch in_pitch, plane stride in_plane,
+ * and leaves the workspace untouched up to factors of about 18; beyond them, for W < 8 and in the
+ * twin it is kept in the workspace, transposed.  All check the workspace the same way.)  in: C planes of H x W fp16 (row pitch in_pitch, plane stride in_plane,
  * in elements); out: C planes of Ho x Wo fp32 (out_pitch, out_plane).
  * start_y / start_x: Ho / Wo int32; coef_y / coef_x: Ho x band_y / Wo x band_x fp16,
  * row-major.  All four are DEVICE pointers, read by the kernels on `stream`.
@@ -185,7 +185,9 @@ hb_status hb_sepblur_valu(const hb_half *in, float *out, int H, int W,
  * 1 <= band <= HB_RESIZE_MAX_SPAN.  Every read is clamped into the image whatever
  * the matrices hold, and any starts are computed correctly: an aligned group of 16
  * outputs whose rows together span more than a few hundred input samples is
- * processed in several rounds (slower, same result).
+ * processed in several rounds (same result).  hb_resize expects starts that advance by about
+ * the scale; starts scattered over much wider ranges cost it up to the whole image per group of
+ * outputs (2048 x 2048 to half the size, every start anywhere in the image: 6 ms).
  */
 size_t hb_resize_workspace_size(int C, int H, int Wo);
 hb_status hb_resize(const hb_half *in, float *out, void *workspace, size_t workspace_bytes,

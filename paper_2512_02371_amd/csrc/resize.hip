@@ -9,7 +9,7 @@
 // times that block is NK products of the usual kind: the image operand is 8 consecutive samples of
 // one row per lane, straight from memory.
 //
-// Both passes run in one launch.  A wave owns 16 output columns x 16 GY output rows: it applies the
+// Both passes run in one launch (but for large factors, see below).  A wave owns 16 output columns x 16 GY output rows: it applies the
 // horizontal matrix to 16 input rows at a time and leaves the result, rounded to fp16, TRANSPOSED in its piece of
 // LDS, T[xo][y], where the vertical pass finds its contraction index y contiguous: out^T = T * coef_y^T ends with
 // a lane owning four consecutive columns of a row.  (The vector-ALU twin keeps two launches with T in the
@@ -21,7 +21,7 @@
 
 namespace hb {
 
-// One pass of the vector-ALU twin.
+// One pass of the two-launch form and of the vector-ALU twin.
 struct BandArgs {
     const half_t* x;                          // [planes][rows][len], row pitch x_pitch, plane stride x_plane
     void* z;                                  // [planes][nout][rows] transposed result, fp16 or fp32
@@ -29,7 +29,7 @@ struct BandArgs {
     const half_t* coef;                       // device: nout x band coefficients
     int rows, len, nout, band, planes;
     int64_t x_pitch, x_plane, z_pitch, z_plane;
-    int ngroups;                              // groups of 16 outputs
+    int ngroups, nruns;                       // groups of 16 outputs; runs of kRzWaves strips per plane
 };
 
 struct ResizeArgs {
@@ -231,6 +231,171 @@ __global__ void __launch_bounds__(64 * RzGeom<SHARED>::kWaves, 4) resize_mfma_ke
     }
 }
 
+// ---------------------------------------------------------------------------
+// The two-launch form for large factors: one kernel that contracts over the memory-contiguous index of its input and
+// writes its result TRANSPOSED, Z[o][r] = sum_j X[r][start[o] + j] coef[o][j], run once per axis with T in the
+// workspace.  A wave owns 64 rows of X and one group of 16 outputs, so the pixels of a wide span are read once per
+// group whatever the rows' matrix is, by as many waves as the image has rows.
+constexpr int kRzTiles = 4;                   // 16-row tiles of X per wave (64 rows r)
+constexpr int kRzWaves = 2;                   // waves per workgroup: 2 strips of 64 rows, one group of 16 outputs (measured: 1, 4, 8 are slower)
+constexpr int kRzMaxChunks = HB_RESIZE_MAX_SPAN / 32;
+
+// Sixteen rows of 64 floats from the accumulators (lane (c, g): row c, columns 16 w + 4 g ..) to
+// fp16 rows in memory, through the wave's LDS patch so that a row leaves as one 128-byte run.
+template <int NW>
+__device__ __forceinline__ void rz_store_rows_half(float* patch, half_t* dst, uint32_t pitch_elems,
+                                                   const floatx4 (&acc)[NW], int lane) {
+    const int c = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int w = 0; w < NW; ++w)
+        *reinterpret_cast<floatx4*>(patch + c * RowPatch<NW>::kPitch + 16 * w + 4 * g) = acc[w];
+    wave_lds_fence();
+    constexpr int kLanesPerRow = 4 * NW, kRowsPerPass = 64 / kLanesPerRow;
+    const int rr = lane / kLanesPerRow, xq = lane - rr * kLanesPerRow;
+#pragma unroll
+    for (int s = 0; s < 16 / kRowsPerPass; ++s) {
+        const int row = s * kRowsPerPass + rr;
+        const floatx4 v = *reinterpret_cast<const floatx4*>(patch + row * RowPatch<NW>::kPitch + 4 * xq);
+        const half4 h = {(half_t)v[0], (half_t)v[1], (half_t)v[2], (half_t)v[3]};
+        *reinterpret_cast<half4_u*>(dst + (size_t)row * pitch_elems + 4 * xq) = h;
+    }
+    wave_lds_fence();
+}
+
+template <bool OUT_HALF>
+__global__ void __launch_bounds__(64 * kRzWaves) band_mfma_kernel(BandArgs p) {
+    constexpr int NW = kRzTiles;
+    // The coefficient block and, once the products are done, the waves' store patches share one piece
+    // of LDS: with both resident a compute unit held too few workgroups to cover the grid in one round.
+    constexpr int kFragBytes = kRzMaxChunks * 64 * 16, kPatchBytes = kRzWaves * RowPatch<NW>::kFloats * 4;
+    __shared__ __attribute__((aligned(16))) char s_mem[kFragBytes > kPatchBytes ? kFragBytes : kPatchBytes];
+    half8* s_frag = reinterpret_cast<half8*>(s_mem);
+    float* s_patch = reinterpret_cast<float*>(s_mem);
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wv = tid >> 6;
+    const int c = lane & 15, g = lane >> 4;
+    // neighbouring groups read neighbouring pieces of the same rows: walk them back to back inside one XCD
+    int wg = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int grp = wg % p.ngroups;
+    wg /= p.ngroups;
+    const int run = wg % p.nruns, plane = wg / p.nruns;
+    const int o0 = 16 * grp;
+
+    // geometry of the group: first sample (even) and number of 32-sample chunks.  Lane column c
+    // reads the start of output o0 + c; the minimum and maximum over the 16 columns come from four
+    // butterfly steps inside each row of 16 lanes, so every lane ends up with the same numbers.
+    // A start below -band (above len - 1) reads nothing but the first (last) sample, and so does
+    // -band (len - 1): clamping it there changes no result and bounds the span by the image.
+    const int o = o0 + c;
+    const bool live = o < p.nout;
+    const int st = live ? clampi(p.start[o], -p.band, p.len - 1) : 0;
+    int lo = live ? st : 0x7fffffff, hi = live ? st + p.band : -0x7fffffff;
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) {
+        lo = min(lo, __shfl_xor(lo, off, 64));
+        hi = max(hi, __shfl_xor(hi, off, 64));
+    }
+    const int first = lo & ~1, nk_all = (hi - first + 31) / 32;
+
+    const int r0 = 64 * (kRzWaves * run + wv);            // this wave's strip of rows
+    const bool active = r0 < p.rows;
+    const half_t* xpl = p.x + (size_t)plane * p.x_plane;
+    const uint32_t rowbytes = (uint32_t)p.x_pitch * 2u;
+    uint32_t rowoff[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) rowoff[w] = (uint32_t)min(r0 + 16 * w + c, p.rows - 1) * rowbytes;
+
+    auto load_chunk = [&](int kk, half8 (&d)[NW]) {
+        const int xs = first + 32 * kk;                   // uniform
+        if (xs >= 0 && xs + 32 <= p.len) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) d[w] = ldg8(xpl, rowoff[w] + 2u * (uint32_t)(xs + 8 * g));
+        } else {
+#pragma unroll
+            for (int w = 0; w < NW; ++w)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int x = clampi(xs + 8 * g + i, 0, p.len - 1);
+                    d[w][i] = *reinterpret_cast<const half_t*>(reinterpret_cast<const char*>(xpl) + (rowoff[w] + 2u * (uint32_t)x));
+                }
+        }
+    };
+    floatx4 acc[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) acc[w] = floatx4{0.f, 0.f, 0.f, 0.f};
+    half8 bufa[NW], bufb[NW];
+    // The coefficient block holds kRzMaxChunks chunks; a group that spans more (a very large factor,
+    // or starts that jump inside the group) takes several rounds of block + products.
+    for (int base = 0; base < nk_all; base += kRzMaxChunks) {
+        const int nk = min(nk_all - base, kRzMaxChunks);
+        if (base) __syncthreads();                        // every wave is done with the previous block
+        // the first window chunk is requested before the coefficient block is built
+        if (active) load_chunk(base, bufa);
+
+        // coefficient block, B-operand layout: lane (c = o, g) holds B[8g + i][o] = coef[o][first + 32 kk + 8g + i - start[o]];
+        // wave wv builds chunks wv, wv + kRzWaves, ...
+        for (int kk = wv; kk < nk; kk += kRzWaves) {
+            half8 f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) f[i] = (half_t)0;
+            if (live) {
+                const int t0 = first + 32 * (base + kk) + 8 * g - st;
+                const half_t* row = p.coef + (size_t)o * p.band;
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if (t0 + i >= 0 && t0 + i < p.band) f[i] = row[t0 + i];
+            }
+            s_frag[kk * 64 + lane] = f;
+        }
+        __syncthreads();
+
+        // two window buffers used alternately: the next chunk is in flight while this one is multiplied
+        auto use_chunk = [&](int kk, const half8 (&d)[NW]) {
+            const half8 f = s_frag[kk * 64 + lane];
+#pragma unroll
+            for (int w = 0; w < NW; ++w) acc[w] = mfma16x16x32(d[w], f, acc[w]);
+        };
+        for (int kk = 0; active && kk < nk; kk += 2) {
+            if (kk + 1 < nk) load_chunk(base + kk + 1, bufb);
+            use_chunk(kk, bufa);
+            if (kk + 1 >= nk) break;
+            if (kk + 2 < nk) load_chunk(base + kk + 2, bufa);
+            use_chunk(kk + 1, bufb);
+        }
+    }
+    __syncthreads();                                      // every wave is done with the coefficient block
+    if (!active) return;
+
+    // D[m = r][n = o]: lane (c = o, g) holds rows r0 + 16 w + 4 g .. + 3 = four consecutive elements of Z's row o
+    float* patch = s_patch + wv * RowPatch<NW>::kFloats;
+    const bool whole = o0 + 16 <= p.nout && r0 + 64 <= p.rows;
+    if (OUT_HALF) {
+        half_t* z = reinterpret_cast<half_t*>(p.z) + (size_t)plane * p.z_plane;
+        if (whole) {
+            rz_store_rows_half<NW>(patch, z + (size_t)o0 * p.z_pitch + r0, (uint32_t)p.z_pitch, acc, lane);
+        } else if (o0 + c < p.nout) {
+            half_t* row = z + (size_t)(o0 + c) * p.z_pitch;
+#pragma unroll
+            for (int w = 0; w < NW; ++w)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int r = r0 + 16 * w + 4 * g + j;
+                    if (r < p.rows) row[r] = (half_t)acc[w][j];
+                }
+        }
+    } else {
+        float* z = reinterpret_cast<float*>(p.z) + (size_t)plane * p.z_plane;
+        if (whole) {
+            store_rows_via_lds<NW, true>(patch, z + (size_t)o0 * p.z_pitch + r0, (uint32_t)p.z_pitch, acc, lane);
+        } else if (o0 + c < p.nout) {
+            float* row = z + (size_t)(o0 + c) * p.z_pitch;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) store4_mask(row, r0 + 16 * w + 4 * g, p.rows, acc[w]);
+        }
+    }
+}
+
 // Vector-ALU twin of one pass.  A workgroup takes one group of 16 outputs and 64 rows of X: the samples
 // the group reads (from its smallest start on, 256 at a time, every index clamped) are staged in LDS
 // with coalesced row loads; a thread owns one output o and four rows, reads a coefficient once and
@@ -319,7 +484,28 @@ static hb_status resize_run(bool valu, const hb_half* in, float* out, void* work
     if (!workspace || workspace_bytes < need || !aligned_to(workspace, 256)) return HB_ERR_WORKSPACE;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
 
-    if (!valu && W >= kRzMinWidth) {
+    // What a group of 16 outputs spans of an axis when its starts advance by the scale
+    auto span = [](int n_in, int n_out, int band) { return (double)(n_out < 16 ? n_out - 1 : 15) * n_in / n_out + band + 1; };
+    const double span_x = span(W, Wo, band_x), span_y = span(H, Ho, band_y);
+    const int groups = ceil_div(Ho, 16);
+    const int64_t waves = (int64_t)C * ceil_div(Wo, 16) * groups;         // of one group each
+    // The one-launch kernel keeps the coefficients of kRzChunks chunks; wider spans it takes chunk by chunk, each one a
+    // round trip, once for every group of rows that needs them.  That pays only while a group spans few rows and the
+    // waves are few (2048 x 2048 -> 1024 x 26 28 us, two launches 60; -> 26 x 26 460 against 99, 16 x 1024 x 1024 -> 500 x 40
+    // 63 against 37).
+    // Nor does it pay where the rows of a group are so many that few workgroups pass over most of the image (2832 x 3696
+    // -> 55 x 210, 370 x 1081 pixels a group: 84 us, two launches 64; 127 x 1655 47 against 77).
+    // Rows that start on odd samples are read at a fraction of the rate, and the one-launch kernel reads a row for every
+    // group of outputs that needs it (8 planes of 2048 rows at a pitch of 2049, factor 9: 71 us against 55; factor 4: 57
+    // against 65; 1024 x 1024 at a pitch of 1025, factor 16: 31 against 29).
+    const bool odd_rows = (in_pitch & 1) || (C > 1 && (in_plane & 1)) || !aligned_to(in, 4);
+    // Large enlargements are bound by their stores, of 64-byte runs here and 256-byte runs there (3 x 2048 x 2048 to three
+    // times the size 222 us, two launches 170); where rows start inside 128-byte lines neither run is whole (227 against 246).
+    const bool line_stores = (double)Ho * Wo >= 2.0 * H * W && (int64_t)C * Ho * Wo > (16 << 20) && out_pitch % 32 == 0 &&
+                             out_plane % 32 == 0 && aligned_to(out, 128);
+    const bool one_launch = W >= kRzMinWidth && (span_x <= 32 * kRzChunks ? span_x * span_y <= 3.2e5 : span_y <= 128 && waves <= 2 * num_cu()) &&
+                            !line_stores && !(odd_rows && span_y > ((int64_t)C * H * W > (6 << 20) ? 120 : 320));
+    if (!valu && one_launch) {
         ResizeArgs r;
         r.in = reinterpret_cast<const half_t*>(in);
         r.out = out;
@@ -342,11 +528,10 @@ static hb_status resize_run(bool valu, const hb_half* in, float* out, void* work
         // Groups of 16 output rows per wave: more share more, while the rows they need fit the wave's LDS and the
         // chip keeps two waves per SIMD (2048 x 2048 from 4096 x 4096: 34 / 29 / 27 us with 1 / 2 / 4; 450 x 450 x 3 from
         // 2048 x 2048: 19 / 29 / 37).  Under one wave per SIMD the waves of a workgroup share one group (256 x 256 from
-        // 4096 x 4096: 20 us against 92).
-        const int groups = ceil_div(Ho, 16);
-        const int64_t waves = (int64_t)C * r.ngx * groups;
+        // 4096 x 4096: 20 us against 92), under two where its rows do not fit a wave's LDS at once (512 x 512 from
+        // 8192 x 8192: 56 against 96; at two 256 x 2048 from 4096 x 4096 33 with a group per wave, 41 shared).
         auto good = [&](int q) { return waves >= 8 * q * num_cu() && 16.0 * q * H / Ho + band_y <= RzGeom<false>::kRows; };
-        const int gq = waves < 4 * num_cu() ? 0 : good(4) ? 4 : good(2) ? 2 : 1;
+        const int gq = waves < (span_y > RzGeom<false>::kRows ? 8 : 4) * num_cu() ? 0 : good(4) ? 4 : good(2) ? 2 : 1;
         r.ngy = gq ? ceil_div(groups, gq * RzGeom<false>::kWaves) : groups;
         const int64_t blocks = (int64_t)C * r.ngx * r.ngy;
         if (blocks > 0x7fffffff) return HB_ERR_UNSUPPORTED;
@@ -388,12 +573,17 @@ static hb_status resize_run(bool valu, const hb_half* in, float* out, void* work
     b.x_plane = (int64_t)Wo * hp;
     b.z_pitch = out_pitch;
     b.z_plane = out_plane;
+    const bool matrix = !valu && W >= kRzMinWidth;
     for (BandArgs* q : {&a, &b}) {
         q->ngroups = ceil_div(q->nout, 16);
-        const int64_t blocks = (int64_t)q->planes * q->ngroups * ceil_div(q->rows, 64);
+        q->nruns = ceil_div(q->rows, 64 * kRzWaves);
+        const int64_t blocks = (int64_t)q->planes * q->ngroups * (matrix ? q->nruns : ceil_div(q->rows, 64));
         if (blocks > 0x7fffffff) return HB_ERR_UNSUPPORTED;
-        if (q == &a) hipLaunchKernelGGL(band_valu_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, st, *q);
-        else hipLaunchKernelGGL(band_valu_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, st, *q);
+        const dim3 grid((unsigned)blocks), block(matrix ? 64 * kRzWaves : 256);
+        if (matrix && q == &a) hipLaunchKernelGGL(band_mfma_kernel<true>, grid, block, 0, st, *q);
+        else if (matrix) hipLaunchKernelGGL(band_mfma_kernel<false>, grid, block, 0, st, *q);
+        else if (q == &a) hipLaunchKernelGGL(band_valu_kernel<true>, grid, block, 0, st, *q);
+        else hipLaunchKernelGGL(band_valu_kernel<false>, grid, block, 0, st, *q);
         const hb_status s = launch_status();
         if (s != HB_OK) return s;
     }

@@ -117,6 +117,40 @@ def test_resize_random_starts_over_the_work_splits(orc, C, H, W, Ho, Wo, by, bx,
     assert np.all(obuf[:, :, Wo:] == 7.0) and np.all(obuf[:, Ho:, :] == 7.0), "wrote outside the output planes"
 
 
+@pytest.mark.parametrize("C,H,W,Ho,Wo", [
+    (1, 700, 900, 10, 13),        # two launches: spans of several hundred samples in both directions, a short last group
+    (2, 131, 1029, 2, 17),        # ... a single row beyond two groups of 64, odd pitch
+    (1, 4200, 500, 50, 20),       # ... factor 84
+    (1, 3, 3000, 3, 60),          # ... few rows: one launch, more than 384 columns
+    (3, 20, 2500, 18, 40),
+    (400, 200, 40, 10, 40),       # waves that share a group of rows too long for one wave: 1200 groups
+    (700, 200, 40, 10, 40),       # 2100: a wave each, in rounds
+    (1, 770, 130, 22, 60),        # rows that start on odd samples and a group that spans many of them: two launches
+])
+def test_resize_large_factors(orc, C, H, W, Ho, Wo):
+    """The routes of the large factors: Lanczos matrices, whose starts advance by the scale."""
+    from paper_2512_02371_amd import hb
+    img = synth.uniform01_f16(9600 + H + W, (C, H, W))
+    sy, cy = lanczos(hb, H, Ho)
+    sx, cx = lanczos(hb, W, Wo)
+    got, obuf = run("hb_resize", img, sy, cy, sx, cx, pitch_extra=1)
+    for c in sorted({0, C // 2, C - 1}):
+        assert_close(got[c], orc.band_resize(img[c], sy, cy, sx, cx), f"plane {c}")
+    assert np.all(obuf[:, :, Wo:] == 7.0) and np.all(obuf[:, Ho:, :] == 7.0), "wrote outside the output planes"
+
+
+def test_resize_large_enlargement(orc):
+    """Outputs of more than 64 MB with rows on line boundaries: two launches."""
+    H, W, Ho, Wo = 40, 2060, 4097, 4128
+    img = synth.uniform01_f16(9650, (1, H, W))
+    rows = lambda seed, n: (synth.random_kernel2d_f16(seed, n, 3).view(np.float16).astype(np.float64) * n).astype(np.float16).view(np.uint16)
+    sy, cy = (np.arange(Ho) * H // Ho).astype(np.int32) - 1, rows(9651, Ho)
+    sx, cx = (np.arange(Wo) * W // Wo).astype(np.int32) - 1, rows(9652, Wo)
+    got, obuf = run("hb_resize", img, sy, cy, sx, cx, pitch_extra=32)
+    assert_close(got[0], orc.band_resize(img[0], sy, cy, sx, cx), "enlargement")
+    assert np.all(obuf[:, :, Wo:] == 7.0) and np.all(obuf[:, Ho:, :] == 7.0), "wrote outside the output planes"
+
+
 @pytest.mark.parametrize("fn", ["hb_resize", "hb_resize_valu"])
 def test_resize_pitched_planes(orc, fn):
     from paper_2512_02371_amd import hb
