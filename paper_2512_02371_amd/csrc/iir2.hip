@@ -110,43 +110,62 @@ __device__ __forceinline__ State2 iir_scan_blocks(const IirArgs& p, const floatx
     return v;
 }
 
+// Run `index` of a channel: n tiles from sample t0 on.
+struct IirRun {
+    const half_t* sig;
+    int64_t t0;
+    int ch, index, n;
+};
+constexpr int kIirAhead = 4;
+// The run of wave w and its first tiles.  SHORT: runs of fewer than kIirAhead tiles.  The tiles that follow are other
+// waves' there: requested as well, 418 channels of 35 tiles in runs of one took 29 us, now 17.
+template <bool SHORT>
+__device__ __forceinline__ void iir_begin(const IirArgs& p, int64_t w, int lane, IirRun& r, half8 (&first)[kIirAhead]) {
+    r.ch = (int)(w / p.nruns);
+    r.index = (int)(w - (int64_t)r.ch * p.nruns);
+    r.n = min(p.run, p.ntiles - r.index * p.run);
+    r.sig = p.in + (int64_t)r.ch * p.in_pitch;
+    r.t0 = (int64_t)r.index * p.run * kIirTile;
+#pragma unroll
+    for (int u = 0; u < kIirAhead; ++u)
+        first[u] = iir_load_tile(r.sig, r.t0 + (int64_t)(SHORT ? min(u, r.n - 1) : u) * kIirTile, p.T, lane);
+}
 // A wave walks over the tiles of its run four at a time; the next four are requested before the current ones are
 // used.  use(i, x) takes tile i of the run.
-constexpr int kIirAhead = 4;
 template <class Use>
-__device__ __forceinline__ void iir_walk(const half_t* sig, int64_t t0, int64_t T, int n, int lane, const half8 (&first)[kIirAhead], Use use) {
+__device__ __forceinline__ void iir_walk(const IirRun& r, int64_t T, int lane, const half8 (&first)[kIirAhead], Use use) {
     half8 cur[kIirAhead], nxt[kIirAhead];
 #pragma unroll
     for (int u = 0; u < kIirAhead; ++u) cur[u] = first[u];
 #pragma unroll 1
-    for (int i = 0; i < n; i += kIirAhead) {
-        if (i + kIirAhead < n) {
+    for (int i = 0; i < r.n; i += kIirAhead) {
+        if (i + kIirAhead < r.n) {
 #pragma unroll
-            for (int u = 0; u < kIirAhead; ++u) nxt[u] = iir_load_tile(sig, t0 + (int64_t)(i + kIirAhead + u) * kIirTile, T, lane);
+            for (int u = 0; u < kIirAhead; ++u) nxt[u] = iir_load_tile(r.sig, r.t0 + (int64_t)(i + kIirAhead + u) * kIirTile, T, lane);
         }
 #pragma unroll
         for (int u = 0; u < kIirAhead; ++u)
-            if (i + u < n) use(i + u, cur[u]);
+            if (i + u < r.n) use(i + u, cur[u]);
 #pragma unroll
         for (int u = 0; u < kIirAhead; ++u) cur[u] = nxt[u];
     }
 }
 
 // 1  end state of every run started from zero
+template <bool SHORT>
 __global__ void __launch_bounds__(256) iir2_state_mfma_kernel(IirArgs p) {
     const int lane = threadIdx.x & 63;
     const int64_t w = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
     if (w >= (int64_t)p.C * p.nruns) return;
-    const int ch = (int)(w / p.nruns), run = (int)(w - (int64_t)ch * p.nruns);
-    const int tile0 = run * p.run, n = min(p.run, p.ntiles - tile0);
-    const half_t* const sig = p.in + (int64_t)ch * p.in_pitch;
-    const int64_t t0 = (int64_t)tile0 * kIirTile;
+    // nobody asks for a channel's last state: with few runs to a channel that is a good part of the launch (500 channels
+    // of five tiles 12.2 us, 11.0 without; with many it is nothing, and 1 x 2^24 samples ran slower without, 35 against 29)
+    if (p.nruns <= 128 && (w + 1) % p.nruns == 0) return;
+    IirRun r;
     half8 first[kIirAhead];
-#pragma unroll
-    for (int u = 0; u < kIirAhead; ++u) first[u] = iir_load_tile(sig, t0 + (int64_t)u * kIirTile, p.T, lane);
+    iir_begin<SHORT>(p, w, lane, r, first);
     const half8 fhi = iir_fragment(p.thi, 1, lane), flo = iir_fragment(p.tlo, 1, lane);
     State2 s{0.f, 0.f};                                   // lane column 15: the state after the tile
-    iir_walk(sig, t0, p.T, n, lane, first, [&](int, const half8& x) {
+    iir_walk(r, p.T, lane, first, [&](int, const half8& x) {
         floatx4 d1 = {0.f, 0.f, 0.f, 0.f};
         d1 = mfma16x16x32(fhi, x, d1);
         d1 = mfma16x16x32(flo, x, d1);
@@ -276,19 +295,16 @@ __global__ void __launch_bounds__(64 * kIirScanWaves) iir2_scan_kernel(IirArgs p
 // 2 x 2^21 samples 9 us behind 4 us of the launch before it, where the scan of 8192 tile states by one workgroup
 // per channel was another 9 (20.4 -> 13.4 us, the host's rate for two launches; 8 x 2^20 20.4 -> 16.0, a copy of the
 // bytes 9).
+template <bool SHORT>
 __global__ void __launch_bounds__(256) iir2_apply_mfma_kernel(IirArgs p) {
     __shared__ __attribute__((aligned(16))) float s_patch[4 * RowPatch<2>::kFloats];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int c = lane & 15, g = lane >> 4;
     const int64_t w = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
     if (w >= (int64_t)p.C * p.nruns) return;
-    const int ch = (int)(w / p.nruns), run = (int)(w - (int64_t)ch * p.nruns);
-    const int tile0 = run * p.run, n = min(p.run, p.ntiles - tile0);
-    const half_t* const sig = p.in + (int64_t)ch * p.in_pitch;
-    const int64_t t0 = (int64_t)tile0 * kIirTile;
+    IirRun r;
     half8 first[kIirAhead];
-#pragma unroll
-    for (int u = 0; u < kIirAhead; ++u) first[u] = iir_load_tile(sig, t0 + (int64_t)u * kIirTile, p.T, lane);
+    iir_begin<SHORT>(p, w, lane, r, first);
     half8 fhi[2], flo[2];
     float ra[2][4], rb[2][4];                 // response of the lane's outputs i = 16 hh + 4 g + j to the block's state
 #pragma unroll
@@ -304,8 +320,8 @@ __global__ void __launch_bounds__(256) iir2_apply_mfma_kernel(IirArgs p) {
     float bsel[4];                            // state map over the c blocks before the lane's block
 #pragma unroll
     for (int i = 0; i < 4; ++i) bsel[i] = p.bsel[c][i];
-    State2 start = iir_state_before(p, p.end + 2 * (int64_t)ch * p.nruns, run, lane);
-    iir_walk(sig, t0, p.T, n, lane, first, [&](int i, const half8& x) {
+    State2 start = iir_state_before(p, p.end + 2 * (int64_t)r.ch * p.nruns, r.index, lane);
+    iir_walk(r, p.T, lane, first, [&](int i, const half8& x) {
         floatx4 d[2];
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
@@ -322,8 +338,8 @@ __global__ void __launch_bounds__(256) iir2_apply_mfma_kernel(IirArgs p) {
         for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
             for (int j = 0; j < 4; ++j) d[hh][j] += ra[hh][j] * mine.a + rb[hh][j] * mine.b;
-        const int64_t t = t0 + (int64_t)i * kIirTile;
-        float* dst = p.out + (int64_t)ch * p.out_pitch + t;
+        const int64_t t = r.t0 + (int64_t)i * kIirTile;
+        float* dst = p.out + (int64_t)r.ch * p.out_pitch + t;
         if (t + kIirTile <= p.T) {
             // the tile is 16 rows (blocks) of 32 consecutive samples
             store_rows_via_lds<2, true>(s_patch + wv * RowPatch<2>::kFloats, dst, kIirBlock, d, lane);
@@ -516,27 +532,35 @@ static hb_status iir2_run(bool valu, const hb_half* in, float* out, int C, int64
         }
     }
 
-    // Runs: as short as leaves at most 1024 of them per channel (the sum over them stays cheap) and one
-    // resident round of waves in all.  Longer runs than one tile only where there are 64 of them: the powers of
-    // the map that are formed then span no more than the signal, whose growth the gain check bounds.
-    a.run = 1;
-    while (a.ntiles > (int64_t)kIirMaxRuns * a.run || ((int64_t)C * a.ntiles > (int64_t)16 * num_cu() * a.run && a.ntiles >= (int64_t)128 * a.run)) a.run *= 2;
+    // Runs: as short as leaves at most 1024 of them per channel (the sum over them stays cheap) and one resident round
+    // of waves in all, half of one for runs of fewer tiles than a wave has in flight (386 channels of ten tiles 11.5 us, 15.1
+    // in a whole one; 14 channels of 1309 25.2 in runs of 16, 23.3 in runs of 8).  Up to four tiles are one run, which needs
+    // no other's state: one launch.  Powers of the map that would span more than the signal meet zeros only (their growth
+    // is not bounded by the gain check) and are left zero.
+    a.run = a.ntiles <= kIirAhead ? kIirAhead : 1;
+    auto round = [&]() { return (int64_t)(a.run < kIirAhead ? 8 : 16) * num_cu() * a.run; };
+    while (a.ntiles > (int64_t)kIirMaxRuns * a.run || ((int64_t)C * a.ntiles > round() && a.run < a.ntiles)) a.run *= 2;
     a.nruns = (a.ntiles + a.run - 1) / a.run;
     for (int j = 0; j < 7; ++j) {
-        const Mat2 rp = mat2_pow(m512, (int64_t)a.run << j);
+        const bool used = ((int64_t)a.run << j) < a.ntiles;
+        const Mat2 rp = used ? mat2_pow(m512, (int64_t)a.run << j) : Mat2{{0.0, 0.0, 0.0, 0.0}};
         for (int i = 0; i < 4; ++i) a.rpow[j][i] = (float)rp.v[i];
     }
 
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    const int64_t waves = (int64_t)C * (valu ? (a.ntiles + 3) / 4 : a.nruns);
-    const dim3 grid((unsigned)((waves + 3) / 4));
+    auto grid = [](int64_t waves) { return dim3((unsigned)((waves + 3) / 4)); };
     if (valu) {
-        hipLaunchKernelGGL(iir2_blocks_valu_kernel<false>, grid, dim3(256), 0, st, a);
+        const int64_t waves = (int64_t)C * ((a.ntiles + 3) / 4);
+        hipLaunchKernelGGL(iir2_blocks_valu_kernel<false>, grid(waves), dim3(256), 0, st, a);
         hipLaunchKernelGGL(iir2_scan_kernel, dim3(C), dim3(64 * kIirScanWaves), 0, st, a);
-        hipLaunchKernelGGL(iir2_blocks_valu_kernel<true>, grid, dim3(256), 0, st, a);
+        hipLaunchKernelGGL(iir2_blocks_valu_kernel<true>, grid(waves), dim3(256), 0, st, a);
     } else {
-        if (a.nruns > 1) hipLaunchKernelGGL(iir2_state_mfma_kernel, grid, dim3(256), 0, st, a);
-        hipLaunchKernelGGL(iir2_apply_mfma_kernel, grid, dim3(256), 0, st, a);
+        const dim3 g = grid((int64_t)C * a.nruns);
+        const bool shorter = a.run < kIirAhead;
+        if (a.nruns > 1 && shorter) hipLaunchKernelGGL(iir2_state_mfma_kernel<true>, g, dim3(256), 0, st, a);
+        else if (a.nruns > 1) hipLaunchKernelGGL(iir2_state_mfma_kernel<false>, g, dim3(256), 0, st, a);
+        if (shorter) hipLaunchKernelGGL(iir2_apply_mfma_kernel<true>, g, dim3(256), 0, st, a);
+        else hipLaunchKernelGGL(iir2_apply_mfma_kernel<false>, g, dim3(256), 0, st, a);
     }
     return launch_status();
 }

@@ -64,6 +64,26 @@ def test_iir2_runs_of_tiles(orc, C, T, alpha, beta):
         assert_close(got[c:c + 1], orc.iir2(sig[c:c + 1], float(np.float32(alpha)), float(np.float32(beta))), f"channel {c}")
 
 
+@pytest.mark.parametrize("C,T", [(3, 4 * 512), (3, 4 * 512 + 1), (5, 5 * 512 - 1), (900, 5 * 512 + 9), (1100, 16 * 512 + 3), (2500, 700),
+                                 (60, 70 * 512 + 5)])
+@pytest.mark.parametrize("alpha,beta", [(1.6, -0.8), (1.9, -0.9025)])
+def test_iir2_many_channels_of_few_tiles(orc, C, T, alpha, beta):
+    """One run a channel (one launch), and runs of two to sixteen tiles with fewer than 64 of them a channel."""
+    sig = synth.uniform_pm1_f16(9800 + C, (C, T))
+    got, _ = run("hb_iir2", sig, alpha, beta)
+    for c in {0, C // 2, C - 1}:
+        assert_close(got[c:c + 1], orc.iir2(sig[c:c + 1], float(np.float32(alpha)), float(np.float32(beta))), f"channel {c}")
+
+
+def test_iir2_growing_response_over_a_short_signal(orc):
+    """Unstable but short enough for the gain check: powers of the state map far beyond the signal overflow fp32 and must
+    not meet the zeros that stand for missing runs."""
+    alpha, beta = 1.002, 0.0                   # 1.002^1700 = 30, 1.002^(64 * 4 * 512) = inf
+    sig = synth.uniform_pm1_f16(9850, (3, 1700))
+    got, _ = run("hb_iir2", sig, alpha, beta)
+    assert_close(got, orc.iir2(sig, float(np.float32(alpha)), float(np.float32(beta))), "growing")
+
+
 @pytest.mark.parametrize("fn", ["hb_iir2", "hb_iir2_valu"])
 def test_iir2_pitched_rows(orc, fn):
     sig = synth.uniform_pm1_f16(9600, (2, 3000))
