@@ -109,11 +109,13 @@ static hb_status conv2d_launch_valu(const T2Args& a, hipStream_t st) {
     return launch_status();
 }
 
-// 128 x 128 output tiles while they give every compute unit its two workgroups, else 64 x 128
+// 128 x 128 output tiles while they give every compute unit its two workgroups and the image is wide enough to need
+// them, else 64 x 128
 template <int NK>
 static hb_status conv2d_launch(T2Args& a, hipStream_t st) {
-    if ((int64_t)ceil_div(a.H, 128) * ceil_div(a.W, 128) >= 2 * num_cu()) return t2_launch<kT2Conv, NK, 4>(a, st);
-    return t2_launch<kT2Conv, NK, 2>(a, st);
+    if (t2_short<kT2Conv, NK, 2>(a)) return t2_launch<kT2Conv, NK, 2, true>(a, st);
+    if (a.W > 64 && (int64_t)ceil_div(a.H, 128) * ceil_div(a.W, 128) >= 2 * num_cu()) return t2_launch<kT2Conv, NK, 4, false>(a, st);
+    return t2_launch<kT2Conv, NK, 2, false>(a, st);
 }
 
 }  // namespace hb

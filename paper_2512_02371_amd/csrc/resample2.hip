@@ -181,6 +181,12 @@ static hb_status rs2_prepare(T2Args& a, bool up, const hb_half* in, float* out, 
     return HB_OK;
 }
 
+template <int MODE, int NK, int NW>
+static hb_status rs2_launch(T2Args& a, hipStream_t st) {
+    if (t2_short<MODE, NK, NW>(a)) return t2_launch<MODE, NK, NW, true>(a, st);
+    return t2_launch<MODE, NK, NW, false>(a, st);
+}
+
 template <class K>
 static hb_status rs2_launch_valu(K kernel, const T2Args& a, int tile_w, int threads, hipStream_t st) {
     const int64_t blocks = (int64_t)ceil_div(a.Ho, 16) * ceil_div(a.Wo, tile_w);
@@ -201,9 +207,9 @@ extern "C" hb_status hb_down2(const hb_half* in, float* out, int H, int W, int64
         return hb_down2_valu(in, out, H, W, in_pitch, out_pitch, taps_host, kh, kw, anchor_y, anchor_x, stream);
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     switch (ceil_div(30 + kw, 16)) {
-        case 2: return t2_launch<kT2Down, 2, 1>(a, st);
-        case 3: return t2_launch<kT2Down, 3, 1>(a, st);
-        default: return t2_launch<kT2Down, 4, 1>(a, st);
+        case 2: return rs2_launch<kT2Down, 2, 1>(a, st);
+        case 3: return rs2_launch<kT2Down, 3, 1>(a, st);
+        default: return rs2_launch<kT2Down, 4, 1>(a, st);
     }
 }
 
@@ -228,8 +234,8 @@ extern "C" hb_status hb_up2(const hb_half* in, float* out, int H, int W, int64_t
     if (W < kT2MinWidth)
         return hb_up2_valu(in, out, H, W, in_pitch, out_pitch, taps_host, kh, kw, anchor_y, anchor_x, stream);
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    if (7 + kw / 2 <= 16) return t2_launch<kT2Up, 1, 2>(a, st);
-    return t2_launch<kT2Up, 2, 2>(a, st);
+    if (7 + kw / 2 <= 16) return rs2_launch<kT2Up, 1, 2>(a, st);
+    return rs2_launch<kT2Up, 2, 2>(a, st);
 }
 
 extern "C" hb_status hb_up2_valu(const hb_half* in, float* out, int H, int W, int64_t in_pitch, int64_t out_pitch,

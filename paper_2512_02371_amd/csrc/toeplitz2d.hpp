@@ -54,9 +54,14 @@ constexpr int kT2Copy = 112;                  // taps per copy: up to position 6
 constexpr int kT2TabRow = 2 * kT2Copy;        // copies and of neighbouring rows fall into different banks
 constexpr int kT2ZeroRows = 2;                // above and below the taps
 
-template <int MODE, int NK, int NW>
+// SHORT (outputs of few rows): the N index of a product is 8 row pairs x 4 runs of tiles beside each other instead
+// of 32 row pairs, and a workgroup's waves lie beside each other.  24 x 100000, 3 x 3 / 32 x 32 taps: 18.0 / 41 us with the
+// tall tile, 10.5 / 22 with this one.
+template <int MODE, int NK, int NW, bool SHORT>
 struct T2Geom {
-    static constexpr int kWx = 2, kWy = MODE == kT2Down ? 1 : 2;          // waves of a workgroup
+    static constexpr int kPairs = SHORT ? 8 : 32, kBeside = 32 / kPairs;  // row pairs, runs of tiles in N
+    static constexpr int kWy = MODE == kT2Down || SHORT ? 1 : 2;          // waves of a workgroup
+    static constexpr int kWx = (MODE == kT2Down ? 2 : 4) / kWy;
     static constexpr int kThreads = 64 * kWx * kWy;
     // The walk over several tiles pays where loads and stores bound the kernel.  hb_conv2d keeps the wider tile instead:
     // fewer LDS reads per product, and no registers left to load ahead.
@@ -64,17 +69,17 @@ struct T2Geom {
     static constexpr int kOccupancy = MODE == kT2Conv ? (NW > 2 ? 2 : 3) : MODE == kT2Down ? 2 : NK > 1 ? 3 : 4;   // waves per SIMD
     static constexpr int kStride = MODE == kT2Conv ? 2 : MODE == kT2Down ? 4 : 1;   // input rows per n
     static constexpr int kTileStep = MODE == kT2Conv ? 16 : MODE == kT2Down ? 32 : 8;
-    static constexpr int kCols = 16 * NW * kWx, kRows = 64 * kWy;         // output tile
-    static constexpr int kChunks = (kTileStep * (NW * kWx - 1) + 16 * NK) / 8;      // of 8 staged pixels per row
+    static constexpr int kCols = 16 * NW * kBeside * kWx, kRows = 2 * kPairs * kWy;         // output tile
+    static constexpr int kChunks = (kTileStep * (NW * kBeside * kWx - 1) + 16 * NK) / 8;      // of 8 staged pixels per row
     static constexpr int kPitch = 8 * (kChunks | 1);
     static constexpr int kPatch = 32 * (16 * NW + 4);                     // floats per wave, see the stores
     // window chunks of a wave: distinct multiples of 8 pixels at which a fragment starts
     static constexpr int kUnit = MODE == kT2Up ? 8 : 16;
     static constexpr int kFrags = (kTileStep * (NW - 1) + 16 * (NK - 1)) / kUnit + 1;
     static constexpr int kMaxSteps = MODE == kT2Conv ? HB_MAX_TAPS_CONV2D + 1 : MODE == kT2Down ? HB_MAX_TAPS_CONV2D + 2 : HB_MAX_TAPS_CONV2D / 2;
-    static constexpr int kPieces = ((kStride * (32 * kWy - 1) + kMaxSteps) * kChunks + kThreads - 1) / kThreads;   // staged per thread
+    static constexpr int kPieces = ((kStride * (kPairs * kWy - 1) + kMaxSteps) * kChunks + kThreads - 1) / kThreads;   // staged per thread
     static int steps(int kh) { return MODE == kT2Conv ? kh + 1 : MODE == kT2Down ? kh + 2 : kh / 2; }
-    static int rows(int kh) { return kStride * (32 * kWy - 1) + steps(kh); }
+    static int rows(int kh) { return kStride * (kPairs * kWy - 1) + steps(kh); }
     static int srows(int kh) { return (rows(kh) + kStride - 1) / kStride; }
     static int tab_rows(int kh) { return MODE == kT2Up ? 2 * kh : kh + 2 * kT2ZeroRows; }
     static size_t image_bytes(int kh) {
@@ -88,9 +93,9 @@ struct T2Geom {
 // wait for everything in front of a barrier it emits).
 __device__ __forceinline__ void t2_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-template <int MODE, int NK, int NW>
-__global__ void __launch_bounds__((T2Geom<MODE, NK, NW>::kThreads), (T2Geom<MODE, NK, NW>::kOccupancy)) toeplitz2d_mfma_kernel(T2Args p, int table_offset) {
-    using G = T2Geom<MODE, NK, NW>;
+template <int MODE, int NK, int NW, bool SHORT>
+__global__ void __launch_bounds__((T2Geom<MODE, NK, NW, SHORT>::kThreads), (T2Geom<MODE, NK, NW, SHORT>::kOccupancy)) toeplitz2d_mfma_kernel(T2Args p, int table_offset) {
+    using G = T2Geom<MODE, NK, NW, SHORT>;
     extern __shared__ __attribute__((aligned(16))) char s_dyn[];
     half_t* const s_px = reinterpret_cast<half_t*>(s_dyn);
     half_t* const s_tab = reinterpret_cast<half_t*>(s_dyn + table_offset);
@@ -180,7 +185,8 @@ __global__ void __launch_bounds__((T2Geom<MODE, NK, NW>::kThreads), (T2Geom<MODE
     const int t0 = 8 * h - (MODE == kT2Conv ? mx : MODE == kT2Down ? 2 * mx : mx >> 1) + kT2Pad;
     const int row0 = MODE == kT2Conv ? kT2ZeroRows - mdy : MODE == kT2Down ? kT2ZeroRows - 2 * mdy : 2 * mdy + (mx & 1);
     const half_t* const tab = s_tab + row0 * kT2TabRow + (t0 & 1 ? kT2Copy + t0 - 1 : t0);
-    const half_t* const px = s_px + (32 * wy + c) * G::kPitch + G::kTileStep * NW * wx + 8 * h;
+    const int pair = c % G::kPairs, beside = c / G::kPairs;
+    const half_t* const px = s_px + (G::kPairs * wy + pair) * G::kPitch + G::kTileStep * NW * (G::kBeside * wx + beside) + 8 * h;
     // stores: lane (n = c, h) holds columns 16 w + 8 (q & 1) + 4h + r of rows 2n + q / 2; a patch turns the 32 rows of
     // one dy into runs of 64 NW bytes
     float* const patch = reinterpret_cast<float*>(s_dyn) + wv * G::kPatch;
@@ -191,7 +197,7 @@ __global__ void __launch_bounds__((T2Geom<MODE, NK, NW>::kThreads), (T2Geom<MODE
     for (int tile = first; tile < last; ++tile) {
         if (G::kWalk && tile + 1 < last) request(tile + 1);           // on its way during the products
         const int ct = tile / p.nrow, rt = tile - ct * p.nrow;        // tiles run down the columns
-        const int xw = G::kCols * ct + 16 * NW * wx, yw = G::kRows * rt + 64 * wy;    // the wave's outputs
+        const int xw = G::kCols * ct + 16 * NW * G::kBeside * wx, yw = G::kRows * rt + 2 * G::kPairs * wy;    // the wave's outputs
         const bool active = xw < p.Wo && yw < p.Ho;       // uniform
         floatx16 total[NW];
 #pragma unroll
@@ -232,7 +238,7 @@ __global__ void __launch_bounds__((T2Geom<MODE, NK, NW>::kThreads), (T2Geom<MODE
         }
         t2_barrier();                                     // the LDS image becomes the waves' store patches
         if (active) {
-            const bool whole = xw + 16 * NW <= p.Wo && yw + 64 <= p.Ho;   // uniform
+            const bool whole = xw + 16 * NW * G::kBeside <= p.Wo && yw + 2 * G::kPairs <= p.Ho;   // uniform
 #pragma unroll
             for (int dy = 0; dy < 2; ++dy) {
 #pragma unroll
@@ -246,9 +252,9 @@ __global__ void __launch_bounds__((T2Geom<MODE, NK, NW>::kThreads), (T2Geom<MODE
                 wave_lds_fence();
 #pragma unroll
                 for (int i = 0; i < 32 / kPer; ++i) {
-                    const int n = kPer * i + rr, y = yw + 2 * n + dy;
+                    const int n = kPer * i + rr, y = yw + 2 * (n % G::kPairs) + dy, x = xw + 16 * NW * (n / G::kPairs) + xx;
                     const floatx4 v = *reinterpret_cast<const floatx4*>(patch + n * kPatchPitch + xx);
-                    float* const dst = p.out + (int64_t)y * p.out_pitch + xw + xx;
+                    float* const dst = p.out + (int64_t)y * p.out_pitch + x;
                     if (whole && p.stream) {
                         __builtin_nontemporal_store(v, reinterpret_cast<floatx4_u*>(dst));
                     } else if (whole) {
@@ -256,7 +262,7 @@ __global__ void __launch_bounds__((T2Geom<MODE, NK, NW>::kThreads), (T2Geom<MODE
                     } else if (y < p.Ho) {
 #pragma unroll
                         for (int k = 0; k < 4; ++k)
-                            if (xw + xx + k < p.Wo) dst[k] = v[k];
+                            if (x + k < p.Wo) dst[k] = v[k];
                     }
                 }
                 wave_lds_fence();
@@ -270,9 +276,17 @@ __global__ void __launch_bounds__((T2Geom<MODE, NK, NW>::kThreads), (T2Geom<MODE
     }
 }
 
+// The short tile where most of the tall ones would be empty and they are more than one round of workgroups; below, its
+// larger workgroups only take longer (8 x 4096, 16 x 16 taps 11.2 us, tall 8.1).
 template <int MODE, int NK, int NW>
+static bool t2_short(const T2Args& a) {
+    using Tall = T2Geom<MODE, NK, NW, false>;
+    return a.Ho <= (MODE == kT2Conv ? 3 * Tall::kRows / 4 : Tall::kRows / 2) && ceil_div(a.Wo, Tall::kCols) > 3 * num_cu();
+}
+
+template <int MODE, int NK, int NW, bool SHORT>
 static hb_status t2_launch(T2Args& a, hipStream_t st) {
-    using G = T2Geom<MODE, NK, NW>;
+    using G = T2Geom<MODE, NK, NW, SHORT>;
     const int64_t tiles = (int64_t)ceil_div(a.Wo, G::kCols) * ceil_div(a.Ho, G::kRows);
     if (tiles > 0x3fffffff) return HB_ERR_UNSUPPORTED;
     // The resampling kernels' runs of 64 and 128 bytes, where they are not whole lines, leave through the L2, which puts
@@ -286,7 +300,7 @@ static hb_status t2_launch(T2Args& a, hipStream_t st) {
     a.nrow = ceil_div(a.Ho, G::kRows);
     a.ntiles = (int)tiles;
     const size_t lds = G::lds_bytes(a.kh);
-    const auto kernel = toeplitz2d_mfma_kernel<MODE, NK, NW>;
+    const auto kernel = toeplitz2d_mfma_kernel<MODE, NK, NW, SHORT>;
     if (allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds) != HB_OK) return HB_ERR_HIP;
     // as many workgroups as are resident at once
     const int64_t fit = num_cu() * std::min<int64_t>((160 << 10) / (lds + sizeof(a.taps)), 4 * G::kOccupancy / (G::kThreads / 64));

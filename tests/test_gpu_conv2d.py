@@ -30,6 +30,12 @@ CASES = [
     (5, 65537, 4, 32, 3, 30),     # 513 tiles of 128 x 128: the wider tile
     (3, 65700, 32, 3, 31, 1),
     (3, 65600, 1, 1, 0, 0),
+    (16, 49600, 7, 17, 3, 8),     # few rows, many columns: the short tile, whole ...
+    (17, 49153, 32, 5, 31, 0),    # ... one row and one column past it
+    (1, 49700, 3, 32, 1, 16),
+    (96, 49216, 2, 3, 0, 2),      # the last height that takes it, and the first that does not
+    (97, 49216, 3, 2, 2, 0),
+    (9000, 9, 5, 5, 2, 2),        # narrow and tall
 ]
 
 
