@@ -385,9 +385,11 @@ static hb_status sep_launch(K kernel, hipStream_t st, SepArgs& a, int ns, int co
     hipLaunchKernelGGL(kernel, dim3((unsigned)((tasks + per_wg - 1) / per_wg)), dim3(256), 0, st, a);
     return launch_status();
 }
-// One window per tile: 8 output steps per task while that leaves the image in one resident round of waves
-// (4096 x 4096: 4096 waves) and for the filters whose NT - 1 extra row tiles weigh most, else 4
-// (8192 x 4096, 16 taps: 33.3 us against 34.0).
+// One window per tile.  8 output steps per task re-read the fewest rows, and pay where they are at least most of a
+// round of waves (3600 x 3600, 64 taps down: 24.5 us, 26.4 with 4 steps) but, for the filters whose NT - 1 extra row tiles
+// weigh little, no more than one (8192 x 4096, 16 taps: 34.0, 33.3 with 4).  Below that 4 steps spread the image over more
+// and shorter waves (2048 x 2048, 16 taps: 8.9 with 8, 7.6 with 4; 1024 x 1024, 10 x 50 taps 9.8, 7.5), and 2 do where the
+// rows end after two (16 x 300000, 5 x 64 taps 16.4, 13.4, 12.4).
 constexpr int kSepOneRoundWaves = 4608;
 template <int NT>
 static hb_status sep_launch_one_window(hipStream_t st, SepArgs& a) {
@@ -396,19 +398,25 @@ static hb_status sep_launch_one_window(hipStream_t st, SepArgs& a) {
     const int xw = a.ax + (a.ax & 1), nct = ceil_div(a.W, cols);
     const int after = cols - 16 - xw + 32;
     interior_range(nct, cols, xw, after > cols ? after : cols, a.W, a.c0, a.c1);
+    const int64_t long_waves = (int64_t)ceil_div(a.H, 128) * nct;
     if constexpr (NT <= 3) {
-        if ((int64_t)ceil_div(a.H, 128) * nct > kSepOneRoundWaves)
+        if (long_waves < kSepOneRoundWaves * 5 / 8 || long_waves > kSepOneRoundWaves)
             return sep_launch(sepblur_mfma_kernel<NT, 4>, st, a, 4, cols, 4);
+    } else {
+        if (a.H <= 32) return sep_launch(sepblur_mfma_kernel<NT, 2>, st, a, 2, cols, 4);
+        if (long_waves < kSepOneRoundWaves * 5 / 12) return sep_launch(sepblur_mfma_kernel<NT, 4>, st, a, 4, cols, 4);
     }
     return sep_launch(sepblur_mfma_kernel<NT, 8>, st, a, 8, cols, 4);
 }
 // The march also serves the short filters where rows of the output start inside 128-byte lines: the runs of its four
-// strips meet in one L2, the lone 128-byte runs of the kernel above do not (16 taps, 4095 x 4095 44 -> 31 us,
-// 1079 x 1917 13 -> 7.7).
+// strips meet in one L2, the lone 128-byte runs of the kernel above do not (16 taps, 4095 x 4095 47 -> 33 us,
+// 2047 x 2045 12.7 -> 9.6).  Beyond some 100 MB of output the lines are no longer put together in time, and the kernel
+// above is the faster one again (4978 x 6366 58 against 62, 8190 x 8190 117 against 125).
+constexpr int64_t kSepMarchShortMax = 24 << 20;           // outputs
 template <int NT>
 static hb_status sep_launch_nt(int nkx, hipStream_t st, SepArgs& a) {
     const bool lines = a.out_pitch % 32 == 0 && aligned_to(a.out, 128);
-    if (nkx == 1 && (lines || NT > 3)) return sep_launch_one_window<NT>(st, a);
+    if (nkx == 1 && (lines || NT > 3 || (int64_t)a.H * a.W > kSepMarchShortMax)) return sep_launch_one_window<NT>(st, a);
     // four workgroups per compute unit are resident; segments beyond 8 steps only cost balance (8192 x 4096, 48
     // taps: 36 us with 8 steps, 42 with the 16 that four workgroups per unit would give)
     const int64_t rowsteps = ceil_div(a.H, 16), nct = ceil_div(a.W, kSepMarchCols), want = 4 * num_cu();

@@ -58,6 +58,40 @@ def test_sepblur_windows_over_both_row_ends(orc, H, W, Tx, ax, Ty, ay):
     assert np.all(obuf[:, W:] == 7.0), "wrote past the row end"
 
 
+@pytest.mark.parametrize("H,W,Tx,ax,Ty,ay,extra", [
+    (2050, 2100, 31, 15, 31, 15, 0),    # the marching kernel, three steps a workgroup, ragged last segment and columns
+    (2048, 2176, 64, 31, 64, 40, 0),    # ... whole segments inside the image
+    (2050, 2100, 16, 7, 16, 8, 1),      # ... one window per tile, rows inside lines
+    (1500, 3970, 50, 49, 5, 0, 3),
+    (1000, 7808, 9, 4, 50, 20, 0),      # all row tiles up front: eight steps a wave for a long column filter ...
+    (500, 1000, 9, 4, 50, 20, 0),       # ... four ...
+    (32, 1500, 17, 8, 64, 31, 0),       # ... two
+    (31, 600, 3, 1, 34, 0, 1),
+    (700, 1300, 15, 6, 18, 9, 12),      # short column filter: four steps
+    (3000, 4096, 9, 4, 9, 4, 0),        # eight
+    (5010, 5041, 5, 2, 17, 3, 0),       # rows inside lines, but too large for the marching kernel
+])
+def test_sepblur_work_splits(orc, H, W, Tx, ax, Ty, ay, extra):
+    """Every split of the work over steps, waves and workgroups, on bands of rows at the top, the middle and the bottom."""
+    import torch
+    from paper_2512_02371_amd import hb
+    gen = torch.Generator(device="cuda:0").manual_seed(H + W)
+    img = torch.randint(0, 2048, (H, W), generator=gen, device="cuda:0", dtype=torch.int16).float().div_(2048).half()
+    tx = synth.gaussian_taps_f16(Tx, max(Tx / 5.0, 0.5))
+    ty = synth.random_taps_f16(4000 + Ty, Ty)
+    obuf, out = padded(torch.zeros((H, W), dtype=torch.float32, device="cuda:0"), W + extra)
+    print(f"H={H} W={W} Tx={Tx} ax={ax} Ty={Ty} ay={ay} pitch+{extra}", flush=True)
+    hb.hb_sepblur(img, out, tx, ax, ty, ay)
+    torch.cuda.synchronize()
+    for r0 in sorted({0, max(0, H // 2 - 50), max(0, H - 100)}):
+        r1 = min(H, r0 + 100)
+        a, b = max(0, r0 - ay), min(H, r1 + Ty - 1 - ay)      # the rows that rows r0 .. r1 - 1 read
+        ref = orc.sepblur(img[a:b].cpu().numpy().view(np.uint16), tx, ax, ty, ay)
+        lo, hi = r0 - a, r1 - a
+        assert_close(out[r0:r1].cpu().numpy(), ref[lo:hi], f"rows {r0}..{r1}")
+    assert bool((obuf[:, W:] == 7.0).all()), "wrote past the row end"
+
+
 @pytest.mark.parametrize("fn", ["hb_sepblur", "hb_sepblur_valu"])
 @pytest.mark.parametrize("extra", [8, 3])
 def test_sepblur_pitched_layouts(orc, fn, extra):
