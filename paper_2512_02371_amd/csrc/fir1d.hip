@@ -324,9 +324,16 @@ static hb_status fir1d_prepare(FirArgs& a, const hb_half* in, float* out, int H,
     a.ntasks = rowsteps * a.nct;
     // The walk of long filters: runs of an even number of tiles, two waves per SIMD in all.  More of them only walk more
     // windows ahead of their run (4096 x 4096, 128 / 256 taps: 20.6 / 25.6 us, with four waves per SIMD 25.8 / 32.0), fewer
-    // leave the chip idle (24.7 / 27.7 with one; 512 x 512 with 256 taps 15 us with one run per row group, 10 so).
+    // leave the chip idle (24.7 / 27.7 with one; 512 x 512 with 256 taps 15 us with one run per row group, 10 so).  Runs
+    // shorter than the windows ahead of them only where there are too few waves otherwise (1749 x 2603, 256 taps 25.9 with
+    // runs of 10 tiles, 20.0 with 20).  Images of a few rows, most of whose lanes are idle, take longer runs (1 x 1000000,
+    // 256 taps 24 -> 18 us) and, where the registers allow four waves per SIMD, more waves (20 taps 11.0 -> 9.3).
     a.ntiles = ceil_div(W, 16);
-    const int runs = std::max(1, std::min(8 * num_cu() / rowsteps, a.ntiles / 4));
+    const int nk = ceil_div(15 + ntaps + (anchor & 1), 32);
+    int runs = std::min((H < 16 && nk <= 3 ? 16 : 8) * num_cu() / rowsteps, a.ntiles / 4);
+    const int long_runs = a.ntiles / ((H < 16 ? 4 : 2) * nk);
+    if ((int64_t)rowsteps * long_runs >= 3 * num_cu()) runs = std::min(runs, long_runs);
+    runs = std::max(1, runs);
     a.run_tiles = (ceil_div(a.ntiles, runs) + 1) & ~1;
     a.nruns = ceil_div(a.ntiles, a.run_tiles);
     const int64_t wtasks = (int64_t)rowsteps * a.nruns;
@@ -352,7 +359,10 @@ extern "C" hb_status hb_fir1d(const hb_half* in, float* out, int H, int W,
     // a 16-column tile reads the 16 + ntaps - 1 pixels from x0 - anchor on (one more when the
     // window is moved to an even pixel): NK windows of 32
     const int nk = ceil_div(15 + ntaps + (anchor & 1), 32);
-    if (W < kFirMinWidth)
+    // narrow images are one short run per row group, whose windows all reach over the row's ends: with rows inside lines
+    // the vector ALU is the faster one (1000 x 100, 159 taps 7.0 us, walked 9.4; 1000 x 128, 200 taps, whole lines 8.3, 6.8;
+    // 50000 x 83, 159 taps 31, 24)
+    if (W < kFirMinWidth || (nk >= 4 && W <= 128 && !a.lines && H <= 32 * num_cu()))
         return hb_fir1d_valu(in, out, H, W, in_pitch, out_pitch, taps_host, ntaps, anchor, stream);
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
 #define HB_FIR_WALK(N)                                                                            \

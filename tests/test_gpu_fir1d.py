@@ -34,6 +34,11 @@ CASES = [
     (3, 65, 16, 15),         # one pixel past a strip
     (2100, 90, 200, 3),      # one run of six tiles per row group
     (31, 4100, 40, 39),      # many runs of four tiles, the last one short
+    (800, 2603, 100, 50),    # runs as long as the windows ahead of them
+    (3, 70001, 20, 3),       # few rows: four waves per SIMD
+    (1, 120000, 200, 199),   # ... two, of longer runs
+    (100, 100, 159, 80),     # narrow, rows inside lines: the vector-ALU kernel
+    (100, 128, 159, 80),     # narrow, whole lines: walked
 ]
 
 
