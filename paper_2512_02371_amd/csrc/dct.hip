@@ -73,9 +73,11 @@ __device__ __forceinline__ void dct_tile_origin(const DctArgs& p, int64_t t, int
 // pixels with plain loads and stores, and the order of the four additions into a pixel is fixed.
 //
 // What bounds it: the fp32 products, 12 x 32 cycles a tile and SIMD (the first product, whose pixels are
-// fp16, is one K = 32 product with E as fp16 hi + lo parts instead of four more), 1.27x for the rim tiles
-// of 64 x 64 patches.  3 x 1024 x 1024: 33.0 -> 23.8 us against four fp32 products with an LDS transpose between
-// each two; 61 tiles a SIMD x 400 cycles of products are 12 us of it.
+// fp16, is two K = 32 products with E as three fp16 parts, together the fp32 number, instead of four more; two parts
+// alone hold 22 of its 24 bits and save 0.2 us), 1.27x for the rim tiles of 64 x 64 patches.  3 x 1024 x 1024: 33.0 ->
+// 22.5 us against four fp32 products with an LDS transpose between each two; 61 tiles a SIMD x 416 cycles of products
+// are 12.5 us of it.  Error against fp64 0.92 of that kernel's on average over images from 64 x 64 to 4 M pixels and
+// thresholds from 0 to 0.5 (1.1 of it above 0.35, where little but the DC bin is left).
 constexpr int kDfWaves = 8;
 template <int PATCH>
 struct DfGeom {
@@ -117,13 +119,14 @@ __global__ void __launch_bounds__(64 * kDfWaves) dct_fused_mfma_kernel(DctArgs p
     for (int i = threadIdx.x; i < PATCH * G::kPitch / 4; i += 64 * kDfWaves)
         *reinterpret_cast<floatx4*>(&s_acc[4 * i]) = floatx4{0.f, 0.f, 0.f, 0.f};
     if (threadIdx.x < 16) s_w2[threadIdx.x] = p.w[threadIdx.x] * p.w[threadIdx.x];
-    half8 e1;                                 // E[c][4g + j] as hi (slots 0..3) and lo (4..7): the slots share a pixel
+    half8 e1, e0 = {0, 0, 0, 0, 0, 0, 0, 0};  // E[c][4g + j] as hi (slots 0..3) and lo (4..7), which share a pixel; the rest
     float ef[4], eb[4];                       // E[c][4g + j] (undoing the scale of the first product), E[4g + j][c]
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const float v = kDfScale * p.e[c * 16 + 4 * g + j];
         e1[j] = (half_t)v;
         e1[4 + j] = (half_t)(v - (float)e1[j]);
+        e0[j] = (half_t)(v - (float)e1[j] - (float)e1[4 + j]);
         ef[j] = (1.f / kDfScale) * p.e[c * 16 + 4 * g + j];
         eb[j] = p.e[(4 * g + j) * 16 + c];
     }
@@ -143,7 +146,7 @@ __global__ void __launch_bounds__(64 * kDfWaves) dct_fused_mfma_kernel(DctArgs p
             // lane (c = row, g) reads pixels (row, 4g .. 4g + 3)
             const half4 px = *reinterpret_cast<const half4*>(&s_px[lane_px + 8 * (ty * G::kPxPitch + tx)]);
             const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-            const floatx4 q = mfma16x16x32(join(px, px), e1, zero);
+            const floatx4 q = mfma16x16x32(join(px, px), e1, mfma16x16x32(join(px, px), e0, zero));
             floatx4 y = zero;
 #pragma unroll
             for (int j = 0; j < 4; ++j) y = mfma16x16x4f32(q[j], ef[j], y);
