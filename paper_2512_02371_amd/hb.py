@@ -127,12 +127,18 @@ def _check(fn: str, code: int) -> None:
 
 # Pointers and the stream handle are passed as plain integers, which ctypes converts to the declared argument
 # types: with torch.cuda.current_stream() and a pointer object per argument the host took 10.5 us for a call of
-# hb_fir1d, now 6.5.
+# hb_fir1d, now 6.5.  The two functions behind torch.cuda.current_stream() are private: without them it does.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> int:
     """Handle of torch's current stream on the current device."""
+    if _raw_stream is None or _device is None:
+        return torch.cuda.current_stream().cuda_stream
     if not torch.cuda.is_initialized():
         torch.cuda.init()
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return _raw_stream(_device())
 
 
 def _taps(t):

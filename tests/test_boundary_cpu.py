@@ -382,3 +382,18 @@ def test_sat2d_noalloc_and_wait_limit_validation(lib):
         assert lib.hb_sat2d_set_wait_limit(7) == 16384         # 0 restored the default
     finally:
         lib.hb_sat2d_set_wait_limit(prev if prev > 0 else 0)
+
+
+def test_stream_handle_without_torchs_private_functions(monkeypatch):
+    """The binding loads, and asks torch's public interface for the stream, where the private shortcuts are gone."""
+    import importlib.util
+    import types
+    import torch
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.delattr(torch._C, name, raising=False)
+    spec = importlib.util.spec_from_file_location("hb_without_shortcuts", hb.__file__)
+    fresh = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(fresh)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=1234))
+    assert fresh._stream() == 1234
