@@ -43,12 +43,6 @@ struct DctArgs : DctTables {
     float threshold;
 };
 
-__device__ __forceinline__ void dct_wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // acc (lane (c, g): rows 4g + j of column c) -> LDS tile [row][column]
 __device__ __forceinline__ void dct_put(float* tile, const floatx4& acc, int c, int g) {
 #pragma unroll
@@ -218,24 +212,24 @@ __global__ void __launch_bounds__(64 * kDctWaves) dct_transform_valu_kernel(DctA
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[j] = (float)src[(int64_t)(4 * g + j) * p.in_pitch + c] * p.w[4 * g + j] * p.w[c];
         dct_put(ta, acc, c, g);                                       // T [row][col]
-        dct_wave_sync();
+        wave_lds_fence();
         dct_mm_valu(ta, kDctPitch, 1, s_d, 1, kDctPitch, acc, c, g);  // Q[r][v] = sum_col T[r][col] D[v][col]
         dct_put(tb, acc, c, g);
-        dct_wave_sync();
+        wave_lds_fence();
         dct_mm_valu(s_d, kDctPitch, 1, tb, kDctPitch, 1, acc, c, g);  // Y[u][v] = sum_r D[u][r] Q[r][v]
 #pragma unroll
         for (int j = 0; j < 4; ++j)
             if (fabsf(acc[j]) < p.threshold && !(c == 0 && g == 0 && j == 0)) acc[j] = 0.f;
         dct_put(ta, acc, c, g);
-        dct_wave_sync();
+        wave_lds_fence();
         dct_mm_valu(s_d, 1, kDctPitch, ta, kDctPitch, 1, acc, c, g);  // R[r][v] = sum_u D[u][r] Y[u][v]
         dct_put(tb, acc, c, g);
-        dct_wave_sync();
+        wave_lds_fence();
         dct_mm_valu(tb, kDctPitch, 1, s_d, kDctPitch, 1, acc, c, g);  // rec[r][col] = sum_v R[r][v] D[v][col]
         float* dst = p.tiles + t * 256;
 #pragma unroll
         for (int j = 0; j < 4; ++j) dst[(4 * g + j) * 16 + c] = acc[j] * p.w[4 * g + j] * p.w[c];
-        dct_wave_sync();
+        wave_lds_fence();
     }
 }
 

@@ -134,19 +134,26 @@ __device__ __forceinline__ void store4_mask(float* __restrict__ row, int x, int 
 __device__ __forceinline__ half8 ldg8(const half_t* base, uint32_t byte_off) {
     return *reinterpret_cast<const half8_u*>(reinterpret_cast<const char*>(base) + byte_off);
 }
-// Output stores.  STREAM = true marks the lines non-temporal (written once, not read back by the
-// kernel).  With the coalesced row stores below, streaming stores measured faster at every output
-// size tried (64 MB to 256 MB per call); the limit stays as a switch for measurements.
+// Output stores.  STREAM = true marks the lines non-temporal (written once, not read back by the kernel): faster wherever
+// a store instruction writes whole lines, at every output size (64 MB to 256 MB per call), and for outputs that the
+// memory-side cache takes in.  Large outputs that leave in parts of lines are better put together in the L2 first: see
+// the rules of hb_sat2d and of hb_down2 / hb_up2.
 template <bool STREAM>
 __device__ __forceinline__ void stg4(float* base, uint32_t byte_off, floatx4 v) {
     floatx4_u* q = reinterpret_cast<floatx4_u*>(reinterpret_cast<char*>(base) + byte_off);
     if (STREAM) __builtin_nontemporal_store(v, q); else *q = v;
 }
-// Outputs up to this many megabytes per call are written with streaming stores.
-#ifndef HB_STREAM_STORE_MAX_MB
-#define HB_STREAM_STORE_MAX_MB (1 << 20)
-#endif
-constexpr int64_t kStreamStoreMaxBytes = (int64_t)HB_STREAM_STORE_MAX_MB << 20;
+// LDS traffic inside one wave: what the wave wrote is there for its own lanes (LDS serves one wave's
+// instructions in order); only the compiler has to be kept from reordering.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// LDS written by this workgroup is there for all of it; loads from memory stay in flight (the compiler puts a
+// wait for everything in front of a barrier it emits).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // Accumulator tiles leave the MFMA with a lane owning four columns of ONE row and the 16 lanes
 // of a quarter-wave owning 16 DIFFERENT rows, so a store instruction would touch each row with
@@ -167,9 +174,7 @@ __device__ __forceinline__ void store_rows_via_lds(float* patch, float* dst, uin
 #pragma unroll
     for (int w = 0; w < NW; ++w)
         *reinterpret_cast<floatx4*>(patch + c * RowPatch<NW>::kPitch + 16 * w + 4 * g) = acc[w];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_fence();
     constexpr int kLanesPerRow = 4 * NW;                  // 16-byte pieces in a row of the patch
     constexpr int kRowsPerPass = 64 / kLanesPerRow;
     const int rr = lane / kLanesPerRow, xq = lane - rr * kLanesPerRow;
@@ -179,16 +184,7 @@ __device__ __forceinline__ void store_rows_via_lds(float* patch, float* dst, uin
         const floatx4 v = *reinterpret_cast<const floatx4*>(patch + row * RowPatch<NW>::kPitch + 4 * xq);
         stg4<STREAM>(dst, ((uint32_t)row * pitch_elems + 4u * xq) * 4u, v);
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
-// LDS traffic inside one wave: what the wave wrote is there for its own lanes (LDS serves one wave's
-// instructions in order); only the compiler has to be kept from reordering.
-__device__ __forceinline__ void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_fence();
 }
 
 // store_rows_via_lds for a tile group at the image border: only rows < rows and columns < cols are

@@ -558,9 +558,7 @@ __device__ __forceinline__ void sat_fused_finish(const SatFusedArgs& p, SatFused
         for (int b2 = 0; b2 < tb; ++b2) A += L.lastrow[t2][b2][kSatTile - 1]; // inside the region, tiles above-left
     L.u.term.row[wv][lane] = R;                           // (the parts were last read before the barrier above)
     L.u.term.col[wv][lane] = C + A;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_fence();
     SAT_STAMP(p.sync, sw * p.nbw + bw, 4);
 
     const int y0 = I0 + kSatTile * ts, x0 = J0 + kSatTile * tb;

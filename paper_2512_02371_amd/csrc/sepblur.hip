@@ -153,10 +153,6 @@ struct SepMarch {
     static constexpr int kChunks = (kSepMarchCols - 16 + 32 * NKX) / 8;   // of 8 pixels, per row
     static constexpr int kPitch = 8 * (kChunks | 1);
 };
-// LDS written by this workgroup is there for all of it; loads from memory stay in flight (the compiler puts a
-// wait for everything in front of a barrier it emits).
-__device__ __forceinline__ void sep_lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 template <int NKX, int NT, bool FULL>
 __device__ __forceinline__ void sep_march(const SepArgs& p, half_t* s_px, float* patch, int x0, int Y0, int nsteps, int lane, int wv) {
     using S = SepMarch<NKX>;
@@ -206,7 +202,7 @@ __device__ __forceinline__ void sep_march(const SepArgs& p, half_t* s_px, float*
 #pragma unroll
             for (int u = 0; u < kPieces; ++u) ahead[d][u] = ahead[d + 1][u];
         load_tile(q + kSepAhead, ahead[kSepAhead - 1]);
-        sep_lds_barrier();                                // also: nobody reads the other buffer any more
+        lds_barrier();                                // also: nobody reads the other buffer any more
 #pragma unroll
         for (int t = 0; t + 1 < NT; ++t)
 #pragma unroll

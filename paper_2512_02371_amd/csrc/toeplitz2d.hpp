@@ -89,10 +89,6 @@ struct T2Geom {
     static size_t lds_bytes(int kh) { return image_bytes(kh) + (size_t)tab_rows(kh) * kT2TabRow * 2; }
 };
 
-// LDS written by this workgroup is there for all of it; loads from memory stay in flight (the compiler puts a
-// wait for everything in front of a barrier it emits).
-__device__ __forceinline__ void t2_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 template <int MODE, int NK, int NW, bool SHORT>
 __global__ void __launch_bounds__((T2Geom<MODE, NK, NW, SHORT>::kThreads), (T2Geom<MODE, NK, NW, SHORT>::kOccupancy)) toeplitz2d_mfma_kernel(T2Args p, int table_offset) {
     using G = T2Geom<MODE, NK, NW, SHORT>;
@@ -159,7 +155,7 @@ __global__ void __launch_bounds__((T2Geom<MODE, NK, NW, SHORT>::kThreads), (T2Ge
     for (int i = 8 * tid; i < p.kh * p.kw; i += 8 * G::kThreads)
         *reinterpret_cast<u32x4*>(s_taps + i) = *reinterpret_cast<const u32x4_u*>(p.taps + i);
     request(first);
-    t2_barrier();
+    lds_barrier();
     // weight table: conv / down row r holds kernel row r - kT2ZeroRows; up row 2 (2s + dy) + dx holds the taps
     // 2t + dx of kernel row 2s + dy
     const int tab_rows = MODE == kT2Up ? 2 * p.kh : p.kh + 2 * kT2ZeroRows;
@@ -178,7 +174,7 @@ __global__ void __launch_bounds__((T2Geom<MODE, NK, NW, SHORT>::kThreads), (T2Ge
         *reinterpret_cast<half8*>(s_tab + 8 * i) = v;
     }
     deliver(first);
-    t2_barrier();
+    lds_barrier();
 
     // lane (m = c, h): eight weights from window position 16 kk + 8h on; lane (n = c, h): eight pixels from there on
     const int mx = c & 15, mdy = c >> 4;
@@ -236,7 +232,7 @@ __global__ void __launch_bounds__((T2Geom<MODE, NK, NW, SHORT>::kThreads), (T2Ge
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        t2_barrier();                                     // the LDS image becomes the waves' store patches
+        lds_barrier();                                     // the LDS image becomes the waves' store patches
         if (active) {
             const bool whole = xw + 16 * NW * G::kBeside <= p.Wo && yw + 2 * G::kPairs <= p.Ho;   // uniform
 #pragma unroll
@@ -269,9 +265,9 @@ __global__ void __launch_bounds__((T2Geom<MODE, NK, NW, SHORT>::kThreads), (T2Ge
             }
         }
         if (G::kWalk && tile + 1 < last) {
-            t2_barrier();                                 // patches read
+            lds_barrier();                                 // patches read
             deliver(tile + 1);
-            t2_barrier();
+            lds_barrier();
         }
     }
 }
