@@ -27,8 +27,11 @@
  *    paper's formula verbatim.  Output has the size of the input; out-of-range
  *    reads clamp the INPUT index to the edge (zero padding for hb_conv3x3).
  *  - Arithmetic: fp16 operands, fp32 accumulation on the matrix units.  A window of the
- *    matrix formulation is a little wider than the filter, with zero coefficients there: a
- *    non-finite sample makes NaN of every output whose window holds it.
+ *    matrix formulation is wider than the filter, with zero coefficients there, so a
+ *    non-finite sample makes NaN of outputs beyond the filter's own reach: up to 47 columns
+ *    and, in hb_sepblur and hb_pyr_level, 31 rows, in hb_down2 and hb_up2 two, in hb_conv2d
+ *    one; in hb_resize those of an aligned group of 16 whose samples lie up to 48 from it;
+ *    in hb_iir2 back to the start of its block of 32, in hb_sat2d of its 64 x 64 tile.
  *  - `stream` is a hipStream_t (passed as void* so that this header needs no HIP
  *    include).  All work is enqueued on it; no call synchronises, allocates, frees
  *    or keeps a pointer.  Input and output buffers must not overlap.
