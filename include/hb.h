@@ -20,8 +20,8 @@
  *    Base pointers need the alignment of their element type only (2 bytes for fp16,
  *    4 for fp32); the kernels run fastest when fp16 base pointers and pitches are
  *    multiples of 4 bytes and fp32 ones multiples of 16 bytes (torch allocations
- *    and even pitches are).  Images narrower than 8
- *    pixels run the vector-ALU kernels.
+ *    and even pitches are).  Images narrower than 8 pixels run the vector-ALU kernels, and so
+ *    do those narrower than 48 in hb_pyr_level and some narrow ones under long filters in hb_fir1d.
  *  - Orientation is correlation, as the paper prints it: O(x) = sum_r I(x + r) K(r).
  *    `anchor` shifts the window, tap r reads x + r - anchor; anchor = 0 is the
  *    paper's formula verbatim.  Output has the size of the input; out-of-range

@@ -323,14 +323,16 @@ static hb_status fir1d_prepare(FirArgs& a, const hb_half* in, float* out, int H,
     if ((int64_t)rowsteps * a.nct > 0x7fffffff / 2) return HB_ERR_UNSUPPORTED;
     a.ntasks = rowsteps * a.nct;
     // The walk of long filters: runs of an even number of tiles, two waves per SIMD in all.  More of them only walk more
-    // windows ahead of their run (4096 x 4096, 128 / 256 taps: 20.6 / 25.6 us, with four waves per SIMD 25.8 / 32.0), fewer
-    // leave the chip idle (24.7 / 27.7 with one; 512 x 512 with 256 taps 15 us with one run per row group, 10 so).  Runs
-    // shorter than the windows ahead of them only where there are too few waves otherwise (1749 x 2603, 256 taps 25.9 with
+    // windows ahead of their run (4096 x 4096, 128 / 256 taps with the input in the memory-side cache: 20.2 / 24.5 us, with
+    // four waves per SIMD 25.8 / 32.0), fewer leave the chip idle (24.7 / 27.7 with one; 512 x 512 with 256 taps 15 us with
+    // one run per row group, 10 so).  The shorter filters, whose registers allow four, take four on large images of
+    // whole lines: more bytes in flight (8192 x 4096, 64 taps, input in the memory-side cache / in memory 41 / 62 us with two,
+    // 34 / 54 with four; 4096 x 4096 18.8 / 28.9, 19.7 / 27.5; rows inside lines 42 / 44 us from memory).  Runs shorter than the windows ahead of them only where there are too few waves otherwise (1749 x 2603, 256 taps 25.9 with
     // runs of 10 tiles, 20.0 with 20).  Images of a few rows, most of whose lanes are idle, take longer runs (1 x 1000000,
-    // 256 taps 24 -> 18 us) and, where the registers allow four waves per SIMD, more waves (20 taps 11.0 -> 9.3).
+    // 256 taps 24 -> 18 us).
     a.ntiles = ceil_div(W, 16);
     const int nk = ceil_div(15 + ntaps + (anchor & 1), 32);
-    int runs = std::min((H < 16 && nk <= 3 ? 16 : 8) * num_cu() / rowsteps, a.ntiles / 4);
+    int runs = std::min((nk <= 3 && (H < 16 || (a.lines && (int64_t)H * W > (24 << 20))) ? 16 : 8) * num_cu() / rowsteps, a.ntiles / 4);
     const int long_runs = a.ntiles / ((H < 16 ? 4 : 2) * nk);
     if ((int64_t)rowsteps * long_runs >= 3 * num_cu()) runs = std::min(runs, long_runs);
     runs = std::max(1, runs);
