@@ -327,9 +327,10 @@ static hb_status fir1d_prepare(FirArgs& a, const hb_half* in, float* out, int H,
     // four waves per SIMD 25.8 / 32.0), fewer leave the chip idle (24.7 / 27.7 with one; 512 x 512 with 256 taps 15 us with
     // one run per row group, 10 so).  The shorter filters, whose registers allow four, take four on large images of
     // whole lines: more bytes in flight (8192 x 4096, 64 taps, input in the memory-side cache / in memory 41 / 62 us with two,
-    // 34 / 54 with four; 4096 x 4096 18.8 / 28.9, 19.7 / 27.5; rows inside lines 42 / 44 us from memory).  Runs shorter than the windows ahead of them only where there are too few waves otherwise (1749 x 2603, 256 taps 25.9 with
-    // runs of 10 tiles, 20.0 with 20).  Images of a few rows, most of whose lanes are idle, take longer runs (1 x 1000000,
-    // 256 taps 24 -> 18 us).
+    // 34 / 54 with four; 4096 x 4096 18.8 / 28.9, 19.7 / 27.5; rows inside lines 42 / 44 us from memory).  Runs shorter than
+    // the windows ahead of them only where there are too few waves otherwise (1749 x 2603, 256 taps 25.9 with runs of 10
+    // tiles, 20.0 with 20).  Images of a few rows, most of whose lanes are idle, take longer runs (1 x 1000000, 256 taps 24 ->
+    // 18 us).
     a.ntiles = ceil_div(W, 16);
     const int nk = ceil_div(15 + ntaps + (anchor & 1), 32);
     int runs = std::min((nk <= 3 && (H < 16 || (a.lines && (int64_t)H * W > (24 << 20))) ? 16 : 8) * num_cu() / rowsteps, a.ntiles / 4);
@@ -363,8 +364,8 @@ extern "C" hb_status hb_fir1d(const hb_half* in, float* out, int H, int W,
     const int nk = ceil_div(15 + ntaps + (anchor & 1), 32);
     // narrow images are one short run per row group, whose windows all reach over the row's ends: with rows inside lines
     // the vector ALU is the faster one (1000 x 100, 159 taps 7.0 us, walked 9.4; 1000 x 128, 200 taps, whole lines 8.3, 6.8;
-    // 50000 x 83, 159 taps 31, 24)
-    if (W < kFirMinWidth || (nk >= 4 && W <= 128 && !a.lines && H <= 32 * num_cu()))
+    // 50000 x 83, 159 taps 31, 24; 3600 x 16, 107 taps 11.2, 6.9)
+    if (W < kFirMinWidth || (nk >= 4 && W > 32 && W <= 128 && !a.lines && H <= 32 * num_cu()))
         return hb_fir1d_valu(in, out, H, W, in_pitch, out_pitch, taps_host, ntaps, anchor, stream);
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
 #define HB_FIR_WALK(N)                                                                            \

@@ -497,14 +497,14 @@ static hb_status resize_run(bool valu, const hb_half* in, float* out, void* work
     // -> 55 x 210, 370 x 1081 pixels a group: 84 us, two launches 64; 127 x 1655 47 against 77).
     // Rows that start on odd samples are read at a fraction of the rate, and the one-launch kernel reads a row for every
     // group of outputs that needs it (8 planes of 2048 rows at a pitch of 2049, factor 9: 71 us against 55; factor 4: 57
-    // against 65; 1024 x 1024 at a pitch of 1025, factor 16: 31 against 29).
+    // against 65; 1024 x 1024 at a pitch of 1025, factor 16: 31 against 29; 5864 x 214 -> 181 x 100 at 215: 17 against 25).
     const bool odd_rows = (in_pitch & 1) || (C > 1 && (in_plane & 1)) || !aligned_to(in, 4);
     // Large enlargements are bound by their stores, of 64-byte runs here and 256-byte runs there (3 x 2048 x 2048 to three
     // times the size 222 us, two launches 170); where rows start inside 128-byte lines neither run is whole (227 against 246).
     const bool line_stores = (double)Ho * Wo >= 2.0 * H * W && (int64_t)C * Ho * Wo > (16 << 20) && out_pitch % 32 == 0 &&
                              out_plane % 32 == 0 && aligned_to(out, 128);
     const bool one_launch = W >= kRzMinWidth && (span_x <= 32 * kRzChunks ? span_x * span_y <= 3.2e5 : span_y <= 128 && waves <= 2 * num_cu()) &&
-                            !line_stores && !(odd_rows && span_y > ((int64_t)C * H * W > (6 << 20) ? 120 : 320));
+                            !line_stores && !(odd_rows && ((int64_t)C * H * W > (6 << 20) ? span_y > 120 : span_x * span_y > 1e5));
     if (!valu && one_launch) {
         ResizeArgs r;
         r.in = reinterpret_cast<const half_t*>(in);

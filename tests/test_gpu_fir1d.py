@@ -108,3 +108,19 @@ def test_fir1d_impulse_and_constant(fn):
         assert got[7, x] == (np.float32(k[r]) if 0 <= r < T else 0.0)
     getattr(hb, fn)(up(synth.f64_to_f16_bits(np.full((H, W), 0.5))), out, taps, a)
     assert np.allclose(out.cpu().numpy(), 0.5 * k.sum(), atol=1e-6)
+
+
+@pytest.mark.parametrize("T,a", [(20, 19), (64, 0)])
+def test_fir1d_large_image_of_whole_lines(orc, T, a):
+    """More runs per row where the image is large, on bands of rows."""
+    import torch
+    from paper_2512_02371_amd import hb
+    H, W = 5030, 5024
+    gen = torch.Generator(device="cuda:0").manual_seed(T)
+    img = torch.randint(0, 2048, (H, W), generator=gen, device="cuda:0", dtype=torch.int16).float().div_(2048).half()
+    out = torch.zeros((H, W), dtype=torch.float32, device="cuda:0")
+    taps = synth.random_taps_f16(T, T)
+    hb.hb_fir1d(img, out, taps, a)
+    for r0 in (0, 2512, H - 30):
+        ref = orc.fir1d(img[r0:r0 + 30].cpu().numpy().view(np.uint16), taps, a)
+        assert_close(out[r0:r0 + 30].cpu().numpy(), ref, f"rows {r0}..")
