@@ -496,15 +496,20 @@ static hb_status resize_run(bool valu, const hb_half* in, float* out, void* work
     // Nor does it pay where the rows of a group are so many that few workgroups pass over most of the image (2832 x 3696
     // -> 55 x 210, 370 x 1081 pixels a group: 84 us, two launches 64; 127 x 1655 47 against 77).
     // Rows that start on odd samples are read at a fraction of the rate, and the one-launch kernel reads a row for every
-    // group of outputs that needs it (8 planes of 2048 rows at a pitch of 2049, factor 9: 71 us against 55; factor 4: 57
-    // against 65; 1024 x 1024 at a pitch of 1025, factor 16: 31 against 29; 5864 x 214 -> 181 x 100 at 215: 17 against 25).
+    // group of outputs that needs it: large images take two (8 planes of 2048 rows at a pitch of 2049, factor 9: 71 us
+    // against 55; factor 4: 57 against 65; small ones gain from one, 874 x 3053 at 3117 -> 13 x 341 49 against 62).
     const bool odd_rows = (in_pitch & 1) || (C > 1 && (in_plane & 1)) || !aligned_to(in, 4);
     // Large enlargements are bound by their stores, of 64-byte runs here and 256-byte runs there (3 x 2048 x 2048 to three
     // times the size 222 us, two launches 170); where rows start inside 128-byte lines neither run is whole (227 against 246).
     const bool line_stores = (double)Ho * Wo >= 2.0 * H * W && (int64_t)C * Ho * Wo > (16 << 20) && out_pitch % 32 == 0 &&
                              out_plane % 32 == 0 && aligned_to(out, 128);
+    // One or two groups of rows as wide as the image leave a wave with a long walk and nothing to share (32 x 200 x 4096 -> 4
+    // x 4000 183 us, two launches 96; 8 x 514 x 8160 -> 30 x 4720 81 against 74); narrow results have fewer products in each
+    // row's pass (64 x 240 x 4096 -> 12 x 600 68 against 82, 12 x 1600 118 against 104).
+    const bool tall = span_y > RzGeom<false>::kRows;
+    const bool few_groups = tall && groups <= 2 && waves >= 8 * num_cu() && 4 * (int64_t)Wo >= W;
     const bool one_launch = W >= kRzMinWidth && (span_x <= 32 * kRzChunks ? span_x * span_y <= 3.2e5 : span_y <= 128 && waves <= 2 * num_cu()) &&
-                            !line_stores && !(odd_rows && ((int64_t)C * H * W > (6 << 20) ? span_y > 120 : span_x * span_y > 1e5));
+                            !line_stores && !few_groups && !(odd_rows && (int64_t)C * H * W > (6 << 20) && span_y > 120);
     if (!valu && one_launch) {
         ResizeArgs r;
         r.in = reinterpret_cast<const half_t*>(in);
@@ -529,9 +534,11 @@ static hb_status resize_run(bool valu, const hb_half* in, float* out, void* work
         // chip keeps two waves per SIMD (2048 x 2048 from 4096 x 4096: 34 / 29 / 27 us with 1 / 2 / 4; 450 x 450 x 3 from
         // 2048 x 2048: 19 / 29 / 37).  Under one wave per SIMD the waves of a workgroup share one group (256 x 256 from
         // 4096 x 4096: 20 us against 92), under two where its rows do not fit a wave's LDS at once (512 x 512 from
-        // 8192 x 8192: 56 against 96; at two 256 x 2048 from 4096 x 4096 33 with a group per wave, 41 shared).
+        // 8192 x 8192: 56 against 96; at two 256 x 2048 from 4096 x 4096 33 with a group per wave, 41 shared), and
+        // where one group is all there is (64 x 240 x 4096 -> 12 x 600 68 against 121).
         auto good = [&](int q) { return waves >= 8 * q * num_cu() && 16.0 * q * H / Ho + band_y <= RzGeom<false>::kRows; };
-        const int gq = waves < (span_y > RzGeom<false>::kRows ? 8 : 4) * num_cu() ? 0 : good(4) ? 4 : good(2) ? 2 : 1;
+        const bool shared = waves < (tall ? 8 : 4) * num_cu() || (tall && groups == 1);
+        const int gq = shared ? 0 : good(4) ? 4 : good(2) ? 2 : 1;
         r.ngy = gq ? ceil_div(groups, gq * RzGeom<false>::kWaves) : groups;
         const int64_t blocks = (int64_t)C * r.ngx * r.ngy;
         if (blocks > 0x7fffffff) return HB_ERR_UNSUPPORTED;

@@ -124,8 +124,10 @@ def test_resize_random_starts_over_the_work_splits(orc, C, H, W, Ho, Wo, by, bx,
     (1, 3, 3000, 3, 60),          # ... few rows: one launch, more than 384 columns
     (3, 20, 2500, 18, 40),
     (400, 200, 40, 10, 40),       # waves that share a group of rows too long for one wave: 1200 groups
-    (700, 200, 40, 10, 40),       # 2100: a wave each, in rounds
-    (1, 770, 130, 22, 60),        # rows that start on odd samples and a group that spans many of them: two launches
+    (700, 200, 40, 10, 40),       # 2100, one to a column: two launches
+    (1100, 200, 130, 10, 32),     # ... narrow results: one launch, shared all the same
+    (240, 560, 48, 34, 40),       # three to a column: a wave each, in rounds
+    (1, 770, 130, 22, 60),        # rows that start on odd samples and a group that spans many of them
 ])
 def test_resize_large_factors(orc, C, H, W, Ho, Wo):
     """The routes of the large factors: Lanczos matrices, whose starts advance by the scale."""
