@@ -96,7 +96,7 @@ static hb_status conv2d_prepare(T2Args& a, const hb_half* in, float* out, int H,
     memcpy(a.taps, taps_host, sizeof(uint16_t) * (size_t)kh * (size_t)kw);
     a.Ho = H;
     a.Wo = W;
-    a.ncol = a.nrow = a.ntiles = a.per_wg = a.stream = a.steps = a.srows = a.rows = 0;
+    a.ncol = a.nrow = a.ntiles = a.stream = a.alias = a.steps = a.srows = a.rows = 0;
     return HB_OK;
 }
 
@@ -109,13 +109,20 @@ static hb_status conv2d_launch_valu(const T2Args& a, hipStream_t st) {
     return launch_status();
 }
 
-// 128 x 128 output tiles while they give every compute unit its two workgroups and the image is wide enough to need
-// them, else 64 x 128
+// Tiles of 64 x 256, 64 x 128 or 64 x 64 outputs.  The middle one is the general one (4096 x 4096, 3 x 3 / 11 x 11 / 20 x 20 taps
+// 19.3 / 21.3 / 34.8 us, with the widest 21.5 / 25.9 / 37.9).  The widest reads the LDS least per product, which counts
+// from 28 kernel rows on (32 x 32: 51.7, 52.5), and leaves fewer partial lines where output rows start inside them
+// (4095 x 4095, 7 x 7: 32.9, 40.6).  The narrowest where the others leave compute units idle (300 x 200, 32 x 32: 9.8,
+// 12.0; 1500 x 1500, 9 x 9: 7.7, 8.3).
 template <int NK>
 static hb_status conv2d_launch(T2Args& a, hipStream_t st) {
     if (t2_short<kT2Conv, NK, 2>(a)) return t2_launch<kT2Conv, NK, 2, true>(a, st);
-    if (a.W > 64 && (int64_t)ceil_div(a.H, 128) * ceil_div(a.W, 128) >= 2 * num_cu()) return t2_launch<kT2Conv, NK, 4, false>(a, st);
-    return t2_launch<kT2Conv, NK, 2, false>(a, st);
+    const int64_t rows = ceil_div(a.H, 64);
+    const bool whole_lines = a.out_pitch % 32 == 0 && aligned_to(a.out, 128);
+    if (a.W > 64 && (a.kh >= 28 || !whole_lines) && rows * ceil_div(a.W, 256) >= 2 * num_cu())
+        return t2_launch<kT2Conv, NK, 4, false>(a, st);
+    if (rows * ceil_div(a.W, 128) >= num_cu() * 5 / 4) return t2_launch<kT2Conv, NK, 2, false>(a, st);
+    return t2_launch<kT2Conv, NK, 1, false>(a, st);
 }
 
 }  // namespace hb

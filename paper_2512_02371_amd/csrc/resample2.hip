@@ -177,7 +177,7 @@ static hb_status rs2_prepare(T2Args& a, bool up, const hb_half* in, float* out, 
     a.ax = ax;
     memset(a.taps, 0, sizeof(a.taps));
     memcpy(a.taps, taps_host, sizeof(uint16_t) * (size_t)kh * (size_t)kw);
-    a.ncol = a.nrow = a.ntiles = a.per_wg = a.stream = a.steps = a.srows = a.rows = 0;
+    a.ncol = a.nrow = a.ntiles = a.stream = a.alias = a.steps = a.srows = a.rows = 0;
     return HB_OK;
 }
 
