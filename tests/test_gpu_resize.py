@@ -176,3 +176,19 @@ def test_resize_full_size(orc):
         s, k = lanczos(hb, H, n)
         got, _ = run("hb_resize", img, s, k, s, k)
         assert_close(got[c], orc.band_resize(img[c], s, k, s, k), f"2048 -> {n}, plane {c}")
+
+
+@pytest.mark.parametrize("band", [2, 26, 28, 34])     # spans of 32 to 64 samples: at, just under and over whole chunks
+@pytest.mark.parametrize("pitch_extra", [0, 1, 2])    # rows on 16 bytes, on every byte pair, on 4 bytes
+def test_resize_first_column_of_a_window(orc, band, pitch_extra):
+    """Windows that start on every residue of eight samples, inside the image and left of it."""
+    H, W, Ho, Wo = 40, 72, 18, 20
+    img = synth.uniform01_f16(9200 + band, (2, H, W))
+    cx = (synth.random_kernel2d_f16(9201, Wo, band).view(np.float16).astype(np.float64) * Wo).astype(np.float16).view(np.uint16)
+    from paper_2512_02371_amd import hb
+    sy, cy = lanczos(hb, H, Ho)
+    for off in range(-9, 9):
+        sx = (off + 2 * np.arange(Wo)).astype(np.int32)
+        got, _ = run("hb_resize", img, sy, cy, sx, cx, pitch_extra)
+        for c in range(2):
+            assert_close(got[c], orc.band_resize(img[c], sy, cy, sx, cx), f"offset {off} plane {c}")
