@@ -22,6 +22,8 @@
 //   products: wave (q, j) owns output rows 2q, 2q+1 of the tile and channel tile j, i.e. 2 x 36
 //   products per tile.  fp32 accumulators are rounded to fp16 (RNE) into a stage shared by the
 //   workgroup and leave as whole 128-byte pixels (1 KB per store instruction).
+#include <algorithm>
+
 #include "hb_device.hpp"
 #include "hb_host.hpp"
 
@@ -383,10 +385,23 @@ static hb_status conv_prepare(ConvArgs& a, const hb_half* in, const hb_half* w, 
     a.tiles_x = ceil_div(W, kCvTX);
     a.tiles_y = ceil_div(H, kCvTY);
     a.ntiles = (int)tiles;
-    // column segments of the MFMA kernel: about one per compute unit, at least 4 tiles long
-    const int want = ceil_div(num_cu(), N * a.tiles_x);
-    int len = ceil_div(a.tiles_y, want);
-    if (len < 4) len = a.tiles_y < 4 ? a.tiles_y : 4;
+    // Column segments of the MFMA kernel: a compute unit holds one workgroup, so the columns are cut into as many equal
+    // segments as fill the chip some whole number of times and not once more.  A round costs its segment's tiles and the
+    // start of a workgroup, weights and first rows, about two tiles' time; the cheapest number of rounds is taken.
+    // Against segments of four tiles at least, rounded to more than one round: 700 x 1300 (246 segments of 15 tiles, not 287
+    // of 13) 94.4 -> 68.9 us, 5 x 400 x 400 88.5 -> 67.9, 8 x 56 x 56 (112 of one tile, not 32 of four) 16.8 -> 8.6.
+    const int64_t columns = (int64_t)N * a.tiles_x, units = num_cu();
+    const int64_t least = (columns + units - 1) / units;
+    int len = a.tiles_y;
+    int64_t cheapest = INT64_MAX;
+    for (int64_t rounds = least; rounds < least + 16; ++rounds) {
+        const int64_t segments = std::min<int64_t>(rounds * units / columns, a.tiles_y);
+        const int64_t tiles_each = (a.tiles_y + segments - 1) / segments, cost = rounds * (tiles_each + 2);
+        if (cost < cheapest) {
+            cheapest = cost;
+            len = (int)tiles_each;
+        }
+    }
     a.seg_len = len;
     a.nseg = ceil_div(a.tiles_y, len);
     return HB_OK;

@@ -64,6 +64,22 @@ def test_conv_benchmark_shape_sampled(orc, fn):
     assert_close(got[0, ys, xs], ref, f"{fn} scattered")
 
 
+@pytest.mark.parametrize("N,H,W", [(1, 520, 160), (2, 300, 200), (2, 700, 130), (9, 17, 930), (3, 500, 610), (1, 14, 14), (40, 5, 250)])
+def test_conv_column_segments(orc, N, H, W):
+    """Columns cut into segments of one tile to many, the last ones shorter, and more columns than compute units:
+    scattered pixels and those on both sides of every tile seam of a column."""
+    x = synth.uniform_pm1_f16(9200 + H, (N, H, W, 64))
+    w = synth.normal_f16(9201, (3, 3, 64, 64), 1 / 24)
+    got = run("hb_conv3x3", x, w)
+    h = synth.hash_u64(9202 + W, 0, 4500)
+    seams = np.array([y for y in range(H) if y % 8 in (0, 7)])
+    ns = (h[:1500] % np.uint64(N)).astype(np.int32)
+    ys = (h[1500:3000] % np.uint64(H)).astype(np.int32)
+    ys[:len(seams)] = seams
+    xs = (h[3000:] % np.uint64(W)).astype(np.int32)
+    assert_close(got[ns, ys, xs], orc.conv3x3_points(x, w, ns, ys, xs), f"hb_conv3x3 {N}x{H}x{W}")
+
+
 def test_conv_rejects_other_channel_counts():
     import torch
     from paper_2512_02371_amd import hb
