@@ -316,12 +316,13 @@ static hb_status dct_run(bool valu, const hb_half* in, float* out, int C, int H,
     const unsigned blocks = (unsigned)(wgs < 4096 ? wgs : 4096);     // waves stride over the tiles
     if (!valu) {
         // one launch: tiles and blend fused, the workspace stays unused
-        // 32 x 32 patches (1.56x the products) while the larger ones would leave compute units idle (512 x 512:
-        // below the host's launch rate of 12.6 us, 17.0 with one workgroup of 64 x 64 on every fourth unit)
+        // 32 x 32 patches (1.56x the products) while there are two of them to a compute unit at most and the larger ones
+        // would leave units idle (512 x 512 6.3 us, 10.1 with 64 x 64 patches; 800 x 800, 625 small ones, 10.9 against 10.3,
+        // 960 x 960 13.4 against 10.6)
         const int64_t patches = (int64_t)C * ceil_div(H, 64) * ceil_div(W, 64);
         const int64_t small = (int64_t)C * ceil_div(H, 32) * ceil_div(W, 32);
         if (patches > 0x7fffffff) return HB_ERR_UNSUPPORTED;
-        if (patches < num_cu())
+        if (patches < num_cu() && small <= 2 * num_cu())
             hipLaunchKernelGGL(dct_fused_mfma_kernel<32>, dim3((unsigned)small), dim3(64 * kDfWaves), 0, st, a);
         else
             hipLaunchKernelGGL(dct_fused_mfma_kernel<64>, dim3((unsigned)patches), dim3(64 * kDfWaves), 0, st, a);

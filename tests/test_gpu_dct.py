@@ -98,6 +98,8 @@ def check(orc, got, img, threshold, what, max_masked=0.5):
     (1, 200, 136, 0.03),
     (5, 512, 512, 0.05),      # 320 patches of 64 x 64: the larger patch
     (4, 520, 456, 0.05),      # 288, the last ones of a row and a column in part outside
+    (2, 512, 512, 0.05),      # 512 patches of 32 x 32, the most that are taken
+    (2, 520, 512, 0.05),      # 544 of them: the larger patch, 144
 ])
 def test_dct_denoise_matches_oracle(orc, fn, C, H, W, thr):
     img = noisy_image(9800 + H + W, C, H, W)
