@@ -40,7 +40,7 @@ struct ResizeArgs {
     int C, H, W, Ho, Wo, band_x, band_y;
     int64_t in_pitch, in_plane, out_pitch, out_plane;
     int ngx, ngy;                             // workgroups across and down
-    int rows16;                               // rows start on 16 bytes
+    int first_mask;                           // of a window's first column: ~7 where rows start on 16 bytes, else ~1
 };
 
 constexpr int kRzChunks = 12;                 // chunks of 32 columns whose coefficients are kept in LDS
@@ -120,8 +120,8 @@ __global__ void __launch_bounds__(64 * RzGeom<SHARED>::kWaves, 4) resize_mfma_ke
     rz_extent(xlo, xhi);
     xlo = __builtin_amdgcn_readfirstlane(xlo) & ~1;
     xhi = __builtin_amdgcn_readfirstlane(xhi);
-    const int nk = (xhi - xlo + 31) / 32;
-    if (p.rows16 && (xhi - (xlo & ~7) + 31) / 32 == nk) xlo &= ~7;
+    const int nk = (xhi - xlo + 31) >> 5, aligned = xlo & p.first_mask;
+    if (xhi - aligned <= 32 * nk) xlo = aligned;
     int glo = sy, ghi = sy + p.band_y;                    // of the lane's group of 16 rows
     rz_extent(glo, ghi);
     int ylo = glo, yhi = ghi;
@@ -146,9 +146,13 @@ __global__ void __launch_bounds__(64 * RzGeom<SHARED>::kWaves, 4) resize_mfma_ke
         const uint32_t row = (uint32_t)clampi(y, 0, p.H - 1) * (uint32_t)p.in_pitch;
         const int xs = xlo + 32 * kk, x = xs + 8 * g;
         if (xs >= 0 && xs + 32 <= p.W) return ldg8(px, 2u * (row + (uint32_t)x));     // uniform
-        // requested inside the row, then shifted into place
-        const half8 v = ldg8(px, 2u * (row + (uint32_t)clampi(x, 0, p.W - 8)));
-        return shift_in_from_left(shift_in_from_right(v, max(x - (p.W - 8), 0)), max(-x, 0));
+        // Requested inside the row, then shifted into place.  The column is hidden from the compiler, which otherwise works
+        // out the masks of all four chunks' shifts ahead of the loop, also for groups inside the image, and spills 40 scalar
+        // registers over them (250 calls on 64 to 4096 rows and columns, factors up to 16: 6 % faster on average, none slower).
+        int xe = x;
+        asm volatile("" : "+v"(xe));
+        const half8 v = ldg8(px, 2u * (row + (uint32_t)clampi(xe, 0, p.W - 8)));
+        return shift_in_from_left(shift_in_from_right(v, max(xe - (p.W - 8), 0)), max(-xe, 0));
     };
     auto rows_ready = [&]() {
         if (SHARED) __syncthreads();
@@ -539,7 +543,7 @@ static hb_status resize_run(bool valu, const hb_half* in, float* out, void* work
         r.out_pitch = out_pitch;
         r.out_plane = out_plane;
         r.ngx = ceil_div(Wo, 16);
-        r.rows16 = in_pitch % 8 == 0 && (C == 1 || in_plane % 8 == 0) && aligned_to(in, 16);
+        r.first_mask = in_pitch % 8 == 0 && (C == 1 || in_plane % 8 == 0) && aligned_to(in, 16) ? ~7 : ~1;
         // Groups of 16 output rows per wave: more share more, while the rows they need fit the wave's LDS and the
         // chip keeps two waves per SIMD (2048 x 2048 from 4096 x 4096: 34 / 29 / 27 us with 1 / 2 / 4; 450 x 450 x 3 from
         // 2048 x 2048: 19 / 29 / 37).  Under one wave per SIMD the waves of a workgroup share one group (256 x 256 from
