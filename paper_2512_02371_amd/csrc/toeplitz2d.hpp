@@ -33,10 +33,9 @@
 #include <algorithm>
 
 #include "hb_device.hpp"
+#include "toeplitz2d_tile.hpp"
 
 namespace hb {
-
-enum T2Mode { kT2Conv, kT2Down, kT2Up };
 
 struct T2Args {
     const half_t* in;
@@ -56,43 +55,6 @@ typedef u32x4 u32x4_u __attribute__((aligned(4)));
 typedef half8 half8_a8 __attribute__((aligned(8)));
 
 constexpr int kT2MinWidth = 8;                // of an image
-constexpr int kT2ZeroRows = 2;                // above and below the taps
-
-// SHORT (outputs of few rows): the N index of a product is 8 row pairs x 4 runs of tiles beside each other instead
-// of 32 row pairs.  16 x 200000, 3 x 3 / 32 x 32 taps: 14.3 / 45 us with the tall tile, 10.2 / 17 with this one.
-template <int MODE, int NK, int NW, bool SHORT>
-struct T2Geom {
-    static constexpr int kPairs = SHORT ? 8 : 32, kBeside = 32 / kPairs;  // row pairs, runs of tiles in N
-    static constexpr int kWx = 4;                                         // waves of a workgroup, beside each other
-    static constexpr int kThreads = 64 * kWx;
-    static constexpr int kOccupancy = MODE == kT2Conv ? (NW > 2 ? 2 : 3) : MODE == kT2Down ? 2 : NK > 1 ? 3 : 4;   // waves per SIMD
-    static constexpr int kStride = MODE == kT2Conv ? 2 : MODE == kT2Down ? 4 : 1;   // input rows per n
-    static constexpr int kTileStep = MODE == kT2Conv ? 16 : MODE == kT2Down ? 32 : 8;
-    static constexpr int kCols = 16 * NW * kBeside * kWx, kRows = 2 * kPairs;         // output tile
-    static constexpr int kChunks = (kTileStep * (NW * kBeside * kWx - 1) + 16 * NK) / 8;      // of 8 staged pixels per row
-    static constexpr int kPitch = 8 * (kChunks | 1);
-    static constexpr int kPatch = 32 * (16 * NW + 4);                     // floats per wave, see the stores
-    // window chunks of a wave: distinct multiples of 8 pixels at which a fragment starts
-    static constexpr int kUnit = MODE == kT2Up ? 8 : 16;
-    static constexpr int kFrags = (kTileStep * (NW - 1) + 16 * (NK - 1)) / kUnit + 1;
-    static constexpr int kMaxSteps = MODE == kT2Conv ? HB_MAX_TAPS_CONV2D + 1 : MODE == kT2Down ? HB_MAX_TAPS_CONV2D + 2 : HB_MAX_TAPS_CONV2D / 2;
-    static constexpr int kPieces = ((kStride * (kPairs - 1) + kMaxSteps) * kChunks + kThreads - 1) / kThreads;   // staged per thread
-    // Weight table.  A lane's eight weights start at position 8h - (its column's shift) + kPad, 1 (conv, up) or 2 (down)
-    // apart, so a row is kept in kCopies copies of kCopy taps, each shifted by kShift, and every run starts on 8 bytes
-    // (down: 16).  Pitches: the lanes served together fall into different banks (conv: blocks of 8 dwords at 0, 40, 16, 56 and, for
-    // the row above, 32 further; up: of 4 dwords at 0, 20, 40, 60 plus 16 and 32; down: of 16 at 0, 48, 32, 16).
-    static constexpr int kCopies = 4, kShift = MODE == kT2Down ? 2 : 1, kPad = MODE == kT2Conv ? 15 : MODE == kT2Down ? 30 : 7;
-    static constexpr int kCopy = MODE == kT2Conv ? 80 : MODE == kT2Down ? 96 : 40, kTabRow = kCopies * kCopy;
-    static int steps(int kh) { return MODE == kT2Conv ? kh + 1 : MODE == kT2Down ? kh + 2 : kh / 2; }
-    static int rows(int kh) { return kStride * (kPairs - 1) + steps(kh); }
-    static int srows(int kh) { return (rows(kh) + kStride - 1) / kStride; }
-    static int tab_rows(int kh) { return MODE == kT2Up ? 2 * kh : kh + 2 * kT2ZeroRows; }
-    static size_t image_bytes(int kh) {
-        const size_t img = (size_t)kStride * srows(kh) * kPitch * 2, patch = (size_t)kWx * kPatch * 4;
-        return img > patch ? img : patch;
-    }
-    static size_t lds_bytes(int kh) { return image_bytes(kh) + (size_t)tab_rows(kh) * kTabRow * 2; }
-};
 
 template <int MODE, int NK, int NW, bool SHORT>
 __global__ void __launch_bounds__((T2Geom<MODE, NK, NW, SHORT>::kThreads), (T2Geom<MODE, NK, NW, SHORT>::kOccupancy)) toeplitz2d_mfma_kernel(T2Args p, int table_offset, int taps_offset) {
@@ -156,12 +118,12 @@ __global__ void __launch_bounds__((T2Geom<MODE, NK, NW, SHORT>::kThreads), (T2Ge
         *reinterpret_cast<u32x4*>(s_taps + i) = *reinterpret_cast<const u32x4_u*>(p.taps + i);
     request();
     lds_barrier();
-    // weight table: conv / down row r holds kernel row r - kT2ZeroRows; up row 2 (2s + dy) + dx holds the taps
+    // weight table: conv / down row r holds kernel row r - G::kZeroRows; up row 2 (2s + dy) + dx holds the taps
     // 2t + dx of kernel row 2s + dy
-    const int tab_rows = MODE == kT2Up ? 2 * p.kh : p.kh + 2 * kT2ZeroRows;
+    const int tab_rows = MODE == kT2Up ? 2 * p.kh : p.kh + 2 * G::kZeroRows;
     for (int i = tid; i < tab_rows * (G::kCopy / 8); i += G::kThreads) {      // one run of a row in all its copies
         const int r = i / (G::kCopy / 8), j = 8 * (i - r * (G::kCopy / 8));
-        const int ry = MODE == kT2Up ? r >> 1 : r - kT2ZeroRows;
+        const int ry = MODE == kT2Up ? r >> 1 : r - G::kZeroRows;
         half_t run[8 + G::kShift * (G::kCopies - 1)];
 #pragma unroll
         for (int k = 0; k < 8 + G::kShift * (G::kCopies - 1); ++k) {
@@ -185,7 +147,7 @@ __global__ void __launch_bounds__((T2Geom<MODE, NK, NW, SHORT>::kThreads), (T2Ge
     // lane (m = c, h): eight weights from window position 16 kk + 8h on; lane (n = c, h): eight pixels from there on
     const int mx = c & 15, mdy = c >> 4;
     const int t0 = 8 * h - (MODE == kT2Conv ? mx : MODE == kT2Down ? 2 * mx : mx >> 1) + G::kPad, t_copy = t0 / G::kShift % G::kCopies;
-    const int row0 = MODE == kT2Conv ? kT2ZeroRows - mdy : MODE == kT2Down ? kT2ZeroRows - 2 * mdy : 2 * mdy + (mx & 1);
+    const int row0 = MODE == kT2Conv ? G::kZeroRows - mdy : MODE == kT2Down ? G::kZeroRows - 2 * mdy : 2 * mdy + (mx & 1);
     const half_t* const tab = s_tab + row0 * G::kTabRow + t_copy * G::kCopy + t0 - G::kShift * t_copy;
     const int pair = c % G::kPairs, beside = c / G::kPairs;
     const half_t* const px = s_px + pair * G::kPitch + G::kTileStep * NW * (G::kBeside * wv + beside) + 8 * h;
@@ -293,8 +255,8 @@ static hb_status t2_launch(T2Args& a, hipStream_t st) {
     a.nrow = ceil_div(a.Ho, G::kRows);
     a.ntiles = (int)tiles;
     // the staged taps get LDS of their own where a compute unit holds as many workgroups with it
-    const size_t shared = G::lds_bytes(a.kh), lds_cu = 160 << 10, taps = ((size_t)a.kh * a.kw * 2 + 15) / 16 * 16;
-    a.alias = lds_cu / (shared + taps) < lds_cu / shared;
+    const size_t shared = G::lds_bytes(a.kh), taps = ((size_t)a.kh * a.kw * 2 + 15) / 16 * 16;
+    a.alias = t2_resident(shared + taps) < t2_resident(shared);
     const size_t lds = a.alias ? shared : shared + taps;
     const auto kernel = toeplitz2d_mfma_kernel<MODE, NK, NW, SHORT>;
     if (allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds) != HB_OK) return HB_ERR_HIP;
