@@ -33,6 +33,11 @@ CASES = [
     ("up2", 16, 49153, 4, 6),            # the short tile and the last height that takes it
     ("up2", 17, 49153, 6, 4),
     ("up2", 8, 49408, 20, 2),
+    ("conv2d", 57, 256, 3, 3),           # whole columns, rows missing from the last tile: vector stores of some rows ...
+    ("conv2d", 1281, 2176, 5, 32),
+    ("down2", 126, 256, 3, 18),
+    ("up2", 17, 128, 6, 6),
+    ("down2", 4098, 8192, 2, 2),         # ... through the L2 (more than 32 MB of output, rows off the 128-byte lines: pitch below)
 ]
 
 
@@ -45,7 +50,7 @@ def test_tile_edges(orc, op, H, W, kh, kw):
     Ho, Wo = {"conv2d": (H, W), "down2": ((H + 1) // 2, (W + 1) // 2), "up2": (2 * H, 2 * W)}[op]
     n = 2 if op == "up2" else 1                            # phases per axis: hb_up2 anchors among kh / 2
     ay, ax = (kh // n - 1) // 2, (kw // n - 1) // 2
-    pitch = (Wo + 31) // 32 * 32 if kh == 28 else Wo
+    pitch = (Wo + 31) // 32 * 32 if kh == 28 else Wo + 1 if H == 4098 else Wo
     obuf, out = padded(torch.zeros((Ho, Wo), dtype=torch.float32, device="cuda:0"), pitch)
     print(f"{op} {H}x{W} {kh}x{kw}", flush=True)
     getattr(hb, "hb_" + op)(up(img), out, k, ay, ax)
