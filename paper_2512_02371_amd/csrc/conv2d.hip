@@ -109,20 +109,15 @@ static hb_status conv2d_launch_valu(const T2Args& a, hipStream_t st) {
     return launch_status();
 }
 
-// Tiles of 64 x 256, 64 x 128 or 64 x 64 outputs.  The middle one is the general one (4096 x 4096, 3 x 3 / 11 x 11 / 20 x 20 taps
-// 19.3 / 21.3 / 34.8 us, with the widest 21.5 / 25.9 / 37.9).  The widest reads the LDS least per product, which counts
-// from 28 kernel rows on (32 x 32: 51.7, 52.5), and leaves fewer partial lines where output rows start inside them
-// (4095 x 4095, 7 x 7: 32.9, 40.6).  The narrowest where the others leave compute units idle (300 x 200, 32 x 32: 9.8,
-// 12.0; 1500 x 1500, 9 x 9: 7.7, 8.3).
 template <int NK>
 static hb_status conv2d_launch(T2Args& a, hipStream_t st) {
-    if (t2_short<kT2Conv, NK, 2>(a)) return t2_launch<kT2Conv, NK, 2, true>(a, st);
-    const int64_t rows = ceil_div(a.H, 64);
-    const bool whole_lines = a.out_pitch % 32 == 0 && aligned_to(a.out, 128);
-    if (a.W > 64 && (a.kh >= 28 || !whole_lines) && rows * ceil_div(a.W, 256) >= 2 * num_cu())
-        return t2_launch<kT2Conv, NK, 4, false>(a, st);
-    if (rows * ceil_div(a.W, 128) >= num_cu() * 5 / 4) return t2_launch<kT2Conv, NK, 2, false>(a, st);
-    return t2_launch<kT2Conv, NK, 1, false>(a, st);
+    const T2Tile t = t2_conv_tile(a.H, a.W, a.kh, a.out_pitch % 16 != 0 || !aligned_to(a.out, 64), num_cu());
+    if (t.shape == kT2Flat) return t2_launch<kT2Conv, NK, 2, kT2Flat>(a, st);
+    switch (t.nw) {
+        case 4: return t2_launch<kT2Conv, NK, 4, kT2Row>(a, st);
+        case 2: return t2_launch<kT2Conv, NK, 2, kT2Row>(a, st);
+        default: return t2_launch<kT2Conv, NK, 1, kT2Row>(a, st);
+    }
 }
 
 }  // namespace hb

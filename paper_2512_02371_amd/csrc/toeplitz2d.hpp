@@ -56,9 +56,9 @@ typedef half8 half8_a8 __attribute__((aligned(8)));
 
 constexpr int kT2MinWidth = 8;                // of an image
 
-template <int MODE, int NK, int NW, bool SHORT>
-__global__ void __launch_bounds__((T2Geom<MODE, NK, NW, SHORT>::kThreads), (T2Geom<MODE, NK, NW, SHORT>::kOccupancy)) toeplitz2d_mfma_kernel(T2Args p, int table_offset, int taps_offset) {
-    using G = T2Geom<MODE, NK, NW, SHORT>;
+template <int MODE, int NK, int NW, T2Shape SHAPE>
+__global__ void __launch_bounds__((T2Geom<MODE, NK, NW, SHAPE>::kThreads), (T2Geom<MODE, NK, NW, SHAPE>::kOccupancy)) toeplitz2d_mfma_kernel(T2Args p, int table_offset, int taps_offset) {
+    using G = T2Geom<MODE, NK, NW, SHAPE>;
     extern __shared__ __attribute__((aligned(16))) char s_dyn[];
     half_t* const s_px = reinterpret_cast<half_t*>(s_dyn);
     half_t* const s_tab = reinterpret_cast<half_t*>(s_dyn + table_offset);
@@ -238,17 +238,9 @@ __global__ void __launch_bounds__((T2Geom<MODE, NK, NW, SHORT>::kThreads), (T2Ge
     }
 }
 
-// The short tile where most of the tall ones would be empty and they are more than one round of workgroups; below, its
-// larger tiles only take longer (20 x 60000, 8 x 8 taps 9.6 us, tall 8.2).
-template <int MODE, int NK, int NW>
-static bool t2_short(const T2Args& a) {
-    using Tall = T2Geom<MODE, NK, NW, false>;
-    return a.Ho <= (MODE == kT2Conv ? 3 * Tall::kRows / 4 : Tall::kRows / 2) && ceil_div(a.Wo, Tall::kCols) > 3 * num_cu();
-}
-
-template <int MODE, int NK, int NW, bool SHORT>
+template <int MODE, int NK, int NW, T2Shape SHAPE>
 static hb_status t2_launch(T2Args& a, hipStream_t st) {
-    using G = T2Geom<MODE, NK, NW, SHORT>;
+    using G = T2Geom<MODE, NK, NW, SHAPE>;
     const int64_t tiles = (int64_t)ceil_div(a.Wo, G::kCols) * ceil_div(a.Ho, G::kRows);
     if (tiles > 0x3fffffff) return HB_ERR_UNSUPPORTED;
     // The resampling kernels' runs of 64 and 128 bytes, where they are not whole lines, leave through the L2, which puts
@@ -265,7 +257,7 @@ static hb_status t2_launch(T2Args& a, hipStream_t st) {
     const size_t shared = G::lds_bytes(a.kh), taps = ((size_t)a.kh * a.kw * 2 + 15) / 16 * 16;
     a.alias = t2_resident(shared + taps) < t2_resident(shared);
     const size_t lds = a.alias ? shared : shared + taps;
-    const auto kernel = toeplitz2d_mfma_kernel<MODE, NK, NW, SHORT>;
+    const auto kernel = toeplitz2d_mfma_kernel<MODE, NK, NW, SHAPE>;
     if (allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds) != HB_OK) return HB_ERR_HIP;
     hipLaunchKernelGGL(kernel, dim3((unsigned)a.ntiles), dim3(G::kThreads), lds, st, a, (int)G::image_bytes(a.kh), (int)shared);
     return launch_status();

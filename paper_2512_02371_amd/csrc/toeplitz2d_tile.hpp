@@ -2,23 +2,26 @@
 // LDS.  Host arithmetic only, also for tests that run without a GPU.
 #pragma once
 #include <stddef.h>
+#include <stdint.h>
 
 #include "hb.h"
 
 namespace hb {
 
 enum T2Mode { kT2Conv, kT2Down, kT2Up };
+enum T2Shape { kT2Row, kT2Flat };             // of a workgroup's waves, see T2Geom
+struct T2Tile { T2Shape shape; int nw; };     // of a call; nw: tiles of 16 columns per wave
 
 constexpr size_t kT2LdsOfCu = 160 << 10, kT2LdsGrain = 1280;          // of a compute unit; LDS is given out in these pieces
 
 // workgroups of so much LDS that a compute unit holds
 inline size_t t2_resident(size_t lds) { return kT2LdsOfCu / ((lds + kT2LdsGrain - 1) / kT2LdsGrain * kT2LdsGrain); }
 
-// SHORT (outputs of few rows): the N index of a product is 8 row pairs x 4 runs of tiles beside each other instead
+// kT2Row: the waves beside each other.  kT2Flat (outputs of few rows): the N index of a product is 8 row pairs x 4 runs of tiles beside each other instead
 // of 32 row pairs.  16 x 200000, 3 x 3 / 32 x 32 taps: 14.3 / 45 us with the tall tile, 10.2 / 17 with this one.
-template <int MODE, int NK, int NW, bool SHORT>
+template <int MODE, int NK, int NW, T2Shape SHAPE>
 struct T2Geom {
-    static constexpr int kPairs = SHORT ? 8 : 32, kBeside = 32 / kPairs;  // row pairs, runs of tiles in N
+    static constexpr int kPairs = SHAPE == kT2Flat ? 8 : 32, kBeside = 32 / kPairs;  // row pairs, runs of tiles in N
     static constexpr int kWx = 4;                                         // waves of a workgroup, beside each other
     static constexpr int kThreads = 64 * kWx;
     static constexpr int kOccupancy = MODE == kT2Conv ? (NW > 2 ? 2 : 3) : MODE == kT2Down ? 2 : NK > 1 ? 3 : 4;   // waves per SIMD
@@ -53,5 +56,29 @@ struct T2Geom {
     }
     static size_t lds_bytes(int kh) { return image_bytes(kh) + (size_t)tab_rows(kh) * kTabRow * 2; }
 };
+
+inline int64_t t2_ceil(int a, int b) { return a / b + (a % b != 0); }
+
+// The short tile where most of the tall ones would be empty and they are more than one round of workgroups; below, its
+// larger tiles only take longer (20 x 60000, 8 x 8 taps 9.6 us, tall 8.2).
+inline bool t2_flat(T2Mode mode, int rows, int cols, int Ho, int Wo, int units) {
+    return Ho <= (mode == kT2Conv ? 3 * rows / 4 : rows / 2) && t2_ceil(Wo, cols) > 3 * units;
+}
+
+// hb_conv2d.  `pieces`: output rows start inside 64-byte pieces of a line.
+//  - 64 x 128 is the general tile (4096 x 4096, 3 x 3 / 11 x 11 / 20 x 20 / 32 x 32 taps 19.3 / 21.3 / 34.8 / 49.5 us, with the widest
+//    21.5 / 25.9 / 37.9 / 54).
+//  - 64 x 256 writes fewer partial pieces, which counts where stores take longer than products (4000 x 4001, 3 x 3 / 16 x 16 /
+//    28 x 5 / 32 x 32: 30.2 / 37.5 / 42.9 / 55.7 us, general 38.9 / 43.2 / 52.6 / 53.0) and its columns are used (32513 x 258, 24 x 24: 44,
+//    general 34; 64527 x 65, 3 x 3: 24, general 12).  A compute unit holds two of its workgroups and three of the general
+//    ones, so it also takes more than one round of work, and nearly two for the tallest kernels (1500 x 5985, 576 tiles, 3 x 3 /
+//    16 x 16 / 28 x 5: 21.1 / 26.1 / 31.9, general 22.9 / 27.8 / 29.2; 3000 x 2977, 564 tiles, 3 x 3: 23.6, general 22.3).
+//  - 64 x 64 where the others leave compute units idle (300 x 200, 32 x 32: 9.8, general 12.0; 1500 x 1500, 9 x 9: 7.7, 8.3).
+inline T2Tile t2_conv_tile(int Ho, int Wo, int kh, bool pieces, int units) {
+    if (t2_flat(kT2Conv, 64, 128, Ho, Wo, units)) return {kT2Flat, 2};
+    const int64_t wide = t2_ceil(Ho, 64) * t2_ceil(Wo, 256);
+    if (pieces && Wo > 768 && kh <= (wide >= 15 * units / 4 ? 29 : wide >= 9 * units / 4 ? 18 : 0)) return {kT2Row, 4};
+    return {kT2Row, t2_ceil(Ho, 64) * t2_ceil(Wo, 128) >= units * 5 / 4 ? 2 : 1};
+}
 
 }  // namespace hb

@@ -8,22 +8,30 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PROGRAM = r"""
 #include <stdio.h>
+#include <stdlib.h>
 #include "toeplitz2d_tile.hpp"
 using namespace hb;
-template <int MODE, int NK, int NW, bool SHORT>
+template <int MODE, int NK, int NW, T2Shape SHAPE>
 void tile(const char* shape) {
-    using G = T2Geom<MODE, NK, NW, SHORT>;
+    using G = T2Geom<MODE, NK, NW, SHAPE>;
     for (int kh = 1 + (MODE == kT2Up); kh <= HB_MAX_TAPS_CONV2D; kh += 1 + (MODE == kT2Up))
         printf("%d %d %d %s %d %d %d %d %d %d %d %d %d %d %d %d %d %d %zu %zu %zu\n", MODE, NK, NW, shape, G::kCols, G::kRows, G::kPairs, G::kStride,
                G::kPitch, G::kCopies, G::kCopy, G::kShift, G::kPad, G::kZeroRows, kh, G::steps(kh), G::srows(kh), G::tab_rows(kh),
                G::image_bytes(kh), G::lds_bytes(kh), t2_resident(G::lds_bytes(kh)));
 }
-int main() {
-#define CONV(nk) tile<kT2Conv, nk, 1, false>("row"); tile<kT2Conv, nk, 2, false>("row"); tile<kT2Conv, nk, 4, false>("row"); tile<kT2Conv, nk, 2, true>("short");
+int main(int argc, char** argv) {
+    if (argc > 1) {                                       // the tile of hb_conv2d for each Ho Wo kh pieces
+        for (int i = 1; i + 3 < argc; i += 4) {
+            const T2Tile t = t2_conv_tile(atoi(argv[i]), atoi(argv[i + 1]), atoi(argv[i + 2]), atoi(argv[i + 3]), 256);
+            printf("%s %d\n", t.shape == kT2Flat ? "flat" : "row", t.nw);
+        }
+        return 0;
+    }
+#define CONV(nk) tile<kT2Conv, nk, 1, kT2Row>("row"); tile<kT2Conv, nk, 2, kT2Row>("row"); tile<kT2Conv, nk, 4, kT2Row>("row"); tile<kT2Conv, nk, 2, kT2Flat>("flat");
     CONV(1) CONV(2) CONV(3)
-#define DOWN(nk) tile<kT2Down, nk, 1, false>("row"); tile<kT2Down, nk, 1, true>("short");
+#define DOWN(nk) tile<kT2Down, nk, 1, kT2Row>("row"); tile<kT2Down, nk, 1, kT2Flat>("flat");
     DOWN(2) DOWN(3) DOWN(4)
-#define UP(nk) tile<kT2Up, nk, 2, false>("row"); tile<kT2Up, nk, 2, true>("short");
+#define UP(nk) tile<kT2Up, nk, 2, kT2Row>("row"); tile<kT2Up, nk, 2, kT2Flat>("flat");
     UP(1) UP(2)
 }
 """
@@ -32,13 +40,18 @@ CONV, DOWN, UP = 0, 1, 2
 
 
 @pytest.fixture(scope="module")
-def tiles(tmp_path_factory):
+def program(tmp_path_factory):
     d = tmp_path_factory.mktemp("tiles")
     src, exe = d / "tiles.cpp", d / "tiles"
     src.write_text(PROGRAM)
     subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2512_02371_amd", "csrc"),
                     str(src), "-o", str(exe)], check=True)
-    lines = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.splitlines()
+    return str(exe)
+
+
+@pytest.fixture(scope="module")
+def tiles(program):
+    lines = subprocess.run([program], check=True, capture_output=True, text=True).stdout.splitlines()
     return [{f: v if f == "shape" else int(v) for f, v in zip(FIELDS, line.split())} for line in lines]
 
 
@@ -71,3 +84,18 @@ def test_general_conv2d_tile_has_three_workgroups_per_compute_unit(tiles):
     kernel rows on)."""
     general = [t for t in tiles if (t["mode"], t["nw"], t["shape"]) == (CONV, 2, "row")]
     assert len(general) == 96 and all(t["resident"] >= 3 for t in general), [(t["nk"], t["kh"], t["lds"]) for t in general if t["resident"] < 3]
+
+
+def conv_tiles(program, calls):
+    out = subprocess.run([program] + [str(int(v)) for c in calls for v in c], check=True, capture_output=True, text=True).stdout.split()
+    return list(zip(out[::2], map(int, out[1::2])))
+
+
+def test_widest_conv2d_tile_only_where_it_is_the_fastest(program):
+    """Not where a quarter of its 256 columns would be empty, nor for rows that start on 64-byte pieces, nor tall kernels."""
+    calls = [(ho, wo, kh, True) for wo in (65, 100, 128, 129, 258, 600) for ho in (30000, 200000, 1000000) for kh in (3, 32)]
+    calls += [(ho, wo, kh, False) for ho, wo in ((4096, 4096), (3464, 3456), (2880, 3056), (8192, 8192)) for kh in (3, 24, 28, 32)]
+    calls += [(4095, 4095, 30, True), (3464, 3457, 19, True), (1500, 5985, 19, True), (3000, 2977, 3, True)]
+    assert all(t != ("row", 4) for t in conv_tiles(program, calls))
+    calls = [(4095, 4095, 29, True), (8000, 1985, 3, True), (3464, 3457, 18, True), (1500, 5985, 1, True)]
+    assert conv_tiles(program, calls) == [("row", 4)] * 4
