@@ -67,7 +67,7 @@ __global__ void __launch_bounds__((T2Geom<MODE, NK, NW, SHAPE>::kThreads), (T2Ge
     uint16_t* const s_taps = reinterpret_cast<uint16_t*>(s_dyn + (p.alias ? 0 : taps_offset));
 
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c = lane & 31, h = lane >> 5;
+    const int c = lane & 31, h = lane >> 5, wx = wv % G::kWx, wy = wv / G::kWx;
     // Every XCD takes one contiguous run of tiles, one below the other: neighbours share their halo pixels in one L2.
     // hb_up2, bound by its stores, sweeps along the rows instead, four tiles to an XCD (4096 x 4096, 16 x 16 taps 16.4 -> 14.6 us).
     const int tile = MODE == kT2Up ? xcd_blocked(blockIdx.x, p.ntiles, 4) : xcd_contiguous(blockIdx.x, p.ntiles);
@@ -150,14 +150,14 @@ __global__ void __launch_bounds__((T2Geom<MODE, NK, NW, SHAPE>::kThreads), (T2Ge
     const int row0 = MODE == kT2Conv ? G::kZeroRows - mdy : MODE == kT2Down ? G::kZeroRows - 2 * mdy : 2 * mdy + (mx & 1);
     const half_t* const tab = s_tab + row0 * G::kTabRow + t_copy * G::kCopy + t0 - G::kShift * t_copy;
     const int pair = c % G::kPairs, beside = c / G::kPairs;
-    const half_t* const px = s_px + pair * G::kPitch + G::kTileStep * NW * (G::kBeside * wv + beside) + 8 * h;
+    const half_t* const px = s_px + (G::kPairs * wy + pair) * G::kPitch + G::kTileStep * NW * (G::kBeside * wx + beside) + 8 * h;
     // stores: lane (n = c, h) holds columns 16 w + 8 (q & 1) + 4h + r of rows 2n + q / 2; a patch turns the 32 rows of
     // one dy into runs of 64 NW bytes
     float* const patch = reinterpret_cast<float*>(s_dyn) + wv * G::kPatch;
     constexpr int kPatchPitch = 16 * NW + 4, kLanes = 4 * NW, kPer = 64 / kLanes;
     const int rr = lane / kLanes, xx = 4 * (lane - rr * kLanes);
 
-    const int xw = G::kCols * ct + 16 * NW * G::kBeside * wv, yw = G::kRows * rt;    // the wave's outputs
+    const int xw = G::kCols * ct + 16 * NW * G::kBeside * wx, yw = G::kRows * rt + 2 * G::kPairs * wy;    // the wave's outputs
     const bool active = xw < p.Wo && yw < p.Ho;       // uniform
     floatx16 total[NW];
 #pragma unroll

@@ -9,7 +9,7 @@
 namespace hb {
 
 enum T2Mode { kT2Conv, kT2Down, kT2Up };
-enum T2Shape { kT2Row, kT2Flat };             // of a workgroup's waves, see T2Geom
+enum T2Shape { kT2Row, kT2Block, kT2Flat };   // of a workgroup's waves, see T2Geom
 struct T2Tile { T2Shape shape; int nw; };     // of a call; nw: tiles of 16 columns per wave
 
 constexpr size_t kT2LdsOfCu = 160 << 10, kT2LdsGrain = 1280;          // of a compute unit; LDS is given out in these pieces
@@ -17,17 +17,17 @@ constexpr size_t kT2LdsOfCu = 160 << 10, kT2LdsGrain = 1280;          // of a co
 // workgroups of so much LDS that a compute unit holds
 inline size_t t2_resident(size_t lds) { return kT2LdsOfCu / ((lds + kT2LdsGrain - 1) / kT2LdsGrain * kT2LdsGrain); }
 
-// kT2Row: the waves beside each other.  kT2Flat (outputs of few rows): the N index of a product is 8 row pairs x 4 runs of tiles beside each other instead
+// kT2Row: the waves beside each other.  kT2Block (narrow outputs): two by two.  kT2Flat (outputs of few rows): the N index of a product is 8 row pairs x 4 runs of tiles beside each other instead
 // of 32 row pairs.  16 x 200000, 3 x 3 / 32 x 32 taps: 14.3 / 45 us with the tall tile, 10.2 / 17 with this one.
 template <int MODE, int NK, int NW, T2Shape SHAPE>
 struct T2Geom {
     static constexpr int kPairs = SHAPE == kT2Flat ? 8 : 32, kBeside = 32 / kPairs;  // row pairs, runs of tiles in N
-    static constexpr int kWx = 4;                                         // waves of a workgroup, beside each other
-    static constexpr int kThreads = 64 * kWx;
+    static constexpr int kWx = SHAPE == kT2Block ? 2 : 4, kWy = SHAPE == kT2Block ? 2 : 1;   // waves of a workgroup, across and down
+    static constexpr int kThreads = 64 * kWx * kWy;
     static constexpr int kOccupancy = MODE == kT2Conv ? (NW > 2 ? 2 : 3) : MODE == kT2Down ? 2 : NK > 1 ? 3 : 4;   // waves per SIMD
     static constexpr int kStride = MODE == kT2Conv ? 2 : MODE == kT2Down ? 4 : 1;   // input rows per n
     static constexpr int kTileStep = MODE == kT2Conv ? 16 : MODE == kT2Down ? 32 : 8;
-    static constexpr int kCols = 16 * NW * kBeside * kWx, kRows = 2 * kPairs;         // output tile
+    static constexpr int kCols = 16 * NW * kBeside * kWx, kRows = 2 * kPairs * kWy;   // output tile
     static constexpr int kChunks = (kTileStep * (NW * kBeside * kWx - 1) + 16 * NK) / 8;      // of 8 staged pixels per row
     static constexpr int kPitch = 8 * (kChunks | 1);
     static constexpr int kPatch = 32 * (16 * NW + 4);                     // floats per wave, see the stores
@@ -35,7 +35,7 @@ struct T2Geom {
     static constexpr int kUnit = MODE == kT2Up ? 8 : 16;
     static constexpr int kFrags = (kTileStep * (NW - 1) + 16 * (NK - 1)) / kUnit + 1;
     static constexpr int kMaxSteps = MODE == kT2Conv ? HB_MAX_TAPS_CONV2D + 1 : MODE == kT2Down ? HB_MAX_TAPS_CONV2D + 2 : HB_MAX_TAPS_CONV2D / 2;
-    static constexpr int kPieces = ((kStride * (kPairs - 1) + kMaxSteps) * kChunks + kThreads - 1) / kThreads;   // staged per thread
+    static constexpr int kPieces = ((kStride * (kPairs * kWy - 1) + kMaxSteps) * kChunks + kThreads - 1) / kThreads;   // staged per thread
     // Weight table.  A lane's eight weights start at position 8h - (its column's shift) + kPad, 1 (conv, up) or 2 (down)
     // apart, so a row is kept in kCopies copies of kCopy taps, each shifted by kShift, and every run starts on 8 bytes
     // (down: 16).  Pitches: the lanes served together fall into different banks (conv: blocks of 8 dwords at 0, 40, 16, 56 and, for
@@ -47,11 +47,11 @@ struct T2Geom {
     // three from 31 kernel rows on (2449 x 2432, 32 x 32 taps 24.8 -> 21.5 us).
     static constexpr int kZeroRows = MODE == kT2Conv ? 1 : 2;
     static int steps(int kh) { return MODE == kT2Conv ? kh + 1 : MODE == kT2Down ? kh + 2 : kh / 2; }
-    static int rows(int kh) { return kStride * (kPairs - 1) + steps(kh); }
+    static int rows(int kh) { return kStride * (kPairs * kWy - 1) + steps(kh); }
     static int srows(int kh) { return (rows(kh) + kStride - 1) / kStride; }
     static int tab_rows(int kh) { return MODE == kT2Up ? 2 * kh : kh + 2 * kZeroRows; }
     static size_t image_bytes(int kh) {                                   // up to the last row that is staged, in the last section
-        const size_t img = ((size_t)(kStride - 1) * srows(kh) + (rows(kh) - kStride) / kStride + 1) * kPitch * 2, patch = (size_t)kWx * kPatch * 4;
+        const size_t img = ((size_t)(kStride - 1) * srows(kh) + (rows(kh) - kStride) / kStride + 1) * kPitch * 2, patch = (size_t)kWx * kWy * kPatch * 4;
         return img > patch ? img : patch;
     }
     static size_t lds_bytes(int kh) { return image_bytes(kh) + (size_t)tab_rows(kh) * kTabRow * 2; }
@@ -66,19 +66,26 @@ inline bool t2_flat(T2Mode mode, int rows, int cols, int Ho, int Wo, int units) 
 }
 
 // hb_conv2d.  `pieces`: output rows start inside 64-byte pieces of a line.
-//  - 64 x 128 is the general tile (4096 x 4096, 3 x 3 / 11 x 11 / 20 x 20 / 32 x 32 taps 19.3 / 21.3 / 34.8 / 49.5 us, with the widest
-//    21.5 / 25.9 / 37.9 / 54).
+//  - 64 x 128 is the general tile (4096 x 4096, 3 x 3 / 11 x 11 / 20 x 20 / 32 x 32 taps 19.3 / 21.3 / 34.8 / 52.9 us, with the widest
+//    21.5 / 25.9 / 37.9 / 53.8; 4000 x 4000, 32 x 32 51.0, 55.8).
 //  - 64 x 256 writes fewer partial pieces, which counts where stores take longer than products (4000 x 4001, 3 x 3 / 16 x 16 /
 //    28 x 5 / 32 x 32: 30.2 / 37.5 / 42.9 / 55.7 us, general 38.9 / 43.2 / 52.6 / 53.0) and its columns are used (32513 x 258, 24 x 24: 44,
 //    general 34; 64527 x 65, 3 x 3: 24, general 12).  A compute unit holds two of its workgroups and three of the general
 //    ones, so it also takes more than one round of work, and nearly two for the tallest kernels (1500 x 5985, 576 tiles, 3 x 3 /
 //    16 x 16 / 28 x 5: 21.1 / 26.1 / 31.9, general 22.9 / 27.8 / 29.2; 3000 x 2977, 564 tiles, 3 x 3: 23.6, general 22.3).
 //  - 64 x 64 where the others leave compute units idle (300 x 200, 32 x 32: 9.8, general 12.0; 1500 x 1500, 9 x 9: 7.7, 8.3).
+//    Also where it has fewer empty columns (87381 x 48, 3 x 3 / 32 x 32: 8.9 / 23.2, general 15.1 / 32.4; 52428 x 160, 9 x 9: 16.4, 18.4),
+//    unless the partial pieces of a low kernel cost more (32513 x 129, 3 x 3: 15.6, general 13.4).
+//  - 32 x 128, two by two waves, for outputs of at most 32 columns, which leave the others' waves idle (524288 x 8, 3 x 3 / 32 x 32
+//    taps 18.3 / 54 us, 64 x 64 29 / 85, general 47 / 120; 131072 x 32: 8.1 / 20.1, 10.5 / 28, 13.8 / 34), and enough rows to fill the
+//    chip twice (9362 x 28, 9 x 9: 6.0, 64 x 64 5.8).
 inline T2Tile t2_conv_tile(int Ho, int Wo, int kh, bool pieces, int units) {
+    if (Wo <= 32 && t2_ceil(Ho, 64) > units) return {kT2Block, 1};
     if (t2_flat(kT2Conv, 64, 128, Ho, Wo, units)) return {kT2Flat, 2};
     const int64_t wide = t2_ceil(Ho, 64) * t2_ceil(Wo, 256);
     if (pieces && Wo > 768 && kh <= (wide >= 15 * units / 4 ? 29 : wide >= 9 * units / 4 ? 18 : 0)) return {kT2Row, 4};
-    return {kT2Row, t2_ceil(Ho, 64) * t2_ceil(Wo, 128) >= units * 5 / 4 ? 2 : 1};
+    const bool half_used = Wo <= 64 || (Wo > 128 && Wo <= 192 && (!pieces || kh >= 16));
+    return {kT2Row, !half_used && t2_ceil(Ho, 64) * t2_ceil(Wo, 128) >= units * 5 / 4 ? 2 : 1};
 }
 
 }  // namespace hb

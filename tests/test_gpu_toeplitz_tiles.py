@@ -13,6 +13,11 @@ CASES = [
     ("conv2d", 64, 64, 3, 2),            # one narrow tile (64 x 64), whole ...
     ("conv2d", 65, 193, 32, 31),         # ... and one past it
     ("conv2d", 63, 127, 31, 1),
+    ("conv2d", 16512, 32, 32, 32),       # the tile for narrow images (32 x 128), whole ...
+    ("conv2d", 16385, 31, 17, 31),       # ... and ragged, with one wave of four at work in the last
+    ("conv2d", 20500, 9, 3, 2),
+    ("conv2d", 20500, 33, 16, 2),        # many tiles of 64 x 64: narrow images of more columns ...
+    ("conv2d", 10300, 160, 3, 17),       # ... and ones that would leave half of a 128-wide tile empty
     ("conv2d", 1280, 2048, 2, 17),       # the middle tile (64 x 128), its first size, whole tiles
     ("conv2d", 1281, 2051, 3, 3),        # ... and ragged
     ("conv2d", 49, 130817, 3, 2),        # the wide tile (64 x 256): rows that start inside lines ...

@@ -23,11 +23,11 @@ int main(int argc, char** argv) {
     if (argc > 1) {                                       // the tile of hb_conv2d for each Ho Wo kh pieces
         for (int i = 1; i + 3 < argc; i += 4) {
             const T2Tile t = t2_conv_tile(atoi(argv[i]), atoi(argv[i + 1]), atoi(argv[i + 2]), atoi(argv[i + 3]), 256);
-            printf("%s %d\n", t.shape == kT2Flat ? "flat" : "row", t.nw);
+            printf("%s %d\n", t.shape == kT2Flat ? "flat" : t.shape == kT2Block ? "block" : "row", t.nw);
         }
         return 0;
     }
-#define CONV(nk) tile<kT2Conv, nk, 1, kT2Row>("row"); tile<kT2Conv, nk, 2, kT2Row>("row"); tile<kT2Conv, nk, 4, kT2Row>("row"); tile<kT2Conv, nk, 2, kT2Flat>("flat");
+#define CONV(nk) tile<kT2Conv, nk, 1, kT2Row>("row"); tile<kT2Conv, nk, 2, kT2Row>("row"); tile<kT2Conv, nk, 4, kT2Row>("row"); tile<kT2Conv, nk, 2, kT2Flat>("flat"); tile<kT2Conv, nk, 1, kT2Block>("block");
     CONV(1) CONV(2) CONV(3)
 #define DOWN(nk) tile<kT2Down, nk, 1, kT2Row>("row"); tile<kT2Down, nk, 1, kT2Flat>("flat");
     DOWN(2) DOWN(3) DOWN(4)
@@ -58,7 +58,7 @@ def tiles(program):
 def test_rows_of_the_image_and_of_the_table(tiles):
     for t in tiles:
         # step s of row pair n reads staged row stride n + s, which lies in section (stride n + s) % stride
-        last = max((s % t["stride"]) * t["srows"] + t["pairs"] - 1 + s // t["stride"] for s in range(t["steps"]))
+        last = max((s % t["stride"]) * t["srows"] + t["rows"] // 2 - 1 + s // t["stride"] for s in range(t["steps"]))
         assert (last + 1) * t["pitch"] * 2 <= t["image"], t
         # of the weight table, step s reads row s + row0
         if t["mode"] == UP:
@@ -99,3 +99,10 @@ def test_widest_conv2d_tile_only_where_it_is_the_fastest(program):
     assert all(t != ("row", 4) for t in conv_tiles(program, calls))
     calls = [(4095, 4095, 29, True), (8000, 1985, 3, True), (3464, 3457, 18, True), (1500, 5985, 1, True)]
     assert conv_tiles(program, calls) == [("row", 4)] * 4
+
+
+def test_narrow_images_take_the_conv2d_tile_that_they_fill(program):
+    """None that is twice as wide as the image, whatever its height."""
+    calls = [(ho, wo, kh, pieces) for wo in (1, 8, 16, 31, 32, 33, 48, 64) for ho in (1, 16384, 16385, 1000000) for kh in (1, 16, 32) for pieces in (0, 1)]
+    for (ho, wo, _, _), tile in zip(calls, conv_tiles(program, calls)):
+        assert tile == (("block", 1) if wo <= 32 and ho > 256 * 64 else ("row", 1))
