@@ -59,10 +59,22 @@ struct T2Geom {
 
 inline int64_t t2_ceil(int a, int b) { return a / b + (a % b != 0); }
 
-// The short tile where most of the tall ones would be empty and they are more than one round of workgroups; below, its
-// larger tiles only take longer (20 x 60000, 8 x 8 taps 9.6 us, tall 8.2).
-inline bool t2_flat(T2Mode mode, int rows, int cols, int Ho, int Wo, int units) {
-    return Ho <= (mode == kT2Conv ? 3 * rows / 4 : rows / 2) && t2_ceil(Wo, cols) > 3 * units;
+// The flat tile for outputs of few rows, where the tall ones' last 64 rows would be a quarter empty or more.
+//  - hb_down2: to 32 x 40000 / 48 x 70000 / 80 x 70000 with 16 x 16 taps 12.0 / 20.4 / 31.1 us, tall 15.4 / 23.0 / 37.9; to 48 x 32768 12.7, tall
+//    11.7; to 32 x 20000 with 3 x 18 8.5, tall 8.0.
+//  - hb_up2: to 66 x 131072 with 4 x 4 taps / 48 x 56000 with 32 x 32 8.5 / 9.1 us, tall 11.8 / 9.4; to 64 x 88000 with 32 x 32 tall is the faster
+//    by 20 %.  Up to 18 taps across also for 49 to 63 rows (60 x 76000, 10 x 10: 7.3, tall 7.9); 2 x 56000, 4 x 4 4.8, tall 4.4.
+//  - hb_conv2d: both have 8192 outputs, three tall or two flat workgroups fit a compute unit, and what a call takes follows the
+//    most that one compute unit gets, `tall` and `flat`.  Many taps: from 3 : 2 on (80 x 49400, 32 x 32, 4 : 2: 18.1 us, tall 26.4; 80 x
+//    70000, 5 : 3: 27.2, 31.5; 34 x 88000, 3 : 3: 27.0, 21.1); fewer: from 2 : 1 on, where the tall ones need three, or 5 : 3 (16 x
+//    98600, 16 x 16, 4 : 1: 10.5, 13.7; 66 x 70000, 16 x 16, 5 : 3: 15.7, 24.1); less than 8 rows of taps, or many rounds of both, as measured (48 x 200000, 3 x 3: 17.3, 20.4).
+inline bool t2_flat(T2Mode mode, int nk, int kh, int Ho, int Wo, int units) {
+    const bool partly = Ho <= 48 || (Ho > 64 && Ho <= 96);
+    if (mode == kT2Up) return (partly || (nk == 1 && Ho < 64)) && Wo > (nk == 1 && Ho <= 32 ? 256 : 192) * units;
+    if (mode == kT2Down) return (Ho <= 32 && nk < 4 ? Wo > 96 * units : Wo > 192 * units) && (Ho <= 32 || (nk < 4 && partly && Ho <= 80));
+    const int64_t tall = (t2_ceil(Ho, 64) * t2_ceil(Wo, 128) + units - 1) / units, flat = (t2_ceil(Ho, 16) * t2_ceil(Wo, 512) + units - 1) / units;
+    if (nk == 3 && kh >= 20 ? 2 * tall >= 3 * flat : kh >= 8 && tall >= 3 && (tall >= 2 * flat || (tall >= 5 && 3 * tall >= 5 * flat))) return Ho <= 96;
+    return (Ho <= 48 && Wo > 384 * units) || (Ho <= 96 && tall >= 7 && 4 * tall >= 5 * flat);
 }
 
 // hb_conv2d.  `pieces`: output rows start inside 64-byte pieces of a line.
@@ -79,9 +91,9 @@ inline bool t2_flat(T2Mode mode, int rows, int cols, int Ho, int Wo, int units) 
 //  - 32 x 128, two by two waves, for outputs of at most 32 columns, which leave the others' waves idle (524288 x 8, 3 x 3 / 32 x 32
 //    taps 18.3 / 54 us, 64 x 64 29 / 85, general 47 / 120; 131072 x 32: 8.1 / 20.1, 10.5 / 28, 13.8 / 34), and enough rows to fill the
 //    chip twice (9362 x 28, 9 x 9: 6.0, 64 x 64 5.8).
-inline T2Tile t2_conv_tile(int Ho, int Wo, int kh, bool pieces, int units) {
+inline T2Tile t2_conv_tile(int Ho, int Wo, int kh, int nk, bool pieces, int units) {
     if (Wo <= 32 && t2_ceil(Ho, 64) > units) return {kT2Block, 1};
-    if (t2_flat(kT2Conv, 64, 128, Ho, Wo, units)) return {kT2Flat, 2};
+    if (t2_flat(kT2Conv, nk, kh, Ho, Wo, units)) return {kT2Flat, 2};
     const int64_t wide = t2_ceil(Ho, 64) * t2_ceil(Wo, 256);
     if (pieces && Wo > 768 && kh <= (wide >= 15 * units / 4 ? 29 : wide >= 9 * units / 4 ? 18 : 0)) return {kT2Row, 4};
     const bool half_used = Wo <= 64 || (Wo > 128 && Wo <= 192 && (!pieces || kh >= 16));

@@ -9,6 +9,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PROGRAM = r"""
 #include <stdio.h>
 #include <stdlib.h>
+#include <string.h>
 #include "toeplitz2d_tile.hpp"
 using namespace hb;
 template <int MODE, int NK, int NW, T2Shape SHAPE>
@@ -20,9 +21,13 @@ void tile(const char* shape) {
                G::image_bytes(kh), G::lds_bytes(kh), t2_resident(G::lds_bytes(kh)));
 }
 int main(int argc, char** argv) {
-    if (argc > 1) {                                       // the tile of hb_conv2d for each Ho Wo kh pieces
-        for (int i = 1; i + 3 < argc; i += 4) {
-            const T2Tile t = t2_conv_tile(atoi(argv[i]), atoi(argv[i + 1]), atoi(argv[i + 2]), atoi(argv[i + 3]), 256);
+    if (argc > 1 && !strcmp(argv[1], "flat")) {           // whether hb_down2 or hb_up2 takes the flat tile for each mode nk Ho Wo
+        for (int i = 2; i + 3 < argc; i += 4) printf("%d\n", t2_flat((T2Mode)atoi(argv[i]), atoi(argv[i + 1]), 16, atoi(argv[i + 2]), atoi(argv[i + 3]), 256));
+        return 0;
+    }
+    if (argc > 1) {                                       // the tile of hb_conv2d for each Ho Wo kh kw pieces
+        for (int i = 1; i + 4 < argc; i += 5) {
+            const T2Tile t = t2_conv_tile(atoi(argv[i]), atoi(argv[i + 1]), atoi(argv[i + 2]), (atoi(argv[i + 3]) + 30) / 16, atoi(argv[i + 4]), 256);
             printf("%s %d\n", t.shape == kT2Flat ? "flat" : t.shape == kT2Block ? "block" : "row", t.nw);
         }
         return 0;
@@ -93,16 +98,27 @@ def conv_tiles(program, calls):
 
 def test_widest_conv2d_tile_only_where_it_is_the_fastest(program):
     """Not where a quarter of its 256 columns would be empty, nor for rows that start on 64-byte pieces, nor tall kernels."""
-    calls = [(ho, wo, kh, True) for wo in (65, 100, 128, 129, 258, 600) for ho in (30000, 200000, 1000000) for kh in (3, 32)]
-    calls += [(ho, wo, kh, False) for ho, wo in ((4096, 4096), (3464, 3456), (2880, 3056), (8192, 8192)) for kh in (3, 24, 28, 32)]
-    calls += [(4095, 4095, 30, True), (3464, 3457, 19, True), (1500, 5985, 19, True), (3000, 2977, 3, True)]
+    calls = [(ho, wo, k, k, True) for wo in (65, 100, 128, 129, 258, 600) for ho in (30000, 200000, 1000000) for k in (3, 32)]
+    calls += [(ho, wo, k, k, False) for ho, wo in ((4096, 4096), (3464, 3456), (2880, 3056), (8192, 8192)) for k in (3, 24, 28, 32)]
+    calls += [(4095, 4095, 30, 30, True), (3464, 3457, 19, 19, True), (1500, 5985, 19, 19, True), (3000, 2977, 3, 3, True)]
     assert all(t != ("row", 4) for t in conv_tiles(program, calls))
-    calls = [(4095, 4095, 29, True), (8000, 1985, 3, True), (3464, 3457, 18, True), (1500, 5985, 1, True)]
+    calls = [(4095, 4095, 29, 29, True), (8000, 1985, 3, 3, True), (3464, 3457, 18, 18, True), (1500, 5985, 1, 1, True)]
     assert conv_tiles(program, calls) == [("row", 4)] * 4
 
 
 def test_narrow_images_take_the_conv2d_tile_that_they_fill(program):
     """None that is twice as wide as the image, whatever its height."""
-    calls = [(ho, wo, kh, pieces) for wo in (1, 8, 16, 31, 32, 33, 48, 64) for ho in (1, 16384, 16385, 1000000) for kh in (1, 16, 32) for pieces in (0, 1)]
-    for (ho, wo, _, _), tile in zip(calls, conv_tiles(program, calls)):
+    calls = [(ho, wo, k, k, pieces) for wo in (1, 8, 16, 31, 32, 33, 48, 64) for ho in (1, 16384, 16385, 1000000) for k in (1, 16, 32) for pieces in (0, 1)]
+    for (ho, wo, _, _, _), tile in zip(calls, conv_tiles(program, calls)):
         assert tile == (("block", 1) if wo <= 32 and ho > 256 * 64 else ("row", 1))
+
+
+def test_outputs_of_few_rows_take_the_flat_tile(program):
+    flat = [(16, 80000, 32, 32, False), (48, 80000, 32, 32, False), (96, 40000, 32, 32, False), (80, 70000, 32, 32, False), (48, 98305, 3, 3, True)]
+    tall = [(34, 88000, 32, 32, False), (16, 32000, 32, 32, False), (64, 80000, 32, 32, False), (97, 300000, 32, 32, False), (48, 98304, 3, 3, False)]
+    assert [shape for shape, _ in conv_tiles(program, flat + tall)] == ["flat"] * 5 + ["row"] * 5
+    # hb_down2 and hb_up2: mode, chunks of the window, Ho, Wo
+    calls = [(DOWN, 2, 32, 24577), (DOWN, 3, 32, 24577), (DOWN, 3, 48, 49153), (DOWN, 3, 80, 49153), (UP, 2, 48, 49153), (UP, 2, 96, 49153), (UP, 1, 63, 49153), (UP, 1, 32, 65537), (UP, 2, 1, 49153),
+             (DOWN, 3, 33, 24577), (DOWN, 3, 49, 300000), (DOWN, 3, 81, 300000), (DOWN, 3, 32, 24576), (UP, 2, 63, 300000), (UP, 1, 64, 300000), (UP, 1, 97, 300000), (UP, 1, 32, 65536)]
+    out = subprocess.run([program, "flat"] + [str(v) for c in calls for v in c], check=True, capture_output=True, text=True).stdout.split()
+    assert out == ["1"] * 9 + ["0"] * 8
