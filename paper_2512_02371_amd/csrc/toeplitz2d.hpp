@@ -169,7 +169,7 @@ __global__ void __launch_bounds__((T2Geom<MODE, NK, NW, SHAPE>::kThreads), (T2Ge
             const half_t* const prow = px + ((s % G::kStride) * p.srows + s / G::kStride) * G::kPitch;
 #pragma unroll
             for (int kk = 0; kk < NK; ++kk)
-                f.a[kk] = MODE == kT2Down ? *reinterpret_cast<const half8*>(trow + 16 * kk) : *reinterpret_cast<const half8_a8*>(trow + 16 * kk);
+                f.a[kk] = MODE == kT2Down && G::kCopies == 4 ? *reinterpret_cast<const half8*>(trow + 16 * kk) : *reinterpret_cast<const half8_a8*>(trow + 16 * kk);
 #pragma unroll
             for (int u = 0; u < G::kFrags; ++u) f.b[u] = *reinterpret_cast<const half8*>(prow + G::kUnit * u);
         };

@@ -9,7 +9,7 @@
 namespace hb {
 
 enum T2Mode { kT2Conv, kT2Down, kT2Up };
-enum T2Shape { kT2Row, kT2Block, kT2Flat };   // of a workgroup's waves, see T2Geom
+enum T2Shape { kT2Row, kT2Block, kT2Flat, kT2FlatPair };   // of a workgroup's waves, see T2Geom
 struct T2Tile { T2Shape shape; int nw; };     // of a call; nw: tiles of 16 columns per wave
 
 constexpr size_t kT2LdsOfCu = 160 << 10, kT2LdsGrain = 1280;          // of a compute unit; LDS is given out in these pieces
@@ -19,10 +19,11 @@ inline size_t t2_resident(size_t lds) { return kT2LdsOfCu / ((lds + kT2LdsGrain 
 
 // kT2Row: the waves beside each other.  kT2Block (narrow outputs): two by two.  kT2Flat (outputs of few rows): the N index of a product is 8 row pairs x 4 runs of tiles beside each other instead
 // of 32 row pairs.  16 x 200000, 3 x 3 / 32 x 32 taps: 14.3 / 45 us with the tall tile, 10.2 / 17 with this one.
+// kT2FlatPair: two waves of that kind, where the LDS of four leaves a compute unit a single workgroup.
 template <int MODE, int NK, int NW, T2Shape SHAPE>
 struct T2Geom {
-    static constexpr int kPairs = SHAPE == kT2Flat ? 8 : 32, kBeside = 32 / kPairs;  // row pairs, runs of tiles in N
-    static constexpr int kWx = SHAPE == kT2Block ? 2 : 4, kWy = SHAPE == kT2Block ? 2 : 1;   // waves of a workgroup, across and down
+    static constexpr int kPairs = SHAPE == kT2Flat || SHAPE == kT2FlatPair ? 8 : 32, kBeside = 32 / kPairs;  // row pairs, runs of tiles in N
+    static constexpr int kWx = SHAPE == kT2Block || SHAPE == kT2FlatPair ? 2 : 4, kWy = SHAPE == kT2Block ? 2 : 1;   // waves of a workgroup, across and down
     static constexpr int kThreads = 64 * kWx * kWy;
     static constexpr int kOccupancy = MODE == kT2Conv ? (NW > 2 ? 2 : 3) : MODE == kT2Down ? 2 : NK > 1 ? 3 : 4;   // waves per SIMD
     static constexpr int kStride = MODE == kT2Conv ? 2 : MODE == kT2Down ? 4 : 1;   // input rows per n
@@ -40,8 +41,10 @@ struct T2Geom {
     // apart, so a row is kept in kCopies copies of kCopy taps, each shifted by kShift, and every run starts on 8 bytes
     // (down: 16).  Pitches: the lanes served together fall into different banks (conv: blocks of 8 dwords at 0, 40, 16, 56 and, for
     // the row above, 32 further; up: of 4 dwords at 0, 20, 40, 60 plus 16 and 32; down: of 16 at 0, 48, 32, 16).
-    static constexpr int kCopies = 4, kShift = MODE == kT2Down ? 2 : 1, kPad = MODE == kT2Conv ? 15 : MODE == kT2Down ? 30 : 7;
-    static constexpr int kCopy = MODE == kT2Conv ? 80 : MODE == kT2Down ? 96 : 40, kTabRow = kCopies * kCopy;
+    // Flat tiles of hb_down2 with many taps keep two copies on 8-byte starts: 14 KB less, so that a compute unit holds two
+    // workgroups (to 32 x 56000, 28 x 28 taps 21.0 -> 16.1 us).  The others are faster with four (by 2 % on average).
+    static constexpr int kCopies = MODE == kT2Down && (SHAPE == kT2FlatPair || (SHAPE == kT2Flat && NK == 4)) ? 2 : 4, kShift = MODE == kT2Down ? 2 : 1, kPad = MODE == kT2Conv ? 15 : MODE == kT2Down ? 30 : 7;
+    static constexpr int kCopy = MODE == kT2Conv ? 80 : MODE == kT2Down ? 96 : 40, kTabRow = kCopies == 2 ? 224 : kCopies * kCopy;
     // Zero rows of the table, above and below the taps: a step reads row s - dy or s - 2 dy.  With two for hb_conv2d as well,
     // and the image's last section as long as the others, a compute unit held two workgroups of the 64 x 128 tile instead of
     // three from 31 kernel rows on (2449 x 2432, 32 x 32 taps 24.8 -> 21.5 us).
@@ -59,6 +62,10 @@ struct T2Geom {
 
 inline int64_t t2_ceil(int a, int b) { return a / b + (a % b != 0); }
 
+// Which flat tile hb_down2 takes: above these kernel rows two workgroups of four waves no longer fit a compute unit (to 16 x
+// 41000, 32 x 32 taps 20.7 us, with two waves each 15.0).
+inline T2Shape t2_down_flat(int nk, int kh) { return kh > (nk == 4 ? 30 : 25) ? kT2FlatPair : kT2Flat; }
+
 // The flat tile for outputs of few rows, where the tall ones' last 64 rows would be a quarter empty or more.
 //  - hb_down2: to 32 x 40000 / 48 x 70000 / 80 x 70000 with 16 x 16 taps 12.0 / 20.4 / 31.1 us, tall 15.4 / 23.0 / 37.9; to 48 x 32768 12.7, tall
 //    11.7; to 32 x 20000 with 3 x 18 8.5, tall 8.0.
@@ -71,7 +78,7 @@ inline int64_t t2_ceil(int a, int b) { return a / b + (a % b != 0); }
 inline bool t2_flat(T2Mode mode, int nk, int kh, int Ho, int Wo, int units) {
     const bool partly = Ho <= 48 || (Ho > 64 && Ho <= 96);
     if (mode == kT2Up) return (partly || (nk == 1 && Ho < 64)) && Wo > (nk == 1 && Ho <= 32 ? 256 : 192) * units;
-    if (mode == kT2Down) return (Ho <= 32 && nk < 4 ? Wo > 96 * units : Wo > 192 * units) && (Ho <= 32 || (nk < 4 && partly && Ho <= 80));
+    if (mode == kT2Down) return Ho <= 32 ? Wo > (nk == 4 ? 128 : 96) * units : partly && Ho <= 80 && Wo > 192 * units && t2_down_flat(nk, kh) == kT2Flat;
     const int64_t tall = (t2_ceil(Ho, 64) * t2_ceil(Wo, 128) + units - 1) / units, flat = (t2_ceil(Ho, 16) * t2_ceil(Wo, 512) + units - 1) / units;
     if (nk == 3 && kh >= 20 ? 2 * tall >= 3 * flat : kh >= 8 && tall >= 3 && (tall >= 2 * flat || (tall >= 5 && 3 * tall >= 5 * flat))) return Ho <= 96;
     return (Ho <= 48 && Wo > 384 * units) || (Ho <= 96 && tall >= 7 && 4 * tall >= 5 * flat);

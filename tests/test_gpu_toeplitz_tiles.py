@@ -32,6 +32,11 @@ CASES = [
     ("down2", 64, 98306, 3, 4),          # the short tile and the last height that takes it
     ("down2", 65, 98306, 4, 3),
     ("down2", 31, 98816, 17, 18),
+    ("down2", 63, 66001, 30, 32),        # few rows, many taps: the flat tile of four waves ...
+    ("down2", 64, 65664, 31, 31),        # ... and of two, whole ...
+    ("down2", 33, 65601, 32, 19),
+    ("down2", 17, 49301, 26, 18),        # ... and with fewer taps across
+    ("down2", 95, 98433, 25, 5),
     ("up2", 32, 64, 16, 16),             # one tile of outputs (64 x 128), whole ...
     ("up2", 33, 65, 32, 32),             # ... and past it
     ("up2", 31, 63, 2, 18),

@@ -34,7 +34,7 @@ int main(int argc, char** argv) {
     }
 #define CONV(nk) tile<kT2Conv, nk, 1, kT2Row>("row"); tile<kT2Conv, nk, 2, kT2Row>("row"); tile<kT2Conv, nk, 4, kT2Row>("row"); tile<kT2Conv, nk, 2, kT2Flat>("flat"); tile<kT2Conv, nk, 1, kT2Block>("block");
     CONV(1) CONV(2) CONV(3)
-#define DOWN(nk) tile<kT2Down, nk, 1, kT2Row>("row"); tile<kT2Down, nk, 1, kT2Flat>("flat");
+#define DOWN(nk) tile<kT2Down, nk, 1, kT2Row>("row"); tile<kT2Down, nk, 1, kT2Flat>("flat"); tile<kT2Down, nk, 1, kT2FlatPair>("flat_pair");
     DOWN(2) DOWN(3) DOWN(4)
 #define UP(nk) tile<kT2Up, nk, 2, kT2Row>("row"); tile<kT2Up, nk, 2, kT2Flat>("flat");
     UP(1) UP(2)
@@ -122,3 +122,10 @@ def test_outputs_of_few_rows_take_the_flat_tile(program):
              (DOWN, 3, 33, 24577), (DOWN, 3, 49, 300000), (DOWN, 3, 81, 300000), (DOWN, 3, 32, 24576), (UP, 2, 63, 300000), (UP, 1, 64, 300000), (UP, 1, 97, 300000), (UP, 1, 32, 65536)]
     out = subprocess.run([program, "flat"] + [str(v) for c in calls for v in c], check=True, capture_output=True, text=True).stdout.split()
     assert out == ["1"] * 9 + ["0"] * 8
+
+
+def test_flat_tiles_fit_a_compute_unit_twice(tiles):
+    """Those of hb_down2 and hb_up2, four waves or, above 25 kernel rows (30 with more than 18 taps across) of hb_down2, two."""
+    for t in tiles:
+        if t["mode"] == UP and t["shape"] == "flat" or t["mode"] == DOWN and t["shape"] == ("flat_pair" if t["kh"] > (30 if t["nk"] == 4 else 25) else "flat"):
+            assert t["resident"] >= 2, t
