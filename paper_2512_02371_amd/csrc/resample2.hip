@@ -183,11 +183,13 @@ static hb_status rs2_prepare(T2Args& a, bool up, const hb_half* in, float* out, 
 
 template <int MODE, int NK, int NW>
 static hb_status rs2_launch(T2Args& a, hipStream_t st) {
-    if (t2_flat((T2Mode)MODE, NK, a.kh, a.Ho, a.Wo, num_cu())) {
-        if constexpr (MODE == kT2Down)
-            if (t2_down_flat(NK, a.kh) == kT2FlatPair) return t2_launch<MODE, NK, NW, kT2FlatPair>(a, st);
-        return t2_launch<MODE, NK, NW, kT2Flat>(a, st);
+    const T2Shape shape = t2_resample_tile((T2Mode)MODE, NK, a.kh, a.Ho, a.Wo, num_cu());
+    if constexpr (MODE == kT2Down) {
+        if (shape == kT2Stack) return t2_launch<MODE, NK, NW, kT2Stack>(a, st);
+        if (shape == kT2FlatPair) return t2_launch<MODE, NK, NW, kT2FlatPair>(a, st);
     }
+    if (shape == kT2Block) return t2_launch<MODE, NK, NW, kT2Block>(a, st);
+    if (shape == kT2Flat) return t2_launch<MODE, NK, NW, kT2Flat>(a, st);
     return t2_launch<MODE, NK, NW, kT2Row>(a, st);
 }
 

@@ -9,7 +9,7 @@
 namespace hb {
 
 enum T2Mode { kT2Conv, kT2Down, kT2Up };
-enum T2Shape { kT2Row, kT2Block, kT2Flat, kT2FlatPair };   // of a workgroup's waves, see T2Geom
+enum T2Shape { kT2Row, kT2Block, kT2Stack, kT2Flat, kT2FlatPair };   // of a workgroup's waves, see T2Geom
 struct T2Tile { T2Shape shape; int nw; };     // of a call; nw: tiles of 16 columns per wave
 
 constexpr size_t kT2LdsOfCu = 160 << 10, kT2LdsGrain = 1280;          // of a compute unit; LDS is given out in these pieces
@@ -17,13 +17,15 @@ constexpr size_t kT2LdsOfCu = 160 << 10, kT2LdsGrain = 1280;          // of a co
 // workgroups of so much LDS that a compute unit holds
 inline size_t t2_resident(size_t lds) { return kT2LdsOfCu / ((lds + kT2LdsGrain - 1) / kT2LdsGrain * kT2LdsGrain); }
 
-// kT2Row: the waves beside each other.  kT2Block (narrow outputs): two by two.  kT2Flat (outputs of few rows): the N index of a product is 8 row pairs x 4 runs of tiles beside each other instead
+// kT2Row: the waves beside each other.  kT2Block and kT2Stack (narrow outputs): two by two, or one
+// below the other.  kT2Flat (outputs of few rows): the N index of a product is 8 row pairs x 4 runs of tiles beside each other instead
 // of 32 row pairs.  16 x 200000, 3 x 3 / 32 x 32 taps: 14.3 / 45 us with the tall tile, 10.2 / 17 with this one.
 // kT2FlatPair: two waves of that kind, where the LDS of four leaves a compute unit a single workgroup.
 template <int MODE, int NK, int NW, T2Shape SHAPE>
 struct T2Geom {
     static constexpr int kPairs = SHAPE == kT2Flat || SHAPE == kT2FlatPair ? 8 : 32, kBeside = 32 / kPairs;  // row pairs, runs of tiles in N
-    static constexpr int kWx = SHAPE == kT2Block || SHAPE == kT2FlatPair ? 2 : 4, kWy = SHAPE == kT2Block ? 2 : 1;   // waves of a workgroup, across and down
+    static constexpr int kWx = SHAPE == kT2Stack ? 1 : SHAPE == kT2Block || SHAPE == kT2FlatPair ? 2 : 4;   // waves of a workgroup, across ...
+    static constexpr int kWy = SHAPE == kT2Stack ? 4 : SHAPE == kT2Block ? 2 : 1;                     // ... and down
     static constexpr int kThreads = 64 * kWx * kWy;
     static constexpr int kOccupancy = MODE == kT2Conv ? (NW > 2 ? 2 : 3) : MODE == kT2Down ? 2 : NK > 1 ? 3 : 4;   // waves per SIMD
     static constexpr int kStride = MODE == kT2Conv ? 2 : MODE == kT2Down ? 4 : 1;   // input rows per n
@@ -41,9 +43,9 @@ struct T2Geom {
     // apart, so a row is kept in kCopies copies of kCopy taps, each shifted by kShift, and every run starts on 8 bytes
     // (down: 16).  Pitches: the lanes served together fall into different banks (conv: blocks of 8 dwords at 0, 40, 16, 56 and, for
     // the row above, 32 further; up: of 4 dwords at 0, 20, 40, 60 plus 16 and 32; down: of 16 at 0, 48, 32, 16).
-    // Flat tiles of hb_down2 with many taps keep two copies on 8-byte starts: 14 KB less, so that a compute unit holds two
+    // Narrow and flat tiles of hb_down2 with many taps keep two copies on 8-byte starts: 14 KB less, so that a compute unit holds two
     // workgroups (to 32 x 56000, 28 x 28 taps 21.0 -> 16.1 us).  The others are faster with four (by 2 % on average).
-    static constexpr int kCopies = MODE == kT2Down && (SHAPE == kT2FlatPair || (SHAPE == kT2Flat && NK == 4)) ? 2 : 4, kShift = MODE == kT2Down ? 2 : 1, kPad = MODE == kT2Conv ? 15 : MODE == kT2Down ? 30 : 7;
+    static constexpr int kCopies = MODE == kT2Down && (SHAPE == kT2FlatPair || (SHAPE != kT2Row && NK == 4)) ? 2 : 4, kShift = MODE == kT2Down ? 2 : 1, kPad = MODE == kT2Conv ? 15 : MODE == kT2Down ? 30 : 7;
     static constexpr int kCopy = MODE == kT2Conv ? 80 : MODE == kT2Down ? 96 : 40, kTabRow = kCopies == 2 ? 224 : kCopies * kCopy;
     // Zero rows of the table, above and below the taps: a step reads row s - dy or s - 2 dy.  With two for hb_conv2d as well,
     // and the image's last section as long as the others, a compute unit held two workgroups of the 64 x 128 tile instead of
@@ -82,6 +84,21 @@ inline bool t2_flat(T2Mode mode, int nk, int kh, int Ho, int Wo, int units) {
     const int64_t tall = (t2_ceil(Ho, 64) * t2_ceil(Wo, 128) + units - 1) / units, flat = (t2_ceil(Ho, 16) * t2_ceil(Wo, 512) + units - 1) / units;
     if (nk == 3 && kh >= 20 ? 2 * tall >= 3 * flat : kh >= 8 && tall >= 3 && (tall >= 2 * flat || (tall >= 5 && 3 * tall >= 5 * flat))) return Ho <= 96;
     return (Ho <= 48 && Wo > 384 * units) || (Ho <= 96 && tall >= 7 && 4 * tall >= 5 * flat);
+}
+
+// hb_down2 and hb_up2.  The tile is 64 rows of 64 (hb_down2) or 128 columns, but for outputs of few rows, see above, and narrow
+// ones, of which it would leave half of the waves or more without work, where their rows still fill the chip:
+//  - hb_down2: 16 columns x 256 rows for at most 16 (131072 x 8 outputs, 16 x 16 taps 13.2 us, 64 x 64 34.2; 262144 x 4, 32 x 32 43 and
+//    85), and 32 x 128 up to 160 where that leaves fewer columns empty (63550 x 17, 16 x 16 12.6 and 20.6; 43691 x 24 12.3 and 17.6).
+//  - hb_up2: 64 x 128 for at most 64 columns (524288 x 32 outputs, 32 x 32 taps 30.2 us, 128 x 64 44.2).
+inline T2Shape t2_resample_tile(T2Mode mode, int nk, int kh, int Ho, int Wo, int units) {
+    if (t2_ceil(Ho, 64) > units) {
+        if (mode == kT2Up && Wo <= 64) return kT2Block;
+        if (mode == kT2Down && Wo <= 16) return kT2Stack;
+        if (mode == kT2Down && Wo <= 160 && 32 * t2_ceil(Wo, 32) < 64 * t2_ceil(Wo, 64)) return kT2Block;
+    }
+    if (!t2_flat(mode, nk, kh, Ho, Wo, units)) return kT2Row;
+    return mode == kT2Down ? t2_down_flat(nk, kh) : kT2Flat;
 }
 
 // hb_conv2d.  `pieces`: output rows start inside 64-byte pieces of a line.

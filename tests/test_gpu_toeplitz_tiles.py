@@ -32,6 +32,14 @@ CASES = [
     ("down2", 64, 98306, 3, 4),          # the short tile and the last height that takes it
     ("down2", 65, 98306, 4, 3),
     ("down2", 31, 98816, 17, 18),
+    ("down2", 32770, 64, 3, 2),          # narrow and tall: the block of 32 x 128 outputs, whole columns ...
+    ("down2", 33023, 45, 17, 16),        # ... and ragged ones
+    ("down2", 32899, 130, 32, 31),
+    ("down2", 33280, 32, 2, 2),          # ... and the stack of 16 x 256
+    ("down2", 32769, 17, 31, 18),
+    ("down2", 33791, 8, 32, 32),
+    ("up2", 8256, 32, 32, 32),           # ... and the block of 64 x 128
+    ("up2", 8193, 31, 4, 18),
     ("down2", 63, 66001, 30, 32),        # few rows, many taps: the flat tile of four waves ...
     ("down2", 64, 65664, 31, 31),        # ... and of two, whole ...
     ("down2", 33, 65601, 32, 19),

@@ -21,22 +21,24 @@ void tile(const char* shape) {
                G::image_bytes(kh), G::lds_bytes(kh), t2_resident(G::lds_bytes(kh)));
 }
 int main(int argc, char** argv) {
-    if (argc > 1 && !strcmp(argv[1], "flat")) {           // whether hb_down2 or hb_up2 takes the flat tile for each mode nk Ho Wo
-        for (int i = 2; i + 3 < argc; i += 4) printf("%d\n", t2_flat((T2Mode)atoi(argv[i]), atoi(argv[i + 1]), 16, atoi(argv[i + 2]), atoi(argv[i + 3]), 256));
+    const char* const shapes[] = {"row", "block", "stack", "flat", "flat_pair"};
+    if (argc > 1 && !strcmp(argv[1], "resample")) {       // the tile of hb_down2 or hb_up2 for each mode nk kh Ho Wo
+        for (int i = 2; i + 4 < argc; i += 5)
+            puts(shapes[t2_resample_tile((T2Mode)atoi(argv[i]), atoi(argv[i + 1]), atoi(argv[i + 2]), atoi(argv[i + 3]), atoi(argv[i + 4]), 256)]);
         return 0;
     }
     if (argc > 1) {                                       // the tile of hb_conv2d for each Ho Wo kh kw pieces
         for (int i = 1; i + 4 < argc; i += 5) {
             const T2Tile t = t2_conv_tile(atoi(argv[i]), atoi(argv[i + 1]), atoi(argv[i + 2]), (atoi(argv[i + 3]) + 30) / 16, atoi(argv[i + 4]), 256);
-            printf("%s %d\n", t.shape == kT2Flat ? "flat" : t.shape == kT2Block ? "block" : "row", t.nw);
+            printf("%s %d\n", shapes[t.shape], t.nw);
         }
         return 0;
     }
 #define CONV(nk) tile<kT2Conv, nk, 1, kT2Row>("row"); tile<kT2Conv, nk, 2, kT2Row>("row"); tile<kT2Conv, nk, 4, kT2Row>("row"); tile<kT2Conv, nk, 2, kT2Flat>("flat"); tile<kT2Conv, nk, 1, kT2Block>("block");
     CONV(1) CONV(2) CONV(3)
-#define DOWN(nk) tile<kT2Down, nk, 1, kT2Row>("row"); tile<kT2Down, nk, 1, kT2Flat>("flat"); tile<kT2Down, nk, 1, kT2FlatPair>("flat_pair");
+#define DOWN(nk) tile<kT2Down, nk, 1, kT2Row>("row"); tile<kT2Down, nk, 1, kT2Flat>("flat"); tile<kT2Down, nk, 1, kT2FlatPair>("flat_pair"); tile<kT2Down, nk, 1, kT2Block>("block"); tile<kT2Down, nk, 1, kT2Stack>("stack");
     DOWN(2) DOWN(3) DOWN(4)
-#define UP(nk) tile<kT2Up, nk, 2, kT2Row>("row"); tile<kT2Up, nk, 2, kT2Flat>("flat");
+#define UP(nk) tile<kT2Up, nk, 2, kT2Row>("row"); tile<kT2Up, nk, 2, kT2Flat>("flat"); tile<kT2Up, nk, 2, kT2Block>("block");
     UP(1) UP(2)
 }
 """
@@ -96,6 +98,10 @@ def conv_tiles(program, calls):
     return list(zip(out[::2], map(int, out[1::2])))
 
 
+def resample_tiles(program, calls):
+    return subprocess.run([program, "resample"] + [str(v) for c in calls for v in c], check=True, capture_output=True, text=True).stdout.split()
+
+
 def test_widest_conv2d_tile_only_where_it_is_the_fastest(program):
     """Not where a quarter of its 256 columns would be empty, nor for rows that start on 64-byte pieces, nor tall kernels."""
     calls = [(ho, wo, k, k, True) for wo in (65, 100, 128, 129, 258, 600) for ho in (30000, 200000, 1000000) for k in (3, 32)]
@@ -117,11 +123,20 @@ def test_outputs_of_few_rows_take_the_flat_tile(program):
     flat = [(16, 80000, 32, 32, False), (48, 80000, 32, 32, False), (96, 40000, 32, 32, False), (80, 70000, 32, 32, False), (48, 98305, 3, 3, True)]
     tall = [(34, 88000, 32, 32, False), (16, 32000, 32, 32, False), (64, 80000, 32, 32, False), (97, 300000, 32, 32, False), (48, 98304, 3, 3, False)]
     assert [shape for shape, _ in conv_tiles(program, flat + tall)] == ["flat"] * 5 + ["row"] * 5
-    # hb_down2 and hb_up2: mode, chunks of the window, Ho, Wo
-    calls = [(DOWN, 2, 32, 24577), (DOWN, 3, 32, 24577), (DOWN, 3, 48, 49153), (DOWN, 3, 80, 49153), (UP, 2, 48, 49153), (UP, 2, 96, 49153), (UP, 1, 63, 49153), (UP, 1, 32, 65537), (UP, 2, 1, 49153),
-             (DOWN, 3, 33, 24577), (DOWN, 3, 49, 300000), (DOWN, 3, 81, 300000), (DOWN, 3, 32, 24576), (UP, 2, 63, 300000), (UP, 1, 64, 300000), (UP, 1, 97, 300000), (UP, 1, 32, 65536)]
-    out = subprocess.run([program, "flat"] + [str(v) for c in calls for v in c], check=True, capture_output=True, text=True).stdout.split()
-    assert out == ["1"] * 9 + ["0"] * 8
+    # hb_down2 and hb_up2: mode, chunks of the window, kernel rows, Ho, Wo
+    flat = [(DOWN, 2, 16, 32, 24577), (DOWN, 3, 25, 32, 24577), (DOWN, 3, 3, 48, 49153), (DOWN, 4, 30, 80, 49153), (DOWN, 4, 30, 32, 32769),
+            (UP, 2, 32, 48, 49153), (UP, 2, 4, 96, 49153), (UP, 1, 4, 63, 49153), (UP, 1, 4, 32, 65537), (UP, 2, 4, 1, 49153)]
+    pair = [(DOWN, 3, 26, 32, 24577), (DOWN, 4, 31, 32, 32769)]
+    tall = [(DOWN, 3, 16, 33, 24577), (DOWN, 3, 16, 49, 300000), (DOWN, 3, 16, 81, 300000), (DOWN, 3, 16, 32, 24576), (DOWN, 4, 16, 32, 32768),
+            (DOWN, 3, 26, 33, 300000), (UP, 2, 4, 63, 300000), (UP, 1, 4, 64, 300000), (UP, 1, 4, 97, 300000), (UP, 1, 4, 32, 65536)]
+    assert resample_tiles(program, flat + pair + tall) == ["flat"] * 10 + ["flat_pair"] * 2 + ["row"] * 10
+
+
+def test_narrow_outputs_of_the_resampling_stages(program):
+    calls = [(mode, 3 if mode == DOWN else 1, 16, ho, wo) for mode in (DOWN, UP) for ho in (16384, 16385, 1 << 20) for wo in (1, 16, 17, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161)]
+    for (mode, _, _, ho, wo), shape in zip(calls, resample_tiles(program, calls)):
+        narrow = ("stack" if wo <= 16 else "block" if wo <= 160 and (wo - 1) % 64 < 32 else "row") if mode == DOWN else "block" if wo <= 64 else "row"
+        assert shape == (narrow if ho > 256 * 64 else "row"), (mode, ho, wo)
 
 
 def test_flat_tiles_fit_a_compute_unit_twice(tiles):
