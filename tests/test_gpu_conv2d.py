@@ -27,13 +27,13 @@ CASES = [
     (130, 9, 16, 32, 0, 31),      # narrower than a window
     (129, 65, 17, 18, 16, 0),     # one past the workgroup tile in both directions
     (127, 63, 32, 17, 1, 16),
-    (5, 65537, 4, 32, 3, 30),     # 513 tiles of 128 x 128: the wider tile
+    (5, 65537, 4, 32, 3, 30),     # one row of 513 tiles of 64 x 128
     (3, 65700, 32, 3, 31, 1),
     (3, 65600, 1, 1, 0, 0),
-    (16, 49600, 7, 17, 3, 8),     # few rows, many columns: the short tile, whole ...
-    (17, 49153, 32, 5, 31, 0),    # ... one row and one column past it
+    (16, 49600, 7, 17, 3, 8),     # few rows, many columns (the flat tile: test_gpu_toeplitz_tiles.py)
+    (17, 49153, 32, 5, 31, 0),
     (1, 49700, 3, 32, 1, 16),
-    (96, 49216, 2, 3, 0, 2),      # the last height that takes it, and the first that does not
+    (96, 49216, 2, 3, 0, 2),      # one and a half tiles high, and one row more
     (97, 49216, 3, 2, 2, 0),
     (9000, 9, 5, 5, 2, 2),        # narrow and tall
 ]

@@ -27,7 +27,7 @@ DOWN_CASES = [
     (258, 7, 9, 5, 4, 2),         # narrower than eight pixels
     (257, 65, 18, 32, 0, 17),     # one past the workgroup tile
     (259, 70001, 3, 4, 1, 2),     # more tiles than workgroups
-    (63, 49301, 9, 17, 4, 8),     # few rows, many columns: the short tile, 32 output rows ...
+    (63, 49301, 9, 17, 4, 8),     # few rows, many columns: the flat tile, 32 output rows ...
     (66, 49301, 2, 5, 1, 4),      # ... and one too many for it
     (1, 50001, 32, 32, 16, 15),
 ]
@@ -48,8 +48,8 @@ UP_CASES = [
     (65, 7, 8, 18, 3, 8),         # narrower than eight pixels
     (65, 33, 32, 20, 15, 9),      # one past the workgroup tile
     (130, 30001, 4, 6, 1, 2),     # more tiles than workgroups
-    (32, 24700, 6, 18, 2, 4),     # few rows, many columns: the short tile, 64 output rows ...
-    (33, 24700, 4, 2, 1, 0),      # ... and one pair too many for it
+    (32, 24700, 6, 18, 2, 4),     # few rows, many columns: one tile of 64 output rows ...
+    (33, 24700, 4, 2, 1, 0),      # ... and one pair too many: the flat tile
     (1, 24651, 32, 32, 8, 7),
 ]
 

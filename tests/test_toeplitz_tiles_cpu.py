@@ -5,6 +5,8 @@ import subprocess
 
 import pytest
 
+from test_gpu_toeplitz_tiles import CASES, output_size
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PROGRAM = r"""
 #include <stdio.h>
@@ -144,3 +146,19 @@ def test_flat_tiles_fit_a_compute_unit_twice(tiles):
     for t in tiles:
         if t["mode"] == UP and t["shape"] == "flat" or t["mode"] == DOWN and t["shape"] == ("flat_pair" if t["kh"] > (30 if t["nk"] == 4 else 25) else "flat"):
             assert t["resident"] >= 2, t
+
+
+def test_gpu_cases_reach_every_tile(program, tiles):
+    """The cases of test_gpu_toeplitz_tiles.py take the tiles that they name, and all there are."""
+    reached = set()
+    for op, H, W, kh, kw, extra, tile in CASES:
+        Ho, Wo = output_size(op, H, W)
+        if op == "conv2d":
+            nk, got = (30 + kw) // 16, "%s %d" % conv_tiles(program, [(Ho, Wo, kh, kw, (Wo + extra) % 16 != 0)])[0]
+        else:
+            nk = (45 + kw) // 16 if op == "down2" else 1 if kw <= 18 else 2
+            got = resample_tiles(program, [(DOWN if op == "down2" else UP, nk, kh, Ho, Wo)])[0]
+        assert got == tile, (op, H, W, kh, kw, got)
+        reached.add((op, nk, tile))
+    names = {CONV: "conv2d", DOWN: "down2", UP: "up2"}
+    assert reached == {(names[t["mode"]], t["nk"], f"{t['shape']} {t['nw']}" if t["mode"] == CONV else t["shape"]) for t in tiles}
