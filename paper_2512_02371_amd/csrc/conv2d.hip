@@ -112,7 +112,7 @@ static hb_status conv2d_launch_valu(const T2Args& a, hipStream_t st) {
 template <int NK>
 static hb_status conv2d_launch(T2Args& a, hipStream_t st) {
     const T2Tile t = t2_conv_tile(a.H, a.W, a.kh, NK, a.out_pitch % 16 != 0 || !aligned_to(a.out, 64), num_cu());
-    if (t.shape == kT2Block) return t2_launch<kT2Conv, NK, 1, kT2Block>(a, st);
+    if (t.shape == kT2Block) return t.nw == 2 ? t2_launch<kT2Conv, NK, 2, kT2Block>(a, st) : t2_launch<kT2Conv, NK, 1, kT2Block>(a, st);
     if (t.shape == kT2Flat) return t2_launch<kT2Conv, NK, 2, kT2Flat>(a, st);
     switch (t.nw) {
         case 4: return t2_launch<kT2Conv, NK, 4, kT2Row>(a, st);

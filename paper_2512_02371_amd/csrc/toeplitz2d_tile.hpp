@@ -114,9 +114,11 @@ inline T2Shape t2_resample_tile(T2Mode mode, int nk, int kh, int Ho, int Wo, int
 //    unless the partial pieces of a low kernel cost more (32513 x 129, 3 x 3: 15.6, general 13.4).
 //  - 32 x 128, two by two waves, for outputs of at most 32 columns, which leave the others' waves idle (524288 x 8, 3 x 3 / 32 x 32
 //    taps 18.3 / 54 us, 64 x 64 29 / 85, general 47 / 120; 131072 x 32: 8.1 / 20.1, 10.5 / 28, 13.8 / 34), and enough rows to fill the
-//    chip twice (9362 x 28, 9 x 9: 6.0, 64 x 64 5.8).
+//    chip twice (9362 x 28, 9 x 9: 6.0, 64 x 64 5.8).  Or 64 x 128, two by two waves, for the columns that those fill (131072 x 64, 3 x 3 / 32 x
+//    32: 11.2 / 32.1, 64 x 64 12.6 / 35.3; 49152 x 64, 3 x 3 7.5 and 7.0; 149796 x 56 17.0 and 14.0).
 inline T2Tile t2_conv_tile(int Ho, int Wo, int kh, int nk, bool pieces, int units) {
     if (Wo <= 32 && t2_ceil(Ho, 64) > units) return {kT2Block, 1};
+    if (Wo > 56 && Wo <= 64 && t2_ceil(Ho, 128) >= 2 * units) return {kT2Block, 2};
     if (t2_flat(kT2Conv, nk, kh, Ho, Wo, units)) return {kT2Flat, 2};
     const int64_t wide = t2_ceil(Ho, 64) * t2_ceil(Wo, 256);
     if (pieces && Wo > 768 && kh <= (wide >= 15 * units / 4 ? 29 : wide >= 9 * units / 4 ? 18 : 0)) return {kT2Row, 4};

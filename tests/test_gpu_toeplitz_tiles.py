@@ -33,6 +33,9 @@ CASES = [
     ("conv2d", 16385, 31, 17, 31, 0, "block 1"),         # ... and ragged, with one wave of four at work in the last
     ("conv2d", 20500, 9, 3, 2, 0, "block 1"),
     ("conv2d", 16999, 8, 7, 1, 0, "block 1"),
+    ("conv2d", 65536, 64, 7, 18, 0, "block 2"),          # ... and 64 x 128 where they fill that
+    ("conv2d", 65430, 61, 16, 2, 0, "block 2"),
+    ("conv2d", 65537, 57, 3, 1, 0, "block 2"),
     ("conv2d", 48, 98337, 3, 2, 0, "flat 2"),            # few rows, many columns: 48 rows are the most ...
     ("conv2d", 49, 98337, 2, 3, 0, "row 2"),             # ... and this one is too many
     ("conv2d", 16, 98560, 7, 17, 0, "flat 2"),           # whole flat tiles

@@ -36,7 +36,7 @@ int main(int argc, char** argv) {
         }
         return 0;
     }
-#define CONV(nk) tile<kT2Conv, nk, 1, kT2Row>("row"); tile<kT2Conv, nk, 2, kT2Row>("row"); tile<kT2Conv, nk, 4, kT2Row>("row"); tile<kT2Conv, nk, 2, kT2Flat>("flat"); tile<kT2Conv, nk, 1, kT2Block>("block");
+#define CONV(nk) tile<kT2Conv, nk, 1, kT2Row>("row"); tile<kT2Conv, nk, 2, kT2Row>("row"); tile<kT2Conv, nk, 4, kT2Row>("row"); tile<kT2Conv, nk, 2, kT2Flat>("flat"); tile<kT2Conv, nk, 1, kT2Block>("block"); tile<kT2Conv, nk, 2, kT2Block>("block");
     CONV(1) CONV(2) CONV(3)
 #define DOWN(nk) tile<kT2Down, nk, 1, kT2Row>("row"); tile<kT2Down, nk, 1, kT2Flat>("flat"); tile<kT2Down, nk, 1, kT2FlatPair>("flat_pair"); tile<kT2Down, nk, 1, kT2Block>("block"); tile<kT2Down, nk, 1, kT2Stack>("stack");
     DOWN(2) DOWN(3) DOWN(4)
@@ -116,9 +116,9 @@ def test_widest_conv2d_tile_only_where_it_is_the_fastest(program):
 
 def test_narrow_images_take_the_conv2d_tile_that_they_fill(program):
     """None that is twice as wide as the image, whatever its height."""
-    calls = [(ho, wo, k, k, pieces) for wo in (1, 8, 16, 31, 32, 33, 48, 64) for ho in (1, 16384, 16385, 1000000) for k in (1, 16, 32) for pieces in (0, 1)]
+    calls = [(ho, wo, k, k, pieces) for wo in (1, 8, 16, 31, 32, 33, 48, 57, 64) for ho in (1, 16384, 16385, 65408, 65409, 1000000) for k in (1, 16, 32) for pieces in (0, 1)]
     for (ho, wo, _, _, _), tile in zip(calls, conv_tiles(program, calls)):
-        assert tile == (("block", 1) if wo <= 32 and ho > 256 * 64 else ("row", 1))
+        assert tile == (("block", 1) if wo <= 32 and ho > 256 * 64 else ("block", 2) if wo > 56 and ho > 511 * 128 else ("row", 1))
 
 
 def test_outputs_of_few_rows_take_the_flat_tile(program):
