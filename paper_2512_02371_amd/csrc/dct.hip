@@ -317,8 +317,8 @@ static hb_status dct_run(bool valu, const hb_half* in, float* out, int C, int H,
     if (!valu) {
         // one launch: tiles and blend fused, the workspace stays unused
         // 32 x 32 patches (1.56x the products) while there are two of them to a compute unit at most and the larger ones
-        // would leave units idle (512 x 512 6.3 us, 10.1 with 64 x 64 patches; 800 x 800, 625 small ones, 10.9 against 10.3,
-        // 960 x 960 13.4 against 10.6)
+        // would leave units idle (512 x 512 6.4 us, 10.2 with 64 x 64 patches; 2 x 512 x 512, 512 small ones, 8.8 against 10.3;
+        // 720 x 736, 529 small ones, 11.1 against 10.4; 960 x 960 13.7 against 10.7)
         const int64_t patches = (int64_t)C * ceil_div(H, 64) * ceil_div(W, 64);
         const int64_t small = (int64_t)C * ceil_div(H, 32) * ceil_div(W, 32);
         if (patches > 0x7fffffff) return HB_ERR_UNSUPPORTED;

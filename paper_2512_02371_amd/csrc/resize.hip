@@ -3,8 +3,8 @@
 //
 // Each axis is one sparse matrix: row o holds `band` coefficients for the input samples
 // start[o] .. start[o] + band - 1.  As in the paper the matrix is treated as block-sparse: the 16
-// rows of an aligned group share one starting index (the smallest of theirs, moved to an even
-// sample) and the band is widened to cover all of them, at the price of some multiplications by
+// rows of an aligned group share one starting index (the smallest of theirs, moved down to an even
+// sample or a multiple of eight) and the band is widened to cover all of them, at the price of some multiplications by
 // zero.  A group of 16 outputs is then a dense 16 x (32 NK) coefficient block, and 16 image rows
 // times that block is NK products of the usual kind: the image operand is 8 consecutive samples of
 // one row per lane, straight from memory.

@@ -13,20 +13,21 @@
 // Before, a wave kept input rows in registers and added every product, shifted by its kernel row, into the
 // output with lane shifts, and those additions took as long as the products.
 //
-// A workgroup is four waves beside each other and makes ONE tile: while it loads or stores, the others of its compute
-// unit multiply, and the dispatcher evens out what they need (walking down a column with the next tile on its way in
-// registers took 22.5 us where this takes 18.6).  4096 x 4096, back to back, before and now: hb_conv2d 3 x 3 / 16 x 16 /
-// 32 x 32 22.5 / 31 / 53 -> 19.3 / 28.5 / 52.5 us; hb_down2 of 4 x 4 / 16 x 16 / 32 x 32 taps 19.6 / 22.6 / 40 -> 16.6 / 18.6 / 26,
-// hb_up2 17.2 / 18.9 / 28 -> 12.7 / 14.6 / 22; a copy of the same bytes takes 18, 9 and 14.  What bounds them now: the
-// matrix units at 32 x 32 conv2d (87 % busy in the product loop, at the 1.5 GHz their load leaves), the loads
-// that all workgroups begin with in hb_down2, the stores in hb_up2.
+// A workgroup is four waves, in general beside each other, and makes ONE tile: while it loads or stores, the others of its
+// compute unit multiply, and the dispatcher evens out what they need (walking down a column with the next tile on its way in
+// registers took 23.6 us where this takes 19.5).  4096 x 4096, launches back to back, walking and now: hb_conv2d 3 x 3 / 16 x 16 /
+// 32 x 32 22.9 / 32.6 / 52.9 -> 20.1 / 26.0 / 51.8 us; hb_down2 of 4 x 4 / 16 x 16 / 32 x 32 taps 20.3 / 23.6 / 42.7 -> 17.4 / 19.5 / 27.3,
+// hb_up2 17.8 / 19.0 / 29.8 -> 13.1 / 16.9 / 23.0; a copy of the same bytes takes 18, 9 and 14.  What bounds them now: at 32 x 32
+// conv2d the products, with the matrix units busy half of the time (0.43-0.54, clock 1.7-2.1 GHz), and the load and store phases of the
+// three workgroups of a compute unit, which they only in part cover; in hb_down2 the loads that all workgroups begin with, in hb_up2
+// the stores.  Which tile a call takes: toeplitz2d_tile.hpp.
 //
 // The window of tile w is the one of tile w - 1 moved by kTileStep pixels, so the chunks are shared:
 // per step a wave reads NK weight fragments and about NW + NK chunks for NW NK products.  The LDS rows that one
 // read touches are consecutive (rows are dealt to kStride sections) at a pitch of an odd multiple of 16
 // bytes: no bank conflicts (an even one doubles them).  Weights come from a zero-padded table of the taps, every row
-// in four shifted copies, so that every run of eight starts on 8 or 16 bytes: a run costs 8 (two 8-byte pieces) or
-// 4.8 LDS cycles, against 16 in pieces of 4 bytes with two copies (a table of all fragments would take 100 KB).  Chains of products end
+// in four shifted copies (two in some tiles of hb_down2), so that every run of eight starts on 8 or 16 bytes: a run costs 8 (two 8-byte
+// pieces) or 4.8 LDS cycles, against 16 in pieces of 4 bytes (a table of all fragments would take 100 KB).  Chains of products end
 // after two steps and are added up outside the matrix unit: error of 32 x 32 taps against fp64 8.5e-8, with chains of 16
 // steps 1.6e-7, for 2 us less.
 #pragma once
