@@ -76,7 +76,8 @@ inline T2Shape t2_down_flat(int nk, int kh) { return kh > (nk == 4 ? 30 : 25) ? 
 //  - hb_conv2d: both have 8192 outputs, three tall or two flat workgroups fit a compute unit, and what a call takes follows the
 //    most that one compute unit gets, `tall` and `flat`.  Many taps: from 3 : 2 on (80 x 49400, 32 x 32, 4 : 2: 18.1 us, tall 26.4; 80 x
 //    70000, 5 : 3: 27.2, 31.5; 34 x 88000, 3 : 3: 27.0, 21.1); fewer: from 2 : 1 on, where the tall ones need three, or 5 : 3 (16 x
-//    98600, 16 x 16, 4 : 1: 10.5, 13.7; 66 x 70000, 16 x 16, 5 : 3: 15.7, 24.1); less than 8 rows of taps, or many rounds of both, as measured (48 x 200000, 3 x 3: 17.3, 20.4).
+//    98600, 16 x 16, 4 : 1: 10.5, 13.7; 66 x 70000, 16 x 16, 5 : 3: 15.7, 24.1); less than 8 rows of taps, or
+//    many rounds of both, as measured (48 x 200000, 3 x 3: 17.3, 20.4).
 inline bool t2_flat(T2Mode mode, int nk, int kh, int Ho, int Wo, int units) {
     const bool partly = Ho <= 48 || (Ho > 64 && Ho <= 96);
     if (mode == kT2Up) return (partly || (nk == 1 && Ho < 64)) && Wo > (nk == 1 && Ho <= 32 ? 256 : 192) * units;
@@ -86,11 +87,11 @@ inline bool t2_flat(T2Mode mode, int nk, int kh, int Ho, int Wo, int units) {
     return (Ho <= 48 && Wo > 384 * units) || (Ho <= 96 && tall >= 7 && 4 * tall >= 5 * flat);
 }
 
-// hb_down2 and hb_up2.  The tile is 64 rows of 64 (hb_down2) or 128 columns, but for outputs of few rows, see above, and narrow
-// ones, of which it would leave half of the waves or more without work, where their rows still fill the chip:
-//  - hb_down2: 16 columns x 256 rows for at most 16 (131072 x 8 outputs, 16 x 16 taps 13.2 us, 64 x 64 34.2; 262144 x 4, 32 x 32 43 and
-//    85), and 32 x 128 up to 160 where that leaves fewer columns empty (63550 x 17, 16 x 16 12.6 and 20.6; 43691 x 24 12.3 and 17.6).
-//  - hb_up2: 64 x 128 for at most 64 columns (524288 x 32 outputs, 32 x 32 taps 30.2 us, 128 x 64 44.2).
+// hb_down2 and hb_up2.  Sizes are rows x columns.  The tile is 64 x 64 (hb_down2) or 64 x 128, but for outputs of few rows, see
+// above, and narrow ones, of which it would leave half of the waves or more without work, where their rows still fill the chip:
+//  - hb_down2: 256 x 16 for at most 16 columns (131072 x 8 outputs, 16 x 16 taps 13.2 us, 64 x 64 34.2; 262144 x 4, 32 x 32 43 and
+//    85), and 128 x 32 up to 160 where that leaves fewer columns empty (63550 x 17, 16 x 16 12.6 and 20.6; 43691 x 24 12.3 and 17.6).
+//  - hb_up2: 128 x 64 for at most 64 columns (524288 x 32 outputs, 32 x 32 taps 30.2 us, 64 x 128 44.2).
 inline T2Shape t2_resample_tile(T2Mode mode, int nk, int kh, int Ho, int Wo, int units) {
     if (t2_ceil(Ho, 64) > units) {
         if (mode == kT2Up && Wo <= 64) return kT2Block;
@@ -101,7 +102,7 @@ inline T2Shape t2_resample_tile(T2Mode mode, int nk, int kh, int Ho, int Wo, int
     return mode == kT2Down ? t2_down_flat(nk, kh) : kT2Flat;
 }
 
-// hb_conv2d.  `pieces`: output rows start inside 64-byte pieces of a line.
+// hb_conv2d, tiles in rows x columns.  `pieces`: output rows start inside 64-byte pieces of a line.
 //  - 64 x 128 is the general tile (4096 x 4096, 3 x 3 / 11 x 11 / 20 x 20 / 32 x 32 taps 19.3 / 21.3 / 34.8 / 52.9 us, with the widest
 //    21.5 / 25.9 / 37.9 / 53.8; 4000 x 4000, 32 x 32 51.0, 55.8).
 //  - 64 x 256 writes fewer partial pieces, which counts where stores take longer than products (4000 x 4001, 3 x 3 / 16 x 16 /
@@ -112,10 +113,10 @@ inline T2Shape t2_resample_tile(T2Mode mode, int nk, int kh, int Ho, int Wo, int
 //  - 64 x 64 where the others leave compute units idle (300 x 200, 32 x 32: 9.8, general 12.0; 1500 x 1500, 9 x 9: 7.7, 8.3).
 //    Also where it has fewer empty columns (87381 x 48, 3 x 3 / 32 x 32: 8.9 / 23.2, general 15.1 / 32.4; 52428 x 160, 9 x 9: 16.4, 18.4),
 //    unless the partial pieces of a low kernel cost more (32513 x 129, 3 x 3: 15.6, general 13.4).
-//  - 32 x 128, two by two waves, for outputs of at most 32 columns, which leave the others' waves idle (524288 x 8, 3 x 3 / 32 x 32
+//  - 128 x 32, two by two waves, for outputs of at most 32 columns, which leave the others' waves idle (524288 x 8, 3 x 3 / 32 x 32
 //    taps 18.3 / 54 us, 64 x 64 29 / 85, general 47 / 120; 131072 x 32: 8.1 / 20.1, 10.5 / 28, 13.8 / 34), and enough rows to fill the
-//    chip twice (9362 x 28, 9 x 9: 6.0, 64 x 64 5.8).  Or 64 x 128, two by two waves, for the columns that those fill (131072 x 64, 3 x 3 / 32 x
-//    32: 11.2 / 32.1, 64 x 64 12.6 / 35.3; 49152 x 64, 3 x 3 7.5 and 7.0; 149796 x 56 17.0 and 14.0).
+//    chip twice (9362 x 28, 9 x 9: 6.0, 64 x 64 5.8).  Or 128 x 64, two by two waves, for the columns that those fill (131072 x 64, 3 x 3 / 32 x
+//    32: 11.2 / 32.1, 64 x 64 12.6 / 35.3; 49152 x 64, 3 x 3 7.7 and 7.1; 149796 x 56 20.2 and 16.7).
 inline T2Tile t2_conv_tile(int Ho, int Wo, int kh, int nk, bool pieces, int units) {
     if (Wo <= 32 && t2_ceil(Ho, 64) > units) return {kT2Block, 1};
     if (Wo > 56 && Wo <= 64 && t2_ceil(Ho, 128) >= 2 * units) return {kT2Block, 2};

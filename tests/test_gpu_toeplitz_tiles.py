@@ -29,11 +29,11 @@ CASES = [
     ("conv2d", 50, 147473, 2, 3, 15, "row 2"),           # ... rows that start on pieces
     ("conv2d", 49, 130817, 3, 2, 0, "row 2"),
     ("conv2d", 49, 130848, 28, 2, 0, "row 2"),
-    ("conv2d", 16512, 32, 32, 32, 0, "block 1"),         # narrow images (32 x 128), whole ...
+    ("conv2d", 16512, 32, 32, 32, 0, "block 1"),         # narrow images (128 x 32), whole ...
     ("conv2d", 16385, 31, 17, 31, 0, "block 1"),         # ... and ragged, with one wave of four at work in the last
     ("conv2d", 20500, 9, 3, 2, 0, "block 1"),
     ("conv2d", 16999, 8, 7, 1, 0, "block 1"),
-    ("conv2d", 65536, 64, 7, 18, 0, "block 2"),          # ... and 64 x 128 where they fill that
+    ("conv2d", 65536, 64, 7, 18, 0, "block 2"),          # ... and 128 x 64 where they fill that
     ("conv2d", 65430, 61, 16, 2, 0, "block 2"),
     ("conv2d", 65537, 57, 3, 1, 0, "block 2"),
     ("conv2d", 48, 98337, 3, 2, 0, "flat 2"),            # few rows, many columns: 48 rows are the most ...
@@ -49,10 +49,10 @@ CASES = [
     ("down2", 126, 126, 15, 2, 0, "row"),
     ("down2", 126, 256, 3, 18, 0, "row"),                # whole columns, rows missing
     ("down2", 4098, 8192, 2, 2, 1, "row"),               # ... through the L2: over 32 MB of output, rows off the 128-byte lines
-    ("down2", 32770, 64, 3, 2, 0, "block"),              # narrow and tall: 32 x 128, whole columns ...
+    ("down2", 32770, 64, 3, 2, 0, "block"),              # narrow and tall: 128 x 32, whole columns ...
     ("down2", 33023, 45, 17, 16, 0, "block"),            # ... and ragged ones
     ("down2", 32899, 130, 32, 31, 0, "block"),
-    ("down2", 33280, 32, 2, 2, 0, "stack"),              # 16 x 256
+    ("down2", 33280, 32, 2, 2, 0, "stack"),              # 256 x 16
     ("down2", 32769, 17, 31, 18, 0, "stack"),
     ("down2", 33791, 8, 32, 32, 0, "stack"),
     ("down2", 64, 98306, 3, 4, 0, "flat"),               # few rows, many columns ...
