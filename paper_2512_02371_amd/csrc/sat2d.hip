@@ -19,6 +19,7 @@
 //   The sums pass uses the same operands: X * 1 for row sums; X * [I|0], X * [0|I] copy the pixels
 //   into accumulator layout (exactly), whose stacked pairs times the all-ones matrix give column
 //   sums.  No cross-lane traffic in that pass at all.
+#include <algorithm>
 #include <atomic>
 
 #include "hb_device.hpp"
@@ -331,7 +332,14 @@ __global__ void __launch_bounds__(256) sat_apply_mfma_kernel(SatArgs p) {
 // pixel after the wait is two additions and the store.  The heavy arithmetic sits before the wait,
 // where it overlaps with the loads of the other waves.
 //
-// Grid-wide wait.  Arrival is a two-level count (up to 16 leaf counters, one root, each on its own
+// What bounds it: memory, in two phases (read 32 MB in 6 us, write 64 MB in 11 at 4096 x 4096) with the local tables, the wait and
+// the carries between them, 8 us in which memory idles if every workgroup takes its phases at the same time (28.0 us with
+// 256 workgroups of 4 x 4 tiles, one to a compute unit).  So the regions of 2 x 4 tiles form two GROUPS, the upper and the lower
+// half of the image, and a compute unit holds a workgroup of each: a region needs the sums of those to its left and above only,
+// so the first group waits for itself alone and stores while the second still loads, adds and waits (23.4 us; 2900 x
+// 2900 25.5 -> 23.6, 2048 x 4096 20.0 -> 17.0).  Small images (2 x 2 tiles), which memory does not bound, are one group.
+//
+// Grid-wide wait, of each group.  Arrival is a two-level count (up to 16 leaf counters, one root, each on its own
 // 128-byte line: arrivals at one address are served one after the other by the memory side); the
 // last arrival raises eight copies of a `go` word and workgroup w polls copy w % 8.  Table data and
 // the words of the wait are written and read with agent-scope accesses (they bypass the per-XCD L2,
@@ -347,6 +355,10 @@ __global__ void __launch_bounds__(256) sat_apply_mfma_kernel(SatArgs p) {
 //   finisher:       observes go == 1; then loads late and todo.
 //   go is raised once, after the late workgroup's load returned 0, hence after its stores were
 //   performed at the memory side: the finisher's loads see them.
+// With two groups, `go` of the first, once performed, counts as one more arrival of the second, so `go` of the second
+// means that every region is published.  A workgroup finishes only regions that it knows to be: those of the first group,
+// and all of them if it is of the second or raised the second's `go` itself.  (The workgroup that raises a group's `go`
+// always passes its own wait, so some workgroup finishes what that group's late ones left.)
 // The host uses this kernel only when the grid fits on the device at once (occupancy query), so the
 // bounded wait ends by `go` unless other work holds compute units for longer than the limit.
 #ifndef HB_SAT_POLL_SLEEP
@@ -354,7 +366,8 @@ __global__ void __launch_bounds__(256) sat_apply_mfma_kernel(SatArgs p) {
 #endif
 struct SatSync {
     static constexpr int kLine = 32;                      // words per 128 bytes
-    static constexpr int kLeaves = 16, kGo = 8, kMaxRegions = 1024;
+    static constexpr int kLeaves = 16, kGo = 8, kMaxRegions = 1024;     // leaves and copies of `go`: halved between two groups
+    static constexpr int kRoot = 16;                      // words from the first group's root to the second's
     unsigned leaf[kLeaves * kLine];
     unsigned root[kLine];
     unsigned go[kGo * kLine];
@@ -376,6 +389,7 @@ struct SatFusedArgs {
     int H, W;
     int64_t in_pitch, out_pitch;
     int nsw, nbw;          // regions down, across
+    int first;             // regions of the first group: they wait for each other only, the others for all
     int Hr, Wr;            // H, W rounded up to whole regions
     float* RS;             // [nbw][Hr]  row y: sum over the columns of region column bw of the rows from its tile row's top to y
     float* CS;             // [nsw][Wr]  column x: sum over the rows of region row sw of the columns from its tile column's left to x
@@ -504,20 +518,38 @@ __device__ __forceinline__ void sat_fused_finish(const SatFusedArgs& p, SatFused
         for (int k = 0; k < kRH / 64; ++k) ar[k] = 0.f;
 #pragma unroll
         for (int k = 0; k < kRW / 64; ++k) ac[k] = 0.f;
-        for (int b2 = wv; b2 < bw; b2 += kWaves) {
-            const float* line = p.RS + (int64_t)b2 * p.Hr + I0;
-#pragma unroll
-            for (int k = 0; k < kRH / 64; ++k) ar[k] += ldf_agent(line + 64 * k + lane);
-        }
-        for (int s2 = wv; s2 < sw; s2 += kWaves) {
-            const float* line = p.CS + (int64_t)s2 * p.Wr + J0;
-#pragma unroll
-            for (int k = 0; k < kRW / 64; ++k) ac[k] += ldf_agent(line + 64 * k + lane);
-        }
         float a = 0.f;
         for (int i = tid; i < sw * bw; i += kThreads) {
             const int s2 = i / bw, b2 = i - s2 * bw;
             a += ldf_agent(p.TOT + (int64_t)s2 * p.nbw + b2);
+        }
+        // four lines of either kind and the totals fly together
+#pragma unroll 1
+        for (int i0 = wv; i0 < max(bw, sw); i0 += 4 * kWaves) {
+            float r[4][kRH / 64], col[4][kRW / 64];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = i0 + u * kWaves;
+                const float* const rline = p.RS + (int64_t)i * p.Hr + I0;
+                const float* const cline = p.CS + (int64_t)i * p.Wr + J0;
+#pragma unroll
+                for (int k = 0; k < kRH / 64; ++k) r[u][k] = 0.f;
+#pragma unroll
+                for (int k = 0; k < kRW / 64; ++k) col[u][k] = 0.f;
+                if (i < bw)
+#pragma unroll
+                    for (int k = 0; k < kRH / 64; ++k) r[u][k] = ldf_agent(rline + 64 * k + lane);
+                if (i < sw)
+#pragma unroll
+                    for (int k = 0; k < kRW / 64; ++k) col[u][k] = ldf_agent(cline + 64 * k + lane);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+#pragma unroll
+                for (int k = 0; k < kRH / 64; ++k) ar[k] += r[u][k];
+#pragma unroll
+                for (int k = 0; k < kRW / 64; ++k) ac[k] += col[u][k];
+            }
         }
 #pragma unroll
         for (int k = 0; k < kRH / 64; ++k) L.u.part.r[wv][64 * k + lane] = ar[k];
@@ -595,7 +627,7 @@ __device__ __forceinline__ void sat_fused_finish(const SatFusedArgs& p, SatFused
 extern __shared__ __attribute__((aligned(16))) unsigned char s_sat_fused_lds[];
 
 template <int TR, int TC, bool STREAM>
-__global__ void __launch_bounds__(64 * TR * TC) sat_fused_kernel(SatFusedArgs p) {
+__global__ void __launch_bounds__(64 * TR * TC, 4) sat_fused_kernel(SatFusedArgs p) {
     using LT = SatFusedLds<TR, TC>;
     constexpr int kWaves = LT::kWaves, kRH = LT::kRH, kRW = LT::kRW;
     LT& L = *reinterpret_cast<LT*>(s_sat_fused_lds);
@@ -606,7 +638,7 @@ __global__ void __launch_bounds__(64 * TR * TC) sat_fused_kernel(SatFusedArgs p)
     // The first turn of this loop is the workgroup's own region (local tables, publish, arrive, wait,
     // finish).  Further turns run only in a finisher, on regions whose workgroups stopped waiting
     // (reload, local tables, finish).  `region` and `own` are the same in every lane.
-    int region = wg;
+    int region = wg, nscan = 0;                           // nscan: regions it may finish for others
     bool own = true;
     SAT_STAMP(S, wg, 0);
     for (;;) {
@@ -652,20 +684,29 @@ __global__ void __launch_bounds__(64 * TR * TC) sat_fused_kernel(SatFusedArgs p)
             SAT_STAMP(S, wg, 2);
             // arrive, then wait (bounded) for the others
             if (tid == 0) {
-                const int nleaf = nwg < SatSync::kLeaves ? nwg : SatSync::kLeaves;
-                const int lf = wg % nleaf;
-                const int leaf_target = (nwg - lf + nleaf - 1) / nleaf;
-                const unsigned old = __hip_atomic_fetch_add(&S->leaf[SatSync::kLine * lf], 1u, __ATOMIC_RELAXED,
-                                                            __HIP_MEMORY_SCOPE_AGENT);
-                if ((int)old + 1 == leaf_target) {
-                    const unsigned r = __hip_atomic_fetch_add(&S->root[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if ((int)r + 1 == nleaf) {
-#pragma unroll
-                        for (int i = 0; i < SatSync::kGo; ++i) st_agent(&S->go[SatSync::kLine * i], 1u);
+                const int ngroups = p.first < nwg ? 2 : 1, group = wg < p.first ? 0 : 1;
+                const int kl = SatSync::kLeaves / ngroups, kg = SatSync::kGo / ngroups;
+                const int id = group ? wg - p.first : wg, n0 = p.first, n1 = nwg - p.first, n = group ? n1 : n0;
+                const int nleaf = min(n, kl), lf = id % nleaf;
+                const int leaf_target = (n - lf + nleaf - 1) / nleaf;
+                bool all = ngroups == 1 || group == 1;    // passing the wait, it knows that every region is published
+                auto arrive = [&](unsigned* w) { return (int)__hip_atomic_fetch_add(w, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1; };
+                auto raise = [&](int g) {
+                    for (int i = 0; i < kg; ++i) st_agent(&S->go[SatSync::kLine * (g * kg + i)], 1u);
+                };
+                if (arrive(&S->leaf[SatSync::kLine * (group * kl + lf)]) == leaf_target &&
+                    arrive(&S->root[SatSync::kRoot * group]) == nleaf + group) {
+                    raise(group);
+                    if (ngroups == 2 && group == 0) {     // the first group is one more arrival of the second
+                        stores_done();
+                        if (arrive(&S->root[SatSync::kRoot]) == min(n1, kl) + 1) {
+                            raise(1);
+                            all = true;
+                        }
                     }
                 }
-                const unsigned* mygo = &S->go[SatSync::kLine * (wg & (SatSync::kGo - 1))];
-                int state = 1;                            // 1 passed, 0 leave
+                const unsigned* mygo = &S->go[SatSync::kLine * (group * kg + id % kg)];
+                int state = all ? 2 : 1;                  // passed: 2 all regions, 1 the first group's are published; 0 leave
                 int polls = 0;
                 while (ld_agent(mygo) == 0u) {
                     if (++polls > p.wait_limit) { state = 0; break; }
@@ -679,13 +720,14 @@ __global__ void __launch_bounds__(64 * TR * TC) sat_fused_kernel(SatFusedArgs p)
                         unsigned expect = 1u;             // (a finisher may have claimed it too: both write the same values)
                         __hip_atomic_compare_exchange_strong(&S->todo[wg], &expect, 2u, __ATOMIC_RELAXED,
                                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        state = 1;
+                        state = all ? 2 : 1;
                     }
                 }
                 L.ctl = state;
             }
             __syncthreads();
             if (L.ctl == 0) return;
+            nscan = __builtin_amdgcn_readfirstlane(L.ctl) == 2 ? nwg : p.first;
             if (tid == 0) late = ld_agent(&S->late[0]);   // in flight during the finish step
             SAT_STAMP(S, wg, 3);
         }
@@ -704,9 +746,9 @@ __global__ void __launch_bounds__(64 * TR * TC) sat_fused_kernel(SatFusedArgs p)
         // finisher duty: wave 0 looks for a marked region and claims it
         if (tid < 64) {
             int found = -1;
-            for (int r0 = 0; r0 < nwg && found < 0; r0 += 64) {
+            for (int r0 = 0; r0 < nscan && found < 0; r0 += 64) {
                 const int r = r0 + lane;
-                const bool marked = r < nwg && ld_agent(&S->todo[r]) == 1u;
+                const bool marked = r < nscan && ld_agent(&S->todo[r]) == 1u;
                 unsigned long long m = __ballot(marked);
                 while (m && found < 0) {
                     const int cand = r0 + __builtin_ctzll(m);
@@ -804,16 +846,18 @@ static size_t sat_workspace_floats(int H, int W) {
     return 2 * (nb * ns * kSatTile) + 2 * (ns * nb * kSatTile) + 2 * ns * nb;   // rs, rcarry, cs, ccarry, tot, es
 }
 
-// Region shapes of the one-launch kernel: 2 x 2 tiles (128 x 128 pixels, 256 threads) for small
-// images, 4 x 4 tiles (256 x 256 pixels, 1024 threads: fewer arrivals at the grid-wide wait, fewer
-// table lines per region) once that still gives 128 regions or more.  0: more regions than the
+// Region shapes of the one-launch kernel, by the tiles across: 2, 2 x 2 tiles (128 x 128 pixels, 256 threads) for small
+// images; 4, 2 x 4 tiles (128 x 256 pixels, 512 threads: fewer arrivals at the grid-wide wait, fewer
+// table lines per region, two groups) once the image has 128 pieces of 256 x 256 or more.  0: more regions than the
 // wait's bookkeeping holds; the three-launch path serves those.
 static int sat_fused_shape(int H, int W) {
     const int64_t ra = (int64_t)ceil_div(H, 128) * ceil_div(W, 128), rb = (int64_t)ceil_div(H, 256) * ceil_div(W, 256);
     if (rb >= 128) return rb <= SatSync::kMaxRegions ? 4 : 0;
     return ra <= SatSync::kMaxRegions ? 2 : 4;            // rb < 128 here
 }
-// floats of the one-launch tables (RS, CS, TOT), rounded up to 64, for region edge `t` tiles
+// Floats set aside for the one-launch tables (RS, CS, TOT) behind those of the three launches, whose room they use as well
+// (nobody needs both): RS and CS of 2 x 4 tiles are at most 385 floats for every four 64 x 64 tiles begun across and two down, the
+// three-launch tables 258 for every tile.
 static size_t sat_fused_table_floats(int H, int W, int t) {
     const size_t e = (size_t)kSatTile * t, nsw = (size_t)ceil_div(H, (int)e), nbw = (size_t)ceil_div(W, (int)e);
     const size_t n = nbw * nsw * e + nsw * nbw * e + nsw * nbw;
@@ -849,24 +893,24 @@ static hb_status sat_prepare(SatArgs& a, const hb_half* in, float* out, int H, i
     return HB_OK;
 }
 
-// The one-launch tables follow the three-launch tables in the workspace (both sized by hb_sat2d_workspace_size).
+// The one-launch tables lie where the three-launch tables would, their SatSync at the end of the workspace.
 static void sat_prepare_fused(SatFusedArgs& f, const SatArgs& a, void* ws, int t, int wait_limit) {
-    const int e = kSatTile * t;
+    const int eh = kSatTile * 2, ew = kSatTile * t;
     f.in = a.in;
     f.out = a.out;
     f.H = a.H;
     f.W = a.W;
     f.in_pitch = a.in_pitch;
     f.out_pitch = a.out_pitch;
-    f.nsw = ceil_div(a.H, e);
-    f.nbw = ceil_div(a.W, e);
-    f.Hr = f.nsw * e;
-    f.Wr = f.nbw * e;
-    float* base = reinterpret_cast<float*>(ws) + ((sat_workspace_floats(a.H, a.W) + 63) & ~(size_t)63);
-    f.RS = base;
+    f.nsw = ceil_div(a.H, eh);
+    f.nbw = ceil_div(a.W, ew);
+    f.first = t == 4 ? (f.nsw + 1) / 2 * f.nbw : f.nsw * f.nbw;
+    f.Hr = f.nsw * eh;
+    f.Wr = f.nbw * ew;
+    f.RS = reinterpret_cast<float*>(ws);
     f.CS = f.RS + (size_t)f.nbw * f.Hr;
     f.TOT = f.CS + (size_t)f.nsw * f.Wr;
-    f.sync = reinterpret_cast<SatSync*>(base + sat_fused_table_floats(a.H, a.W, t));
+    f.sync = reinterpret_cast<SatSync*>(f.RS + ((sat_workspace_floats(a.H, a.W) + 63) & ~(size_t)63) + sat_fused_table_floats(a.H, a.W, t));
     f.wait_limit = wait_limit;
 }
 
@@ -894,24 +938,24 @@ struct SatCapacity { int shape2 = -1, shape4 = -1; };
 static SatCapacity g_sat_capacity[kMaxDevices];
 static std::mutex g_sat_mu;
 
-template <int T, bool STREAM>
+template <int TC, bool STREAM>
 static hb_status sat_fused_launch(const SatFusedArgs& f, hipStream_t st) {
-    auto kernel = sat_fused_kernel<T, T, STREAM>;
-    const size_t lds = sizeof(SatFusedLds<T, T>);
+    auto kernel = sat_fused_kernel<2, TC, STREAM>;
+    const size_t lds = sizeof(SatFusedLds<2, TC>);
     hb_status s = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds);
     if (s != HB_OK) return s;
     hipLaunchKernelGGL(sat_sync_clear_kernel, dim3(1), dim3(256), 0, st, f.sync);
-    hipLaunchKernelGGL(kernel, dim3(f.nsw * f.nbw), dim3(64 * T * T), lds, st, f);
+    hipLaunchKernelGGL(kernel, dim3(f.nsw * f.nbw), dim3(64 * 2 * TC), lds, st, f);
     return launch_status();
 }
 
-template <int T>
+template <int TC>
 static int sat_fused_capacity_query() {
-    auto kernel = sat_fused_kernel<T, T, true>;
-    const size_t lds = sizeof(SatFusedLds<T, T>);
+    auto kernel = sat_fused_kernel<2, TC, true>;
+    const size_t lds = sizeof(SatFusedLds<2, TC>);
     if (allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds) != HB_OK) return 0;
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 64 * T * T, lds) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 64 * 2 * TC, lds) != hipSuccess) return 0;
     const int ncu = device_num_cu();
     return ncu > 0 && per_cu > 0 ? per_cu * ncu : 0;
 }
@@ -938,7 +982,7 @@ static hb_status sat_launch_mfma(const SatArgs& a, void* ws, hipStream_t st) {
     if (t) {
         SatFusedArgs f;
         sat_prepare_fused(f, a, ws, t, g_sat_wait_limit.load());
-        if (f.nsw * f.nbw <= sat_fused_capacity(t)) {
+        if (f.nsw * f.nbw <= std::min(sat_fused_capacity(t), (int)SatSync::kMaxRegions)) {
             if (t == 2) return stream_stores ? sat_fused_launch<2, true>(f, st) : sat_fused_launch<2, false>(f, st);
             return stream_stores ? sat_fused_launch<4, true>(f, st) : sat_fused_launch<4, false>(f, st);
         }

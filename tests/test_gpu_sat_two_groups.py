@@ -1,0 +1,28 @@
+"""hb_sat2d where its regions of 128 x 256 pixels form two groups: one region row (a single group), two, odd numbers of them,
+ragged ends and the most that are resident, waiting or giving up at once.  0/1 images: every partial sum stays below
+2^24, so fp32 sums in any order are exact and the table is compared bit for bit."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("limit", [0, -1])                    # the default, "stop waiting at once"
+@pytest.mark.parametrize("H,W,extra", [(128, 32768, 0), (129, 32765, 3), (300, 32001, 0), (16384, 500, 0), (2817, 2815, 5),
+                                       (4096, 4096, 0), (4095, 4093, 1)])
+def test_two_groups_are_exact(H, W, extra, limit):
+    import torch
+    from paper_2512_02371_amd import hb
+    gen = torch.Generator(device="cuda").manual_seed(H + 7 * W)
+    x = (torch.rand(H, W + extra, generator=gen, device="cuda") < 0.4).half()[:, :W]
+    out = torch.full((H, W + extra), 7.0, device="cuda")
+    ws = torch.full((hb.hb_sat2d_workspace_size(H, W),), 0xff, dtype=torch.uint8, device="cuda")
+    print(f"hb_sat2d {H}x{W}+{extra} limit {limit}", flush=True)
+    prev = hb.hb_sat2d_set_wait_limit(limit)
+    try:
+        hb.hb_sat2d(x, out[:, :W], ws)
+        torch.cuda.synchronize()
+    finally:
+        hb.hb_sat2d_set_wait_limit(prev)
+    want = x.cpu().double().cumsum(0).cumsum(1)
+    assert torch.equal(out[:, :W].cpu().double(), want)
+    assert bool((out[:, W:] == 7.0).all()), "wrote past the row end"
