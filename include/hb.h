@@ -279,15 +279,14 @@ hb_status hb_dct_denoise_valu(const hb_half *in, float *out, int C, int H, int W
  * hb_sat2d_workspace_size(H, W) bytes, 256-byte aligned; its contents on entry do
  * not matter and are undefined on exit.  Two calls that run concurrently need
  * two workspaces.
- * Images of up to 1024 regions of 256 x 256 pixels whose workgroups are all resident
- * at once (4096 x 4096 is 256 regions) run as ONE kernel that reads the image once:
+ * Images of up to 1024 regions of 128 x 256 pixels whose workgroups are all resident
+ * at once (4096 x 4096 is 512 regions) run as ONE kernel that reads the image once:
  * every workgroup forms the local table of its region in registers, publishes the
- * region's row, column and total sums in the workspace, waits until all regions have
- * published, adds the sums of the regions to its left and above, and stores.  The
+ * region's row, column and total sums in the workspace, waits until all regions (for
+ * those of the upper half: of that half) have published, adds the sums of the regions to its left and above, and stores.  The
  * wait is bounded (hb_sat2d_set_wait_limit): a workgroup that reaches the bound marks
  * its region and exits, and the workgroups that got through finish the marked regions
- * from memory, so the kernel ends whatever the scheduling.  A small kernel ahead of it
- * on the same stream clears the wait's counters.  Larger images take three launches
+ * from memory, so the kernel ends whatever the scheduling.  Larger images take three launches
  * (tile sums, scans of the carries, apply) and read the image twice.
  */
 size_t hb_sat2d_workspace_size(int H, int W);

@@ -21,6 +21,7 @@
 //   sums.  No cross-lane traffic in that pass at all.
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 
 #include "hb_device.hpp"
 #include "hb_host.hpp"
@@ -359,6 +360,13 @@ __global__ void __launch_bounds__(256) sat_apply_mfma_kernel(SatArgs p) {
 // means that every region is published.  A workgroup finishes only regions that it knows to be: those of the first group,
 // and all of them if it is of the second or raised the second's `go` itself.  (The workgroup that raises a group's `go`
 // always passes its own wait, so some workgroup finishes what that group's late ones left.)
+// The words of the wait hold anything when the kernel starts.  The launch's number `call` (unlike any other launch's) tells
+// whether they are this launch's: workgroup 0 exchanges it for `claim`, clears the words if it was the first, and then writes it
+// to `ready`, which every workgroup has to find there before it arrives; one that has looked for long does the clearing
+// itself, through the same exchange, so nobody waits for a workgroup that does not run.  The last arrival of all wipes
+// `claim` and `ready`, which nobody reads from then on: a launch that is replayed from a graph with the same number finds
+// its words not ready again.  A kernel ahead of this one that cleared them cost a launch and 1 to 1.5 us (1079 x 1917 15.9 ->
+// 14.5 us, 2048 x 4096 17.0 -> 15.5, 1024 x 1024 11.1 -> 10.1).
 // The host uses this kernel only when the grid fits on the device at once (occupancy query), so the
 // bounded wait ends by `go` unless other work holds compute units for longer than the limit.
 #ifndef HB_SAT_POLL_SLEEP
@@ -368,10 +376,11 @@ struct SatSync {
     static constexpr int kLine = 32;                      // words per 128 bytes
     static constexpr int kLeaves = 16, kGo = 8, kMaxRegions = 1024;     // leaves and copies of `go`: halved between two groups
     static constexpr int kRoot = 16;                      // words from the first group's root to the second's
+    static constexpr int kReady = 8, kClaim = 8;          // words at which the lines of `go` and `late` have `ready` and `claim`
     unsigned leaf[kLeaves * kLine];
     unsigned root[kLine];
-    unsigned go[kGo * kLine];
-    unsigned late[kLine];
+    unsigned go[kGo * kLine];                             // each copy with one of `ready` (64 bits)
+    unsigned late[kLine];                                 // with `claim` (64 bits)
     unsigned todo[kMaxRegions];                           // 0 idle, 1 waiting for a finisher, 2 claimed
 #ifdef HB_SAT_TIMING
     unsigned long long stamp[kMaxRegions][8];             // measurement builds only: phase time stamps per workgroup
@@ -382,6 +391,12 @@ struct SatSync {
 #else
 #define SAT_STAMP(S, wg, i) do { } while (0)
 #endif
+
+constexpr int kSatClaimPolls = 64;                        // of `ready`, after which a workgroup offers to clear
+// The second group holds its requests back for 1.5 us (units of 64 clocks), or they would share the memory with the first
+// group's, which everything waits for: 4096 x 4096 23.6 -> 23.0 us, 2900 x 2900 22.6 -> 20.7; a third of it and less gives
+// nothing, 3 us 23.8 and 21.8.
+constexpr int kSatSecondDelay = 56;
 
 struct SatFusedArgs {
     const half_t* in;
@@ -395,6 +410,7 @@ struct SatFusedArgs {
     float* CS;             // [nsw][Wr]  column x: sum over the rows of region row sw of the columns from its tile column's left to x
     float* TOT;            // [nsw][nbw] region totals
     SatSync* sync;
+    unsigned long long call;                              // of this launch, see SatSync
     int wait_limit;
 };
 
@@ -413,10 +429,35 @@ __device__ __forceinline__ void stf_agent(float* p, float v) {
 // all earlier stores of this lane performed, and no memory access moved across this point
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-__global__ void __launch_bounds__(256) sat_sync_clear_kernel(SatSync* s) {
-    unsigned* w = reinterpret_cast<unsigned*>(s);
-    constexpr int kWords = (SatSync::kLeaves + 1 + SatSync::kGo + 1) * SatSync::kLine + SatSync::kMaxRegions;
-    for (int i = threadIdx.x; i < kWords; i += 256) w[i] = 0u;
+__device__ __forceinline__ unsigned long long* sat_ready(SatSync* s, int copy) {
+    return reinterpret_cast<unsigned long long*>(&s->go[SatSync::kLine * copy + SatSync::kReady]);
+}
+__device__ __forceinline__ unsigned long long* sat_claim(SatSync* s) {
+    return reinterpret_cast<unsigned long long*>(&s->late[SatSync::kClaim]);
+}
+__device__ __forceinline__ unsigned sat_add(unsigned* w) {
+    return __hip_atomic_fetch_add(w, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+}
+// By the last arrival of all, when nobody reads these any more: leaves no trace of this launch's number.
+__device__ __forceinline__ void sat_forget_call(SatSync* s) {
+    for (int i = 0; i < SatSync::kGo; ++i) __hip_atomic_store(sat_ready(s, i), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(sat_claim(s), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Taking on the clearing of the wait's words: whether no other workgroup of this launch has.
+__device__ __forceinline__ bool sat_take(SatSync* s, unsigned long long call) {
+    return __hip_atomic_exchange(sat_claim(s), call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != call;
+}
+// Lanes 0 .. n - 1 of one wave: the clearing, and, once that is performed, `ready`.
+__device__ __forceinline__ void sat_clear(SatSync* s, int nwg, int lane, int n) {
+    for (int i = lane; i < SatSync::kLeaves; i += n) st_agent(&s->leaf[SatSync::kLine * i], 0u);
+    for (int i = lane; i < SatSync::kGo; i += n) st_agent(&s->go[SatSync::kLine * i], 0u);
+    for (int i = lane; i < 2; i += n) st_agent(&s->root[SatSync::kRoot * i], 0u);
+    if (lane == 0) st_agent(&s->late[0], 0u);
+    for (int i = lane; i < nwg; i += n) st_agent(&s->todo[i], 0u);
+}
+__device__ __forceinline__ void sat_set_ready(SatSync* s, unsigned long long call, int lane, int n) {
+    stores_done();
+    for (int i = lane; i < SatSync::kGo; i += n) __hip_atomic_store(sat_ready(s, i), call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 template <int TR, int TC>
@@ -442,9 +483,9 @@ static_assert(RowPatch<4>::kFloats % 4 == 0, "patches stay 16-byte aligned");
 
 // Before the wait, per wave: load the tile and build its local table in registers; its last row,
 // last column (and so its total) go to LDS.  Lt[rt][t]: lane (c, g) holds row 16 rt + c, columns 16 t + 4 g + v.
-template <int TR, int TC>
+template <int TR, int TC, class F>
 __device__ __forceinline__ void sat_fused_local(const SatFusedArgs& p, SatFusedLds<TR, TC>& L,
-                                                int y0, int x0, int ts, int tb, int lane, floatx4 (&Lt)[4][4]) {
+                                                int y0, int x0, int ts, int tb, int lane, floatx4 (&Lt)[4][4], F&& requested) {
     const int c = lane & 15, g = lane >> 4;
     half8 X[4][2];
     if (y0 + kSatTile <= p.H && x0 + kSatTile <= p.W) {
@@ -462,6 +503,7 @@ __device__ __forceinline__ void sat_fused_local(const SatFusedArgs& p, SatFusedL
             for (int blk = 0; blk < 2; ++blk)
                 X[rt][blk] = load8_zero(p.in, p.in_pitch, y0 + 16 * rt + c, x0 + 32 * blk + 8 * g, p.H, p.W);
     }
+    requested();
     half8 tri[2];                                         // Ut[m][k] = (k <= m + 16 half)
 #pragma unroll
     for (int h = 0; h < 2; ++h)
@@ -652,7 +694,18 @@ __global__ void __launch_bounds__(64 * TR * TC, 4) sat_fused_kernel(SatFusedArgs
         const int ts = wv / TC, tb = wv - ts * TC;
         const int sw = region / p.nbw, bw = region - sw * p.nbw;
         floatx4 Lt[4][4];
-        sat_fused_local<TR, TC>(p, L, kRH * sw + kSatTile * ts, kRW * bw + kSatTile * tb, ts, tb, lane, Lt);
+        // The last wave of workgroup 0 clears the words of the wait on the side: it asks for the task, requests its pixels, clears, and
+        // says so when its tile is done (clearing first, its pixels came last and everybody waited: 4096 x 4096 26.9 us).
+        if (own && wg >= p.first) __builtin_amdgcn_s_sleep(kSatSecondDelay);
+        const bool clears = own && wg == 0 && wv == kWaves - 1;
+        bool took = false;
+        if (clears && lane == 0) took = sat_take(S, p.call);
+        sat_fused_local<TR, TC>(p, L, kRH * sw + kSatTile * ts, kRW * bw + kSatTile * tb, ts, tb, lane, Lt, [&]() {
+            if (!clears) return;
+            took = __builtin_amdgcn_readfirstlane((int)took);
+            if (took) sat_clear(S, nwg, lane, 64);
+        });
+        if (clears && took) sat_set_ready(S, p.call, lane, 64);
         __syncthreads();
         unsigned late = 0u;
         if (own) {
@@ -684,22 +737,30 @@ __global__ void __launch_bounds__(64 * TR * TC, 4) sat_fused_kernel(SatFusedArgs
             SAT_STAMP(S, wg, 2);
             // arrive, then wait (bounded) for the others
             if (tid == 0) {
+                unsigned long long* const ready = sat_ready(S, wg & (SatSync::kGo - 1));
+                for (int polls = 0; __hip_atomic_load(ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != p.call; ++polls) {
+                    if (polls == kSatClaimPolls && sat_take(S, p.call)) {
+                        sat_clear(S, nwg, 0, 1);
+                        sat_set_ready(S, p.call, 0, 1);
+                    }
+                    __builtin_amdgcn_s_sleep(HB_SAT_POLL_SLEEP);
+                }
                 const int ngroups = p.first < nwg ? 2 : 1, group = wg < p.first ? 0 : 1;
                 const int kl = SatSync::kLeaves / ngroups, kg = SatSync::kGo / ngroups;
                 const int id = group ? wg - p.first : wg, n0 = p.first, n1 = nwg - p.first, n = group ? n1 : n0;
                 const int nleaf = min(n, kl), lf = id % nleaf;
                 const int leaf_target = (n - lf + nleaf - 1) / nleaf;
                 bool all = ngroups == 1 || group == 1;    // passing the wait, it knows that every region is published
-                auto arrive = [&](unsigned* w) { return (int)__hip_atomic_fetch_add(w, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1; };
                 auto raise = [&](int g) {
                     for (int i = 0; i < kg; ++i) st_agent(&S->go[SatSync::kLine * (g * kg + i)], 1u);
+                    if (g == ngroups - 1) sat_forget_call(S);
                 };
-                if (arrive(&S->leaf[SatSync::kLine * (group * kl + lf)]) == leaf_target &&
-                    arrive(&S->root[SatSync::kRoot * group]) == nleaf + group) {
+                if ((int)sat_add(&S->leaf[SatSync::kLine * (group * kl + lf)]) == leaf_target &&
+                    (int)sat_add(&S->root[SatSync::kRoot * group]) == nleaf + group) {
                     raise(group);
                     if (ngroups == 2 && group == 0) {     // the first group is one more arrival of the second
                         stores_done();
-                        if (arrive(&S->root[SatSync::kRoot]) == min(n1, kl) + 1) {
+                        if ((int)sat_add(&S->root[SatSync::kRoot]) == min(n1, kl) + 1) {
                             raise(1);
                             all = true;
                         }
@@ -944,7 +1005,6 @@ static hb_status sat_fused_launch(const SatFusedArgs& f, hipStream_t st) {
     const size_t lds = sizeof(SatFusedLds<2, TC>);
     hb_status s = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds);
     if (s != HB_OK) return s;
-    hipLaunchKernelGGL(sat_sync_clear_kernel, dim3(1), dim3(256), 0, st, f.sync);
     hipLaunchKernelGGL(kernel, dim3(f.nsw * f.nbw), dim3(64 * 2 * TC), lds, st, f);
     return launch_status();
 }
@@ -974,6 +1034,15 @@ static int sat_fused_capacity(int t) {
     return c.shape4;
 }
 
+// A number that no other launch of the process has, and that what lies in memory has by a chance of 2^-64.
+static unsigned long long sat_next_call() {
+    static std::atomic<unsigned long long> count{(unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count()};
+    unsigned long long z = (count.fetch_add(1) + (unsigned long long)reinterpret_cast<uintptr_t>(&count)) * 0x9e3779b97f4a7c15ull;
+    z = (z ^ (z >> 31)) * 0xbf58476d1ce4e5b9ull;          // every step a bijection
+    z ^= z >> 29;
+    return z ? z : 1;
+}
+
 static hb_status sat_launch_mfma(const SatArgs& a, void* ws, hipStream_t st) {
     // Rows whose 16-byte pieces are misaligned leave through the L2, which puts the lines that two pieces share together
     // (4095 x 4093 38.5 us, streamed 49), unless the output fits the memory-side cache (2047 x 2045 20.8, streamed 19.0).
@@ -982,6 +1051,7 @@ static hb_status sat_launch_mfma(const SatArgs& a, void* ws, hipStream_t st) {
     if (t) {
         SatFusedArgs f;
         sat_prepare_fused(f, a, ws, t, g_sat_wait_limit.load());
+        f.call = sat_next_call();
         if (f.nsw * f.nbw <= std::min(sat_fused_capacity(t), (int)SatSync::kMaxRegions)) {
             if (t == 2) return stream_stores ? sat_fused_launch<2, true>(f, st) : sat_fused_launch<2, false>(f, st);
             return stream_stores ? sat_fused_launch<4, true>(f, st) : sat_fused_launch<4, false>(f, st);

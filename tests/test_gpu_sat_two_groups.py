@@ -26,3 +26,31 @@ def test_two_groups_are_exact(H, W, extra, limit):
     want = x.cpu().double().cumsum(0).cumsum(1)
     assert torch.equal(out[:, :W].cpu().double(), want)
     assert bool((out[:, W:] == 7.0).all()), "wrote past the row end"
+
+
+@pytest.mark.parametrize("H,W", [(200, 300), (2817, 2815)])
+def test_replays_with_whatever_the_workspace_holds(H, W):
+    """A captured call replayed on new images, its workspace as the last replay left it, used by an eager call or overwritten."""
+    import torch
+    from paper_2512_02371_amd import hb
+    x = torch.zeros((H, W), dtype=torch.float16, device="cuda")
+    out = torch.empty((H, W), device="cuda")
+    ws = torch.full((hb.hb_sat2d_workspace_size(H, W),), 0xff, dtype=torch.uint8, device="cuda")
+    print(f"hb_sat2d {H}x{W} replayed", flush=True)
+    hb.hb_sat2d(x, out, ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        hb.hb_sat2d(x, out, ws)
+    saved = ws.clone()
+    for i in range(6):
+        x.copy_(torch.rand(H, W, device="cuda") < 0.3)
+        if i == 2:
+            hb.hb_sat2d(x, torch.empty_like(out), ws)
+        elif i == 3:
+            ws.fill_(0x55)
+        elif i == 5:
+            ws.copy_(saved)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out.cpu().double(), x.cpu().double().cumsum(0).cumsum(1)), f"replay {i}"

@@ -128,3 +128,58 @@ def test_workspace_holds_the_tables_of_both_region_shapes():
                 nsw, nbw = up(H, 128), up(W, ew)
                 room = 2 * up(H, ew) * up(W, ew) * ew          # what follows the three-launch tables, at least
                 assert nsw * nbw * (128 + ew + 1) <= three + room, (H, W, tc)
+
+
+class Words:
+    """The words of the wait, with anything in them before the first launch."""
+
+    def __init__(self, seed):
+        rng = random.Random(seed)
+        self.mu = threading.Lock()
+        self.claim, self.ready, self.arrived = (rng.choice((0, 5, 77)) for _ in range(3))
+
+
+def launch(w, call, nwg, slots, patience, rng):
+    sem, seen = threading.Semaphore(slots), []
+
+    def take():
+        with w.mu:
+            mine, w.claim = w.claim != call, call
+        if mine:
+            time.sleep(rng.random() * 3e-4)
+            w.arrived = 0
+            w.ready = call
+
+    def workgroup(wg):
+        with sem:
+            if wg == 0:
+                take()
+            polls = 0
+            while w.ready != call:
+                polls += 1
+                if polls == patience:
+                    take()
+                time.sleep(1e-5)
+            with w.mu:
+                w.arrived += 1
+                seen.append(w.arrived)
+                if w.arrived == nwg:
+                    w.ready = w.claim = 0
+
+    threads = [threading.Thread(target=workgroup, args=(i,), daemon=True) for i in range(nwg)]
+    rng.shuffle(threads)
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(timeout=30)
+        assert not t.is_alive(), "a workgroup never ended"
+    return seen
+
+
+@pytest.mark.parametrize("nwg,slots,patience", [(1, 1, 3), (17, 17, 1000), (17, 4, 3), (40, 1, 2), (40, 40, 1)])
+def test_words_are_cleared_once_before_the_first_arrival(nwg, slots, patience):
+    """Launches with numbers of their own and replays of one number, workgroup 0 first or last to run."""
+    rng = random.Random(nwg + slots)
+    w = Words(nwg)
+    for call in (1001, 1002, 1002, 1002, 1003, 1002):
+        assert launch(w, call, nwg, slots, patience, rng) == list(range(1, nwg + 1))
