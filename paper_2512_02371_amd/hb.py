@@ -127,7 +127,7 @@ def _check(fn: str, code: int) -> None:
 
 # Pointers and the stream handle are passed as plain integers, which ctypes converts to the declared argument
 # types: with torch.cuda.current_stream() and a pointer object per argument the host took 10.5 us for a call of
-# hb_fir1d, now 6.5.  The two functions behind torch.cuda.current_stream() are private: without them it does.
+# hb_fir1d, 6.5 without.  The two functions behind torch.cuda.current_stream() are private: without them it does.
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _device = getattr(torch._C, "_cuda_getDevice", None)
 
@@ -141,27 +141,41 @@ def _stream() -> int:
     return _raw_stream(_device())
 
 
+# On the host a call costs its launch (3.4 us) and what is done here; with two array conversions and an address object per tap
+# array, and a question to the tensor per stride and dimension, that was 3.6 of 7.0 us.
+_U16, _F16 = np.dtype(np.uint16), np.dtype(np.float16)
+
+
 def _taps(t):
-    """Host fp16 bit patterns -> (keep-alive array, address, count)."""
-    a = np.ascontiguousarray(t)
-    if a.dtype == np.float16:
-        a = a.view(np.uint16)
-    a = np.ascontiguousarray(a, dtype=np.uint16)
-    return a, a.ctypes.data, a.size
+    """Host fp16 bit patterns -> (row-major bytes, which ctypes passes by address and the library copies; count)."""
+    if type(t) is not np.ndarray or (t.dtype is not _U16 and t.dtype is not _F16):
+        t = np.asarray(t)
+        if t.dtype != np.float16:
+            t = np.asarray(t, dtype=np.uint16)
+    return t.tobytes(), t.size
 
 
 def _img2d(t, dtype):
-    assert t.is_cuda and t.dim() == 2 and t.dtype == dtype and t.stride(1) == 1, "row-major 2-D CUDA tensor expected"
+    s = t.stride()
+    assert t.is_cuda and len(s) == 2 and t.dtype == dtype and s[1] == 1, "row-major 2-D CUDA tensor expected"
     H, W = t.shape
-    return t.data_ptr(), H, W, t.stride(0)
+    return t.data_ptr(), H, W, s[0]
+
+
+def _planes(t, dtype):
+    """A 3-D tensor of row-major planes -> (address, planes, height, width, row pitch, plane stride)."""
+    s = t.stride()
+    assert t.is_cuda and len(s) == 3 and t.dtype == dtype and s[2] == 1
+    C, H, W = t.shape
+    return t.data_ptr(), C, H, W, s[1], s[0]
 
 
 def _fir(name, inp, out, taps, anchor):
     pi, H, W, ip = _img2d(inp, torch.float16)
     po, Ho, Wo, op = _img2d(out, torch.float32)
     assert (H, W) == (Ho, Wo)
-    keep, pt, n = _taps(taps)
-    _check(name, getattr(load(), name)(pi, po, H, W, ip, op, pt, n, int(anchor), _stream()))
+    bits, n = _taps(taps)
+    _check(name, getattr(_lib or load(), name)(pi, po, H, W, ip, op, bits, n, int(anchor), _stream()))
     return out
 
 
@@ -179,9 +193,9 @@ def _conv2d(name, inp, out, taps2d, anchor_y, anchor_x, shape=lambda H, W: (H, W
     assert shape(H, W) == (Ho, Wo), "output shape"
     k = np.asarray(taps2d)
     assert k.ndim == 2, "kh x kw tap array expected"
-    keep, pt, n = _taps(k)
-    _check(name, getattr(load(), name)(pi, po, H, W, ip, op, pt, int(k.shape[0]), int(k.shape[1]),
-                                        int(anchor_y), int(anchor_x), _stream()))
+    bits, n = _taps(k)
+    _check(name, getattr(_lib or load(), name)(pi, po, H, W, ip, op, bits, k.shape[0], k.shape[1],
+                                               int(anchor_y), int(anchor_x), _stream()))
     return out
 
 
@@ -222,15 +236,12 @@ def hb_dct_denoise_workspace_size(C, H, W):
 
 
 def _dct(name, inp, out, threshold, workspace):
-    assert inp.is_cuda and inp.dim() == 3 and inp.dtype == torch.float16 and inp.stride(2) == 1
-    assert out.is_cuda and out.dim() == 3 and out.dtype == torch.float32 and out.stride(2) == 1
-    assert tuple(inp.shape) == tuple(out.shape)
+    pi, C, H, W, ip, il = _planes(inp, torch.float16)
+    po, Co, Ho, Wo, op, ol = _planes(out, torch.float32)
+    assert (C, H, W) == (Co, Ho, Wo)
     assert workspace.is_cuda and workspace.dtype == torch.uint8 and workspace.is_contiguous()
-    C, H, W = (int(v) for v in inp.shape)
-    _check(name, getattr(load(), name)(
-        inp.data_ptr(), out.data_ptr(), C, H, W,
-        int(inp.stride(1)), int(inp.stride(0)), int(out.stride(1)), int(out.stride(0)), float(threshold),
-        workspace.data_ptr(), int(workspace.numel()), _stream()))
+    _check(name, getattr(_lib or load(), name)(pi, po, C, H, W, ip, il, op, ol, float(threshold),
+                                               workspace.data_ptr(), workspace.numel(), _stream()))
     return out
 
 
@@ -255,8 +266,8 @@ def _iir2(name, inp, out, alpha, beta, workspace):
     po, Co, To, op = _img2d(out, torch.float32)
     assert (C, T) == (Co, To)
     assert workspace.is_cuda and workspace.dtype == torch.uint8 and workspace.is_contiguous()
-    _check(name, getattr(load(), name)(pi, po, C, T, ip, op, float(alpha), float(beta),
-                                        workspace.data_ptr(), int(workspace.numel()), _stream()))
+    _check(name, getattr(_lib or load(), name)(pi, po, C, T, ip, op, float(alpha), float(beta),
+                                               workspace.data_ptr(), workspace.numel(), _stream()))
     return out
 
 
@@ -288,22 +299,23 @@ def hb_lanczos3_matrix(n_in, n_out):
     return start, coef
 
 
+def _matrix(start, coef, n):
+    """A banded matrix of n rows -> (address of its starts, of its coefficients, band)."""
+    assert start.is_cuda and start.dtype == torch.int32 and start.is_contiguous() and start.shape == (n,)
+    shape = coef.shape
+    assert coef.is_cuda and coef.dtype == torch.float16 and coef.is_contiguous() and len(shape) == 2 and shape[0] == n
+    return start.data_ptr(), coef.data_ptr(), shape[1]
+
+
 def _resize(name, inp, out, workspace, start_y, coef_y, start_x, coef_x):
-    assert inp.is_cuda and inp.dim() == 3 and inp.dtype == torch.float16 and inp.stride(2) == 1
-    assert out.is_cuda and out.dim() == 3 and out.dtype == torch.float32 and out.stride(2) == 1
-    C, H, W = (int(v) for v in inp.shape)
-    Co, Ho, Wo = (int(v) for v in out.shape)
+    pi, C, H, W, ip, il = _planes(inp, torch.float16)
+    po, Co, Ho, Wo, op, ol = _planes(out, torch.float32)
     assert C == Co
-    for st, cf, n in ((start_y, coef_y, Ho), (start_x, coef_x, Wo)):
-        assert st.is_cuda and st.dtype == torch.int32 and st.is_contiguous() and tuple(st.shape) == (n,)
-        assert cf.is_cuda and cf.dtype == torch.float16 and cf.is_contiguous() and cf.dim() == 2 and cf.shape[0] == n
+    py, ky, by = _matrix(start_y, coef_y, Ho)
+    px, kx, bx = _matrix(start_x, coef_x, Wo)
     assert workspace.is_cuda and workspace.dtype == torch.uint8 and workspace.is_contiguous()
-    _check(name, getattr(load(), name)(
-        inp.data_ptr(), out.data_ptr(),
-        workspace.data_ptr(), int(workspace.numel()), C, H, W, Ho, Wo,
-        int(inp.stride(1)), int(inp.stride(0)), int(out.stride(1)), int(out.stride(0)),
-        start_y.data_ptr(), coef_y.data_ptr(), int(coef_y.shape[1]),
-        start_x.data_ptr(), coef_x.data_ptr(), int(coef_x.shape[1]), _stream()))
+    _check(name, getattr(_lib or load(), name)(pi, po, workspace.data_ptr(), workspace.numel(), C, H, W, Ho, Wo,
+                                               ip, il, op, ol, py, ky, by, px, kx, bx, _stream()))
     return out
 
 
@@ -319,9 +331,9 @@ def _sep(name, inp, out, tx, ax, ty, ay):
     pi, H, W, ip = _img2d(inp, torch.float16)
     po, Ho, Wo, op = _img2d(out, torch.float32)
     assert (H, W) == (Ho, Wo)
-    kx, px, nx = _taps(tx)
-    ky, py, ny = _taps(ty)
-    _check(name, getattr(load(), name)(pi, po, H, W, ip, op, px, nx, int(ax), py, ny, int(ay), _stream()))
+    bx, nx = _taps(tx)
+    by, ny = _taps(ty)
+    _check(name, getattr(_lib or load(), name)(pi, po, H, W, ip, op, bx, nx, int(ax), by, ny, int(ay), _stream()))
     return out
 
 
@@ -343,8 +355,7 @@ def _sat(name, inp, out, workspace):
     assert (H, W) == (Ho, Wo)
     assert workspace.is_cuda and workspace.is_contiguous()
     nbytes = workspace.numel() * workspace.element_size()
-    _check(name, getattr(load(), name)(pi, po, H, W, ip, op, workspace.data_ptr(),
-                                       nbytes, _stream()))
+    _check(name, getattr(_lib or load(), name)(pi, po, H, W, ip, op, workspace.data_ptr(), nbytes, _stream()))
     return out
 
 
@@ -378,8 +389,7 @@ def _conv(name, x, w, out):
     N, H, W, Ci = x.shape
     Co = w.shape[3]
     assert tuple(w.shape) == (3, 3, Ci, Co) and tuple(out.shape) == (N, H, W, Co)
-    _check(name, getattr(load(), name)(x.data_ptr(), w.data_ptr(),
-                                       out.data_ptr(), N, H, W, Ci, Co, _stream()))
+    _check(name, getattr(_lib or load(), name)(x.data_ptr(), w.data_ptr(), out.data_ptr(), N, H, W, Ci, Co, _stream()))
     return out
 
 
@@ -400,7 +410,7 @@ def _pyr(name, inp, res, down):
         assert (Hd, Wd) == (H // 2, W // 2)
     else:
         pd, dp = None, 0
-    _check(name, getattr(load(), name)(pi, pr, pd, H, W, ip, rp, dp, _stream()))
+    _check(name, getattr(_lib or load(), name)(pi, pr, pd, H, W, ip, rp, dp, _stream()))
     return res
 
 
