@@ -19,3 +19,19 @@ def test_three_scaled_fp16_parts_are_the_fp32_weight():
     assert np.array_equal(hi.astype(np.float64) + lo.astype(np.float64) + rest.astype(np.float64), exact)
     assert not np.array_equal(hi.astype(np.float64) + lo.astype(np.float64), exact)
     assert np.all(np.isfinite(hi))
+
+
+def test_the_kernel_s_tables_are_the_windowed_dct():
+    """The tables in the source: E and its transpose to the last bit of fp32, the window."""
+    import os
+    import re
+    src = open(os.path.join(os.path.dirname(__file__), "..", "paper_2512_02371_amd", "csrc", "dct.hip")).read()
+
+    def table(name):
+        body = re.search(name + r"\[\d+\] = \{([^}]*)\}", src).group(1)
+        return np.array([float(v.rstrip("f")) for v in re.findall(r"[-+.\de]+f", body)], np.float64).astype(np.float32)
+
+    e = windowed_dct()
+    assert np.array_equal(table("kDctE").reshape(16, 16), e)
+    assert np.array_equal(table("kDctEt").reshape(16, 16), e.T)
+    assert np.array_equal(table("kDctW"), np.sin(np.pi * (np.arange(16) + 0.5) / 16).astype(np.float32))
