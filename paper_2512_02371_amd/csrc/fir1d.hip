@@ -112,33 +112,38 @@ __global__ void __launch_bounds__(256) fir1d_mfma_kernel(FirArgs p) {
 //
 // In the kernel above every product loads its own window, NK loads of 16 rows x 64 bytes per
 // 16 x 16 outputs, and with long filters those loads are all the kernel does (256 taps: 9 KB requested
-// per 1 KB of outputs; the matrix units idle).  But window u (the 32 pixels from 16 u - aw on) is the
-// kk-th window of tile u - 2 kk for every kk < NK: here a wave walks along a run of tiles of one
-// 16-row group, loads each window ONCE and multiplies it with all NK fragments, each product going
-// to the accumulator of its own tile.  2 NK - 1 tiles are open at any time (a ring of 2 NK
-// accumulators, indexed at compile time: the walk is unrolled over one turn of the ring); a tile is
-// complete 2 NK - 2 steps after its first window, and completed tiles leave in pairs through the LDS
-// patch as 128-byte runs.  A pixel is requested twice (windows of 32 at a stride of 16) instead of
-// 2 NK times.  Windows that reach over the row ends are shifted into place when they are used:
+// per 1 KB of outputs; the matrix units idle).  Here a wave walks along a run of tiles of one
+// 16-row group and loads every pixel ONCE, in windows of 32 side by side.  Tiles go in PAIRS: window v (the 32 pixels from
+// 32 v - aw on) is the kk-th window of the even tile of pair v - kk for every kk < NK, and of the odd one, 16 pixels further, for
+// every kk < NKO, with Toeplitz fragments that are shifted by 16; NKO is NK or NK + 1.  So a window feeds up to 2 NKO products, each
+// into the accumulator of its own tile.  NKO pairs are open at any time (a ring
+// of accumulators, indexed at compile time: the walk is unrolled over one turn of the ring); a pair is
+// complete NKO - 1 steps after its first window and leaves through the LDS
+// patch as 128-byte runs.  Windows that reach over the row ends are shifted into place when they are used:
 // the Toeplitz matrix is indexed by window position, so the border rule needs nothing else.
-// Runs start 2 NK - 2 windows early (products into accumulators of tiles left of the run are
+// Runs start NKO - 1 windows early (products into accumulators of tiles left of the run are
 // computed and dropped), the price of cutting a row into several tasks.
+// What bounds it: the bytes that the waves have in flight, NKO KB each.  With windows of 32 pixels at a stride of 16, one step a
+// tile, every pixel was requested twice and half of those bytes were the same ones: 4096 x 4096, 40 / 64 / 256 taps 18.6 / 18.8 / 25.2
+// -> 17.3 / 17.6 / 22.3 us, 8192 x 8192, 30 taps 124 -> 101, 4095 x 4095, 100 taps 37.8 -> 25.9.  Twice as many windows in flight: no
+// faster (256 taps 24.6 us).
 // Waves per workgroup of the walk: the longest filters (few, long-lived waves of 100+ registers) run
 // best as single-wave workgroups, the shorter ones four to a workgroup (measured).
 constexpr int fir_walk_waves(int nk) { return nk >= 7 ? 1 : 4; }
 
-template <int NK>
+template <int NK, int NKO>
 __global__ void __launch_bounds__(64 * fir_walk_waves(NK)) fir1d_walk_kernel(FirArgs p) {
-    constexpr int R = 2 * NK;
     constexpr int WV = fir_walk_waves(NK);
     __shared__ __attribute__((aligned(16))) float s_patch[WV][RowPatch<4>::kFloats];
     const int lane = threadIdx.x & 63;
     const int c = lane & 15, g = lane >> 4;
     const int e = p.anchor & 1;
     const int aw = p.anchor + e;
-    half8 coef[NK];
+    half8 even[NK], odd[NKO];
 #pragma unroll
-    for (int kk = 0; kk < NK; ++kk) coef[kk] = tap_run(p.taps.tab, 32 * kk + 8 * g - c - e);
+    for (int kk = 0; kk < NK; ++kk) even[kk] = tap_run(p.taps.tab, 32 * kk + 8 * g - c - e);
+#pragma unroll
+    for (int kk = 0; kk < NKO; ++kk) odd[kk] = tap_run(p.taps.tab, 32 * kk - 16 + 8 * g - c - e);
 
     const int wgpos = xcd_contiguous(blockIdx.x, gridDim.x);
     const int task = __builtin_amdgcn_readfirstlane(wgpos * WV + (threadIdx.x >> 6));
@@ -146,18 +151,17 @@ __global__ void __launch_bounds__(64 * fir_walk_waves(NK)) fir1d_walk_kernel(Fir
     const int rg = task / p.nruns, run = task - rg * p.nruns;
     const int t0 = run * p.run_tiles;                     // first tile of the run
     const int L = min(p.run_tiles, p.ntiles - t0);        // its tiles
-    const int nsteps = L + 2 * (NK - 1);                  // windows t0 .. t0 + nsteps - 1
+    const int npairs = (L + 1) / 2, nsteps = npairs + NKO - 1;        // pairs of tiles, windows
     const int y0 = 16 * rg;
     const uint32_t rowoff = (uint32_t)min(y0 + c, p.H - 1) * (uint32_t)p.in_pitch * 2u;
     float* patch = s_patch[threadIdx.x >> 6];
     const bool rows16 = y0 + 16 <= p.H;
 
-    auto load_window = [&](int u) { return fir_request(p, rowoff, 16 * (t0 + u) - aw + 8 * g); };
-    auto window_inside = [&](int u) {                     // uniform
-        const int xs = 16 * (t0 + u) - aw;
+    auto load_window = [&](int v) { return fir_request(p, rowoff, 16 * t0 + 32 * v - aw + 8 * g); };
+    auto window_inside = [&](int v) {                     // uniform
+        const int xs = 16 * t0 + 32 * v - aw;
         return xs >= 0 && xs + 32 <= p.W;
     };
-    floatx4 done[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
     // Rows that start inside a 128-byte line: columns 32 k + o .. 32 k + o + 31 of the run are a line of the row, o its
     // first column's distance to the next line.  The patch keeps the last two pairs, and with pair k the line that ends in
     // it leaves, whole: pairs stored as they are would write two parts of a line (100 taps, 4095 x 4095 63 us
@@ -188,16 +192,16 @@ __global__ void __launch_bounds__(64 * fir_walk_waves(NK)) fir1d_walk_kernel(Fir
         }
         wave_lds_fence();
     };
-    // the pair of tiles tb, tb + 1 (tb even, relative to the run), completed in the two steps before
-    auto store_pair = [&](int tb) {
-        if (tb < 0 || tb >= L) return;
-        const int x = 16 * (t0 + tb);
+    // pair j of the run, completed in the step before
+    auto store_pair = [&](int j, const floatx4 (&done)[2]) {
+        if (j < 0 || j >= npairs) return;
+        const int tb = 2 * j, x = 16 * (t0 + tb);
         if (!p.lines) {                                   // uniform
 #pragma unroll
             for (int w = 0; w < 2; ++w)
                 *reinterpret_cast<floatx4*>(patch + c * RowPatch<4>::kPitch + ((16 * (tb + w)) & 63) + 4 * g) = done[w];
             wave_lds_fence();
-            store_line(tb / 2);
+            store_line(j);
         } else if (rows16 && x + 32 <= p.W) {
             store_rows_via_lds<2, true>(patch, p.out + (int64_t)y0 * p.out_pitch + x, (uint32_t)p.out_pitch, done, lane);
         } else if (y0 + c < p.H) {
@@ -207,36 +211,35 @@ __global__ void __launch_bounds__(64 * fir_walk_waves(NK)) fir1d_walk_kernel(Fir
         }
     };
 
-    floatx4 acc[R];
-#pragma unroll
-    for (int i = 0; i < R; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
-    // NK windows in flight: the longer the filter, the more products a window feeds and the further
+    floatx4 acc[NKO][2];
+    // as many windows in flight as a tile needs: the longer the filter, the more products a window feeds and the further
     // ahead the loads have to run to cover their latency
-    half8 win[NK];
+    half8 win[NKO];
 #pragma unroll
-    for (int i = 0; i < NK; ++i) win[i] = load_window(i < nsteps ? i : 0);
+    for (int i = 0; i < NKO; ++i) win[i] = load_window(min(i, nsteps - 1));
     int ub = 0;
-    // one step: window ub + S against every fragment; the tile whose last window this was leaves its slot
+    // one step: window v = ub + S against every fragment, pair v - kk in slot (v - kk) % NKO; the pair before it in slot S is complete
     auto step = [&](auto sc) {
         constexpr int S = decltype(sc)::value;
-        const int u = ub + S;
-        if (S % 2 == 0) store_pair(u - R);                // before the loads: loads and stores share one counter
-        if (u < nsteps) {
-            if (!window_inside(u)) win[S % NK] = fir_clamped(p, win[S % NK], 16 * (t0 + u) - aw + 8 * g);
+        const int v = ub + S;
+        store_pair(v - NKO, acc[S]);                      // before the loads: loads and stores share one counter
+        if (v < nsteps) {
+            if (!window_inside(v)) win[S] = fir_clamped(p, win[S], 16 * t0 + 32 * v - aw + 8 * g);
             auto product = [&](auto kc) {
-                constexpr int KK = decltype(kc)::value, slot = ((S - 2 * KK) % R + R) % R;
-                acc[slot] = mfma16x16x32(coef[KK], win[S % NK], acc[slot]);
+                constexpr int KK = decltype(kc)::value, slot = (S - KK + NKO) % NKO;
+                const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+                if constexpr (KK < NK) acc[slot][0] = mfma16x16x32(even[KK], win[S], KK == 0 ? zero : acc[slot][0]);
+                acc[slot][1] = mfma16x16x32(odd[KK], win[S], KK == 0 ? zero : acc[slot][1]);
             };
-            unrolled_steps<NK>(product);
-            constexpr int last = (S + 2) % R;             // slot of tile u - 2 (NK - 1)
-            done[S & 1] = acc[last];
-            acc[last] = floatx4{0.f, 0.f, 0.f, 0.f};
-            if (u + NK < nsteps) win[S % NK] = load_window(u + NK);
+            unrolled_steps<NKO>(product);
+            if (v + NKO < nsteps) win[S] = load_window(v + NKO);
         }
     };
+#pragma unroll
+    for (int i = 0; i < NKO; ++i) acc[i][0] = acc[i][1] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-    for (ub = 0; ub < nsteps; ub += R) unrolled_steps<R>(step);
-    store_pair(ub - R);
+    for (ub = 0; ub < nsteps; ub += NKO) unrolled_steps<NKO>(step);
+    store_pair(ub - NKO, acc[0]);
     if (!p.lines) store_line((L + 1) / 2);                // what is left of the last line
 }
 
@@ -322,18 +325,17 @@ static hb_status fir1d_prepare(FirArgs& a, const hb_half* in, float* out, int H,
     a.nct = ceil_div(W, 16 * HB_FIR_TILES);
     if ((int64_t)rowsteps * a.nct > 0x7fffffff / 2) return HB_ERR_UNSUPPORTED;
     a.ntasks = rowsteps * a.nct;
-    // The walk of long filters: runs of an even number of tiles, two waves per SIMD in all.  More of them only walk more
-    // windows ahead of their run (4096 x 4096, 128 / 256 taps with the input in the memory-side cache: 20.2 / 24.5 us, with
-    // four waves per SIMD 25.8 / 32.0), fewer leave the chip idle (24.7 / 27.7 with one; 512 x 512 with 256 taps 15 us with
-    // one run per row group, 10 so).  The shorter filters, whose registers allow four, take four on large images of
-    // whole lines: more bytes in flight (8192 x 4096, 64 taps, input in the memory-side cache / in memory 41 / 62 us with two,
-    // 34 / 54 with four; 4096 x 4096 18.8 / 28.9, 19.7 / 27.5; rows inside lines 42 / 44 us from memory).  Runs shorter than
+    // The walk of long filters: runs of an even number of tiles.  More waves have more bytes in flight and walk more windows ahead
+    // of their runs.  From four windows on one wave per SIMD in all (4096 x 4096, 256 / 200 taps 22.8 / 21.0 us, 25.1 / 23.8 with
+    // two; 1749 x 2603, 150 taps 12.7, 16.6; with three quarters of one 4096 x 4096 23.9 / 20.5, but 8192 x 4096, 256 taps 50.2
+    // against 38.4).  Shorter filters two (4096 x 4096, 40 / 80 taps 17.3 / 18.6, with one 18.3 / 19.1), and four on
+    // large images of whole lines (8192 x 4096, 64 taps in memory 54 us against 62 when it was measured).  Runs shorter than
     // the windows ahead of them only where there are too few waves otherwise (1749 x 2603, 256 taps 25.9 with runs of 10
-    // tiles, 20.0 with 20).  Images of a few rows, most of whose lanes are idle, take longer runs (1 x 1000000, 256 taps 24 ->
-    // 18 us).
+    // tiles, 20.0 with 20).  Images of a few rows, most of whose lanes are idle, take two or four (1 x 1000000, 100 taps 10.7 us,
+    // 13.4 with one) and longer runs (256 taps 24 -> 18).
     a.ntiles = ceil_div(W, 16);
     const int nk = ceil_div(15 + ntaps + (anchor & 1), 32);
-    int runs = std::min((nk <= 3 && (H < 16 || (a.lines && (int64_t)H * W > (24 << 20))) ? 16 : 8) * num_cu() / rowsteps, a.ntiles / 4);
+    int runs = std::min((nk >= 4 ? (H < 16 ? 8 : 4) : H < 16 || (a.lines && (int64_t)H * W > (24 << 20)) ? 16 : 8) * num_cu() / rowsteps, a.ntiles / 4);
     const int long_runs = a.ntiles / ((H < 16 ? 4 : 2) * nk);
     if ((int64_t)rowsteps * long_runs >= 3 * num_cu()) runs = std::min(runs, long_runs);
     runs = std::max(1, runs);
@@ -368,19 +370,24 @@ extern "C" hb_status hb_fir1d(const hb_half* in, float* out, int H, int W,
     if (W < kFirMinWidth || (nk >= 4 && W > 32 && W <= 128 && !a.lines && H <= 32 * num_cu()))
         return hb_fir1d_valu(in, out, H, W, in_pitch, out_pitch, taps_host, ntaps, anchor, stream);
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+    const int nko = ceil_div(31 + ntaps + (anchor & 1), 32);
+#define HB_FIR_WALK_AS(N, NO)                                                                     \
+    hipLaunchKernelGGL((fir1d_walk_kernel<N, NO>), dim3(ceil_div(a.wtasks, fir_walk_waves(N))), dim3(64 * fir_walk_waves(N)), 0, st, a)
 #define HB_FIR_WALK(N)                                                                            \
     case N:                                                                                       \
-        hipLaunchKernelGGL(fir1d_walk_kernel<N>, dim3(ceil_div(a.wtasks, fir_walk_waves(N))),     \
-                           dim3(64 * fir_walk_waves(N)), 0, st, a);                               \
+        if (nko > N) HB_FIR_WALK_AS(N, N + 1);                                                    \
+        else HB_FIR_WALK_AS(N, N);                                                                \
         break;
     switch (nk) {
         // one window per tile: nothing to share between tiles, every wave takes one strip of tiles
         case 1: hipLaunchKernelGGL(fir1d_mfma_kernel, dim3(ceil_div(a.ntasks, 4)), dim3(256), 0, st, a); break;
         // long filters: the walk along the row, every window loaded once
-        HB_FIR_WALK(2) HB_FIR_WALK(3) HB_FIR_WALK(4) HB_FIR_WALK(5) HB_FIR_WALK(6) HB_FIR_WALK(7) HB_FIR_WALK(8) HB_FIR_WALK(9)
+        HB_FIR_WALK(2) HB_FIR_WALK(3) HB_FIR_WALK(4) HB_FIR_WALK(5) HB_FIR_WALK(6) HB_FIR_WALK(7) HB_FIR_WALK(8)
+        case 9: HB_FIR_WALK_AS(9, 9); break;
         default: return HB_ERR_UNSUPPORTED;
     }
 #undef HB_FIR_WALK
+#undef HB_FIR_WALK_AS
     return launch_status();
 }
 

@@ -17,7 +17,7 @@ namespace hb {
 // kTapPad + t holds taps[t] for 0 <= t < ntaps and zero for every other t in
 // [-kTapPad, MAXT + 48)), from which a Toeplitz fragment is eight consecutive entries.
 // MAXT is the largest tap count of the entry point (hb_fir1d: 256, hb_sepblur: 64 per axis).
-constexpr int kTapPad = 16;
+constexpr int kTapPad = 32;
 template <int MAXT>
 struct TapsT {
     uint16_t tab[kTapPad + MAXT + 48];
