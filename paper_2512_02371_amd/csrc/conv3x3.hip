@@ -278,6 +278,9 @@ __global__ void __launch_bounds__(kCvThreads) conv3x3_mfma_kernel(ConvArgs p) {
             for (int v = 0; v < 16; ++v) acc[u][v] = 0.f;
         cv_rows(s_ring, row, wf, L, acc);
         __builtin_amdgcn_sched_barrier(0);
+        // The stage is free once every wave has read the previous tile out of it: met here, after the products, and not at the end of
+        // a turn, so that the stores go out while other waves multiply (8 x 56 x 56 8.6 -> 8.3 us, 700 x 1300 75.9 -> 74.7).
+        if (k > 0) asm volatile("s_barrier" ::: "memory");
         // accumulators -> stage: lane (c32, h) holds channels 32 j + 8 q + 4 h + (0..3) of pixel c32
 #pragma unroll
         for (int u = 0; u < 2; ++u)
@@ -305,7 +308,6 @@ __global__ void __launch_bounds__(kCvThreads) conv3x3_mfma_kernel(ConvArgs p) {
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4s, v), orsrc, ovoff,
                                                    osoff + (uint32_t)(2 * i) * (uint32_t)(p.W * kCvC * 2), 0);
         }
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // stage read, free for the next tile
         rb += 8;
         if (rb >= kCvRing) rb -= kCvRing;
     }
