@@ -697,7 +697,7 @@ __global__ void __launch_bounds__(64 * TR * TC, 4) sat_fused_kernel(SatFusedArgs
         // The last wave of workgroup 0 clears the words of the wait on the side: it asks for the task, requests its pixels, clears, and
         // says so when its tile is done (clearing first, its pixels came last and everybody waited: 4096 x 4096 26.9 us).
         if (own && wg >= p.first) __builtin_amdgcn_s_sleep(kSatSecondDelay);
-        const bool clears = own && wg == 0 && wv == kWaves - 1;
+        const bool clears = own && nwg > 1 && wg == 0 && wv == kWaves - 1;
         bool took = false;
         if (clears && lane == 0) took = sat_take(S, p.call);
         sat_fused_local<TR, TC>(p, L, kRH * sw + kSatTile * ts, kRW * bw + kSatTile * tb, ts, tb, lane, Lt, [&]() {
@@ -708,7 +708,7 @@ __global__ void __launch_bounds__(64 * TR * TC, 4) sat_fused_kernel(SatFusedArgs
         if (clears && took) sat_set_ready(S, p.call, lane, 64);
         __syncthreads();
         unsigned late = 0u;
-        if (own) {
+        if (own && nwg > 1) {                             // one region: nobody to wait for
             SAT_STAMP(S, wg, 1);
             // publish the region's sums: the tiles' last columns added across a tile row, last rows down a tile column
             if (tid < kRH) {
@@ -955,8 +955,8 @@ static hb_status sat_prepare(SatArgs& a, const hb_half* in, float* out, int H, i
 }
 
 // The one-launch tables lie where the three-launch tables would, their SatSync at the end of the workspace.
-static void sat_prepare_fused(SatFusedArgs& f, const SatArgs& a, void* ws, int t, int wait_limit) {
-    const int eh = kSatTile * 2, ew = kSatTile * t;
+static void sat_prepare_fused(SatFusedArgs& f, const SatArgs& a, void* ws, int tc, int wait_limit) {
+    const int eh = kSatTile * 2, ew = kSatTile * tc;
     f.in = a.in;
     f.out = a.out;
     f.H = a.H;
@@ -965,13 +965,13 @@ static void sat_prepare_fused(SatFusedArgs& f, const SatArgs& a, void* ws, int t
     f.out_pitch = a.out_pitch;
     f.nsw = ceil_div(a.H, eh);
     f.nbw = ceil_div(a.W, ew);
-    f.first = t == 4 ? (f.nsw + 1) / 2 * f.nbw : f.nsw * f.nbw;
+    f.first = tc == 4 ? (f.nsw + 1) / 2 * f.nbw : f.nsw * f.nbw;
     f.Hr = f.nsw * eh;
     f.Wr = f.nbw * ew;
     f.RS = reinterpret_cast<float*>(ws);
     f.CS = f.RS + (size_t)f.nbw * f.Hr;
     f.TOT = f.CS + (size_t)f.nsw * f.Wr;
-    f.sync = reinterpret_cast<SatSync*>(f.RS + ((sat_workspace_floats(a.H, a.W) + 63) & ~(size_t)63) + sat_fused_table_floats(a.H, a.W, t));
+    f.sync = reinterpret_cast<SatSync*>(f.RS + ((sat_workspace_floats(a.H, a.W) + 63) & ~(size_t)63) + sat_fused_table_floats(a.H, a.W, tc));
     f.wait_limit = wait_limit;
 }
 
@@ -1047,9 +1047,18 @@ static hb_status sat_launch_mfma(const SatArgs& a, void* ws, hipStream_t st) {
     // Rows whose 16-byte pieces are misaligned leave through the L2, which puts the lines that two pieces share together
     // (4095 x 4093 38.5 us, streamed 49), unless the output fits the memory-side cache (2047 x 2045 20.8, streamed 19.0).
     const bool stream_stores = (a.out_pitch % 4 == 0 && aligned_to(a.out, 16)) || (int64_t)a.H * a.W * 4 <= (32 << 20);
+    SatFusedArgs f;
+    // An image of at most 128 x 256 pixels is one region, which publishes and waits for nothing (100 x 100 9.6 us, 6.7 so; 128 x 256, two
+    // regions before, 9.2 and 8.0; a region of 256 x 256 for 255 x 201 17.2, four of 128 x 128 11.5).
+    if (a.H <= 128 && a.W <= 256) {
+        const int tc = a.W <= 128 ? 2 : 4;
+        sat_prepare_fused(f, a, ws, tc, 0);
+        f.call = 0;
+        if (tc == 2) return stream_stores ? sat_fused_launch<2, true>(f, st) : sat_fused_launch<2, false>(f, st);
+        return stream_stores ? sat_fused_launch<4, true>(f, st) : sat_fused_launch<4, false>(f, st);
+    }
     const int t = sat_fused_shape(a.H, a.W);
     if (t) {
-        SatFusedArgs f;
         sat_prepare_fused(f, a, ws, t, g_sat_wait_limit.load());
         f.call = sat_next_call();
         if (f.nsw * f.nbw <= std::min(sat_fused_capacity(t), (int)SatSync::kMaxRegions)) {

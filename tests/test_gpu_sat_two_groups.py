@@ -1,4 +1,4 @@
-"""hb_sat2d where its regions of 128 x 256 pixels form two groups: one region row (a single group), two, odd numbers of them,
+"""hb_sat2d where an image is one region and where its regions of 128 x 256 pixels form two groups: one region row (a single group), two, odd numbers of them,
 ragged ends and the most that are resident, waiting or giving up at once.  0/1 images: every partial sum stays below
 2^24, so fp32 sums in any order are exact and the table is compared bit for bit."""
 import pytest
@@ -7,7 +7,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("limit", [0, -1])                    # the default, "stop waiting at once"
-@pytest.mark.parametrize("H,W,extra", [(128, 32768, 0), (129, 32765, 3), (300, 32001, 0), (16384, 500, 0), (2817, 2815, 5),
+@pytest.mark.parametrize("H,W,extra", [(1, 129, 0), (128, 256, 0), (128, 257, 3), (129, 256, 0), (127, 128, 1), (128, 32768, 0), (129, 32765, 3), (300, 32001, 0), (16384, 500, 0), (2817, 2815, 5),
                                        (4096, 4096, 0), (4095, 4093, 1)])
 def test_two_groups_are_exact(H, W, extra, limit):
     import torch
