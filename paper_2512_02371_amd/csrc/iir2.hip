@@ -40,7 +40,7 @@ struct IirArgs {
     float bpow[4][4];                         // state map over 2^j blocks, j = 0..3 (in-tile scan)
     float bsel[16][4];                        // state map over b blocks, b = 0..15
     float ca[kIirBlock], cb[kIirBlock];       // response of output i to the initial state (Y_-1, Y_-2)
-    uint16_t thi[kIirBlock], tlo[kIirBlock];  // impulse response h_0..h_31 as rounded fp16 + rounded remainder
+    uint16_t thi[2 * kIirBlock], tlo[2 * kIirBlock];   // impulse response h_31..h_0, then zeros, as rounded fp16 + rounded remainder
     float alpha, beta;
 };
 
@@ -53,13 +53,10 @@ __device__ __forceinline__ State2 iir_step(const float (&m)[4], State2 s, float 
 }
 
 // A-operand fragment of the triangular Toeplitz matrix for output rows 16 hh + c: lane (c, g) holds
-// T(16 hh + c, 8g + i) = h_{16 hh + c - 8g - i} (0 above the diagonal).
-__device__ __forceinline__ half8 iir_fragment(const uint16_t (&t)[kIirBlock], int hh, int lane) {
-    const int d0 = 16 * hh + (lane & 15) - 8 * (lane >> 4);
-    half8 f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) f[i] = (d0 - i >= 0 && d0 - i < kIirBlock) ? __builtin_bit_cast(half_t, t[d0 - i]) : (half_t)0;
-    return f;
+// T(16 hh + c, 8g + i) = h_{16 hh + c - 8g - i} (0 above the diagonal): eight consecutive entries of the table, one load (with a load
+// per entry 8 x 2^20 samples took 15.5 us, 14.9 so).
+__device__ __forceinline__ half8 iir_fragment(const uint16_t (&t)[2 * kIirBlock], int hh, int lane) {
+    return *reinterpret_cast<const half8_u*>(t + kIirBlock - 1 - 16 * hh - (lane & 15) + 8 * (lane >> 4));
 }
 
 // The 512 samples of a tile as the B operand X^T: lane (c = block, g) holds samples 32 c + 8 g .. + 7
@@ -151,6 +148,19 @@ __device__ __forceinline__ void iir_walk(const IirRun& r, int64_t T, int lane, c
     }
 }
 
+// The end state of a run started from zero, in lane column 15.
+__device__ __forceinline__ State2 iir_end_state(const IirArgs& p, const IirRun& r, const half8 (&first)[kIirAhead], const half8& fhi, const half8& flo, int lane) {
+    State2 s{0.f, 0.f};                                   // lane column 15: the state after the tile
+    iir_walk(r, p.T, lane, first, [&](int, const half8& x) {
+        floatx4 d1 = {0.f, 0.f, 0.f, 0.f};
+        d1 = mfma16x16x32(fhi, x, d1);
+        d1 = mfma16x16x32(flo, x, d1);
+        const State2 e = iir_scan_blocks(p, d1, lane);
+        s = iir_step(p.m512, s, e.a, e.b);
+    });
+    return s;
+}
+
 // 1  end state of every run started from zero
 template <bool SHORT>
 __global__ void __launch_bounds__(256) iir2_state_mfma_kernel(IirArgs p) {
@@ -164,14 +174,7 @@ __global__ void __launch_bounds__(256) iir2_state_mfma_kernel(IirArgs p) {
     half8 first[kIirAhead];
     iir_begin<SHORT>(p, w, lane, r, first);
     const half8 fhi = iir_fragment(p.thi, 1, lane), flo = iir_fragment(p.tlo, 1, lane);
-    State2 s{0.f, 0.f};                                   // lane column 15: the state after the tile
-    iir_walk(r, p.T, lane, first, [&](int, const half8& x) {
-        floatx4 d1 = {0.f, 0.f, 0.f, 0.f};
-        d1 = mfma16x16x32(fhi, x, d1);
-        d1 = mfma16x16x32(flo, x, d1);
-        const State2 e = iir_scan_blocks(p, d1, lane);
-        s = iir_step(p.m512, s, e.a, e.b);
-    });
+    const State2 s = iir_end_state(p, r, first, fhi, flo, lane);
     if (lane == 15) {
         p.end[2 * w] = s.a;
         p.end[2 * w + 1] = s.b;
@@ -295,64 +298,102 @@ __global__ void __launch_bounds__(64 * kIirScanWaves) iir2_scan_kernel(IirArgs p
 // 2 x 2^21 samples 9 us behind 4 us of the launch before it, where the scan of 8192 tile states by one workgroup
 // per channel was another 9 (20.4 -> 13.4 us, the host's rate for two launches; 8 x 2^20 20.4 -> 16.0, a copy of the
 // bytes 9).
-template <bool SHORT>
-__global__ void __launch_bounds__(256) iir2_apply_mfma_kernel(IirArgs p) {
-    __shared__ __attribute__((aligned(16))) float s_patch[4 * RowPatch<2>::kFloats];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int c = lane & 15, g = lane >> 4;
-    const int64_t w = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
-    if (w >= (int64_t)p.C * p.nruns) return;
-    IirRun r;
-    half8 first[kIirAhead];
-    iir_begin<SHORT>(p, w, lane, r, first);
+struct IirCoefs {
     half8 fhi[2], flo[2];
     float ra[2][4], rb[2][4];                 // response of the lane's outputs i = 16 hh + 4 g + j to the block's state
+    float bsel[4];                            // state map over the c blocks before the lane's block
+};
+__device__ __forceinline__ void iir_coefs(const IirArgs& p, int lane, IirCoefs& k) {
+    const int c = lane & 15, g = lane >> 4;
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
-        fhi[hh] = iir_fragment(p.thi, hh, lane);
-        flo[hh] = iir_fragment(p.tlo, hh, lane);
+        k.fhi[hh] = iir_fragment(p.thi, hh, lane);
+        k.flo[hh] = iir_fragment(p.tlo, hh, lane);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            ra[hh][j] = p.ca[16 * hh + 4 * g + j];
-            rb[hh][j] = p.cb[16 * hh + 4 * g + j];
+            k.ra[hh][j] = p.ca[16 * hh + 4 * g + j];
+            k.rb[hh][j] = p.cb[16 * hh + 4 * g + j];
         }
     }
-    float bsel[4];                            // state map over the c blocks before the lane's block
 #pragma unroll
-    for (int i = 0; i < 4; ++i) bsel[i] = p.bsel[c][i];
-    State2 start = iir_state_before(p, p.end + 2 * (int64_t)r.ch * p.nruns, r.index, lane);
+    for (int i = 0; i < 4; ++i) k.bsel[i] = p.bsel[c][i];
+}
+// The outputs of a run from the true state before it.
+__device__ __forceinline__ void iir_outputs(const IirArgs& p, const IirRun& r, const half8 (&first)[kIirAhead], const IirCoefs& k, State2 start,
+                                            float* patch, int lane) {
+    const int c = lane & 15, g = lane >> 4;
     iir_walk(r, p.T, lane, first, [&](int i, const half8& x) {
         floatx4 d[2];
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
             d[hh] = floatx4{0.f, 0.f, 0.f, 0.f};
-            d[hh] = mfma16x16x32(fhi[hh], x, d[hh]);
-            d[hh] = mfma16x16x32(flo[hh], x, d[hh]);
+            d[hh] = mfma16x16x32(k.fhi[hh], x, d[hh]);
+            d[hh] = mfma16x16x32(k.flo[hh], x, d[hh]);
         }
         // state before block c = (tile state carried across c blocks) + (blocks 0 .. c-1 from zero)
         const State2 incl = iir_scan_blocks(p, d[1], lane);
-        const State2 mine = iir_step(bsel, start, iir_row_shr<1>(incl.a), iir_row_shr<1>(incl.b));
+        const State2 mine = iir_step(k.bsel, start, iir_row_shr<1>(incl.a), iir_row_shr<1>(incl.b));
         start = iir_step(p.m512, start, __shfl(incl.a, 15, 64), __shfl(incl.b, 15, 64));
         // lane (c = block, g) holds outputs i = 16 hh + 4 g + j of its block: add the response to the block's state
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) d[hh][j] += ra[hh][j] * mine.a + rb[hh][j] * mine.b;
+            for (int j = 0; j < 4; ++j) d[hh][j] += k.ra[hh][j] * mine.a + k.rb[hh][j] * mine.b;
         const int64_t t = r.t0 + (int64_t)i * kIirTile;
         float* dst = p.out + (int64_t)r.ch * p.out_pitch + t;
         if (t + kIirTile <= p.T) {
             // the tile is 16 rows (blocks) of 32 consecutive samples
-            store_rows_via_lds<2, true>(s_patch + wv * RowPatch<2>::kFloats, dst, kIirBlock, d, lane);
+            store_rows_via_lds<2, true>(patch, dst, kIirBlock, d, lane);
         } else {
 #pragma unroll
             for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const int k = 32 * c + 16 * hh + 4 * g + j;
-                    if (t + k < p.T) dst[k] = d[hh][j];
+                    const int n = 32 * c + 16 * hh + 4 * g + j;
+                    if (t + n < p.T) dst[n] = d[hh][j];
                 }
         }
     });
+}
+
+template <bool SHORT>
+__global__ void __launch_bounds__(256) iir2_apply_mfma_kernel(IirArgs p) {
+    __shared__ __attribute__((aligned(16))) float s_patch[4 * RowPatch<2>::kFloats];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t w = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
+    if (w >= (int64_t)p.C * p.nruns) return;
+    IirRun r;
+    half8 first[kIirAhead];
+    IirCoefs k;                               // requested first: loads arrive in order, and these are quick (2 x 2^21 12.0 -> 11.7 us)
+    iir_coefs(p, lane, k);
+    __builtin_amdgcn_sched_barrier(0);
+    iir_begin<SHORT>(p, w, lane, r, first);
+    const State2 start = iir_state_before(p, p.end + 2 * (int64_t)r.ch * p.nruns, r.index, lane);
+    iir_outputs(p, r, first, k, start, s_patch + wv * RowPatch<2>::kFloats, lane);
+}
+
+// Both in one launch for short signals: a workgroup takes a channel, a wave a run of tiles, of which the first four stay in its
+// registers, and the end states pass through LDS.  One compute unit moves all bytes of a channel, so this is the faster form only
+// while they are few: see the rule at the launch.
+constexpr int kIirChannelWaves = 16;
+__global__ void __launch_bounds__(64 * kIirChannelWaves) iir2_channel_mfma_kernel(IirArgs p) {
+    __shared__ __attribute__((aligned(16))) float s_patch[kIirChannelWaves * RowPatch<2>::kFloats];
+    __shared__ float s_end[kIirChannelWaves][2];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    IirRun r;
+    half8 first[kIirAhead];
+    iir_begin<true>(p, (int64_t)blockIdx.x * p.nruns + wv, lane, r, first);
+    IirCoefs k;
+    iir_coefs(p, lane, k);
+    const State2 e = iir_end_state(p, r, first, k.fhi[1], k.flo[1], lane);
+    if (lane == 15) {
+        s_end[wv][0] = e.a;
+        s_end[wv][1] = e.b;
+    }
+    __syncthreads();
+    State2 start{0.f, 0.f};
+    for (int q = 0; q < wv; ++q) start = iir_step(p.rpow[0], start, s_end[q][0], s_end[q][1]);
+    iir_outputs(p, r, first, k, start, s_patch + wv * RowPatch<2>::kFloats, lane);
 }
 
 // Vector-ALU twin of both launches: a lane owns one block of 32 samples and runs the recursion
@@ -500,8 +541,10 @@ static hb_status iir2_run(bool valu, const hb_half* in, float* out, int C, int64
     }
     for (int i = 0; i < kIirBlock; ++i) {
         if (!(fabs(h[i]) < 3.0e4) || !(fabs(ca[i]) < 1.0e30) || !(fabs(cb[i]) < 1.0e30)) return HB_ERR_UNSUPPORTED;
-        a.thi[i] = float_to_half_bits((float)h[i]);
-        a.tlo[i] = float_to_half_bits((float)(h[i] - (double)half_bits_to_float(a.thi[i])));
+        const int r = kIirBlock - 1 - i;
+        a.thi[r] = float_to_half_bits((float)h[i]);
+        a.tlo[r] = float_to_half_bits((float)(h[i] - (double)half_bits_to_float(a.thi[r])));
+        a.thi[kIirBlock + i] = a.tlo[kIirBlock + i] = 0;
         a.ca[i] = (float)ca[i];
         a.cb[i] = (float)cb[i];
     }
@@ -540,6 +583,11 @@ static hb_status iir2_run(bool valu, const hb_half* in, float* out, int C, int64
     a.run = a.ntiles <= kIirAhead ? kIirAhead : 1;
     auto round = [&]() { return (int64_t)(a.run < kIirAhead ? 8 : 16) * num_cu() * a.run; };
     while (a.ntiles > (int64_t)kIirMaxRuns * a.run || ((int64_t)C * a.ntiles > round() && a.run < a.ntiles)) a.run *= 2;
+    // A workgroup per channel in one launch, while each has a compute unit to itself: runs of up to four tiles, or eight where
+    // most units have one (T = 2500 .. 16384, 1 to 256 channels 10.2 us, 7.0 so; 32768, 1 / 64 / 256 channels 10.0 / 9.1 / 14.8, 8.4 / 9.0 /
+    // 12.4; 65536, 64 / 100 / 200 channels 10.7 / 14.0 / 21.9, 12.9 / 12.9 / 17.7; 400 x 8192 10.3, 11.9).
+    const bool channel = !valu && a.ntiles > kIirAhead && C <= num_cu() && a.ntiles <= (2 * C >= num_cu() ? 8 : 4) * kIirChannelWaves;
+    if (channel) a.run = ceil_div(a.ntiles, kIirChannelWaves);
     a.nruns = (a.ntiles + a.run - 1) / a.run;
     for (int j = 0; j < 7; ++j) {
         const bool used = ((int64_t)a.run << j) < a.ntiles;
@@ -554,6 +602,8 @@ static hb_status iir2_run(bool valu, const hb_half* in, float* out, int C, int64
         hipLaunchKernelGGL(iir2_blocks_valu_kernel<false>, grid(waves), dim3(256), 0, st, a);
         hipLaunchKernelGGL(iir2_scan_kernel, dim3(C), dim3(64 * kIirScanWaves), 0, st, a);
         hipLaunchKernelGGL(iir2_blocks_valu_kernel<true>, grid(waves), dim3(256), 0, st, a);
+    } else if (channel) {
+        hipLaunchKernelGGL(iir2_channel_mfma_kernel, dim3(C), dim3(64 * a.nruns), 0, st, a);
     } else {
         const dim3 g = grid((int64_t)C * a.nruns);
         const bool shorter = a.run < kIirAhead;
