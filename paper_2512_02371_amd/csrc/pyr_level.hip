@@ -25,8 +25,6 @@
 // product (NS + 1 row tiles): it lives for one memory round trip plus its arithmetic, and what keeps the
 // memory busy is the number of such waves.  8192 x 8192 with the coarser level 96 us, a copy of the bytes 73 to 79;
 // 1024 x 1024 5.9, the rate of the host's launches.
-#include <algorithm>
-
 #include "hb_device.hpp"
 #include "hb_host.hpp"
 
@@ -39,7 +37,6 @@ struct PyrArgs {
     int H, W, Hd, Wd;
     int64_t in_pitch, res_pitch, down_pitch;
     int nct, ntasks;   // 32-column strips; strips x segments of 16 NS rows
-    int group;         // neighbouring workgroups that an XCD takes
 };
 
 // w and the two phases of 2w as zero-padded runs: entry kPyrPad + t of a row is its weight t.  A fragment is eight (or
@@ -187,7 +184,9 @@ template <int NS, bool DOWN>
 __global__ void __launch_bounds__(256, 4) pyr_mfma_kernel(PyrArgs p) {
     __shared__ __attribute__((aligned(16))) float s_patch[4][RowPatch<kPyrNW>::kFloats];
     const int lane = threadIdx.x & 63;
-    const int task = __builtin_amdgcn_readfirstlane(xcd_blocked(blockIdx.x, gridDim.x, p.group) * 4 + (threadIdx.x >> 6));
+    // of every 32 workgroups an XCD takes four neighbours: the chip sweeps through the image in launch
+    // order and neighbouring tasks meet in one L2
+    const int task = __builtin_amdgcn_readfirstlane(xcd_blocked(blockIdx.x, gridDim.x, 4) * 4 + (threadIdx.x >> 6));
     if (task >= p.ntasks) return;
     const int seg = task / p.nct, ct = task - seg * p.nct;
     const int x0 = 16 * kPyrNW * ct, Y0 = 16 * NS * seg;
@@ -301,7 +300,7 @@ static hb_status pyr_prepare(PyrArgs& a, const hb_half* in, float* res, hb_half*
     a.in_pitch = in_pitch;
     a.res_pitch = res_pitch;
     a.down_pitch = down_pitch;
-    a.nct = a.ntasks = a.group = 0;
+    a.nct = a.ntasks = 0;
     return HB_OK;
 }
 
@@ -310,10 +309,6 @@ static hb_status pyr_launch(PyrArgs& a, hipStream_t st) {
     const int64_t ntasks = (int64_t)a.nct * ceil_div(a.H, 16 * NS);
     if (ntasks > 0x7fffffff - 4) return HB_ERR_UNSUPPORTED;
     a.ntasks = (int)ntasks;
-    // Of every 8 `group` workgroups an XCD takes `group` neighbours: the chip sweeps through the image in launch
-    // order, and neighbouring tasks meet in one L2, those below each other as well where eight groups are a row of strips
-    // (8192 x 8192 with 4 / 8 / 16 of them 90.8 / 89.3 / 89.7 us, 4096 x 4096 with 2 / 4 / 8 20.9 / 19.9 / 20.2).
-    a.group = std::min(std::max(a.nct / 32, 4), 16);
     const dim3 grid((unsigned)((ntasks + 3) / 4));
     if (a.down) hipLaunchKernelGGL((pyr_mfma_kernel<NS, true>), grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL((pyr_mfma_kernel<NS, false>), grid, dim3(256), 0, st, a);
