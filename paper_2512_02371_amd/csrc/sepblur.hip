@@ -413,9 +413,11 @@ template <int NT>
 static hb_status sep_launch_nt(int nkx, hipStream_t st, SepArgs& a) {
     const bool lines = a.out_pitch % 32 == 0 && aligned_to(a.out, 128);
     if (nkx == 1 && (lines || NT > 3 || (int64_t)a.H * a.W > kSepMarchShortMax)) return sep_launch_one_window<NT>(st, a);
-    // four workgroups per compute unit are resident; segments beyond 8 steps only cost balance (8192 x 4096, 48
-    // taps: 36 us with 8 steps, 42 with the 16 that four workgroups per unit would give)
-    const int64_t rowsteps = ceil_div(a.H, 16), nct = ceil_div(a.W, kSepMarchCols), want = 4 * num_cu();
+    // Segments as long as leaves two workgroups per compute unit: every one requests and filters NT - 1 row tiles ahead of its
+    // own (with the four that are resident, segments half as long, 1079 x 1917, 31 / 60 taps 8.7 / 11.3 us, 7.4 / 8.8 so; 2048 x 2048,
+    // 31 / 64 taps 8.6 / 11.1, 8.1 / 9.8; with one 9.1 / 10.5).  Beyond 8 steps they only cost balance (8192 x 4096, 48
+    // taps: 36 us with 8 steps, 42 with 16).
+    const int64_t rowsteps = ceil_div(a.H, 16), nct = ceil_div(a.W, kSepMarchCols), want = 2 * num_cu();
     const int steps = (int)std::min<int64_t>((rowsteps * nct + want - 1) / want, 8);
     if constexpr (NT <= 3) {
         if (nkx == 1) return sep_launch(sepblur_march_mfma_kernel<1, NT>, st, a, steps, kSepMarchCols, 1);
