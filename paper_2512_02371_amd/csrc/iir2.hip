@@ -12,7 +12,8 @@
 // Two launches: (1) local products, the end state of every run of 512-sample tiles as if it started from zero;
 // (2) the true state before a run from the end states of the runs before it, local products again, block states
 // from the true tile state, outputs = local outputs + response of the block's initial state.  (The vector-ALU twin
-// keeps a launch of its own for the scan of the tile states in between.)
+// keeps a launch of its own for the scan of the tile states in between.)  Short signals of few channels take both steps
+// in one launch, a workgroup per channel, and signals of up to four tiles need the second only.
 //
 // The impulse response is not an fp16 number: T is split into a rounded part and the rounded
 // remainder (two products), which leaves a relative coefficient error of about 2^-22.
@@ -53,10 +54,16 @@ __device__ __forceinline__ State2 iir_step(const float (&m)[4], State2 s, float 
 }
 
 // A-operand fragment of the triangular Toeplitz matrix for output rows 16 hh + c: lane (c, g) holds
-// T(16 hh + c, 8g + i) = h_{16 hh + c - 8g - i} (0 above the diagonal): eight consecutive entries of the table, one load (with a load
-// per entry 8 x 2^20 samples took 15.5 us, 14.9 so).
+// T(16 hh + c, 8g + i) = h_{16 hh + c - 8g - i} (0 above the diagonal): eight consecutive entries of the table.  WIDE: one load (with a
+// load per entry 8 x 2^20 samples took 16.1 us, 15.4 so); a load per entry where the runs are long, see the kernels below.
+template <bool WIDE = true>
 __device__ __forceinline__ half8 iir_fragment(const uint16_t (&t)[2 * kIirBlock], int hh, int lane) {
-    return *reinterpret_cast<const half8_u*>(t + kIirBlock - 1 - 16 * hh - (lane & 15) + 8 * (lane >> 4));
+    if constexpr (WIDE) return *reinterpret_cast<const half8_u*>(t + kIirBlock - 1 - 16 * hh - (lane & 15) + 8 * (lane >> 4));
+    const int d0 = 16 * hh + (lane & 15) - 8 * (lane >> 4);
+    half8 f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) f[i] = (d0 - i >= 0 && d0 - i < kIirBlock) ? __builtin_bit_cast(half_t, t[kIirBlock - 1 - d0 + i]) : (half_t)0;
+    return f;
 }
 
 // The 512 samples of a tile as the B operand X^T: lane (c = block, g) holds samples 32 c + 8 g .. + 7
@@ -114,7 +121,9 @@ struct IirRun {
     int ch, index, n;
 };
 constexpr int kIirAhead = 4;
-// The run of wave w and its first tiles.  SHORT: runs of fewer than kIirAhead tiles.  The tiles that follow are other
+// Runs of fewer than kIirAhead tiles (and single runs), of kIirAhead, of more: the kernels' forms.
+constexpr int kIirShort = 0, kIirEven = 1, kIirLong = 2;
+// The run of wave w and its first tiles.  SHORT: runs that may have fewer than kIirAhead tiles.  The tiles that follow are other
 // waves' there: requested as well, 418 channels of 35 tiles in runs of one took 29 us, now 17.
 template <bool SHORT>
 __device__ __forceinline__ void iir_begin(const IirArgs& p, int64_t w, int lane, IirRun& r, half8 (&first)[kIirAhead]) {
@@ -162,7 +171,7 @@ __device__ __forceinline__ State2 iir_end_state(const IirArgs& p, const IirRun& 
 }
 
 // 1  end state of every run started from zero
-template <bool SHORT>
+template <int FORM>
 __global__ void __launch_bounds__(256) iir2_state_mfma_kernel(IirArgs p) {
     const int lane = threadIdx.x & 63;
     const int64_t w = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
@@ -172,8 +181,8 @@ __global__ void __launch_bounds__(256) iir2_state_mfma_kernel(IirArgs p) {
     if (p.nruns <= 128 && (w + 1) % p.nruns == 0) return;
     IirRun r;
     half8 first[kIirAhead];
-    iir_begin<SHORT>(p, w, lane, r, first);
-    const half8 fhi = iir_fragment(p.thi, 1, lane), flo = iir_fragment(p.tlo, 1, lane);
+    iir_begin<FORM == kIirShort>(p, w, lane, r, first);
+    const half8 fhi = iir_fragment<FORM != kIirLong>(p.thi, 1, lane), flo = iir_fragment<FORM != kIirLong>(p.tlo, 1, lane);
     const State2 s = iir_end_state(p, r, first, fhi, flo, lane);
     if (lane == 15) {
         p.end[2 * w] = s.a;
@@ -303,12 +312,13 @@ struct IirCoefs {
     float ra[2][4], rb[2][4];                 // response of the lane's outputs i = 16 hh + 4 g + j to the block's state
     float bsel[4];                            // state map over the c blocks before the lane's block
 };
+template <bool WIDE = true>
 __device__ __forceinline__ void iir_coefs(const IirArgs& p, int lane, IirCoefs& k) {
     const int c = lane & 15, g = lane >> 4;
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
-        k.fhi[hh] = iir_fragment(p.thi, hh, lane);
-        k.flo[hh] = iir_fragment(p.tlo, hh, lane);
+        k.fhi[hh] = iir_fragment<WIDE>(p.thi, hh, lane);
+        k.flo[hh] = iir_fragment<WIDE>(p.tlo, hh, lane);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             k.ra[hh][j] = p.ca[16 * hh + 4 * g + j];
@@ -318,45 +328,57 @@ __device__ __forceinline__ void iir_coefs(const IirArgs& p, int lane, IirCoefs& 
 #pragma unroll
     for (int i = 0; i < 4; ++i) k.bsel[i] = p.bsel[c][i];
 }
-// The outputs of a run from the true state before it.
-__device__ __forceinline__ void iir_outputs(const IirArgs& p, const IirRun& r, const half8 (&first)[kIirAhead], const IirCoefs& k, State2 start,
-                                            float* patch, int lane) {
-    const int c = lane & 15, g = lane >> 4;
-    iir_walk(r, p.T, lane, first, [&](int i, const half8& x) {
-        floatx4 d[2];
+// Local products of a tile from a zero state: lane (c = block, g) holds outputs i = 16 hh + 4 g + j of its block.
+__device__ __forceinline__ void iir_products(const IirCoefs& k, const half8& x, floatx4 (&d)[2]) {
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-            d[hh] = floatx4{0.f, 0.f, 0.f, 0.f};
-            d[hh] = mfma16x16x32(k.fhi[hh], x, d[hh]);
-            d[hh] = mfma16x16x32(k.flo[hh], x, d[hh]);
-        }
-        // state before block c = (tile state carried across c blocks) + (blocks 0 .. c-1 from zero)
-        const State2 incl = iir_scan_blocks(p, d[1], lane);
-        const State2 mine = iir_step(k.bsel, start, iir_row_shr<1>(incl.a), iir_row_shr<1>(incl.b));
-        start = iir_step(p.m512, start, __shfl(incl.a, 15, 64), __shfl(incl.b, 15, 64));
-        // lane (c = block, g) holds outputs i = 16 hh + 4 g + j of its block: add the response to the block's state
+    for (int hh = 0; hh < 2; ++hh) {
+        d[hh] = floatx4{0.f, 0.f, 0.f, 0.f};
+        d[hh] = mfma16x16x32(k.fhi[hh], x, d[hh]);
+        d[hh] = mfma16x16x32(k.flo[hh], x, d[hh]);
+    }
+}
+// The outputs of tile i of a run from its products, the scan of its blocks and the true state before it, which moves on.
+__device__ __forceinline__ void iir_finish_tile(const IirArgs& p, const IirRun& r, int i, floatx4 (&d)[2], const State2& incl, const IirCoefs& k,
+                                                State2& start, float* patch, int lane) {
+    const int c = lane & 15, g = lane >> 4;
+    // state before block c = (tile state carried across c blocks) + (blocks 0 .. c-1 from zero)
+    const State2 mine = iir_step(k.bsel, start, iir_row_shr<1>(incl.a), iir_row_shr<1>(incl.b));
+    start = iir_step(p.m512, start, __shfl(incl.a, 15, 64), __shfl(incl.b, 15, 64));
+    // add the response to the block's state
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) d[hh][j] += k.ra[hh][j] * mine.a + k.rb[hh][j] * mine.b;
+    const int64_t t = r.t0 + (int64_t)i * kIirTile;
+    float* dst = p.out + (int64_t)r.ch * p.out_pitch + t;
+    if (t + kIirTile <= p.T) {
+        // the tile is 16 rows (blocks) of 32 consecutive samples
+        store_rows_via_lds<2, true>(patch, dst, kIirBlock, d, lane);
+    } else {
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) d[hh][j] += k.ra[hh][j] * mine.a + k.rb[hh][j] * mine.b;
-        const int64_t t = r.t0 + (int64_t)i * kIirTile;
-        float* dst = p.out + (int64_t)r.ch * p.out_pitch + t;
-        if (t + kIirTile <= p.T) {
-            // the tile is 16 rows (blocks) of 32 consecutive samples
-            store_rows_via_lds<2, true>(patch, dst, kIirBlock, d, lane);
-        } else {
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int n = 32 * c + 16 * hh + 4 * g + j;
-                    if (t + n < p.T) dst[n] = d[hh][j];
-                }
-        }
+            for (int j = 0; j < 4; ++j) {
+                const int n = 32 * c + 16 * hh + 4 * g + j;
+                if (t + n < p.T) dst[n] = d[hh][j];
+            }
+    }
+}
+// The outputs of a run from the true state before it.
+__device__ __forceinline__ void iir_outputs(const IirArgs& p, const IirRun& r, const half8 (&first)[kIirAhead], const IirCoefs& k, State2 start,
+                                            float* patch, int lane) {
+    iir_walk(r, p.T, lane, first, [&](int i, const half8& x) {
+        floatx4 d[2];
+        iir_products(k, x, d);
+        iir_finish_tile(p, r, i, d, iir_scan_blocks(p, d[1], lane), k, start, patch, lane);
     });
 }
 
-template <bool SHORT>
+// What a wave requests first: its coefficients where a run is the four tiles in flight (loads arrive in order, and these are
+// quick: 64 x 131072 samples 15.0 us, 15.7 with the samples first), its samples in the other forms (400 x 2500 9.7 us with the coefficients first,
+// 9.2 so; 1000 x 2049 10.2, 9.3).  Long runs also load their fragments entry by entry, and so come to their products one after the other:
+// 8 x 2^21 26.5 us with one load each and the coefficients first, 25.6 so, 1 x 2^24 31.4 and 29.5, 257 x 32769 22.3 and 21.0.
+template <int FORM>
 __global__ void __launch_bounds__(256) iir2_apply_mfma_kernel(IirArgs p) {
     __shared__ __attribute__((aligned(16))) float s_patch[4 * RowPatch<2>::kFloats];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -364,36 +386,64 @@ __global__ void __launch_bounds__(256) iir2_apply_mfma_kernel(IirArgs p) {
     if (w >= (int64_t)p.C * p.nruns) return;
     IirRun r;
     half8 first[kIirAhead];
-    IirCoefs k;                               // requested first: loads arrive in order, and these are quick (2 x 2^21 12.0 -> 11.7 us)
-    iir_coefs(p, lane, k);
-    __builtin_amdgcn_sched_barrier(0);
-    iir_begin<SHORT>(p, w, lane, r, first);
+    IirCoefs k;
+    if constexpr (FORM == kIirEven) {
+        iir_coefs(p, lane, k);
+        __builtin_amdgcn_sched_barrier(0);
+        iir_begin<false>(p, w, lane, r, first);
+    } else {
+        iir_begin<FORM == kIirShort>(p, w, lane, r, first);
+        iir_coefs<FORM != kIirLong>(p, lane, k);
+    }
     const State2 start = iir_state_before(p, p.end + 2 * (int64_t)r.ch * p.nruns, r.index, lane);
     iir_outputs(p, r, first, k, start, s_patch + wv * RowPatch<2>::kFloats, lane);
 }
 
-// Both in one launch for short signals: a workgroup takes a channel, a wave a run of tiles, of which the first four stay in its
-// registers, and the end states pass through LDS.  One compute unit moves all bytes of a channel, so this is the faster form only
-// while they are few: see the rule at the launch.
+// Both in one launch for short signals: a workgroup takes a channel, a wave a run of tiles, and the end states pass through LDS.  One
+// compute unit does all of a channel's work, so this is the faster form only while that is little: see the rule at the
+// launch.  What bounds it: the vector instructions of its 16 waves.  KEPT: runs of up to four tiles keep their products and
+// the scans of their blocks in registers from the first pass to the second (1 x 32768 samples 8.5 us with both done twice).
 constexpr int kIirChannelWaves = 16;
+template <bool KEPT>
 __global__ void __launch_bounds__(64 * kIirChannelWaves) iir2_channel_mfma_kernel(IirArgs p) {
     __shared__ __attribute__((aligned(16))) float s_patch[kIirChannelWaves * RowPatch<2>::kFloats];
     __shared__ float s_end[kIirChannelWaves][2];
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    float* const patch = s_patch + wv * RowPatch<2>::kFloats;
     IirRun r;
     half8 first[kIirAhead];
     iir_begin<true>(p, (int64_t)blockIdx.x * p.nruns + wv, lane, r, first);
     IirCoefs k;
     iir_coefs(p, lane, k);
-    const State2 e = iir_end_state(p, r, first, k.fhi[1], k.flo[1], lane);
+    floatx4 d[kIirAhead][2];
+    State2 incl[kIirAhead], e{0.f, 0.f};
+    if constexpr (KEPT) {
+#pragma unroll
+        for (int u = 0; u < kIirAhead; ++u)
+            if (u < r.n) {                                // uniform
+                iir_products(k, first[u], d[u]);
+                incl[u] = iir_scan_blocks(p, d[u][1], lane);
+                e = iir_step(p.m512, e, incl[u].a, incl[u].b);
+            }
+    } else {
+        e = iir_end_state(p, r, first, k.fhi[1], k.flo[1], lane);
+    }
     if (lane == 15) {
         s_end[wv][0] = e.a;
         s_end[wv][1] = e.b;
     }
     __syncthreads();
+    const float ea = s_end[lane & 15][0], eb = s_end[lane & 15][1];
+    auto from_lane = [](float v, int l) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l)); };
     State2 start{0.f, 0.f};
-    for (int q = 0; q < wv; ++q) start = iir_step(p.rpow[0], start, s_end[q][0], s_end[q][1]);
-    iir_outputs(p, r, first, k, start, s_patch + wv * RowPatch<2>::kFloats, lane);
+    for (int q = 0; q < wv; ++q) start = iir_step(p.rpow[0], start, from_lane(ea, q), from_lane(eb, q));
+    if constexpr (KEPT) {
+#pragma unroll
+        for (int u = 0; u < kIirAhead; ++u)
+            if (u < r.n) iir_finish_tile(p, r, u, d[u], incl[u], k, start, patch, lane);
+    } else {
+        iir_outputs(p, r, first, k, start, patch, lane);
+    }
 }
 
 // Vector-ALU twin of both launches: a lane owns one block of 32 samples and runs the recursion
@@ -584,9 +634,15 @@ static hb_status iir2_run(bool valu, const hb_half* in, float* out, int C, int64
     auto round = [&]() { return (int64_t)(a.run < kIirAhead ? 8 : 16) * num_cu() * a.run; };
     while (a.ntiles > (int64_t)kIirMaxRuns * a.run || ((int64_t)C * a.ntiles > round() && a.run < a.ntiles)) a.run *= 2;
     // A workgroup per channel in one launch, while each has a compute unit to itself: runs of up to four tiles, or eight where
-    // most units have one (T = 2500 .. 16384, 1 to 256 channels 10.2 us, 7.0 so; 32768, 1 / 64 / 256 channels 10.0 / 9.1 / 14.8, 8.4 / 9.0 /
-    // 12.4; 65536, 64 / 100 / 200 channels 10.7 / 14.0 / 21.9, 12.9 / 12.9 / 17.7; 400 x 8192 10.3, 11.9).
-    const bool channel = !valu && a.ntiles > kIirAhead && C <= num_cu() && a.ntiles <= (2 * C >= num_cu() ? 8 : 4) * kIirChannelWaves;
+    // most units have one (T = 2500 .. 16384, 1 to 256 channels 10.2 us, 6.9 so; 32768, 1 / 64 / 256 channels 10.4 / 10.4 / 14.8, 8.4 / 9.0 /
+    // 12.4; 65536, 64 / 100 / 200 channels 10.7 / 14.0 / 21.9, 12.9 / 12.9 / 17.7; 400 x 8192 10.3, 11.9).  One to 16 channels owe
+    // this to the host, which takes 9.4 us for two launches: their kernels, replayed from a graph, take 6.5 us for 32768 samples, this one 7.9.
+    // Signals that start between dwords cost one compute unit more than they cost many: only up to three tiles a run with few
+    // channels (16 x 32767 9.8 us with two launches, 11.2 with one, 16 x 20001 9.4 to 10.7 and 9.5; 32 x 32767 12.0 and 11.4),
+    // and up to eight only from three channels to four units on (160 x 40001 / 50001 16.6 / 18.0 and 18.4 / 20.0, 200 x 18.2 / 21.8 and 18.8 / 20.1).
+    const bool even = aligned_to(in, 4) && (C == 1 || in_pitch % 2 == 0);
+    const int most = C > num_cu() || valu ? 0 : (even ? 2 * C >= num_cu() : 4 * C >= 3 * num_cu()) ? 8 : even || 8 * C >= num_cu() ? 4 : 3;
+    const bool channel = a.ntiles > kIirAhead && a.ntiles <= most * kIirChannelWaves;
     if (channel) a.run = ceil_div(a.ntiles, kIirChannelWaves);
     a.nruns = (a.ntiles + a.run - 1) / a.run;
     for (int j = 0; j < 7; ++j) {
@@ -603,14 +659,17 @@ static hb_status iir2_run(bool valu, const hb_half* in, float* out, int C, int64
         hipLaunchKernelGGL(iir2_scan_kernel, dim3(C), dim3(64 * kIirScanWaves), 0, st, a);
         hipLaunchKernelGGL(iir2_blocks_valu_kernel<true>, grid(waves), dim3(256), 0, st, a);
     } else if (channel) {
-        hipLaunchKernelGGL(iir2_channel_mfma_kernel, dim3(C), dim3(64 * a.nruns), 0, st, a);
+        if (a.run <= kIirAhead) hipLaunchKernelGGL(iir2_channel_mfma_kernel<true>, dim3(C), dim3(64 * a.nruns), 0, st, a);
+        else hipLaunchKernelGGL(iir2_channel_mfma_kernel<false>, dim3(C), dim3(64 * a.nruns), 0, st, a);
     } else {
         const dim3 g = grid((int64_t)C * a.nruns);
-        const bool shorter = a.run < kIirAhead;
-        if (a.nruns > 1 && shorter) hipLaunchKernelGGL(iir2_state_mfma_kernel<true>, g, dim3(256), 0, st, a);
-        else if (a.nruns > 1) hipLaunchKernelGGL(iir2_state_mfma_kernel<false>, g, dim3(256), 0, st, a);
-        if (shorter) hipLaunchKernelGGL(iir2_apply_mfma_kernel<true>, g, dim3(256), 0, st, a);
-        else hipLaunchKernelGGL(iir2_apply_mfma_kernel<false>, g, dim3(256), 0, st, a);
+        auto both = [&](auto state, auto apply) {
+            if (a.nruns > 1) hipLaunchKernelGGL(state, g, dim3(256), 0, st, a);
+            hipLaunchKernelGGL(apply, g, dim3(256), 0, st, a);
+        };
+        if (a.run < kIirAhead || a.nruns == 1) both(iir2_state_mfma_kernel<kIirShort>, iir2_apply_mfma_kernel<kIirShort>);
+        else if (a.run == kIirAhead) both(iir2_state_mfma_kernel<kIirEven>, iir2_apply_mfma_kernel<kIirEven>);
+        else both(iir2_state_mfma_kernel<kIirLong>, iir2_apply_mfma_kernel<kIirLong>);
     }
     return launch_status();
 }
