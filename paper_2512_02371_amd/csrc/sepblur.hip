@@ -409,16 +409,44 @@ static hb_status sep_launch_one_window(hipStream_t st, SepArgs& a) {
 // 2047 x 2045 12.7 -> 9.6).  Beyond some 100 MB of output the lines are no longer put together in time, and the kernel
 // above is the faster one again (4978 x 6366 58 against 62, 8190 x 8190 117 against 125).
 constexpr int64_t kSepMarchShortMax = 24 << 20;           // outputs
+// Row tiles (steps) of a segment of the march.  Every segment requests and filters NT - 1 row tiles ahead of its own, so
+// long ones save work: as long as leaves two workgroups per compute unit (1079 x 1917, 31 / 60 taps 7.4 / 8.8 us, with
+// the four that are resident 8.7 / 11.3; 2048 x 2048, 31 / 64 taps 8.6 / 10.3 and 9.4 / 11.9; with one 9.1 / 10.5), of eight steps
+// at most (8192 x 4096, 48 taps: 36 us with 8 steps, 42 with 16).  From about ten steps per unit (`all` in all columns) up to where
+// both rules give eight, something else weighs more:
+//  - Output rows of whole lines, or of half lines under more than 17 taps down: three or four workgroups a unit hide more
+//    of each other's loads (3072 x 3072, 31 / 48 / 64 taps 12.8 / 13.1 / 14.3 us, with two 14.1 / 14.3 / 15.9; 2160 x 3840, 40 x 5 taps 10.8 and 11.9;
+//    1500 x 6000, 31 / 64 taps 13.7 / 14.8 and 14.3 / 16.3; 3600 x 3600, 48 taps 18.6 and 19.7).
+//  - Other rows: two or three steps.  The parts of a line that two workgroups write meet in the L2 only while these keep in step,
+//    which they do for a few rows, and with short filters that weighs more in smaller images too (3000 x 3000, 16 / 31 / 48 taps 13.6 /
+//    16.7 / 17.1 us, with eight steps 17.5 / 18.3 / 18.8; 1800 x 1808, 16 taps 6.7, with four 7.0; 2000 x 3000, 16 x 33 taps 10.9, with six 11.9; 2700 x
+//    1500, 31 taps 9.3, with four 9.9).  Where input rows start between dwords a row tile costs more: only in large images, and three
+//    (3333 x 3333, 5 / 31 / 48 taps 20.1 / 20.7 / 21.8, with eight 23.7 / 24.4 / 24.4; 64 taps 23.9 with five, 25.0 with three; 1801 x 1811, 5 / 31 taps
+//    9.1 / 10.4 with two, 8.1 / 9.7 with the four that two workgroups a unit give; 2401 x 2603 14.0 / 15.0 and 13.2 / 14.3).
+static int sep_march_steps(const SepArgs& a, int nkx, int nt, bool lines) {
+    const int64_t cu = num_cu(), rowsteps = ceil_div(a.H, 16), nct = ceil_div(a.W, kSepMarchCols), all = rowsteps * nct;
+    auto steps_for = [&](int64_t wgs) { return (int)std::min<int64_t>((all + wgs - 1) / wgs, 8); };
+    const int two = steps_for(2 * cu);
+    const bool half_lines = a.out_pitch % 16 == 0 && aligned_to(a.out, 64), even = a.in_pitch % 2 == 0 && aligned_to(a.in, 4);
+    if (all <= 4 * cu || all > 28 * cu) return two;
+    if (lines || (half_lines && nt > 2)) {
+        if (nt <= 3) return all > (nt == 3 ? 10 : 8) * cu ? steps_for(4 * cu) : two;
+        return all > 24 * cu ? steps_for(4 * cu) : all > 16 * cu ? steps_for(3 * cu) : two;
+    }
+    if (!even) return all <= 16 * cu ? two : nt <= 4 ? 3 : 5;
+    const int few = all > 20 * cu ? 3 : 2;
+    if (nt <= 2) return half_lines && nkx >= 2 && all <= 8 * cu ? two : few;
+    if (all > 24 * cu) return steps_for(4 * cu);
+    if (all > 16 * cu) return nt == 3 ? few : nt == 4 ? 3 : two;
+    if (nt > 3 || (all > 8 * cu && all <= 10 * cu)) return two;
+    if (all > 10 * cu) return nkx == 1 ? 2 : two;
+    return 8 * nct * ((rowsteps + two - 1) / two) >= 15 * cu ? 2 : two;       // nearly two workgroups to every unit
+}
 template <int NT>
 static hb_status sep_launch_nt(int nkx, hipStream_t st, SepArgs& a) {
     const bool lines = a.out_pitch % 32 == 0 && aligned_to(a.out, 128);
     if (nkx == 1 && (lines || NT > 3 || (int64_t)a.H * a.W > kSepMarchShortMax)) return sep_launch_one_window<NT>(st, a);
-    // Segments as long as leaves two workgroups per compute unit: every one requests and filters NT - 1 row tiles ahead of its
-    // own (with the four that are resident, segments half as long, 1079 x 1917, 31 / 60 taps 8.7 / 11.3 us, 7.4 / 8.8 so; 2048 x 2048,
-    // 31 / 64 taps 8.6 / 11.1, 8.1 / 9.8; with one 9.1 / 10.5).  Beyond 8 steps they only cost balance (8192 x 4096, 48
-    // taps: 36 us with 8 steps, 42 with 16).
-    const int64_t rowsteps = ceil_div(a.H, 16), nct = ceil_div(a.W, kSepMarchCols), want = 2 * num_cu();
-    const int steps = (int)std::min<int64_t>((rowsteps * nct + want - 1) / want, 8);
+    const int steps = sep_march_steps(a, nkx, NT, lines);
     if constexpr (NT <= 3) {
         if (nkx == 1) return sep_launch(sepblur_march_mfma_kernel<1, NT>, st, a, steps, kSepMarchCols, 1);
     }
