@@ -328,14 +328,23 @@ static hb_status fir1d_prepare(FirArgs& a, const hb_half* in, float* out, int H,
     // The walk of long filters: runs of an even number of tiles.  More waves have more bytes in flight and walk more windows ahead
     // of their runs.  From four windows on one wave per SIMD in all (4096 x 4096, 256 / 200 taps 22.8 / 21.0 us, 25.1 / 23.8 with
     // two; 1749 x 2603, 150 taps 12.7, 16.6; with three quarters of one 4096 x 4096 23.9 / 20.5, but 8192 x 4096, 256 taps 50.2
-    // against 38.4).  Shorter filters two (4096 x 4096, 40 / 80 taps 17.3 / 18.6, with one 18.3 / 19.1), and four on
-    // large images of whole lines (8192 x 4096, 64 taps in memory 54 us against 62 when it was measured).  Runs shorter than
+    // against 38.4), but two where large outputs have rows that start inside lines and the input's do not start between
+    // dwords, whose shifting is work that one wave per SIMD already fills (2900 x 2900, 100 / 200 taps 15.7 / 17.9 us with one wave,
+    // 13.5 / 16.9 with two, 4500 x 4500 40.9 / 42.3 and 35.8 / 36.5, 2000 x 3000, 100 taps 12.1 and 11.2; 2401 x 2603, 14.1 and 15.8,
+    // 2000 x 3000, 200 taps 14.6 and 14.2, 5000 x 5000 44.1 and 47.2).
+    // Shorter filters two (4096 x 4096, 40 / 80 taps 17.3 / 18.6, with one 18.3 / 19.1), and four on
+    // large images of whole lines (8192 x 4096, 64 taps from memory 39.8 us, 45.8 with two).  Runs shorter than
     // the windows ahead of them only where there are too few waves otherwise (1749 x 2603, 256 taps 25.9 with runs of 10
-    // tiles, 20.0 with 20).  Images of a few rows, most of whose lanes are idle, take two or four (1 x 1000000, 100 taps 10.7 us,
-    // 13.4 with one) and longer runs (256 taps 24 -> 18).
+    // tiles, 20.0 with 20).  Images of a few rows, most of whose lanes are idle, take two or three (8 x 500000, 34 taps 10.7 us with
+    // four, 9.5 so; 1 x 1000000, 100 taps 10.7, 13.4 with one) and longer runs (256 taps 24 -> 18).
     a.ntiles = ceil_div(W, 16);
     const int nk = ceil_div(15 + ntaps + (anchor & 1), 32);
-    int runs = std::min((nk >= 4 ? (H < 16 ? 8 : 4) : H < 16 || (a.lines && (int64_t)H * W > (24 << 20)) ? 16 : 8) * num_cu() / rowsteps, a.ntiles / 4);
+    const bool even = in_pitch % 2 == 0 && aligned_to(in, 4);
+    const int64_t px = (int64_t)H * W;
+    int waves = 8;                                        // per compute unit
+    if (nk <= 3) waves = H < 16 ? 12 : a.lines && px > (24 << 20) ? 16 : 8;
+    else if (H >= 16) waves = !a.lines && even && (nk <= 6 ? px >= (4 << 20) : px >= (8 << 20) && px <= (20 << 20)) ? 8 : 4;
+    int runs = std::min(waves * num_cu() / rowsteps, a.ntiles / 4);
     const int long_runs = a.ntiles / ((H < 16 ? 4 : 2) * nk);
     if ((int64_t)rowsteps * long_runs >= 3 * num_cu()) runs = std::min(runs, long_runs);
     runs = std::max(1, runs);
