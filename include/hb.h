@@ -278,15 +278,18 @@ hb_status hb_dct_denoise_valu(const hb_half *in, float *out, int C, int H, int W
  * in: H x W fp16, out: H x W fp32.  `workspace` is device scratch of at least
  * hb_sat2d_workspace_size(H, W) bytes, 256-byte aligned; its contents on entry do
  * not matter and are undefined on exit.  Two calls that run concurrently need
- * two workspaces.
- * Images of up to 1024 regions of 128 x 256 pixels whose workgroups are all resident
- * at once (4096 x 4096 is 512 regions) run as ONE kernel that reads the image once:
+ * two workspaces (on one they end, but with tables that are wrong).
+ * Images of up to 1024 regions of 128 x 128 pixels, or 128 x 256 from 128 pieces of 256 x 256 on, whose workgroups are all
+ * resident at once (4096 x 4096 is 512 of the larger regions) run as ONE kernel that reads the image once:
  * every workgroup forms the local table of its region in registers, publishes the
  * region's row, column and total sums in the workspace, waits until all regions (for
- * those of the upper half: of that half) have published, adds the sums of the regions to its left and above, and stores.  The
+ * those of the upper half of an image of larger regions: of that half) have published, adds the sums of the regions to its left
+ * and above, and stores.  The
  * wait is bounded (hb_sat2d_set_wait_limit): a workgroup that reaches the bound marks
  * its region and exits, and the workgroups that got through finish the marked regions
- * from memory, so the kernel ends whatever the scheduling.  Larger images take three launches
+ * from memory, so the kernel ends whatever the scheduling.  Before it counts itself in, a workgroup looks for the mark that the
+ * words of the wait have been cleared for this launch; that depends only on the workgroup that took on the clearing, which is
+ * running and waits for nobody.  An image of one region waits for nothing, and larger images take three launches
  * (tile sums, scans of the carries, apply) and read the image twice.
  */
 size_t hb_sat2d_workspace_size(int H, int W);
@@ -319,7 +322,8 @@ hb_status hb_sat2d_noalloc(const hb_half *in, float *out, int H, int W,
  * workgroup spends in the grid-wide wait before it hands its region to a finisher.
  * polls > 0 sets the limit, 0 restores the default (16384), a negative value makes every
  * workgroup that does not find the wait already over stop at once (tests use it to run
- * the finisher path).  Whatever the value, every kernel exits and the result is the same.
+ * the finisher path) and clear the words of the wait itself where it finds them not cleared yet.  Whatever the value, every
+ * kernel exits and the result is the same.
  * Process-wide; read when a call is enqueued.  Returns the previous limit.
  */
 int hb_sat2d_set_wait_limit(int polls);

@@ -25,6 +25,7 @@
 
 #include "hb_device.hpp"
 #include "hb_host.hpp"
+#include "sat_wait.hpp"
 
 namespace hb {
 
@@ -340,59 +341,19 @@ __global__ void __launch_bounds__(256) sat_apply_mfma_kernel(SatArgs p) {
 // so the first group waits for itself alone and stores while the second still loads, adds and waits (23.4 us; 2900 x
 // 2900 25.5 -> 23.6, 2048 x 4096 20.0 -> 17.0).  Small images (2 x 2 tiles), which memory does not bound, are one group.
 //
-// Grid-wide wait, of each group.  Arrival is a two-level count (up to 16 leaf counters, one root, each on its own
-// 128-byte line: arrivals at one address are served one after the other by the memory side); the
-// last arrival raises eight copies of a `go` word and workgroup w polls copy w % 8.  Table data and
-// the words of the wait are written and read with agent-scope accesses (they bypass the per-XCD L2,
-// so no cache write-back or invalidation is needed; a write-back per workgroup costs ~20 ns each,
-// one after the other).  The wait is BOUNDED: after `wait_limit` polls a workgroup stops waiting.
-// It has already arrived, so the count still completes when the last workgroup gets to run; a
-// workgroup that stopped waiting marks its region in `todo`, raises `late` and leaves, unless `go`
-// came up meanwhile.  Every workgroup that passes the wait reads `late` (raised before `go` by
-// construction, see below) and, if it is set, claims marked regions one by one, reloads their
-// pixels and finishes them.  So every wave exits whatever the residency, and every region is
-// finished by someone:
-//   late workgroup: store todo[r], late; wait for the stores; load go.  go == 0 -> leave.
-//   finisher:       observes go == 1; then loads late and todo.
-//   go is raised once, after the late workgroup's load returned 0, hence after its stores were
-//   performed at the memory side: the finisher's loads see them.
-// With two groups, `go` of the first, once performed, counts as one more arrival of the second, so `go` of the second
-// means that every region is published.  A workgroup finishes only regions that it knows to be: those of the first group,
-// and all of them if it is of the second or raised the second's `go` itself.  (The workgroup that raises a group's `go`
-// always passes its own wait, so some workgroup finishes what that group's late ones left.)
-// The words of the wait hold anything when the kernel starts.  The launch's number `call` (unlike any other launch's) tells
-// whether they are this launch's: workgroup 0 exchanges it for `claim`, clears the words if it was the first, and then writes it
-// to `ready`, which every workgroup has to find there before it arrives; one that has looked for long does the clearing
-// itself, through the same exchange, so nobody waits for a workgroup that does not run.  The last arrival of all wipes
-// `claim` and `ready`, which nobody reads from then on: a launch that is replayed from a graph with the same number finds
-// its words not ready again.  A kernel ahead of this one that cleared them cost a launch and 1 to 1.5 us (1079 x 1917 15.9 ->
-// 14.5 us, 2048 x 4096 17.0 -> 15.5, 1024 x 1024 11.1 -> 10.1).
+// The grid-wide wait, of each group, is described with its steps in sat_wait.hpp.  The kernel clears the words of the wait itself: a kernel
+// ahead of this one that did cost a launch and 1 to 1.5 us (1079 x 1917 15.9 -> 14.5 us, 2048 x 4096 17.0 -> 15.1, 1024 x 1024 11.1 -> 10.2).
 // The host uses this kernel only when the grid fits on the device at once (occupancy query), so the
 // bounded wait ends by `go` unless other work holds compute units for longer than the limit.
 #ifndef HB_SAT_POLL_SLEEP
 #define HB_SAT_POLL_SLEEP 3                               // s_sleep units (64 clocks each) between two polls of `go`
 #endif
-struct SatSync {
-    static constexpr int kLine = 32;                      // words per 128 bytes
-    static constexpr int kLeaves = 16, kGo = 8, kMaxRegions = 1024;     // leaves and copies of `go`: halved between two groups
-    static constexpr int kRoot = 16;                      // words from the first group's root to the second's
-    static constexpr int kReady = 8, kClaim = 8;          // words at which the lines of `go` and `late` have `ready` and `claim`
-    unsigned leaf[kLeaves * kLine];
-    unsigned root[kLine];
-    unsigned go[kGo * kLine];                             // each copy with one of `ready` (64 bits)
-    unsigned late[kLine];                                 // with `claim` (64 bits)
-    unsigned todo[kMaxRegions];                           // 0 idle, 1 waiting for a finisher, 2 claimed
-#ifdef HB_SAT_TIMING
-    unsigned long long stamp[kMaxRegions][8];             // measurement builds only: phase time stamps per workgroup
-#endif
-};
 #ifdef HB_SAT_TIMING
 #define SAT_STAMP(S, wg, i) do { if (threadIdx.x == 0) (S)->stamp[wg][i] = wall_clock64(); } while (0)
 #else
 #define SAT_STAMP(S, wg, i) do { } while (0)
 #endif
 
-constexpr int kSatClaimPolls = 64;                        // of `ready`, after which a workgroup offers to clear
 // The second group holds its requests back for 1.5 us (units of 64 clocks), or they would share the memory with the first
 // group's, which everything waits for: 4096 x 4096 23.6 -> 23.0 us, 2900 x 2900 22.6 -> 20.7; a third of it and less gives
 // nothing, 3 us 23.8 and 21.8.
@@ -410,55 +371,41 @@ struct SatFusedArgs {
     float* CS;             // [nsw][Wr]  column x: sum over the rows of region row sw of the columns from its tile column's left to x
     float* TOT;            // [nsw][nbw] region totals
     SatSync* sync;
-    unsigned long long call;                              // of this launch, see SatSync
-    int wait_limit;
+    unsigned long long call;                              // of this launch, see sat_wait.hpp
+    int wait_limit, claim_polls;
 };
 
-__device__ __forceinline__ unsigned ld_agent(const unsigned* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_agent(unsigned* p, unsigned v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ float ldf_agent(const float* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void stf_agent(float* p, float v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// all earlier stores of this lane performed, and no memory access moved across this point
-__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-__device__ __forceinline__ unsigned long long* sat_ready(SatSync* s, int copy) {
-    return reinterpret_cast<unsigned long long*>(&s->go[SatSync::kLine * copy + SatSync::kReady]);
-}
-__device__ __forceinline__ unsigned long long* sat_claim(SatSync* s) {
-    return reinterpret_cast<unsigned long long*>(&s->late[SatSync::kClaim]);
-}
-__device__ __forceinline__ unsigned sat_add(unsigned* w) {
-    return __hip_atomic_fetch_add(w, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
-}
-// By the last arrival of all, when nobody reads these any more: leaves no trace of this launch's number.
-__device__ __forceinline__ void sat_forget_call(SatSync* s) {
-    for (int i = 0; i < SatSync::kGo; ++i) __hip_atomic_store(sat_ready(s, i), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(sat_claim(s), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// Taking on the clearing of the wait's words: whether no other workgroup of this launch has.
-__device__ __forceinline__ bool sat_take(SatSync* s, unsigned long long call) {
-    return __hip_atomic_exchange(sat_claim(s), call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != call;
-}
-// Lanes 0 .. n - 1 of one wave: the clearing, and, once that is performed, `ready`.
-__device__ __forceinline__ void sat_clear(SatSync* s, int nwg, int lane, int n) {
-    for (int i = lane; i < SatSync::kLeaves; i += n) st_agent(&s->leaf[SatSync::kLine * i], 0u);
-    for (int i = lane; i < SatSync::kGo; i += n) st_agent(&s->go[SatSync::kLine * i], 0u);
-    for (int i = lane; i < 2; i += n) st_agent(&s->root[SatSync::kRoot * i], 0u);
-    if (lane == 0) st_agent(&s->late[0], 0u);
-    for (int i = lane; i < nwg; i += n) st_agent(&s->todo[i], 0u);
-}
-__device__ __forceinline__ void sat_set_ready(SatSync* s, unsigned long long call, int lane, int n) {
-    stores_done();
-    for (int i = lane; i < SatSync::kGo; i += n) __hip_atomic_store(sat_ready(s, i), call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+struct SatMem {
+    template <class T>
+    static __device__ __forceinline__ T load(const T* p) {
+        return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    template <class T>
+    static __device__ __forceinline__ void store(T* p, T v) {
+        __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    static __device__ __forceinline__ unsigned add(unsigned* p) {
+        return __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+    }
+    template <class T>
+    static __device__ __forceinline__ T exchange(T* p, T v) {
+        return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    static __device__ __forceinline__ bool claim(unsigned* p) {
+        unsigned expect = 1u;
+        return __hip_atomic_compare_exchange_strong(p, &expect, 2u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // all earlier stores of this lane performed, and no memory access moved across this point
+    static __device__ __forceinline__ void performed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+    static __device__ __forceinline__ void pause() { __builtin_amdgcn_s_sleep(HB_SAT_POLL_SLEEP); }
+};
+using SatGrid = SatWait<SatMem>;
 
 template <int TR, int TC>
 struct SatFusedLds {
@@ -699,13 +646,13 @@ __global__ void __launch_bounds__(64 * TR * TC, 4) sat_fused_kernel(SatFusedArgs
         if (own && wg >= p.first) __builtin_amdgcn_s_sleep(kSatSecondDelay);
         const bool clears = own && nwg > 1 && wg == 0 && wv == kWaves - 1;
         bool took = false;
-        if (clears && lane == 0) took = sat_take(S, p.call);
+        if (clears && lane == 0) took = SatGrid::take(S, p.call);
         sat_fused_local<TR, TC>(p, L, kRH * sw + kSatTile * ts, kRW * bw + kSatTile * tb, ts, tb, lane, Lt, [&]() {
             if (!clears) return;
             took = __builtin_amdgcn_readfirstlane((int)took);
-            if (took) sat_clear(S, nwg, lane, 64);
+            if (took) SatGrid::clear(S, nwg, lane, 64);
         });
-        if (clears && took) sat_set_ready(S, p.call, lane, 64);
+        if (clears && took) SatGrid::set_ready(S, p.call, lane, 64);
         __syncthreads();
         unsigned late = 0u;
         if (own && nwg > 1) {                             // one region: nobody to wait for
@@ -732,64 +679,15 @@ __global__ void __launch_bounds__(64 * TR * TC, 4) sat_fused_kernel(SatFusedArgs
                     for (int b2 = 0; b2 < TC; ++b2) v += L.lastrow[t2][b2][kSatTile - 1];
                 stf_agent(p.TOT + wg, v);
             }
-            stores_done();
+            SatMem::performed();
             __syncthreads();
             SAT_STAMP(S, wg, 2);
             // arrive, then wait (bounded) for the others
-            if (tid == 0) {
-                unsigned long long* const ready = sat_ready(S, wg & (SatSync::kGo - 1));
-                for (int polls = 0; __hip_atomic_load(ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != p.call; ++polls) {
-                    if (polls == kSatClaimPolls && sat_take(S, p.call)) {
-                        sat_clear(S, nwg, 0, 1);
-                        sat_set_ready(S, p.call, 0, 1);
-                    }
-                    __builtin_amdgcn_s_sleep(HB_SAT_POLL_SLEEP);
-                }
-                const int ngroups = p.first < nwg ? 2 : 1, group = wg < p.first ? 0 : 1;
-                const int kl = SatSync::kLeaves / ngroups, kg = SatSync::kGo / ngroups;
-                const int id = group ? wg - p.first : wg, n0 = p.first, n1 = nwg - p.first, n = group ? n1 : n0;
-                const int nleaf = min(n, kl), lf = id % nleaf;
-                const int leaf_target = (n - lf + nleaf - 1) / nleaf;
-                bool all = ngroups == 1 || group == 1;    // passing the wait, it knows that every region is published
-                auto raise = [&](int g) {
-                    for (int i = 0; i < kg; ++i) st_agent(&S->go[SatSync::kLine * (g * kg + i)], 1u);
-                    if (g == ngroups - 1) sat_forget_call(S);
-                };
-                if ((int)sat_add(&S->leaf[SatSync::kLine * (group * kl + lf)]) == leaf_target &&
-                    (int)sat_add(&S->root[SatSync::kRoot * group]) == nleaf + group) {
-                    raise(group);
-                    if (ngroups == 2 && group == 0) {     // the first group is one more arrival of the second
-                        stores_done();
-                        if ((int)sat_add(&S->root[SatSync::kRoot]) == min(n1, kl) + 1) {
-                            raise(1);
-                            all = true;
-                        }
-                    }
-                }
-                const unsigned* mygo = &S->go[SatSync::kLine * (group * kg + id % kg)];
-                int state = all ? 2 : 1;                  // passed: 2 all regions, 1 the first group's are published; 0 leave
-                int polls = 0;
-                while (ld_agent(mygo) == 0u) {
-                    if (++polls > p.wait_limit) { state = 0; break; }
-                    __builtin_amdgcn_s_sleep(HB_SAT_POLL_SLEEP);
-                }
-                if (state == 0) {                         // stop waiting: hand the region to a finisher
-                    st_agent(&S->todo[wg], 1u);
-                    st_agent(&S->late[0], 1u);
-                    stores_done();
-                    if (ld_agent(mygo) != 0u) {           // the count completed meanwhile: finish it here after all
-                        unsigned expect = 1u;             // (a finisher may have claimed it too: both write the same values)
-                        __hip_atomic_compare_exchange_strong(&S->todo[wg], &expect, 2u, __ATOMIC_RELAXED,
-                                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        state = all ? 2 : 1;
-                    }
-                }
-                L.ctl = state;
-            }
+            if (tid == 0) L.ctl = SatGrid::arrive(S, wg, nwg, p.first, p.call, p.wait_limit, p.claim_polls);
             __syncthreads();
             if (L.ctl == 0) return;
             nscan = __builtin_amdgcn_readfirstlane(L.ctl) == 2 ? nwg : p.first;
-            if (tid == 0) late = ld_agent(&S->late[0]);   // in flight during the finish step
+            if (tid == 0) late = SatMem::load(&S->late[0]);   // in flight during the finish step
             SAT_STAMP(S, wg, 3);
         }
 
@@ -809,17 +707,13 @@ __global__ void __launch_bounds__(64 * TR * TC, 4) sat_fused_kernel(SatFusedArgs
             int found = -1;
             for (int r0 = 0; r0 < nscan && found < 0; r0 += 64) {
                 const int r = r0 + lane;
-                const bool marked = r < nscan && ld_agent(&S->todo[r]) == 1u;
+                const bool marked = r < nscan && SatMem::load(&S->todo[r]) == 1u;
                 unsigned long long m = __ballot(marked);
                 while (m && found < 0) {
                     const int cand = r0 + __builtin_ctzll(m);
                     m &= m - 1;
                     int won = 0;
-                    if (lane == 0) {
-                        unsigned expect = 1u;
-                        won = __hip_atomic_compare_exchange_strong(&S->todo[cand], &expect, 2u, __ATOMIC_RELAXED,
-                                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 1 : 0;
-                    }
+                    if (lane == 0) won = SatMem::claim(&S->todo[cand]) ? 1 : 0;
                     if (__shfl(won, 0, 64)) found = cand;
                 }
             }
@@ -973,6 +867,7 @@ static void sat_prepare_fused(SatFusedArgs& f, const SatArgs& a, void* ws, int t
     f.TOT = f.CS + (size_t)f.nsw * f.Wr;
     f.sync = reinterpret_cast<SatSync*>(f.RS + ((sat_workspace_floats(a.H, a.W) + 63) & ~(size_t)63) + sat_fused_table_floats(a.H, a.W, tc));
     f.wait_limit = wait_limit;
+    f.claim_polls = wait_limit > 0 ? kSatClaimPolls : 0;
 }
 
 }  // namespace hb
