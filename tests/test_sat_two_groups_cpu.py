@@ -6,7 +6,9 @@ second group, whose `go` therefore stands for all.  Claims: every thread ends, e
 finished before all regions that it reads (those of the first group, or all) have published, and the workspace holds
 the tables of both region shapes.
 """
+import os
 import random
+import re
 import threading
 import time
 
@@ -117,17 +119,33 @@ def test_two_groups_end_and_finish_every_region(nwg, first, slots, wait_limit):
 
 
 def test_workspace_holds_the_tables_of_both_region_shapes():
+    """The tables lie at the workspace's start and the words of the wait at its end, in the room that the library asks for."""
+    from paper_2512_02371_amd import hb
+    text = open(os.path.join(os.path.dirname(__file__), "..", "paper_2512_02371_amd", "csrc", "sat_wait.hpp")).read()
+    k = {n: int(v) for n, v in re.findall(r"\b(k\w+) = (\d+)", text)}
+    words = (k["kLeaves"] + 1 + k["kGo"] + 1) * k["kLine"] + k["kMaxRegions"]
+    assert words == 26 * 32 + 1024
+
     def up(a, b):
         return -(-a // b)
 
-    for H in (1, 64, 65, 128, 129, 257, 1000, 2896, 4096, 9000, 40000, 1 << 20):
-        for W in (1, 64, 65, 256, 257, 300, 1917, 4096, 33000, 1 << 20):
-            three = 258 * up(W, 64) * up(H, 64)
-            for tc in (2, 4):
-                ew = 64 * tc
-                nsw, nbw = up(H, 128), up(W, ew)
-                room = 2 * up(H, ew) * up(W, ew) * ew          # what follows the three-launch tables, at least
-                assert nsw * nbw * (128 + ew + 1) <= three + room, (H, W, tc)
+    rng = random.Random(5)
+    sizes = [(H, W) for H in (1, 64, 65, 128, 129, 257, 1000, 2896, 4096, 9000, 40000, 1 << 20)
+             for W in (1, 64, 65, 256, 257, 300, 1917, 4096, 33000, 1 << 20)]
+    sizes += [tuple(int(2 ** rng.uniform(0, 17)) for _ in range(2)) for _ in range(3000)]
+    taken = set()
+    for H, W in sizes:
+        small, pieces = up(H, 128) * up(W, 128), up(H, 256) * up(W, 256)
+        if pieces >= 128 and pieces > k["kMaxRegions"]:
+            continue                                       # three launches
+        tc = 4 if pieces >= 128 or small > k["kMaxRegions"] else 2
+        nsw, nbw = up(H, 128), up(W, 64 * tc)
+        if H <= 128 and W <= 256:
+            continue                                       # one region publishes nothing
+        taken.add(tc)
+        room = hb.hb_sat2d_workspace_size(H, W) // 4 - words
+        assert nsw * nbw * (128 + 64 * tc + 1) <= room, (H, W, tc)
+    assert taken == {2, 4}
 
 
 class Words:
