@@ -45,8 +45,10 @@
  *    number of compute units, the LDS limit already granted to each kernel, how many
  *    workgroups of the one-launch summed-area kernel are resident at once, and the
  *    address of hb_sat2d_noalloc's array (each looked up at the first call that needs
- *    it on that device); process-wide, the wait limit of hb_sat2d_set_wait_limit and
- *    the constant tables of hb_dct_denoise (computed at its first call).
+ *    it on that device); process-wide, the wait limit of hb_sat2d_set_wait_limit, the
+ *    number of the last one-launch call of hb_sat2d (each call takes the next; a captured call keeps its
+ *    own, and every replay of it wipes it from the workspace before it ends) and
+ *    the constant tables of hb_dct_denoise_valu (computed at its first call).
  *    None of it depends on the data of a call.
  *  - Every stage has a `_valu` twin with the same signature and results that uses
  *    only vector-ALU FMAs (no MFMA): the ablation that shows what the matrix units

@@ -108,12 +108,12 @@ __global__ void __launch_bounds__(256) fir1d_mfma_kernel(FirArgs p) {
 }
 
 // ---------------------------------------------------------------------------
-// Long filters (three or more windows per tile): the walk along the row.
+// Long filters (two or more windows per tile): the walk along the row.
 //
 // In the kernel above every product loads its own window, NK loads of 16 rows x 64 bytes per
 // 16 x 16 outputs, and with long filters those loads are all the kernel does (256 taps: 9 KB requested
 // per 1 KB of outputs; the matrix units idle).  Here a wave walks along a run of tiles of one
-// 16-row group and loads every pixel ONCE, in windows of 32 side by side.  Tiles go in PAIRS: window v (the 32 pixels from
+// 16-row group and loads every pixel of it once, in windows of 32 side by side.  Tiles go in PAIRS: window v (the 32 pixels from
 // 32 v - aw on) is the kk-th window of the even tile of pair v - kk for every kk < NK, and of the odd one, 16 pixels further, for
 // every kk < NKO, with Toeplitz fragments that are shifted by 16; NKO is NK or NK + 1.  So a window feeds up to 2 NKO products, each
 // into the accumulator of its own tile.  NKO pairs are open at any time (a ring
@@ -121,12 +121,13 @@ __global__ void __launch_bounds__(256) fir1d_mfma_kernel(FirArgs p) {
 // complete NKO - 1 steps after its first window and leaves through the LDS
 // patch as 128-byte runs.  Windows that reach over the row ends are shifted into place when they are used:
 // the Toeplitz matrix is indexed by window position, so the border rule needs nothing else.
-// Runs start NKO - 1 windows early (products into accumulators of tiles left of the run are
-// computed and dropped), the price of cutting a row into several tasks.
-// What bounds it: the bytes that the waves have in flight, NKO KB each.  With windows of 32 pixels at a stride of 16, one step a
-// tile, every pixel was requested twice and half of those bytes were the same ones: 4096 x 4096, 40 / 64 / 256 taps 18.6 / 18.8 / 25.2
-// -> 17.3 / 17.6 / 22.3 us, 8192 x 8192, 30 taps 124 -> 101, 4095 x 4095, 100 taps 37.8 -> 25.9.  Twice as many windows in flight: no
-// faster (256 taps 24.6 us).
+// A run of n pairs walks n + NKO - 1 windows, the last NKO - 1 of them the next run's too (what they and the first windows
+// add to pairs outside the run is dropped): the price of cutting a row into several tasks.
+// What it gains: with windows of 32 pixels at a stride of 16, one step a
+// tile, every pixel was requested twice: 4096 x 4096, 40 / 64 / 256 taps 18.6 / 18.8 / 25.2
+// -> 17.3 / 17.6 / 22.3 us, 8192 x 8192, 30 taps 124 -> 101, 4095 x 4095, 100 taps 37.8 -> 25.9.  What bounds it is not the bytes in flight
+// alone (NKO KB a wave; with twice as many windows ahead 256 taps took 24.6 us): from four windows on half the waves, each
+// walking fewer windows for its neighbour (with 256 taps one in five, one in three with two waves per SIMD), are mostly the faster.
 // Waves per workgroup of the walk: the longest filters (few, long-lived waves of 100+ registers) run
 // best as single-wave workgroups, the shorter ones four to a workgroup (measured).
 constexpr int fir_walk_waves(int nk) { return nk >= 7 ? 1 : 4; }
@@ -216,7 +217,7 @@ __global__ void __launch_bounds__(64 * fir_walk_waves(NK)) fir1d_walk_kernel(Fir
     // ahead the loads have to run to cover their latency
     half8 win[NKO];
 #pragma unroll
-    for (int i = 0; i < NKO; ++i) win[i] = load_window(min(i, nsteps - 1));
+    for (int i = 0; i < NKO; ++i) win[i] = load_window(i);              // nsteps >= NKO
     int ub = 0;
     // one step: window v = ub + S against every fragment, pair v - kk in slot (v - kk) % NKO; the pair before it in slot S is complete
     auto step = [&](auto sc) {
@@ -374,8 +375,9 @@ extern "C" hb_status hb_fir1d(const hb_half* in, float* out, int H, int W,
     // window is moved to an even pixel): NK windows of 32
     const int nk = ceil_div(15 + ntaps + (anchor & 1), 32);
     // narrow images are one short run per row group, whose windows all reach over the row's ends: with rows inside lines
-    // the vector ALU is the faster one (1000 x 100, 159 taps 7.0 us, walked 9.4; 1000 x 128, 200 taps, whole lines 8.3, 6.8;
-    // 50000 x 83, 159 taps 31, 24; 3600 x 16, 107 taps 11.2, 6.9)
+    // the vector ALU is the faster one (1000 x 100, 100 / 159 taps 5.4 / 6.7 us, walked 7.4 / 8.3, but 200 taps 8.3 and 7.8; 8192 x 65, 200 taps 8.7
+    // and 9.3), with whole lines (1000 x 128, 100 / 200 taps 5.4 / 8.3, 4.9 / 5.3) and in tall images (20000 x 100, 159 taps 15, 11;
+    // 50000 x 83 31, 21) it is not, nor below 33 columns (3600 x 16, 100 taps 10.5, 5.6)
     if (W < kFirMinWidth || (nk >= 4 && W > 32 && W <= 128 && !a.lines && H <= 32 * num_cu()))
         return hb_fir1d_valu(in, out, H, W, in_pitch, out_pitch, taps_host, ntaps, anchor, stream);
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);

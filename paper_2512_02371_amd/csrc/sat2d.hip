@@ -355,8 +355,9 @@ __global__ void __launch_bounds__(256) sat_apply_mfma_kernel(SatArgs p) {
 #endif
 
 // The second group holds its requests back for 1.5 us (units of 64 clocks), or they would share the memory with the first
-// group's, which everything waits for: 4096 x 4096 23.6 -> 23.0 us, 2900 x 2900 22.6 -> 20.7; a third of it and less gives
-// nothing, 3 us 23.8 and 21.8.
+// group's, which everything waits for: 4096 x 4096 23.6 -> 22.8 us, 2900 x 2900 23.4 -> 21.4, 1500 x 6000 19.3 -> 18.7, 65536 x 256
+// 25.8 -> 24.8; half of it gives a part of that, 3 us less.  The smallest images of two groups neither gain nor lose (200 x 20000
+// 16.8 and 16.9, 2816 x 2816 15.9, 400 x 16384 14.7 and 15.0).
 constexpr int kSatSecondDelay = 56;
 
 struct SatFusedArgs {
