@@ -4,25 +4,32 @@
 //
 // MFMA formulation, transposed so that a lane ends with consecutive output channels of one pixel:
 //   O'[m][n] = sum_k Wt[m][k] * X[k][n]     m = output channel, n = pixel, k = (tap, input channel)
-// with v_mfma_f32_32x32x16_f16: 32 channels x 32 pixels per product, K = 16 input channels.
-//   A (coefficients): the 9 x 64 x 32 weights of one 32-channel tile live in the registers of a
-//     wave for the whole kernel (36 K-steps x 8 halves per lane = 144 registers), gathered once.
-//   B (pixels): a workgroup walks DOWN a column of 8 x 32 pixel tiles.  The image rows it needs
-//     (34 pixels x 64 channels each, with the one-pixel halo) stream through a ring of 26 rows in
-//     LDS: a tile reads 10 of them, the 8 new rows of the next tile have landed, those of the tile
-//     after that are in flight, and the two halo rows between vertically adjacent tiles are
-//     fetched once.  Rows arrive by buffer loads that write LDS directly, in the image's own order
-//     (pixel-major, 128 bytes per pixel) with the eight 16-byte channel pieces of a pixel permuted
+// with v_mfma_f32_16x16x32_f16: 16 channels x 16 pixels per product, K = 32 input channels.
+//   A wave walks DOWN a strip of 32 pixels on its own, one to a SIMD: it holds the 9 x 64 x 64 weights in 288 registers (256 of
+//     them accumulation registers, from which the products read them), the twelve pixel fragments of ONE image row in
+//     48 and the sums of two output rows in 64.  Row r belongs to output row r - 1 with kernel row 2, to r with 1 and to
+//     r + 1 with 0: 48 products each, after which a finished row is rounded to fp16 (RNE) and leaves.  So a pixel is
+//     read from LDS once per horizontal tap, and no wave ever waits for another one.
+//   Image rows (34 pixels x 64 channels each, with the one-pixel halo) stream through a ring of eight rows in LDS that belongs
+//     to the wave: one is in use, seven are on their way.  They arrive by buffer loads that write LDS directly, in the image's
+//     own order (pixel-major, 128 bytes per pixel) with the eight 16-byte channel pieces of a pixel permuted
 //     by an XOR with bits 1..3 of the pixel index: a row is a few contiguous 1 KB copies, and the
 //     16-byte reads of 16 consecutive pixels at one channel piece still fall into 64 different
 //     banks for every tap shift (the overlapped view of Eq. 1: the three horizontal taps read the
 //     same LDS row at pixel offsets 0, 1, 2).  Pixels outside the image arrive as zeros (requested
 //     beyond the end of the buffer descriptor), which is the zero padding.
-//   A workgroup has 8 waves, two per SIMD, so that one wave's LDS reads hide behind the other's
-//   products: wave (q, j) owns output rows 2q, 2q+1 of the tile and channel tile j, i.e. 2 x 36
-//   products per tile.  fp32 accumulators are rounded to fp16 (RNE) into a stage shared by the
-//   workgroup and leave as whole 128-byte pixels (1 KB per store instruction).
+//   Everything but the products (fragments of the next row, its requests, the way out of the last one through an LDS stage of the
+//     wave, whole 128-byte pixels, 1 KB per store instruction) stands between two products, one or two instructions at a time: an instruction
+//     costs a wave that is alone on its SIMD issue time, and least there.
+//
+// What bounds it: power, then memory.  1 x 1024 x 1024: 65 us (58.5 while the input is in the memory-side cache) against 80 (76) for
+// eight waves that shared 8 x 32 tiles with v_mfma_f32_32x32x16_f16 and met twice a tile; zeros instead of pixels 44 against 55.
+// A loop of nothing but products with operands like these sustains 1.85 PFLOP/s in 16 x 16 x 32 and 1.65 in 32 x 32 x 16 (clock
+// 1.5 to 1.8 GHz; zeros 2.3 in both), a library product of 8192^3 1.25.  Non-temporal stores: 58.5 us, cached ones 66.4 (4 x 300 x 200 17.8, 22.7).
+// The weights come straight to LDS and leave it by transposing reads: with a pass through registers and 64-bit task arithmetic the start
+// of a workgroup took 2 us more (8 x 56 x 56 8.0 us, 5.7 now, 8.1 before; 3 x 100 x 100 9.5, 7.0, 8.6).
 #include <algorithm>
+#include <utility>
 
 #include "hb_device.hpp"
 #include "hb_host.hpp"
@@ -41,7 +48,8 @@ struct ConvArgs {
     int N, H, W;
     int tiles_x, tiles_y;      // per image
     int ntiles;                // N * tiles_y * tiles_x
-    int seg_len, nseg;         // MFMA kernel: tiles per column segment, segments per column
+    int seg_len, nseg;         // MFMA kernel: rows per column segment, segments per column
+    uint32_t ntasks;           // strips of 32 pixels x segments
 };
 
 // LDS layout of the vector-ALU twin: [row][16-channel chunk][8-channel half][pixel][8 channels].
@@ -49,267 +57,298 @@ __device__ __forceinline__ int cv_lds_index(int r, int kc, int half, int px) {
     return (((r * 4 + kc) * 2 + half) * kCvPx + px) * 8;
 }
 
-// LDS ring of the MFMA kernel: kCvRing rows of 34 pixels x 128 bytes; channel piece cp (16 bytes) of
+// A strip's rows in LDS, a ring per wave: kCvRing rows of 34 pixels x 128 bytes; channel piece cp (16 bytes) of
 // pixel px sits in slot cp ^ ((px >> 1) & 7) of the pixel's eight.
-constexpr int kCvThreads = 512;
-constexpr int kCvRing = 26;                               // 10 in use + 8 landed + 8 in flight
+constexpr int kCvWaves = 4;
+constexpr int kCvRing = 8;                                // one in use, seven on their way
 constexpr int kCvRowBytes = kCvPx * 128;                  // 4352
-constexpr int kCvRowSlots = kCvPx * 8;                    // 272 16-byte slots
-constexpr int kCvRowLoads = (kCvRowSlots + 63) / 64;      // 5 loads per row, the last one 16 lanes wide
-constexpr int kCvRingBytes = kCvRing * kCvRowBytes;       // 113152
+constexpr int kCvRowLoads = 5;                            // of 64 x 16 bytes per row, the last one of 16 lanes
+constexpr int kCvRingBytes = kCvRing * kCvRowBytes;       // 34816 per wave
+constexpr int kCvStream = 2;                               // stores: non-temporal
 constexpr uint32_t kCvOutside = 0x80000000u;              // offset beyond any descriptor used here
-// Output stage: 8 rows x 32 pixels x 64 channels of fp16, 144-byte pixel pitch (conflict-free reads).
+// Output stage of a wave: 32 pixels x 64 channels of fp16, 144-byte pixel pitch (conflict-free both ways).
 constexpr int kCvStagePitch = 144;
-constexpr int kCvStageBytes = kCvTY * kCvTX * kCvStagePitch;   // 36864
+constexpr int kCvStageBytes = kCvTX * kCvStagePitch;      // 4608
+// The weights pass through LDS on their way to the registers: taps 2w, 2w + 1 in wave w's ring behind the rows that are requested
+// ahead of them, tap 8 in the stages.
+constexpr int kCvTapBytes = kCvC * kCvC * 2;              // 8192
+constexpr int kCvEarly = 3;                               // rows requested ahead of the weights' arrival
+static_assert(kCvEarly * kCvRowBytes + 2 * kCvTapBytes <= kCvRingBytes && kCvTapBytes <= kCvWaves * kCvStageBytes, "room for the weights");
 
-// A value the compiler must take as new: what is computed from it is computed again where it is
-// used, instead of being kept in registers (or spilled) across the whole tile loop.
-__device__ __forceinline__ int cv_fresh(int v) {
-    asm volatile("" : "+v"(v));
-    return v;
-}
-
-// One LDS-direct load: the active lanes copy 16 bytes each from base + voff (per lane) to LDS at
-// lds_addr + 16 * lane (lds_addr wave-uniform).  Written as assembly so that the compiler keeps no
-// book on it: it would make LDS reads of other ring rows wait for these loads, which are meant to
-// stay in flight for two tiles.  The waits that order them are explicit in the tile loop.
-typedef uint32_t u32x4s __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void cv_dma16(u32x4s rsrc, uint32_t lds_addr, uint32_t voff) {
-    uint32_t m0_before;                                   // M0 cannot be named as clobbered: it is put back
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds\n\t"
-                 "s_mov_b32 m0, %0"
-                 : "=&s"(m0_before) : "s"(lds_addr), "v"(voff), "s"(rsrc) : "memory");
-}
 __device__ __forceinline__ uint32_t cv_lds_addr(const void* p) {
     return (uint32_t)(size_t)(__attribute__((address_space(3))) const void*)p;
 }
-
-// Per-lane byte offsets of the kCvRowLoads loads of a row, from the row's pixel x0-1: slot 64 c + lane
-// holds channel piece (lane & 7) ^ ((px >> 1) & 7) of pixel px = 8 c + lane / 8.  Pixels left or right
-// of the image get an offset beyond the descriptor (they arrive as zeros).
-struct CvRowOff {
-    uint32_t off[kCvRowLoads];
+template <int I>
+struct CvInt {
+    static constexpr int value = I;
 };
-__device__ __forceinline__ CvRowOff cv_row_offsets(const ConvArgs& p, int x0, int lane) {
-    CvRowOff d;
-#pragma unroll
-    for (int c = 0; c < kCvRowLoads; ++c) {
-        const int px = 8 * c + (lane >> 3);
-        const int cp = (lane & 7) ^ ((px >> 1) & 7);
-        const int x = x0 - 1 + px;
-        d.off[c] = (x >= 0 && x < p.W) ? (uint32_t)(px * 128 + 16 * cp) : kCvOutside;
-    }
-    return d;
+template <class F, int... J>
+__device__ __forceinline__ void cv_each(F f, std::integer_sequence<int, J...>) {
+    (f(CvInt<J>{}), ...);
 }
-
-// Requests image row y, pixels x0-1 .. x0+32, of image n into ring row `rrow`: kCvRowLoads loads by
-// the calling wave.  A row outside the image gets a descriptor of length zero: it arrives as zeros.
-__device__ __forceinline__ void cv_request_row(const ConvArgs& p, const CvRowOff& d, int n, int y, int x0,
-                                               char* ring, int rrow, int lane) {
-    const bool yok = y >= 0 && y < p.H;                   // uniform
-    // the descriptor starts at the (possibly virtual) pixel (y, x0-1); lanes outside the image never
-    // reach memory
-    const uint64_t org = (uint64_t)(p.in + (((int64_t)n * p.H + (yok ? y : 0)) * p.W + (x0 - 1)) * kCvC);
-    const u32x4s rs = {(uint32_t)org, (uint32_t)(org >> 32) & 0xffffu, yok ? 0x7fffffffu : 0u, 0x00020000u};
-    const uint32_t lds0 = cv_lds_addr(ring) + (uint32_t)(rrow * kCvRowBytes);
-#pragma unroll
-    for (int c = 0; c < kCvRowLoads - 1; ++c) cv_dma16(rs, lds0 + 1024u * c, d.off[c]);
-    if (lane < kCvRowSlots - 64 * (kCvRowLoads - 1))      // the row ends after 272 slots
-        cv_dma16(rs, lds0 + 1024u * (kCvRowLoads - 1), d.off[kCvRowLoads - 1]);
+// LDS-direct loads: the active lanes copy 16 bytes each from the descriptor's base + voff (per lane) + OFFSET to LDS at M0 + OFFSET + 16 * lane.
+// Written as assembly so that the compiler keeps no book on them: it would make LDS reads of other ring rows
+// wait for these loads, which are meant to stay in flight for rows.  The waits that order them are explicit.
+// No other instruction of this kernel uses M0.
+__device__ __forceinline__ void cv_lds_base(uint32_t lds_addr) { asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" ::"s"(lds_addr) : "memory"); }
+template <int OFFSET>
+__device__ __forceinline__ void cv_dma16(u32x4 rsrc, uint32_t voff) {
+    asm volatile("buffer_load_dwordx4 %0, %1, 0 offen offset:%2 lds" ::"v"(voff), "s"(rsrc), "n"(OFFSET) : "memory");
 }
-
-// Two output rows (2 x 32 pixels) x 32 channels from four ring rows (byte offsets row[0..3] from the
-// ring base, wave-uniform).  The four rows under the two output rows are read once per (channel
-// chunk, horizontal tap) and serve both output rows: 48 reads for 72 products, in 12 groups of
-// 4 reads + 6 products.  The reads of a group are issued kCvAhead groups before its products (the
-// scheduling barriers pin that order), so that an LDS read has the time of 6 * kCvAhead products.
-#ifndef HB_CONV_AHEAD
-#define HB_CONV_AHEAD 1
-#endif
-constexpr int kCvAhead = HB_CONV_AHEAD;
-// Lane part of the LDS byte address of group grp = 3 kc + kx: pixel c32 + kx, channel piece 2 kc + h,
-// which sits in slot (2 kc) ^ (h ^ s) of the pixel (s = the pixel's permutation).  The twelve values
-// are formed once per kernel: every instruction between two products costs the matrix pipe issue time.
-__device__ __forceinline__ int cv_lane_part(int grp, int c32, int h) {
-    const int kc = grp / 3, kx = grp - 3 * kc;
-    const int px = c32 + kx;
-    return px * 128 + ((32 * kc) ^ (16 * (h ^ ((px >> 1) & 7))));
+template <int LANES>                                      // the first LANES < 32 lanes only (all are active outside)
+__device__ __forceinline__ void cv_dma16_part(u32x4 rsrc, uint32_t voff) {
+    asm volatile("s_mov_b64 exec, %2\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds\n\ts_mov_b64 exec, -1" ::"v"(voff), "s"(rsrc), "n"((1 << LANES) - 1) : "memory");
 }
-__device__ __forceinline__ void cv_rows(const char* ring, const int (&row)[4], const half8 (&wf)[36], const int (&L)[12],
-                                        floatx16 (&acc)[2]) {
-    half8 b[kCvAhead + 1][4];
-    auto read_group = [&](int grp, half8 (&dst)[4]) {
-        const int a = L[grp];
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) dst[rr] = *reinterpret_cast<const half8*>(ring + (a + row[rr]));
-    };
-#pragma unroll
-    for (int g0 = 0; g0 < kCvAhead; ++g0) {
-        read_group(g0, b[g0]);
-        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-    }
-#pragma unroll
-    for (int grp = 0; grp < 12; ++grp) {
-        const int kc = grp / 3, kx = grp - 3 * kc;
-        if (grp + kCvAhead < 12) {
-            read_group(grp + kCvAhead, b[(grp + kCvAhead) % (kCvAhead + 1)]);
-            __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-        }
-        const half8 (&bb)[4] = b[grp % (kCvAhead + 1)];
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-            if (rr <= 2) acc[0] = mfma32x32x16(wf[(3 * rr + kx) * 4 + kc], bb[rr], acc[0]);
-            if (rr >= 1) acc[1] = mfma32x32x16(wf[(3 * (rr - 1) + kx) * 4 + kc], bb[rr], acc[1]);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
-    }
+template <int N>
+__device__ __forceinline__ void cv_wait_loads() {         // all but the newest N memory instructions of this wave are done
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
+__device__ __forceinline__ void cv_pin() { __builtin_amdgcn_sched_barrier(0); }
 
-__global__ void __launch_bounds__(kCvThreads) conv3x3_mfma_kernel(ConvArgs p) {
-    __shared__ __attribute__((aligned(16))) char s_ring[kCvRingBytes];
-    __shared__ __attribute__((aligned(16))) char s_stage[kCvStageBytes];
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c32 = lane & 31, h = lane >> 5;
-    const int j = wv >> 2;                                // channel tile of this wave
-    const int ro = 2 * (wv & 3);                          // its two output rows inside the tile
+__global__ void __launch_bounds__(64 * kCvWaves, 1) conv3x3_mfma_kernel(ConvArgs p) {
+    __shared__ __attribute__((aligned(128))) char s_ring[kCvWaves * kCvRingBytes];
+    __shared__ __attribute__((aligned(128))) char s_stage[kCvWaves * kCvStageBytes];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c = lane & 15, g = lane >> 4;
+    char* const ring = s_ring + wv * kCvRingBytes;
+    char* const stage = s_stage + wv * kCvStageBytes;
+    const uint32_t ring0 = cv_lds_addr(ring);
 
-    // task = column segment: image n, tile column cx, tile rows ty0 .. ty0 + len - 1
-    const int task = blockIdx.x;
-    const int per_img = p.tiles_x * p.nseg;
-    const int n = task / per_img;
-    const int sg = (task - n * per_img) / p.tiles_x, cx = task - n * per_img - sg * p.tiles_x;
-    const int ty0 = sg * p.seg_len;
-    const int len = min(p.seg_len, p.tiles_y - ty0);
-    const int x0 = cx * kCvTX;
-    const int ys = ty0 * kCvTY - 1;                       // image row held by ring row 0 at the start
-
-    const CvRowOff d = cv_row_offsets(p, x0, lane);
-
-    // start-up, part 1: rows 0..9 of the first tile go out before anything else (waves 0, 1 take two
-    // rows each) and land in ring rows 0..9 while the weights are staged
-    if (wv < 2) cv_request_row(p, d, n, ys + wv, x0, s_ring, wv, lane);
-    cv_request_row(p, d, n, ys + 2 + wv, x0, s_ring, 2 + wv, lane);
-
-    // coefficient fragments: wf[s] lane (c32, h) = w[tap][16 kc + 8h + i][32 j + c32], s = 4 tap + kc.
-    // The weights arrive with the output channel innermost; a fragment wants eight consecutive INPUT
-    // channels per lane.  They pass through LDS once, transposed on the way in: coalesced 16-byte
-    // reads of eight output channels, 4-byte writes to [tap][co][ci] with a 144-byte pitch per
-    // (tap, co), so that each fragment is one conflict-free 16-byte read.  Taps 0..6 use ring rows
-    // 10..25 (free until the second tile's rows are requested), taps 7, 8 the output stage.
-    half8 wf[36];
+    // weights, as they are in memory (rows of 64 output channels per input channel) but for the 32-byte pairs of a row, which
+    // change places with bits 1 and 3 of the input channel: the transposing reads below meet no bank twice
     {
-        constexpr int kWPitch = 144;                      // bytes per (tap, output channel): 64 ci + pad
-        constexpr int kWTap = kCvC * kWPitch;             // 9216 bytes per tap
-        constexpr int kTapsInRing = 7;
-        static_assert(kTapsInRing * kWTap <= (kCvRing - 10) * kCvRowBytes, "taps 0..6 must fit ring rows 10..25");
-        static_assert((9 - kTapsInRing) * kWTap <= kCvStageBytes, "taps 7, 8 must fit the output stage");
-        char* const wring = s_ring + 10 * kCvRowBytes;
-        // a thread takes the same eight output channels of TWO neighbouring input channels and writes
-        // eight 4-byte pairs; with the input-channel pair as the fastest lane index the 64 writes of an
-        // instruction fall into 64 different banks (2-byte writes, one input channel at a time, took
-        // twice the instructions and met two lanes in every bank word)
-        for (int i = tid; i < 9 * (kCvC / 2) * (kCvC / 8); i += kCvThreads) {
-            const int cip = i & 31, cog = (i >> 5) & 7, tap = i >> 8;
-            const half8 v0 = reinterpret_cast<const half8*>(p.w)[(tap * kCvC + 2 * cip) * 8 + cog];      // w[tap][2 cip][8 cog ..]
-            const half8 v1 = reinterpret_cast<const half8*>(p.w)[(tap * kCvC + 2 * cip + 1) * 8 + cog];
-            char* dst = (tap < kTapsInRing ? wring + tap * kWTap : s_stage + (tap - kTapsInRing) * kWTap) +
-                        8 * cog * kWPitch + 4 * cip;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                typedef half_t half2v __attribute__((ext_vector_type(2)));
-                *reinterpret_cast<half2v*>(dst + e * kWPitch) = half2v{v0[e], v1[e]};
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int s = 0; s < 36; ++s) {
-            const int tap = s >> 2;
-            const char* src = tap < kTapsInRing ? wring + tap * kWTap : s_stage + (tap - kTapsInRing) * kWTap;
-            wf[s] = *reinterpret_cast<const half8*>(src + (32 * j + c32) * kWPitch + 2 * (16 * (s & 3) + 8 * h));
-        }
-        __syncthreads();
+        const uint64_t w = (uint64_t)p.w + 2 * kCvTapBytes * (uint32_t)wv, w8 = (uint64_t)p.w + 8 * kCvTapBytes + 2048 * wv;
+        const u32x4 rs = {(uint32_t)w, (uint32_t)(w >> 32) & 0xffffu, 0x7fffffffu, 0x00020000u};
+        const u32x4 rs8 = {(uint32_t)w8, (uint32_t)(w8 >> 32) & 0xffffu, 0x7fffffffu, 0x00020000u};
+        // slot 64 i + lane: input channel 8 i + lane / 8, piece lane % 8
+        auto source = [&](int i) {
+            const int ci = 8 * i + (lane >> 3);
+            return (uint32_t)(128 * (lane >> 3) + 16 * ((lane & 7) ^ (ci & 2) ^ ((ci >> 1) & 4)));
+        };
+        const uint32_t even = source(0), odd = source(1);
+        cv_each([&](auto index) {
+            constexpr int i = decltype(index)::value;     // of 1 KB
+            if constexpr (i % 4 == 0) cv_lds_base(ring0 + kCvEarly * kCvRowBytes + 1024 * i);
+            cv_dma16<1024 * (i % 4)>(rs, (i % 2 ? odd : even) + 4096 * (i / 4));
+        }, std::make_integer_sequence<int, 16>{});
+        cv_lds_base(cv_lds_addr(s_stage) + 2048 * wv);
+        cv_dma16<0>(rs8, even);
+        cv_dma16<1024>(rs8, odd);
     }
 
-    // output: a descriptor over image n; thread t stores pieces t, t + 512, ... of the 8 x 32 x 8 pieces
-    // of a tile (8 lanes per pixel): row (t >> 8) + 2 i, pixel (t >> 3) & 31, piece t & 7
-    const int64_t obytes = (int64_t)p.H * p.W * kCvC * 2;     // < 2 GiB (host check)
-    const __amdgpu_buffer_rsrc_t orsrc = __builtin_amdgcn_make_buffer_rsrc(
-        p.out + (int64_t)n * p.H * p.W * kCvC, 0, (int)obytes, 0x00020000);
-    const int opx = (tid >> 3) & 31, opiece = tid & 7, orow0 = tid >> 8;
-    const uint32_t ovoff = (x0 + opx < p.W) ? (uint32_t)(((orow0 * p.W + x0 + opx) * kCvC + 8 * opiece) * 2) : kCvOutside;
-    const char* sread = s_stage + (orow0 * kCvTX + opx) * kCvStagePitch + 16 * opiece;
-    char* swrite = s_stage + (ro * kCvTX + c32) * kCvStagePitch + (32 * j + 4 * h) * 2;
+    // task = column segment: image n, strip of 32 pixels, rows y0 .. y0 + len - 1.  The waves of a workgroup take tasks beside each other.
+    const uint32_t task = (uint32_t)xcd_contiguous(blockIdx.x, gridDim.x) * kCvWaves + wv;
+    const bool active = task < p.ntasks;
+    const uint32_t per_img = (uint32_t)p.tiles_x * p.nseg;
+    const uint32_t n = active ? task / per_img : 0u, rest = active ? task - n * per_img : 0u;
+    const uint32_t sg = rest / (uint32_t)p.tiles_x;
+    const int x0 = kCvTX * (int)(rest - sg * p.tiles_x);
+    const int y0 = (int)sg * p.seg_len, len = min(p.seg_len, p.H - y0);
+    const uint32_t row_bytes = (uint32_t)p.W * 128u;
 
-    // start-up, part 2: the 8 new rows of the second tile, now that ring rows 10..17 are free
-    // (only the first tile's rows have to be there now: everything but this wave's newest request)
-    if (len > 1) {
-        cv_request_row(p, d, n, ys + 10 + wv, x0, s_ring, 10 + wv, lane);
-        asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
-    } else {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // Requests, rows y0 - 1, y0, ... one after the other: slot 64 i + lane of a row holds channel piece (lane & 7) ^ ((px >> 1) & 7) of pixel
+    // px = 8 i + lane / 8 (image column x0 - 1 + px).  Pixels left and right of the image lie beyond the descriptor and arrive as zeros;
+    // a row outside the image, or that the segment doesn't need, has a descriptor of length zero.
+    uint32_t off[kCvRowLoads];
+#pragma unroll
+    for (int i = 0; i < kCvRowLoads; ++i) {
+        const int px = 8 * i + (lane >> 3), x = x0 - 1 + px;
+        off[i] = x >= 0 && x < p.W ? (uint32_t)(128 * (lane >> 3) + (i == 4 ? 4096 : 0) + 16 * ((lane & 7) ^ ((px >> 1) & 7))) : kCvOutside;
     }
-    __syncthreads();
+    uint64_t from = (uint64_t)p.in + (((int64_t)n * p.H + (y0 - 1)) * p.W + (x0 - 1)) * 128;
+    int from_y = y0 - 1;
+    const int end_y = active ? min(p.H, y0 + len + 1) : 0;
+    uint32_t from_at = ring0;
+    u32x4 from_rs;
+    auto aim_request = [&]() {
+        from_rs = u32x4{(uint32_t)from, (uint32_t)(from >> 32) & 0xffffu, (uint32_t)from_y < (uint32_t)end_y ? 0x7fffffffu : 0u, 0x00020000u};
+        cv_lds_base(from_at);
+    };
+    auto request = [&](auto part) {
+        constexpr int i = decltype(part)::value;
+        if constexpr (i < 4) {
+            cv_dma16<1024 * i>(from_rs, off[i]);
+        } else {
+            cv_lds_base(from_at + 4096);
+            cv_dma16_part<16>(from_rs, off[4]);
+        }
+    };
+    auto next_request = [&]() {
+        from += row_bytes;
+        ++from_y;
+        from_at += kCvRowBytes;
+        if (from_at == ring0 + kCvRingBytes) from_at = ring0;
+    };
+    auto request_row = [&]() {
+        aim_request();
+        cv_each(request, std::make_integer_sequence<int, kCvRowLoads>{});
+        next_request();
+    };
+#pragma unroll 1
+    for (int r = 0; r < kCvEarly; ++r) request_row();
 
-    int L[12];
+    // coefficient fragments: wf[ct][s] lane (c, g) = w[tap][32 kc + 8g + i][16 ct + c], s = 2 tap + kc
+    half8 wf[4][18];
+    cv_wait_loads<kCvEarly * kCvRowLoads>();
+    lds_barrier();
+    {
+        // a transposing read: lane 4 r + q of 16 points at elements 4q .. 4q + 3 of row r, and lane c receives element c of the four rows
+        const int ci = 8 * g + (c >> 2);                  // bits 1 and 3 are those of 32 kc + ci, and of ci + 4
+        const int t = 128 * ci + 8 * (c & 3), flip = 32 * (((ci >> 1) & 1) | ((ci >> 2) & 2));
+        int at[4];
 #pragma unroll
-    for (int grp = 0; grp < 12; ++grp) L[grp] = cv_lane_part(grp, c32, h);
-    int rb = 0;                                           // ring row of the tile's first row: 8 k mod 26
-    for (int k = 0; k < len; ++k) {
-        // the rows of tile k + 2 take the ring rows that tile k - 1 has released
-        const bool req = k + 2 < len;                     // uniform
-        if (req) {
-            int rr2 = rb + 18 + wv;
-            if (rr2 >= kCvRing) rr2 -= kCvRing;
-            cv_request_row(p, d, n, ys + 8 * k + 18 + wv, x0, s_ring, rr2, lane);
+        for (int ct = 0; ct < 4; ++ct) at[ct] = t + ((32 * ct) ^ flip);
+        typedef short short4v __attribute__((ext_vector_type(4)));
+        auto read = [&](int ct, int s, int u) {
+            const int tap = s >> 1;
+            const char* base = tap < 8 ? s_ring + (tap >> 1) * kCvRingBytes + kCvEarly * kCvRowBytes + (tap & 1) * kCvTapBytes : s_stage;
+            return __builtin_bit_cast(half4, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                                 (__attribute__((address_space(3))) short4v*)(base + at[ct] + 4096 * (s & 1) + 512 * u)));
+        };
+#pragma unroll
+        for (int s = 0; s < 18; ++s)
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct) wf[ct][s] = join(read(ct, s, 0), read(ct, s, 1));
+    }
+    lds_barrier();
+    if (!active) {
+        cv_wait_loads<0>();                               // nothing may arrive in LDS that is no longer this workgroup's
+        return;
+    }
+    // 64 of the 72 fragments live in the accumulation registers
+#pragma unroll
+    for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+        for (int s = 0; s < 16; ++s) asm volatile("" : "+a"(wf[ct][s]));
+#pragma unroll 1
+    for (int r = kCvEarly; r < kCvRing; ++r) request_row();
+
+    // pixel fragments of the row in use: b[pt][i] lane (c, g) = channels 32 kc + 8g .. + 7 of pixel 16 pt + c + kx, i = 2 kx + kc
+    half8 b[2][6];
+    int part[3];
+#pragma unroll
+    for (int kx = 0; kx < 3; ++kx) part[kx] = (c + kx) * 128 + 16 * (g ^ (((c + kx) >> 1) & 7));
+    uint32_t row_at = 0;
+    auto load = [&](int pt, int i) { b[pt][i] = *reinterpret_cast<const half8*>(ring + row_at + ((part[i >> 1] ^ (64 * (i & 1))) + 2048 * pt)); };
+    auto next_row = [&]() { row_at = row_at + kCvRowBytes == kCvRingBytes ? 0 : row_at + kCvRowBytes; };
+
+    // the 48 products of a row with kernel row KY, and after product j what between(j) puts there
+    auto products = [&](auto ky, floatx4 (&acc)[4][2], auto between) {
+        constexpr int KY = decltype(ky)::value;
+        cv_each([&](auto index) {
+            constexpr int j = decltype(index)::value, pt = j / 24, ct = j / 6 % 4, i = j % 6;
+            acc[ct][pt] = mfma16x16x32(wf[ct][6 * KY + i], b[pt][i], KY == 0 && i == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : acc[ct][pt]);
+            cv_pin();
+            between(index);
+            cv_pin();
+        }, std::make_integer_sequence<int, 48>{});
+    };
+
+    // way out: lane (c, g) holds channels 16 ct + 4g .. + 3 of pixel 16 pt + c
+    char* const put = stage + c * kCvStagePitch + 8 * g;
+    const char* const get = stage + (lane >> 3) * kCvStagePitch + 16 * (lane & 7);
+    auto lay = [&](int i, const half4& v) { *reinterpret_cast<half4*>(put + 16 * kCvStagePitch * (i >> 2) + 32 * (i & 3)) = v; };      // i = 4 pt + ct
+    half8 line[4];
+    auto take = [&](int i) { line[i] = *reinterpret_cast<const half8*>(get + 8 * i * kCvStagePitch); };
+    const uint32_t cols = (uint32_t)min(kCvTX, p.W - x0) * 128u;          // bytes of a row of the strip; what lies beyond is dropped
+    uint64_t to = (uint64_t)p.out + (((int64_t)n * p.H + y0) * p.W + x0) * 128;
+    auto give = [&](int i) {
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(to), 0, (int)cols, 0x00020000);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, line[i]), rs, 16 * lane + 1024 * i, 0, kCvStream);
+    };
+
+    // Row r of the segment (-1 .. len) contributes to output rows r - 1 (kernel row 2), r (1) and r + 1 (0).
+    floatx4 acc0[4][2], acc1[4][2];
+    constexpr CvInt<0> ky0{};
+    constexpr CvInt<1> ky1{};
+    constexpr CvInt<2> ky2{};
+    // kernel row 0: starts output row r + 1; row r + kCvRing is requested into the place of row r, and the fragments of row r + 1 take those of row r
+    auto first = [&](floatx4 (&acc)[4][2]) {
+        products(ky0, acc, [&](auto index) {
+            constexpr int j = decltype(index)::value;
+            if constexpr (j == 0) aim_request();
+            if constexpr (j == 2) request(CvInt<0>{});
+            if constexpr (j == 5) request(CvInt<1>{});
+            if constexpr (j == 8) request(CvInt<2>{});
+            if constexpr (j == 11) request(CvInt<3>{});
+            if constexpr (j == 14) request(CvInt<4>{});
+            if constexpr (j == 16) next_request();
+            if constexpr (j == 17) next_row();
+            if constexpr (j == 19) cv_wait_loads<kCvRowLoads * (kCvRing - 1)>();          // row r + 1 is there
+            if constexpr (j >= 24 && j < 36 && j % 2 == 0) load(0, (j - 24) / 2);
+        });
+    };
+    auto next = [&]() {                                   // there is no output row r + 1: the fragments alone
+        next_row();
+        cv_wait_loads<kCvRowLoads * (kCvRing - 2)>();
+#pragma unroll
+        for (int i = 0; i < 6; ++i) load(0, i);
+        cv_pin();
+    };
+    auto last = [&](floatx4 (&acc)[4][2]) {
+        products(ky2, acc, [&](auto index) {
+            constexpr int j = decltype(index)::value;
+            if constexpr (j >= 1 && j < 13 && j % 2 == 1) load(1, j / 2);
+        });
+    };
+    auto middle = [&](floatx4 (&acc)[4][2], const floatx4 (&done)[4][2]) {
+        products(ky1, acc, [&](auto index) {
+            constexpr int j = decltype(index)::value;
+            if constexpr (j >= 2 && j < 26 && (j - 2) % 3 == 0) lay((j - 2) / 3, to_half4(done[(j - 2) / 3 & 3][(j - 2) / 12]));
+            if constexpr (j == 25) wave_lds_fence();
+            if constexpr (j >= 26 && j < 30) take(j - 26);
+            if constexpr (j >= 40 && j % 2 == 0) give((j - 40) / 2);
+            if constexpr (j == 47) to += row_bytes;
+        });
+        wave_lds_fence();
+    };
+    auto finish = [&](floatx4 (&done)[4][2]) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) lay(i, to_half4(done[i & 3][i >> 2]));
+        wave_lds_fence();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) take(i);
+        cv_wait_loads<0>();                               // as above
+#pragma unroll
+        for (int i = 0; i < 4; ++i) give(i);
+    };
+
+    cv_wait_loads<kCvRowLoads * (kCvRing - 1)>();         // row -1
+#pragma unroll
+    for (int i = 0; i < 12; ++i) load(i / 6, i % 6);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");    // read, before its place is requested over
+    cv_pin();
+    first(acc0);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) load(1, i);
+    cv_pin();
+    products(ky1, acc0, [](auto) {});
+    if (len == 1) {
+        next();
+        last(acc0);
+        finish(acc0);
+        return;
+    }
+    first(acc1);
+    for (int r = 1;; r += 2) {
+        last(acc0);
+        middle(acc1, acc0);
+        if (r + 1 == len) {
+            next();
+            last(acc1);
+            finish(acc1);
+            return;
         }
-        __builtin_amdgcn_sched_barrier(0);                // the requests go out before the first product
-        int row[4];
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-            int r = rb + ro + rr;
-            if (r >= kCvRing) r -= kCvRing;
-            row[rr] = r * kCvRowBytes;
+        first(acc0);
+        last(acc1);
+        middle(acc0, acc1);
+        if (r + 2 == len) {
+            next();
+            last(acc0);
+            finish(acc0);
+            return;
         }
-        floatx16 acc[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[u][v] = 0.f;
-        cv_rows(s_ring, row, wf, L, acc);
-        __builtin_amdgcn_sched_barrier(0);
-        // The stage is free once every wave has read the previous tile out of it: met here, after the products, and not at the end of
-        // a turn, so that the stores go out while other waves multiply (8 x 56 x 56 8.6 -> 8.3 us, 700 x 1300 75.9 -> 74.7).
-        if (k > 0) asm volatile("s_barrier" ::: "memory");
-        // accumulators -> stage: lane (c32, h) holds channels 32 j + 8 q + 4 h + (0..3) of pixel c32
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                half4 v4;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v4[r] = (half_t)acc[u][4 * q + r];
-                *reinterpret_cast<half4*>(swrite + u * (kCvTX * kCvStagePitch) + 16 * q) = v4;
-            }
-        // Meeting point.  A wave waits for all its memory instructions but the newest request (loads
-        // and stores retire in order): its row of the NEXT tile has landed, the previous tile's
-        // stores are done.  The barrier instructions are written out: the compiler would put a wait
-        // for ALL memory instructions in front of one it emits itself.
-        static_assert(kCvRowLoads == 5, "the counted wait below is written for five loads per request");
-        if (req) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
-        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // next rows complete, this tile's rows released, stage written
-        // stage -> memory: 8 lanes per pixel, 1 KB per store instruction; rows below the image fall
-        // behind the end of the descriptor and are dropped
-        const uint32_t osoff = (uint32_t)((ty0 + k) * kCvTY) * (uint32_t)(p.W * kCvC * 2);
-#pragma unroll
-        for (int i = 0; i < kCvTY * kCvTX * 8 / kCvThreads; ++i) {
-            const half8 v = *reinterpret_cast<const half8*>(sread + 2 * i * (kCvTX * kCvStagePitch));
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4s, v), orsrc, ovoff,
-                                                   osoff + (uint32_t)(2 * i) * (uint32_t)(p.W * kCvC * 2), 0);
-        }
-        rb += 8;
-        if (rb >= kCvRing) rb -= kCvRing;
+        first(acc1);
     }
 }
 
@@ -387,25 +426,24 @@ static hb_status conv_prepare(ConvArgs& a, const hb_half* in, const hb_half* w, 
     a.tiles_x = ceil_div(W, kCvTX);
     a.tiles_y = ceil_div(H, kCvTY);
     a.ntiles = (int)tiles;
-    // Column segments of the MFMA kernel: a compute unit holds one workgroup, so the columns are cut into as many equal
-    // segments as fill the chip some whole number of times and not once more.  A round costs its segment's tiles and the
-    // start of a workgroup, weights and first rows, about two tiles' time; the cheapest number of rounds is taken.
-    // Against segments of four tiles at least, rounded to more than one round: 700 x 1300 (246 segments of 15 tiles, not 287
-    // of 13) 94.4 -> 68.9 us, 5 x 400 x 400 88.5 -> 67.9, 8 x 56 x 56 (112 of one tile, not 32 of four) 16.8 -> 8.6.
-    const int64_t columns = (int64_t)N * a.tiles_x, units = num_cu();
-    const int64_t least = (columns + units - 1) / units;
-    int len = a.tiles_y;
+    // Column segments of the MFMA kernel: a compute unit holds four waves, so the strips are cut into as many equal segments as fill the
+    // chip some whole number of times and not once more.  A round costs its segment's rows and the start of a workgroup, weights
+    // and first rows, about three rows' time (a row 1 to 1.5 us); the cheapest number of rounds is taken.
+    const int64_t columns = (int64_t)N * a.tiles_x, waves = (int64_t)kCvWaves * num_cu();
+    const int64_t least = (columns + waves - 1) / waves;
+    int len = H;
     int64_t cheapest = INT64_MAX;
     for (int64_t rounds = least; rounds < least + 16; ++rounds) {
-        const int64_t segments = std::min<int64_t>(rounds * units / columns, a.tiles_y);
-        const int64_t tiles_each = (a.tiles_y + segments - 1) / segments, cost = rounds * (tiles_each + 2);
+        const int64_t segments = std::min<int64_t>(rounds * waves / columns, H);
+        const int64_t rows_each = (H + segments - 1) / segments, cost = rounds * (rows_each + 3);
         if (cost < cheapest) {
             cheapest = cost;
-            len = (int)tiles_each;
+            len = (int)rows_each;
         }
     }
     a.seg_len = len;
-    a.nseg = ceil_div(a.tiles_y, len);
+    a.nseg = ceil_div(H, len);
+    a.ntasks = (uint32_t)(columns * a.nseg);              // at most 16 rounds more than columns
     return HB_OK;
 }
 
@@ -417,9 +455,9 @@ extern "C" hb_status hb_conv3x3(const hb_half* in_nhwc, const hb_half* w_hwio, h
     ConvArgs a;
     hb_status s = conv_prepare(a, in_nhwc, w_hwio, out_nhwc, N, H, W, Cin, Cout);
     if (s != HB_OK) return s;
-    const int64_t blocks = (int64_t)N * a.tiles_x * a.nseg;
+    const int64_t blocks = ((int64_t)a.ntasks + kCvWaves - 1) / kCvWaves;
     if (blocks > 0x7fffffff) return HB_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(conv3x3_mfma_kernel, dim3((unsigned)blocks), dim3(kCvThreads), 0,
+    hipLaunchKernelGGL(conv3x3_mfma_kernel, dim3((unsigned)blocks), dim3(64 * kCvWaves), 0,
                        reinterpret_cast<hipStream_t>(stream), a);
     return launch_status();
 }

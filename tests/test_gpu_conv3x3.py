@@ -80,6 +80,22 @@ def test_conv_column_segments(orc, N, H, W):
     assert_close(got[ns, ys, xs], orc.conv3x3_points(x, w, ns, ys, xs), f"hb_conv3x3 {N}x{H}x{W}")
 
 
+@pytest.mark.parametrize("N,H,W", [(1, 1, 40), (1, 2, 31), (1, 3, 33), (2, 130, 1), (1, 37, 2100), (5, 41, 1700), (1, 1025, 65), (700, 3, 64)])
+def test_conv_strips(orc, N, H, W):
+    """Segments of one, two, three and many rows, strips of one to 32 pixels, workgroups with one to four strips, one round of them
+    and more: every output of small images, the first and last rows and columns and scattered pixels of the others."""
+    x = synth.uniform_pm1_f16(9300 + H, (N, H, W, 64))
+    w = synth.normal_f16(9301, (3, 3, 64, 64), 1 / 24)
+    got = run("hb_conv3x3", x, w)
+    if N * H * W < 20000:
+        assert_close(got, orc.conv3x3(x, w), f"hb_conv3x3 {N}x{H}x{W}")
+        return
+    h = synth.hash_u64(9302 + W, 0, 9000)
+    ns, ys, xs = ((h[k::3] % np.uint64(m)).astype(np.int32) for k, m in enumerate((N, H, W)))
+    ns[:2], ys[:400:2], ys[1:400:2], xs[400:800:2], xs[401:800:2] = (0, N - 1), 0, H - 1, 0, W - 1
+    assert_close(got[ns, ys, xs], orc.conv3x3_points(x, w, ns, ys, xs), f"hb_conv3x3 {N}x{H}x{W}")
+
+
 def test_conv_rejects_other_channel_counts():
     import torch
     from paper_2512_02371_amd import hb
