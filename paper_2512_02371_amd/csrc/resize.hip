@@ -89,14 +89,19 @@ __device__ __forceinline__ void rz_extent(int& lo, int& hi) {
 #undef HB_RZ_STEP
 }
 
+template <int I>
+struct RzInt {
+    static constexpr int value = I;
+};
+
 // What bounds it: a wave's chain of dependent round trips (starts -> pixels and coefficients -> vertical products ->
 // stores) where waves are few, and its instructions (the geometry of a group is 600 of them) where they are many: GY
 // groups of rows per wave share them and the rows that neighbouring groups both need.  As two launches with T in
 // memory: 3 x 2048 x 2048 -> 450 27.7 -> 19.4 us, 4096 x 4096 -> 2048 36 -> 27, -> 256 39 -> 20.
-template <int GY, bool SHARED>
-__global__ void __launch_bounds__(64 * RzGeom<SHARED>::kWaves, 4) resize_mfma_kernel(ResizeArgs p) {
+template <int GY, bool SHARED, bool ODD>
+__global__ void __launch_bounds__(64 * RzGeom<SHARED>::kWaves, ODD && !SHARED ? 3 : 4) resize_mfma_kernel(ResizeArgs p) {
     constexpr int kWaves = RzGeom<SHARED>::kWaves, kRows = RzGeom<SHARED>::kRows, kPitch = RzGeom<SHARED>::kPitch;
-    __shared__ __attribute__((aligned(16))) half8 s_frag[kRzChunks * 64];
+    __shared__ __attribute__((aligned(16))) half8 s_frag[(ODD ? 2 : 1) * kRzChunks * 64];
     __shared__ __attribute__((aligned(16))) half_t s_rows[(SHARED ? 1 : kWaves) * 16 * kPitch];
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = lane & 15, g = lane >> 4;
@@ -118,10 +123,12 @@ __global__ void __launch_bounds__(64 * RzGeom<SHARED>::kWaves, 4) resize_mfma_ke
     const int sy = clampi(p.start_y[min(yo0 + (lane & (16 * GY - 1)), p.Ho - 1)], -p.band_y, p.H - 1);
     int xlo = sx, xhi = sx + p.band_x;
     rz_extent(xlo, xhi);
-    xlo = __builtin_amdgcn_readfirstlane(xlo) & ~1;
+    const half_t* const px = p.in + (int64_t)plane * p.in_plane;
+    // ODD: the rows that start on an odd sample are read from one sample further left
+    xlo = (__builtin_amdgcn_readfirstlane(xlo) & ~1) - (ODD ? 1 : 0);
     xhi = __builtin_amdgcn_readfirstlane(xhi);
     const int nk = (xhi - xlo + 31) >> 5, aligned = xlo & p.first_mask;
-    if (xhi - aligned <= 32 * nk) xlo = aligned;
+    if (!ODD && xhi - aligned <= 32 * nk) xlo = aligned;
     int glo = sy, ghi = sy + p.band_y;                    // of the lane's group of 16 rows
     rz_extent(glo, ghi);
     int ylo = glo, yhi = ghi;
@@ -134,17 +141,19 @@ __global__ void __launch_bounds__(64 * RzGeom<SHARED>::kWaves, 4) resize_mfma_ke
     yhi = __builtin_amdgcn_readfirstlane(yhi);
 
     // coefficient blocks, B-operand layout: lane (c = o, g) holds coef[o][first + 32 kk + 8g + i - start[o]]
-    auto frag_x = [&](int kk) { return rz_coef8(p.coef_x, p.Wo, p.band_x, xo, xlo + 32 * kk + 8 * g - sx); };
-    for (int kk = wv; kk < min(nk, kRzChunks); kk += kWaves) s_frag[kk * 64 + lane] = frag_x(kk);
+    const int x_even = xlo + (ODD ? 1 : 0);
+    auto frag_x = [&](int kk, int from) { return rz_coef8(p.coef_x, p.Wo, p.band_x, xo, from + 32 * kk + 8 * g - sx); };
+    for (int kk = wv; kk < min(nk, kRzChunks); kk += kWaves) s_frag[kk * 64 + lane] = frag_x(kk, x_even);
+    if (ODD)
+        for (int kk = kWaves - 1 - wv; kk < min(nk, kRzChunks); kk += kWaves) s_frag[(kRzChunks + kk) * 64 + lane] = frag_x(kk, xlo);
 
-    const half_t* const px = p.in + (int64_t)plane * p.in_plane;
     half_t* const rows = s_rows + (SHARED ? 0 : wv * 16 * kPitch);        // T
     floatx4 out[GY];
 #pragma unroll
     for (int q = 0; q < GY; ++q) out[q] = floatx4{0.f, 0.f, 0.f, 0.f};
-    auto load = [&](int y, int kk) {                      // chunk kk of row y
+    auto load_from = [&](int y, int xs) {                 // 32 columns of row y from xs on
         const uint32_t row = (uint32_t)clampi(y, 0, p.H - 1) * (uint32_t)p.in_pitch;
-        const int xs = xlo + 32 * kk, x = xs + 8 * g;
+        const int x = xs + 8 * g;
         if (xs >= 0 && xs + 32 <= p.W) return ldg8(px, 2u * (row + (uint32_t)x));     // uniform
         // Requested inside the row, then shifted into place.  The column is hidden from the compiler, which otherwise works
         // out the masks of all four chunks' shifts ahead of the loop, also for groups inside the image, and spills 40 scalar
@@ -154,6 +163,7 @@ __global__ void __launch_bounds__(64 * RzGeom<SHARED>::kWaves, 4) resize_mfma_ke
         const half8 v = ldg8(px, 2u * (row + (uint32_t)clampi(xe, 0, p.W - 8)));
         return shift_in_from_left(shift_in_from_right(v, max(xe - (p.W - 8), 0)), max(-xe, 0));
     };
+    auto load = [&](int y, int kk) { return load_from(y, x_even + 32 * kk); };
     auto rows_ready = [&]() {
         if (SHARED) __syncthreads();
         else wave_lds_fence();
@@ -162,8 +172,157 @@ __global__ void __launch_bounds__(64 * RzGeom<SHARED>::kWaves, 4) resize_mfma_ke
     __syncthreads();
     if (yo0 >= p.Ho) return;                              // SHARED: no such workgroup
 
+    auto vertical = [&](int base) {                       // with the rows that T holds from base on
+#pragma unroll
+        for (int q = 0; q < GY; ++q) {
+            const int vsy = __shfl(sy, 16 * q + c, 64), vo = min(yo0 + 16 * q + c, p.Ho - 1);
+            const int first = ylo + ((__builtin_amdgcn_readlane(glo, 16 * q) - ylo) & ~7);   // 16-byte pieces of T
+            const int hi = __builtin_amdgcn_readlane(ghi, 16 * q);
+            // chunks that start in this round, four coefficient loads at a time
+            const int k_first = max(base - first + 31, 0) / 32, k_end = min(hi - first + 31, base + kRows - first + 31) / 32;
 #pragma unroll 1
-    for (int base = ylo; base < yhi; base += kRows) {
+            for (int k0 = k_first; k0 < k_end; k0 += 4) {
+                half8 f[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (k0 + k < k_end) f[k] = rz_coef8(p.coef_y, p.Ho, p.band_y, vo, first + 32 * (k0 + k) + 8 * g - vsy);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (k0 + k < k_end)
+                        out[q] = mfma16x16x32(*reinterpret_cast<const half8*>(rows + c * kPitch + first + 32 * (k0 + k) - base + 8 * g), f[k], out[q]);
+            }
+        }
+    };
+    // ODD: rows start on even and odd samples in turn, and of a row read from an odd one on every lane's 16 bytes are several cache
+    // accesses.  Here the even and the odd rows of 32 are two operands, each of which is read from whole dwords with coefficients that
+    // start where its window does; what they give is put together again on its way to T (3 x 1912 x 2923 -> 671 x 1025 39.3 -> 25.9 us).
+    // For groups inside the rows whose rows fit T, the others take the general loop.
+    auto short_loop = [&](auto chunks, int base, int tiles) {
+        constexpr int NK = decltype(chunks)::value, kAhead = 2;       // units of 32 rows in flight
+        const int first_odd = (int)((reinterpret_cast<uintptr_t>(px) >> 1) + (uintptr_t)(intptr_t)base) & 1;    // row base starts on an odd sample
+        // (hidden from the compiler, which otherwise works out the addresses of all four loops ahead of the first)
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        const int lc = l & 15, lg = l >> 4;
+        half8 f[2][NK];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int k = 0; k < NK; ++k) f[u][k] = s_frag[((u ^ first_odd) ? kRzChunks + k : k) * 64 + l];
+        half8 d[kAhead][2][NK];
+        auto request = [&](int t, half8 (&to)[2][NK]) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int y = base + 32 * t + 2 * lc + u, xs = x_even - (u ^ first_odd);
+                const uint32_t at = (uint32_t)clampi(y, 0, p.H - 1) * (uint32_t)p.in_pitch + (uint32_t)(xs + 8 * lg);
+                const char* const q = reinterpret_cast<const char*>(px) + (uint64_t)(2u * at);
+#pragma unroll
+                for (int k = 0; k < NK; ++k) to[u][k] = *reinterpret_cast<const half8_u*>(q + 64 * k);
+            }
+        };
+        const int units = tiles / 2;
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a)
+            if (t_first + a * t_step < units) request(t_first + a * t_step, d[a]);
+#pragma unroll 1
+        for (int t = t_first; t < units; t += kAhead * t_step) {
+#pragma unroll
+            for (int a = 0; a < kAhead; ++a) {
+                const int ta = t + a * t_step;
+                if (ta >= units) break;
+                floatx4 acc[2];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    acc[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int k = 0; k < NK; ++k) acc[u] = mfma16x16x32(d[a][u][k], f[u][k], acc[u]);
+                }
+                if (ta + kAhead * t_step < units) request(ta + kAhead * t_step, d[a]);
+                half8 h;                                  // rows 8g .. 8g + 7 of the unit
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    h[2 * j] = (half_t)acc[0][j];
+                    h[2 * j + 1] = (half_t)acc[1][j];
+                }
+                *reinterpret_cast<half8*>(rows + lc * kPitch + 32 * ta + 8 * lg) = h;
+            }
+        }
+    };
+    // The same for five chunks and more: up to four of them at a time, the next ones in flight, coefficients from LDS.
+    auto long_loop = [&](int base, int tiles) {
+        const int first_odd = (int)((reinterpret_cast<uintptr_t>(px) >> 1) + (uintptr_t)(intptr_t)base) & 1, units = tiles / 2;
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        const int lc = l & 15, lg = l >> 4;
+        auto request = [&](int t, int k0, half8 (&to)[2][4]) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int y = base + 32 * t + 2 * lc + u, xs = x_even - (u ^ first_odd) + 32 * k0;
+                const uint32_t at = (uint32_t)clampi(y, 0, p.H - 1) * (uint32_t)p.in_pitch + (uint32_t)(xs + 8 * lg);
+                const char* const q = reinterpret_cast<const char*>(px) + (uint64_t)(2u * at);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (k0 + k < nk) to[u][k] = *reinterpret_cast<const half8_u*>(q + 64 * k);        // uniform
+            }
+        };
+        floatx4 acc[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
+        auto use = [&](int t, int k0, const half8 (&d)[2][4]) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (k0 + k < nk) {
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) acc[u] = mfma16x16x32(d[u][k], s_frag[((u ^ first_odd) * kRzChunks + k0 + k) * 64 + l], acc[u]);
+                }
+            if (k0 + 4 < nk) return;
+            half8 h;                                      // rows 8g .. 8g + 7 of the unit
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                h[2 * j] = (half_t)acc[0][j];
+                h[2 * j + 1] = (half_t)acc[1][j];
+            }
+            *reinterpret_cast<half8*>(rows + lc * kPitch + 32 * t + 8 * lg) = h;
+            acc[0] = acc[1] = floatx4{0.f, 0.f, 0.f, 0.f};
+        };
+        auto advance = [&](int& t, int& k0) {
+            k0 += 4;
+            if (k0 >= nk) {
+                k0 = 0;
+                t += t_step;
+            }
+        };
+        half8 d0[2][4], d1[2][4];
+        int t = t_first, k0 = 0;
+        if (t < units) request(t, k0, d0);
+#pragma unroll 1
+        while (t < units) {
+            int tn = t, kn = k0;
+            advance(tn, kn);
+            if (tn < units) request(tn, kn, d1);
+            use(t, k0, d0);
+            if (tn >= units) break;
+            t = tn;
+            k0 = kn;
+            advance(t, k0);
+            if (t < units) request(t, k0, d0);
+            use(tn, kn, d1);
+        }
+    };
+    const bool short_group = ODD && xlo >= 0 && x_even + 32 * nk <= p.W && yhi - ylo <= kRows && nk <= kRzChunks;    // uniform
+    if constexpr (ODD) {
+        if (short_group) {
+            const int base = ylo, tiles = (yhi - base + 31) / 32 * 2;
+            if (!SHARED || wv == 0) *reinterpret_cast<half8*>(rows + c * kPitch + 16 * tiles + 8 * g) = half8{};
+            if (nk == 1) short_loop(RzInt<1>{}, base, tiles);
+            else if (nk == 2) short_loop(RzInt<2>{}, base, tiles);
+            else if (nk == 3) short_loop(RzInt<3>{}, base, tiles);
+            else if (nk == 4) short_loop(RzInt<4>{}, base, tiles);
+            else long_loop(base, tiles);
+            rows_ready();
+            if (!SHARED || wv == 0) vertical(base);
+        }
+    }
+#pragma unroll 1
+    for (int base = ylo; !short_group && base < yhi; base += kRows) {
         // T of rows base .. base + rows - 1; a chunk of the vertical pass that starts before base + kRows may reach
         // 32 rows further, real ones or, after the last, zeros
         const bool last = yhi - base <= kRows;
@@ -208,31 +367,13 @@ __global__ void __launch_bounds__(64 * RzGeom<SHARED>::kWaves, 4) resize_mfma_ke
             for (int t = t_first; t < tiles; t += t_step) {
                 floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-                for (int kk = 0; kk < nk; ++kk) acc = mfma16x16x32(load(base + 16 * t + c, kk), frag_x(kk), acc);
+                for (int kk = 0; kk < nk; ++kk) acc = mfma16x16x32(load(base + 16 * t + c, kk), frag_x(kk, x_even), acc);
                 keep(t, acc);
             }
         }
         rows_ready();
         if (SHARED && wv != 0) continue;
-#pragma unroll
-        for (int q = 0; q < GY; ++q) {
-            const int vsy = __shfl(sy, 16 * q + c, 64), vo = min(yo0 + 16 * q + c, p.Ho - 1);
-            const int first = ylo + ((__builtin_amdgcn_readlane(glo, 16 * q) - ylo) & ~7);   // 16-byte pieces of T
-            const int hi = __builtin_amdgcn_readlane(ghi, 16 * q);
-            // chunks that start in this round, four coefficient loads at a time
-            const int k_first = max(base - first + 31, 0) / 32, k_end = min(hi - first + 31, base + kRows - first + 31) / 32;
-#pragma unroll 1
-            for (int k0 = k_first; k0 < k_end; k0 += 4) {
-                half8 f[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (k0 + k < k_end) f[k] = rz_coef8(p.coef_y, p.Ho, p.band_y, vo, first + 32 * (k0 + k) + 8 * g - vsy);
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (k0 + k < k_end)
-                        out[q] = mfma16x16x32(*reinterpret_cast<const half8*>(rows + c * kPitch + first + 32 * (k0 + k) - base + 8 * g), f[k], out[q]);
-            }
-        }
+        vertical(base);
     }
     if (SHARED && wv != 0) return;
     // D[m = xo][n = yo]: lane (c = yo, g) holds columns 4g .. 4g + 3 of its row
@@ -509,9 +650,12 @@ static hb_status resize_run(bool valu, const hb_half* in, float* out, void* work
     // Nor does it pay where the rows of a group are so many that few workgroups pass over most of the image (2832 x 3696
     // -> 55 x 210, 370 x 1081 pixels a group: 84 us, two launches 64; 127 x 1655 47 against 77).
     // Rows that start on odd samples are read at a fraction of the rate, and the one-launch kernel reads a row for every
-    // group of outputs that needs it: large images take two (8 planes of 2048 rows at a pitch of 2049, factor 9: 71 us
-    // against 55; factor 4: 57 against 65; small ones gain from one, 874 x 3053 at 3117 -> 13 x 341 49 against 62).
-    const bool odd_rows = (in_pitch & 1) || (C > 1 && (in_plane & 1)) || !aligned_to(in, 4);
+    // group of outputs that needs it.  Odd pitches: large images and many groups take the kernel that reads even and odd rows apart (8 planes
+    // of 2048 rows at a pitch of 2049, factors 4 / 9: 57 / two launches 55 -> 45 / 44 us; 1947 x 6281 -> 214 x 690 28.9 -> 18.9; 4095 x 4095 -> 900
+    // 45 -> 29; 901 x 1001 -> 800 x 900 6.0 -> 5.6; few groups of small images gain nothing: 2 x 600 x 603 -> 40 18.6, 19.2).  Other
+    // large images of such rows take two launches (874 x 3053 at 3117 -> 13 x 341 49 with one, 62 with two).
+    const bool apart = (in_pitch & 1) && (waves > num_cu() || (int64_t)C * H * W > (6 << 20));
+    const bool odd_rows = !apart && ((in_pitch & 1) || (C > 1 && (in_plane & 1)) || !aligned_to(in, 4));
     // Large enlargements are bound by their stores, of 64-byte runs here and 256-byte runs there (3 x 2048 x 2048 to three
     // times the size 222 us, two launches 170); where rows start inside 128-byte lines neither run is whole (227 against 246).
     const bool line_stores = (double)Ho * Wo >= 2.0 * H * W && (int64_t)C * Ho * Wo > (16 << 20) && out_pitch % 32 == 0 &&
@@ -557,10 +701,15 @@ static hb_status resize_run(bool valu, const hb_half* in, float* out, void* work
         const int64_t blocks = (int64_t)C * r.ngx * r.ngy;
         if (blocks > 0x7fffffff) return HB_ERR_UNSUPPORTED;
         const dim3 grid((unsigned)blocks), block(64 * RzGeom<false>::kWaves);
-        if (gq == 4) hipLaunchKernelGGL((resize_mfma_kernel<4, false>), grid, block, 0, st, r);
-        else if (gq == 2) hipLaunchKernelGGL((resize_mfma_kernel<2, false>), grid, block, 0, st, r);
-        else if (gq == 1) hipLaunchKernelGGL((resize_mfma_kernel<1, false>), grid, block, 0, st, r);
-        else hipLaunchKernelGGL((resize_mfma_kernel<1, true>), grid, dim3(64 * RzGeom<true>::kWaves), 0, st, r);
+        auto launch = [&](auto odd) {
+            constexpr bool ODD = decltype(odd)::value != 0;
+            if (gq == 4) hipLaunchKernelGGL((resize_mfma_kernel<4, false, ODD>), grid, block, 0, st, r);
+            else if (gq == 2) hipLaunchKernelGGL((resize_mfma_kernel<2, false, ODD>), grid, block, 0, st, r);
+            else if (gq == 1) hipLaunchKernelGGL((resize_mfma_kernel<1, false, ODD>), grid, block, 0, st, r);
+            else hipLaunchKernelGGL((resize_mfma_kernel<1, true, ODD>), grid, dim3(64 * RzGeom<true>::kWaves), 0, st, r);
+        };
+        if (apart) launch(RzInt<1>{});
+        else launch(RzInt<0>{});
         return launch_status();
     }
 

@@ -192,3 +192,29 @@ def test_resize_first_column_of_a_window(orc, band, pitch_extra):
         got, _ = run("hb_resize", img, sy, cy, sx, cx, pitch_extra)
         for c in range(2):
             assert_close(got[c], orc.band_resize(img[c], sy, cy, sx, cx), f"offset {off} plane {c}")
+
+
+@pytest.mark.parametrize("first", [0, 1])             # the image's first row starts on an even or an odd sample
+@pytest.mark.parametrize("C,H,W,Ho,Wo", [
+    (1, 300, 1201, 290, 1190), (3, 131, 1003, 97, 700), (1, 517, 1555, 300, 601), (1, 800, 2001, 300, 444),      # windows of one to four chunks
+    (1, 1001, 3301, 181, 600), (1, 1500, 4601, 150, 307), (2, 1400, 2401, 100, 160),                             # of more
+    (1, 190, 40001, 17, 5000), (1, 2701, 2601, 40, 40),                                                          # few rows of groups; shared by a workgroup's waves
+])
+def test_resize_even_and_odd_rows_apart(orc, C, H, W, Ho, Wo, first):
+    """Odd pitches of large images and many groups: rows that start on even and on odd samples are read apart."""
+    import torch
+    from paper_2512_02371_amd import hb
+    (sy, cy), (sx, cx) = lanczos(hb, H, Ho), lanczos(hb, W, Wo)
+    img = synth.uniform01_f16(3000 + H + first, (C, H, W))
+    base = torch.full((C, H, W + 1 + W % 2), float("nan"), dtype=torch.float16, device="cuda:0")      # an odd pitch
+    d_in = base[:, :, first:first + W]
+    d_in.copy_(up(img))
+    assert d_in.stride(1) % 2 == 1
+    out = torch.full((C, Ho, Wo), 7.0, dtype=torch.float32, device="cuda:0")
+    ws = torch.empty(hb.hb_resize_workspace_size(C, H, Wo), dtype=torch.uint8, device="cuda:0")
+    dev = lambda a: torch.from_numpy(a).to("cuda:0")
+    print(f"hb_resize C={C} {H}x{W} -> {Ho}x{Wo} first {first}", flush=True)
+    hb.hb_resize(d_in, out, ws, dev(sy), dev(cy.view(np.float16)), dev(sx), dev(cx.view(np.float16)))
+    torch.cuda.synchronize()
+    for ch in range(C):
+        assert_close(out[ch].cpu().numpy(), orc.band_resize(img[ch], sy, cy, sx, cx), f"hb_resize {H}x{W} -> {Ho}x{Wo} plane {ch}")
