@@ -45,14 +45,16 @@ struct FirArgs {
     float* out;
     int H, W;
     int64_t in_pitch, out_pitch;
-    int T, anchor;
+    int T, anchor, nk, nko;
     int nct;             // strips per row group
     int ntasks;          // strips x row groups
     int lines;           // every row of the output starts a 128-byte line
+    int step, lean;      // rows of a group are `step` apart, its windows start as their addresses want it: see FirRows
     int ntiles, run_tiles, nruns, wtasks;   // the walk of long filters: tiles per row, per run, runs per row group, tasks
     TapsT<HB_MAX_TAPS_FIR1D> taps;
 };
 
+constexpr int kFirApartRows = 17;             // of an image whose even and odd rows are taken apart
 constexpr int kFirMinWidth = 8;               // of an image for those loads
 // Eight pixels from column xs on of the row at byte offset rowoff, requested from an address inside the row
 // (W >= 8); fir_clamped() shifts what reaches over the row's ends into place, which is the column clamp.
@@ -63,26 +65,43 @@ __device__ __forceinline__ half8 fir_clamped(const FirArgs& p, half8 v, int xs) 
     return shift_in_from_left(shift_in_from_right(v, max(xs - (p.W - 8), 0)), max(-xs, 0));
 }
 
+// A group of 16 rows.  Where rows start on odd pixels (LEAN), a window that starts on an even one is no run of whole dwords, and
+// every lane's 16 bytes are several cache accesses.  There the windows of a group start on the pixel that makes their address
+// even, one further left or not, with the coefficients moved by as much; of an odd pitch that is another one in every second row, and a
+// group has every second row (p.step = 2): the even ones of 32, then the odd ones.  4095 x 4095, 8 / 40 / 256 taps 33.7 / 25.9 / 31.0 -> 23.3 /
+// 24.0 / 28.1 us, 2047 x 2047 10.8 / 11.2 / 17.0 -> 8.0 / 8.9 / 14.7, 300 x 8191, 8 taps 8.7 -> 5.9, 17 x 3001, 100 taps 6.9 -> 6.2.
+struct FirRows {
+    int y0, e;                                // first row; pixels that its windows start left of the anchor's
+};
+template <bool LEAN>
+__device__ __forceinline__ FirRows fir_rows(const FirArgs& p, int rg) {
+    if constexpr (!LEAN) return {16 * rg, p.anchor & 1};
+    const int y0 = p.step == 2 ? 32 * (rg >> 1) + (rg & 1) : 16 * rg;
+    return {y0, (int)((reinterpret_cast<uintptr_t>(p.in) >> 1) + (uintptr_t)y0 * (uintptr_t)p.in_pitch + (uintptr_t)p.anchor) & 1};
+}
+
 // One window per tile (up to 17 taps): nothing to share between tiles or steps.  A wave takes HB_FIR_TILES tiles of one
 // 16-row group, all requested up front, and leaves.  A strip at the image's border shifts its pixels into place in
 // registers (with the clamp folded into per-tile coefficients from tables in the kernel arguments the 256 x 256 launch
 // took 5.0 us, now 3.8; 4096 x 4096 20.7 -> 19.0, a copy 18.3).
+template <bool LEAN>
 __global__ void __launch_bounds__(256) fir1d_mfma_kernel(FirArgs p) {
     constexpr int NW = HB_FIR_TILES;
     __shared__ __attribute__((aligned(16))) float s_patch[4][RowPatch<NW>::kFloats];
     const int lane = threadIdx.x & 63;
     const int c = lane & 15, g = lane >> 4;
-    const int e = p.anchor & 1;
-    const int aw = p.anchor + e;              // window start, left of the tile
     // (tasks in plain launch order: with one contiguous eighth of the tasks per XCD this kernel measured
     // 10 % slower on tall images, 100 against 89 us on 262144 x 256; groups of 2 to 8 neighbours per XCD
     // measured within 2 % of the plain order there)
     const int task = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
     if (task >= p.ntasks) return;
     const int rg = task / p.nct, ct = task - rg * p.nct;
-    const int x0 = 16 * NW * ct, y0 = 16 * rg;
+    const FirRows rows = fir_rows<LEAN>(p, rg);
+    const int apart = LEAN ? p.step : 1;
+    const int e = rows.e, aw = p.anchor + e;              // window start, left of the tile
+    const int x0 = 16 * NW * ct, y0 = rows.y0;
     const bool inside = x0 >= aw && x0 + 16 * (NW - 1) - aw + 32 <= p.W && x0 + 16 * NW <= p.W;   // uniform
-    const uint32_t rowoff = (uint32_t)min(y0 + c, p.H - 1) * (uint32_t)p.in_pitch * 2u;
+    const uint32_t rowoff = (uint32_t)min(y0 + apart * c, p.H - 1) * (uint32_t)p.in_pitch * 2u;
     half8 px[NW];
 #pragma unroll
     for (int w = 0; w < NW; ++w) px[w] = fir_request(p, rowoff, x0 - aw + 16 * w + 8 * g);
@@ -103,8 +122,9 @@ __global__ void __launch_bounds__(256) fir1d_mfma_kernel(FirArgs p) {
     }
     float* const dst = p.out + (int64_t)y0 * p.out_pitch + x0;
     float* const patch = s_patch[threadIdx.x >> 6];
-    if (inside && y0 + 16 <= p.H) store_rows_via_lds<NW, true>(patch, dst, (uint32_t)p.out_pitch, acc, lane);
-    else store_rows_via_lds_masked<NW, true>(patch, dst, p.out_pitch, acc, lane, p.H - y0, p.W - x0);
+    const int64_t pitch = apart * p.out_pitch;
+    if (inside && y0 + 15 * apart < p.H) store_rows_via_lds<NW, true>(patch, dst, (uint32_t)pitch, acc, lane);
+    else store_rows_via_lds_masked<NW, true>(patch, dst, pitch, acc, lane, (p.H - y0 + apart - 1) / apart, p.W - x0);
 }
 
 // ---------------------------------------------------------------------------
@@ -132,31 +152,34 @@ __global__ void __launch_bounds__(256) fir1d_mfma_kernel(FirArgs p) {
 // best as single-wave workgroups, the shorter ones four to a workgroup (measured).
 constexpr int fir_walk_waves(int nk) { return nk >= 7 ? 1 : 4; }
 
-template <int NK, int NKO>
+template <int NK, int NKO, bool LEAN>
 __global__ void __launch_bounds__(64 * fir_walk_waves(NK)) fir1d_walk_kernel(FirArgs p) {
     constexpr int WV = fir_walk_waves(NK);
     __shared__ __attribute__((aligned(16))) float s_patch[WV][RowPatch<4>::kFloats];
     const int lane = threadIdx.x & 63;
     const int c = lane & 15, g = lane >> 4;
-    const int e = p.anchor & 1;
-    const int aw = p.anchor + e;
     half8 even[NK], odd[NKO];
+    auto coefficients = [&](int e) {
 #pragma unroll
-    for (int kk = 0; kk < NK; ++kk) even[kk] = tap_run(p.taps.tab, 32 * kk + 8 * g - c - e);
+        for (int kk = 0; kk < NK; ++kk) even[kk] = tap_run(p.taps.tab, 32 * kk + 8 * g - c - e);
 #pragma unroll
-    for (int kk = 0; kk < NKO; ++kk) odd[kk] = tap_run(p.taps.tab, 32 * kk - 16 + 8 * g - c - e);
+        for (int kk = 0; kk < NKO; ++kk) odd[kk] = tap_run(p.taps.tab, 32 * kk - 16 + 8 * g - c - e);
+    };
+    if constexpr (!LEAN) coefficients(p.anchor & 1);
 
     const int wgpos = xcd_contiguous(blockIdx.x, gridDim.x);
     const int task = __builtin_amdgcn_readfirstlane(wgpos * WV + (threadIdx.x >> 6));
     if (task >= p.wtasks) return;
     const int rg = task / p.nruns, run = task - rg * p.nruns;
+    const FirRows rows = fir_rows<LEAN>(p, rg);
+    const int y0 = rows.y0, aw = p.anchor + rows.e, apart = LEAN ? p.step : 1;
+    if constexpr (LEAN) coefficients(rows.e);
     const int t0 = run * p.run_tiles;                     // first tile of the run
     const int L = min(p.run_tiles, p.ntiles - t0);        // its tiles
     const int npairs = (L + 1) / 2, nsteps = npairs + NKO - 1;        // pairs of tiles, windows
-    const int y0 = 16 * rg;
-    const uint32_t rowoff = (uint32_t)min(y0 + c, p.H - 1) * (uint32_t)p.in_pitch * 2u;
+    const uint32_t rowoff = (uint32_t)min(y0 + apart * c, p.H - 1) * (uint32_t)p.in_pitch * 2u;
     float* patch = s_patch[threadIdx.x >> 6];
-    const bool rows16 = y0 + 16 <= p.H;
+    const bool rows16 = y0 + 15 * apart < p.H;
 
     auto load_window = [&](int v) { return fir_request(p, rowoff, 16 * t0 + 32 * v - aw + 8 * g); };
     auto window_inside = [&](int v) {                     // uniform
@@ -171,7 +194,7 @@ __global__ void __launch_bounds__(64 * fir_walk_waves(NK)) fir1d_walk_kernel(Fir
     int o[2];
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-        const int64_t at = (int64_t)(reinterpret_cast<uintptr_t>(p.out) / 4) + (int64_t)(y0 + 8 * s + (lane >> 3)) * p.out_pitch + 16 * t0;
+        const int64_t at = (int64_t)(reinterpret_cast<uintptr_t>(p.out) / 4) + (int64_t)(y0 + apart * (8 * s + (lane >> 3))) * p.out_pitch + 16 * t0;
         o[s] = (int)(-at & 31);
     }
     auto store_line = [&](int k) {                        // the one that ends in pair k
@@ -181,8 +204,8 @@ __global__ void __launch_bounds__(64 * fir_walk_waves(NK)) fir1d_walk_kernel(Fir
             floatx4 v;
 #pragma unroll
             for (int i = 0; i < 4; ++i) v[i] = patch[row * RowPatch<4>::kPitch + ((col + i) & 63)];
-            if (y0 + row >= p.H) continue;
-            float* const q = p.out + (int64_t)(y0 + row) * p.out_pitch + 16 * t0 + col;
+            if (y0 + apart * row >= p.H) continue;
+            float* const q = p.out + (int64_t)(y0 + apart * row) * p.out_pitch + 16 * t0 + col;
             if (col >= 0 && col + 4 <= limit) {
                 __builtin_nontemporal_store(v, reinterpret_cast<floatx4_u*>(q));
             } else {
@@ -204,9 +227,9 @@ __global__ void __launch_bounds__(64 * fir_walk_waves(NK)) fir1d_walk_kernel(Fir
             wave_lds_fence();
             store_line(j);
         } else if (rows16 && x + 32 <= p.W) {
-            store_rows_via_lds<2, true>(patch, p.out + (int64_t)y0 * p.out_pitch + x, (uint32_t)p.out_pitch, done, lane);
-        } else if (y0 + c < p.H) {
-            float* row = p.out + (int64_t)(y0 + c) * p.out_pitch;
+            store_rows_via_lds<2, true>(patch, p.out + (int64_t)y0 * p.out_pitch + x, (uint32_t)(apart * p.out_pitch), done, lane);
+        } else if (y0 + apart * c < p.H) {
+            float* row = p.out + (int64_t)(y0 + apart * c) * p.out_pitch;
             store4_mask(row, x + 4 * g, p.W, done[0]);
             if (tb + 1 < L) store4_mask(row, x + 16 + 4 * g, p.W, done[1]);
         }
@@ -322,7 +345,19 @@ static hb_status fir1d_prepare(FirArgs& a, const hb_half* in, float* out, int H,
     a.lines = out_pitch % 32 == 0 && aligned_to(out, 128);
     a.T = ntaps;
     a.anchor = anchor;
-    const int rowsteps = ceil_div(H, 16);
+    // Windows: NK of 32 pixels under a tile, NKO under a pair of tiles.  Odd starts are met where the windows have room for the pixel more
+    // (17, 33, 49, ... taps would take another window for every tile) and the rows fill more than one group.  Small images of few waves are as
+    // long as one wave is, whose coefficients then wait for its place: two or three windows and seven to nine, which hide least of that, only
+    // from 384 K pixels on (200 x 501, 40 / 200 / 256 taps 5.48 / 7.05 / 7.58 us and 5.60 / 7.43 / 7.99 so, 300 x 3001 6.21 / 10.59 / 11.50 and
+    // 5.99 / 9.38 / 10.29; one window and four to six there 4.35 / 7.00 / 7.82 and 4.00 / 6.83 / 7.56 with 8 / 100 / 130 taps).
+    a.nk = ceil_div(15 + ntaps + (anchor & 1), 32);
+    a.nko = ceil_div(31 + ntaps + (anchor & 1), 32);
+    const bool even = in_pitch % 2 == 0 && aligned_to(in, 4);
+    a.lean = !even && ceil_div(16 + ntaps, 32) == a.nk && ceil_div(32 + ntaps, 32) == a.nko && H >= kFirApartRows &&
+             (a.nk == 1 || (a.nk >= 4 && a.nk <= 6) || (int64_t)H * W >= (3 << 17)) &&
+             out_pitch <= ((int64_t)1 << 25);             // 32-bit byte offsets inside a group of 32 rows
+    a.step = a.lean && in_pitch % 2 ? 2 : 1;
+    const int rowsteps = a.step == 2 ? 2 * ceil_div(H, 32) : ceil_div(H, 16);
     a.nct = ceil_div(W, 16 * HB_FIR_TILES);
     if ((int64_t)rowsteps * a.nct > 0x7fffffff / 2) return HB_ERR_UNSUPPORTED;
     a.ntasks = rowsteps * a.nct;
@@ -339,8 +374,7 @@ static hb_status fir1d_prepare(FirArgs& a, const hb_half* in, float* out, int H,
     // tiles, 20.0 with 20).  Images of a few rows, most of whose lanes are idle, take two or three (8 x 500000, 34 taps 10.7 us with
     // four, 9.5 so; 1 x 1000000, 100 taps 10.7, 13.4 with one) and longer runs (256 taps 24 -> 18).
     a.ntiles = ceil_div(W, 16);
-    const int nk = ceil_div(15 + ntaps + (anchor & 1), 32);
-    const bool even = in_pitch % 2 == 0 && aligned_to(in, 4);
+    const int nk = a.nk;
     const int64_t px = (int64_t)H * W;
     int waves = 8;                                        // per compute unit
     if (nk <= 3) waves = H < 16 ? 12 : a.lines && px > (24 << 20) ? 16 : 8;
@@ -358,6 +392,28 @@ static hb_status fir1d_prepare(FirArgs& a, const hb_half* in, float* out, int H,
     return HB_OK;
 }
 
+template <bool LEAN>
+static hb_status fir1d_launch(const FirArgs& a, hipStream_t st) {
+#define HB_FIR_WALK_AS(N, NO)                                                                     \
+    hipLaunchKernelGGL((fir1d_walk_kernel<N, NO, LEAN>), dim3(ceil_div(a.wtasks, fir_walk_waves(N))), dim3(64 * fir_walk_waves(N)), 0, st, a)
+#define HB_FIR_WALK(N)                                                                            \
+    case N:                                                                                       \
+        if (a.nko > N) HB_FIR_WALK_AS(N, N + 1);                                                  \
+        else HB_FIR_WALK_AS(N, N);                                                                \
+        break;
+    switch (a.nk) {
+        // one window per tile: nothing to share between tiles, every wave takes one strip of tiles
+        case 1: hipLaunchKernelGGL(fir1d_mfma_kernel<LEAN>, dim3(ceil_div(a.ntasks, 4)), dim3(256), 0, st, a); break;
+        // long filters: the walk along the row, every window loaded once
+        HB_FIR_WALK(2) HB_FIR_WALK(3) HB_FIR_WALK(4) HB_FIR_WALK(5) HB_FIR_WALK(6) HB_FIR_WALK(7) HB_FIR_WALK(8)
+        case 9: HB_FIR_WALK_AS(9, 9); break;
+        default: break;
+    }
+#undef HB_FIR_WALK
+#undef HB_FIR_WALK_AS
+    return launch_status();
+}
+
 }  // namespace hb
 
 extern "C" hb_status hb_fir1d_valu(const hb_half* in, float* out, int H, int W,
@@ -373,7 +429,7 @@ extern "C" hb_status hb_fir1d(const hb_half* in, float* out, int H, int W,
     if (s != HB_OK) return s;
     // a 16-column tile reads the 16 + ntaps - 1 pixels from x0 - anchor on (one more when the
     // window is moved to an even pixel): NK windows of 32
-    const int nk = ceil_div(15 + ntaps + (anchor & 1), 32);
+    const int nk = a.nk;
     // narrow images are one short run per row group, whose windows all reach over the row's ends: with rows inside lines
     // the vector ALU is the faster one (1000 x 100, 100 / 159 taps 5.4 / 6.7 us, walked 7.4 / 8.3, but 200 taps 8.3 and 7.8; 8192 x 65, 200 taps 8.7
     // and 9.3), with whole lines (1000 x 128, 100 / 200 taps 5.4 / 8.3, 4.9 / 5.3) and in tall images (20000 x 100, 159 taps 15, 11;
@@ -381,25 +437,7 @@ extern "C" hb_status hb_fir1d(const hb_half* in, float* out, int H, int W,
     if (W < kFirMinWidth || (nk >= 4 && W > 32 && W <= 128 && !a.lines && H <= 32 * num_cu()))
         return hb_fir1d_valu(in, out, H, W, in_pitch, out_pitch, taps_host, ntaps, anchor, stream);
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    const int nko = ceil_div(31 + ntaps + (anchor & 1), 32);
-#define HB_FIR_WALK_AS(N, NO)                                                                     \
-    hipLaunchKernelGGL((fir1d_walk_kernel<N, NO>), dim3(ceil_div(a.wtasks, fir_walk_waves(N))), dim3(64 * fir_walk_waves(N)), 0, st, a)
-#define HB_FIR_WALK(N)                                                                            \
-    case N:                                                                                       \
-        if (nko > N) HB_FIR_WALK_AS(N, N + 1);                                                    \
-        else HB_FIR_WALK_AS(N, N);                                                                \
-        break;
-    switch (nk) {
-        // one window per tile: nothing to share between tiles, every wave takes one strip of tiles
-        case 1: hipLaunchKernelGGL(fir1d_mfma_kernel, dim3(ceil_div(a.ntasks, 4)), dim3(256), 0, st, a); break;
-        // long filters: the walk along the row, every window loaded once
-        HB_FIR_WALK(2) HB_FIR_WALK(3) HB_FIR_WALK(4) HB_FIR_WALK(5) HB_FIR_WALK(6) HB_FIR_WALK(7) HB_FIR_WALK(8)
-        case 9: HB_FIR_WALK_AS(9, 9); break;
-        default: return HB_ERR_UNSUPPORTED;
-    }
-#undef HB_FIR_WALK
-#undef HB_FIR_WALK_AS
-    return launch_status();
+    return a.lean ? fir1d_launch<true>(a, st) : fir1d_launch<false>(a, st);
 }
 
 extern "C" hb_status hb_fir1d_valu(const hb_half* in, float* out, int H, int W,

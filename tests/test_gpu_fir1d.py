@@ -124,3 +124,14 @@ def test_fir1d_large_image_of_whole_lines(orc, T, a):
     for r0 in (0, 2512, H - 30):
         ref = orc.fir1d(img[r0:r0 + 30].cpu().numpy().view(np.uint16), taps, a)
         assert_close(out[r0:r0 + 30].cpu().numpy(), ref, f"rows {r0}..")
+
+
+@pytest.mark.parametrize("H,W,T,a", [(17, 201, 3, 1), (18, 64, 16, 0), (33, 333, 17, 3), (96, 97, 17, 4), (97, 129, 18, 17), (16, 90, 8, 3),
+                                     (384, 1031, 48, 2), (383, 1027, 48, 3), (400, 1001, 49, 11), (31, 515, 100, 99), (32, 515, 160, 1),
+                                     (193, 2051, 255, 0), (200, 2001, 256, 100), (79, 701, 256, 99)])
+@pytest.mark.parametrize("extra,offset", [(0, 0), (1, 0), (2, 1), (27, 4)])
+def test_fir1d_even_and_odd_rows_apart(orc, H, W, T, a, extra, offset):
+    """Rows that start on odd pixels, every second one or all of them, around the groups of 32 rows and the windows' room."""
+    img, taps, got, obuf = run("hb_fir1d", H, W, T, a, pitch_extra=extra, offset=offset)
+    assert_close(got, orc.fir1d(img, taps, a), f"{H}x{W} T={T} pitch+{extra} off {offset}")
+    assert np.all(obuf[:, W:] == 7.0), "wrote past the row end"
