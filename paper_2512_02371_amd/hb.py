@@ -3,7 +3,8 @@
 Argument marshalling only: every function takes torch CUDA tensors (used purely
 as device memory), pulls out pointers, shapes and pitches, and calls the entry
 point of the same name on torch's current stream.  There is no fallback: if the
-library is missing, ``load()`` raises.
+library is missing, ``load()`` raises.  The usual calls are marshalled by the
+extension module ``_calls``, all others here.
 """
 from __future__ import annotations
 
@@ -44,6 +45,7 @@ SYMBOLS = [
 ]
 
 _lib = None
+_calls = None               # the native marshalling of the usual calls (csrc/calls.cpp), once the library is loaded
 
 
 class HbError(RuntimeError):
@@ -54,7 +56,7 @@ class HbError(RuntimeError):
 
 def load() -> ctypes.CDLL:
     """Load libhb.so (built by ``__graft_entry__.build()``); raise if it is absent."""
-    global _lib
+    global _lib, _calls
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -110,6 +112,13 @@ def load() -> ctypes.CDLL:
     L.hb_sat2d_workspace_size.argtypes = [I, I]
     L.hb_sat2d_workspace_size.restype = ctypes.c_size_t
     _lib = L
+    # built against one torch: with another it does not load, and ctypes makes every call
+    try:
+        from . import _calls as native
+        native.bind({name: ctypes.cast(getattr(L, name), vp).value for name in SYMBOLS[1:]}, HbError)
+        _calls = native
+    except ImportError:
+        pass
     return L
 
 
@@ -141,8 +150,8 @@ def _stream() -> int:
     return _raw_stream(_device())
 
 
-# On the host a call costs its launch (3.4 us) and what is done here; with two array conversions and an address object per tap
-# array, and a question to the tensor per stride and dimension, that was 3.6 of 7.0 us.
+# On the host a call costs its launch (3.4 us) and what is done here or in _calls; with two array conversions and an address object
+# per tap array, and a question to the tensor per stride and dimension, that was 3.6 of 7.0 us.
 _U16, _F16 = np.dtype(np.uint16), np.dtype(np.float16)
 
 
@@ -180,6 +189,8 @@ def _fir(name, inp, out, taps, anchor):
 
 
 def hb_fir1d(inp, out, taps, anchor):
+    if _calls is not None and _calls.fir1d(inp, out, taps, anchor):
+        return out
     return _fir("hb_fir1d", inp, out, taps, anchor)
 
 
@@ -200,6 +211,8 @@ def _conv2d(name, inp, out, taps2d, anchor_y, anchor_x, shape=lambda H, W: (H, W
 
 
 def hb_conv2d(inp, out, taps2d, anchor_y, anchor_x):
+    if _calls is not None and _calls.conv2d(inp, out, taps2d, anchor_y, anchor_x):
+        return out
     return _conv2d("hb_conv2d", inp, out, taps2d, anchor_y, anchor_x)
 
 
@@ -216,6 +229,8 @@ def _double_shape(H, W):
 
 
 def hb_down2(inp, out, taps2d, anchor_y, anchor_x):
+    if _calls is not None and _calls.down2(inp, out, taps2d, anchor_y, anchor_x):
+        return out
     return _conv2d("hb_down2", inp, out, taps2d, anchor_y, anchor_x, _half_shape)
 
 
@@ -224,6 +239,8 @@ def hb_down2_valu(inp, out, taps2d, anchor_y, anchor_x):
 
 
 def hb_up2(inp, out, taps2d, anchor_y, anchor_x):
+    if _calls is not None and _calls.up2(inp, out, taps2d, anchor_y, anchor_x):
+        return out
     return _conv2d("hb_up2", inp, out, taps2d, anchor_y, anchor_x, _double_shape)
 
 
@@ -246,6 +263,8 @@ def _dct(name, inp, out, threshold, workspace):
 
 
 def hb_dct_denoise(inp, out, threshold, workspace):
+    if _calls is not None and _calls.dct_denoise(inp, out, threshold, workspace):
+        return out
     return _dct("hb_dct_denoise", inp, out, threshold, workspace)
 
 
@@ -272,6 +291,8 @@ def _iir2(name, inp, out, alpha, beta, workspace):
 
 
 def hb_iir2(inp, out, alpha, beta, workspace):
+    if _calls is not None and _calls.iir2(inp, out, alpha, beta, workspace):
+        return out
     return _iir2("hb_iir2", inp, out, alpha, beta, workspace)
 
 
@@ -320,6 +341,8 @@ def _resize(name, inp, out, workspace, start_y, coef_y, start_x, coef_x):
 
 
 def hb_resize(inp, out, workspace, start_y, coef_y, start_x, coef_x):
+    if _calls is not None and _calls.resize(inp, out, workspace, start_y, coef_y, start_x, coef_x):
+        return out
     return _resize("hb_resize", inp, out, workspace, start_y, coef_y, start_x, coef_x)
 
 
@@ -338,6 +361,8 @@ def _sep(name, inp, out, tx, ax, ty, ay):
 
 
 def hb_sepblur(inp, out, taps_x, anchor_x, taps_y, anchor_y):
+    if _calls is not None and _calls.sepblur(inp, out, taps_x, anchor_x, taps_y, anchor_y):
+        return out
     return _sep("hb_sepblur", inp, out, taps_x, anchor_x, taps_y, anchor_y)
 
 
@@ -360,6 +385,8 @@ def _sat(name, inp, out, workspace):
 
 
 def hb_sat2d(inp, out, workspace):
+    if _calls is not None and _calls.sat2d(inp, out, workspace):
+        return out
     return _sat("hb_sat2d", inp, out, workspace)
 
 
@@ -394,6 +421,8 @@ def _conv(name, x, w, out):
 
 
 def hb_conv3x3(x_nhwc, w_hwio, out_nhwc):
+    if _calls is not None and _calls.conv3x3(x_nhwc, w_hwio, out_nhwc):
+        return out_nhwc
     return _conv("hb_conv3x3", x_nhwc, w_hwio, out_nhwc)
 
 
@@ -415,6 +444,8 @@ def _pyr(name, inp, res, down):
 
 
 def hb_pyr_level(inp, residual, down=None):
+    if _calls is not None and _calls.pyr_level(inp, residual, down):
+        return residual
     return _pyr("hb_pyr_level", inp, residual, down)
 
 
