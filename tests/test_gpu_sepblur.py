@@ -133,3 +133,15 @@ def test_sepblur_full_benchmark_size_sampled_bands(orc):
         ref = orc.sepblur(img[lo:hi], t, 7, t, 7)
         a, b = (0 if lo == 0 else 16), (hi - lo if hi == H else hi - lo - 16)
         assert_close(out[lo + a:lo + b].cpu().numpy(), ref[a:b], f"rows {lo + a}..{lo + b}")
+
+
+@pytest.mark.parametrize("H,W,Tx,ax,Ty,ay,extra", [
+    (17, 128, 16, 7, 18, 3, 0), (16, 128, 16, 7, 18, 3, 0), (33, 161, 3, 1, 34, 33, 0),       # marched, and all row tiles up front
+    (25, 160, 17, 0, 35, 30, 0), (24, 160, 17, 0, 35, 30, 0), (33, 70, 9, 4, 64, 0, 1), (32, 70, 9, 4, 64, 0, 1),
+    (47, 16512, 16, 8, 17, 16, 0), (48, 16512, 16, 8, 17, 16, 0), (79, 16512, 5, 2, 40, 7, 0), (80, 16512, 5, 2, 64, 7, 0),
+    (1024, 1792, 9, 4, 64, 31, 0), (1040, 1920, 9, 4, 64, 31, 0), (1040, 1920, 9, 4, 50, 31, 0),
+    (5010, 5041, 5, 2, 17, 3, 0), (5010, 5056, 5, 2, 50, 3, 0), (5010, 5056, 5, 2, 64, 3, 0), (5010, 5042, 5, 2, 50, 3, 0),
+])
+def test_sepblur_one_window_marched_or_not(orc, H, W, Tx, ax, Ty, ay, extra):
+    """Filters of up to 17 taps along x on either side of every line between their two kernels."""
+    test_sepblur_work_splits(orc, H, W, Tx, ax, Ty, ay, extra)
