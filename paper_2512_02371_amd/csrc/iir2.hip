@@ -637,12 +637,13 @@ static hb_status iir2_run(bool valu, const hb_half* in, float* out, int C, int64
     // most units have one (T = 2500 .. 16384, 1 to 256 channels 10.2 us, 6.9 so; 32768, 1 / 64 / 256 channels 10.4 / 10.4 / 14.8, 8.4 / 9.0 /
     // 12.4; 65536, 64 / 100 / 200 channels 10.7 / 14.0 / 21.9, 12.9 / 12.9 / 17.7; 400 x 8192 10.3, 11.9).  One to 16 channels owe
     // this to the host, which takes 9.4 us for two launches: their kernels, replayed from a graph, take 6.5 us for 32768 samples, this one 7.9.
-    // Signals that start between dwords cost one compute unit more than they cost many: only up to three tiles a run with few
-    // channels (16 x 32767 9.8 us with two launches, 11.2 with one, 16 x 20001 9.4 to 10.7 and 9.5; 32 x 32767 12.0 and 11.4),
+    // Signals that start between dwords cost one compute unit more than they cost many: with few channels only up to 38 tiles
+    // (2 / 16 x 18433 8.3 / 8.6 us, two launches 8.6 / 8.8, 16387 7.9 / 8.2 and 8.4 / 8.6, 20001 9.1 / 9.5 and 8.6 / 8.9, 24575 10.6 / 11.0 and 8.6 / 8.8), up to three
+    // tiles a run from a tenth of the units on (31 x 20001 9.6 and 10.8; 24 x 9.6 and 8.6), four from an eighth (32 x 32767 12.0 and 11.4),
     // and up to eight only from three channels to four units on (160 x 40001 / 50001 16.6 / 18.0 and 18.4 / 20.0, 200 x 18.2 / 21.8 and 18.8 / 20.1).
     const bool even = aligned_to(in, 4) && (C == 1 || in_pitch % 2 == 0);
     const int most = C > num_cu() || valu ? 0 : (even ? 2 * C >= num_cu() : 4 * C >= 3 * num_cu()) ? 8 : even || 8 * C >= num_cu() ? 4 : 3;
-    const bool channel = a.ntiles > kIirAhead && a.ntiles <= most * kIirChannelWaves;
+    const bool channel = a.ntiles > kIirAhead && a.ntiles <= (most == 3 && 10 * C < num_cu() ? 38 : most * kIirChannelWaves);
     if (channel) a.run = ceil_div(a.ntiles, kIirChannelWaves);
     a.nruns = (a.ntiles + a.run - 1) / a.run;
     for (int j = 0; j < 7; ++j) {

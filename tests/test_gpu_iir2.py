@@ -123,3 +123,11 @@ def test_iir2_full_size(orc):
     sig = synth.uniform_pm1_f16(9700, (C, T))
     got, _ = run("hb_iir2", sig, 1.6, -0.8)
     assert_close(got, orc.iir2(sig, float(np.float32(1.6)), float(np.float32(-0.8))), "2 x 2^21")
+
+
+@pytest.mark.parametrize("C,T", [(2, 38 * 512 - 1), (2, 38 * 512 + 1), (25, 38 * 512 - 1), (25, 38 * 512 + 1), (26, 38 * 512 + 1), (31, 48 * 512 - 1), (31, 48 * 512 + 1)])
+def test_iir2_odd_rows_in_one_launch_or_two(orc, C, T):
+    sig = synth.uniform_pm1_f16(9900 + C, (C, T))
+    got, _ = run("hb_iir2", sig, 1.6, -0.8)
+    ref = orc.iir2(sig, float(np.float32(1.6)), float(np.float32(-0.8)))
+    assert_close(got, ref, f"C={C} T={T}")
