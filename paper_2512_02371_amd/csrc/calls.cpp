@@ -13,6 +13,7 @@
 #include <c10/hip/HIPStream.h>
 
 #include <cstring>
+#include <exception>
 
 #include "hb.h"
 
@@ -138,12 +139,14 @@ PyObject* made(const char* name, F call) {
 }
 
 // What torch throws while a tensor is asked (memory that may not be had, for one) hb.py meets again, as an error of its own.
+// Nothing but exceptions is caught: a daemon thread that wants the interpreter's lock back after the interpreter has ended is unwound
+// through here, and the process aborts if that unwinding is stopped.
 template <int N, class F>
 PyObject* guarded(Py_ssize_t n, F f) {
     if (n != N) Py_RETURN_FALSE;
     try {
         if (usual_state()) return f();
-    } catch (...) {
+    } catch (const std::exception&) {
     }
     Py_RETURN_FALSE;
 }
