@@ -17,15 +17,11 @@
 // with A[m][k] = taps[k - m - e] (zero outside the taps): A_K itself, built once per
 // wave from a zero-padded tap table.  In D' a lane owns four consecutive output
 // columns of one row, so the result leaves with one 16-byte store per lane.
-#include <algorithm>
 #include <utility>
 
+#include "fir1d_plan.hpp"
 #include "hb_device.hpp"
 #include "hb_host.hpp"
-
-#ifndef HB_FIR_TILES
-#define HB_FIR_TILES 4        // 16-column tiles per wave strip
-#endif
 
 namespace hb {
 
@@ -45,17 +41,15 @@ struct FirArgs {
     float* out;
     int H, W;
     int64_t in_pitch, out_pitch;
-    int T, anchor, nk, nko;
+    int T, anchor;
     int nct;             // strips per row group
     int ntasks;          // strips x row groups
     int lines;           // every row of the output starts a 128-byte line
-    int step, lean;      // rows of a group are `step` apart, its windows start as their addresses want it: see FirRows
     int ntiles, run_tiles, nruns, wtasks;   // the walk of long filters: tiles per row, per run, runs per row group, tasks
     TapsT<HB_MAX_TAPS_FIR1D> taps;
+    int step;            // rows of a group are this far apart: see FirRows
 };
 
-constexpr int kFirApartRows = 17;             // of an image whose even and odd rows are taken apart
-constexpr int kFirMinWidth = 8;               // of an image for those loads
 // Eight pixels from column xs on of the row at byte offset rowoff, requested from an address inside the row
 // (W >= 8); fir_clamped() shifts what reaches over the row's ends into place, which is the column clamp.
 __device__ __forceinline__ half8 fir_request(const FirArgs& p, uint32_t rowoff, int xs) {
@@ -148,10 +142,6 @@ __global__ void __launch_bounds__(256) fir1d_mfma_kernel(FirArgs p) {
 // -> 17.3 / 17.6 / 22.3 us, 8192 x 8192, 30 taps 124 -> 101, 4095 x 4095, 100 taps 37.8 -> 25.9.  What bounds it is not the bytes in flight
 // alone (NKO KB a wave; with twice as many windows ahead 256 taps took 24.6 us): from four windows on half the waves, each
 // walking fewer windows for its neighbour (with 256 taps one in five, one in three with two waves per SIMD), are mostly the faster.
-// Waves per workgroup of the walk: the longest filters (few, long-lived waves of 100+ registers) run
-// best as single-wave workgroups, the shorter ones four to a workgroup (measured).
-constexpr int fir_walk_waves(int nk) { return nk >= 7 ? 1 : 4; }
-
 template <int NK, int NKO, bool LEAN>
 __global__ void __launch_bounds__(64 * fir_walk_waves(NK)) fir1d_walk_kernel(FirArgs p) {
     constexpr int WV = fir_walk_waves(NK);
@@ -327,7 +317,7 @@ __global__ void __launch_bounds__(256) fir1d_valu_kernel(FirArgs p) {
     store4_mask(orow, x0 + xl + 4, p.W, floatx4{acc[4], acc[5], acc[6], acc[7]});
 }
 
-static hb_status fir1d_prepare(FirArgs& a, const hb_half* in, float* out, int H, int W,
+static hb_status fir1d_prepare(FirArgs& a, FirPlan& plan, const hb_half* in, float* out, int H, int W,
                                int64_t in_pitch, int64_t out_pitch,
                                const hb_half* taps_host, int ntaps, int anchor) {
     hb_status s = check_image(in, out, H, W, in_pitch, out_pitch);
@@ -345,47 +335,15 @@ static hb_status fir1d_prepare(FirArgs& a, const hb_half* in, float* out, int H,
     a.lines = out_pitch % 32 == 0 && aligned_to(out, 128);
     a.T = ntaps;
     a.anchor = anchor;
-    // Windows: NK of 32 pixels under a tile, NKO under a pair of tiles.  Odd starts are met where the windows have room for the pixel more
-    // (17, 33, 49, ... taps would take another window for every tile) and the rows fill more than one group.  Small images of few waves are as
-    // long as one wave is, whose coefficients then wait for its place: two or three windows and seven to nine, which hide least of that, only
-    // from 384 K pixels on (200 x 501, 40 / 200 / 256 taps 5.48 / 7.05 / 7.58 us and 5.60 / 7.43 / 7.99 so, 300 x 3001 6.21 / 10.59 / 11.50 and
-    // 5.99 / 9.38 / 10.29; one window and four to six there 4.35 / 7.00 / 7.82 and 4.00 / 6.83 / 7.56 with 8 / 100 / 130 taps).
-    a.nk = ceil_div(15 + ntaps + (anchor & 1), 32);
-    a.nko = ceil_div(31 + ntaps + (anchor & 1), 32);
-    const bool even = in_pitch % 2 == 0 && aligned_to(in, 4);
-    a.lean = !even && ceil_div(16 + ntaps, 32) == a.nk && ceil_div(32 + ntaps, 32) == a.nko && H >= kFirApartRows &&
-             (a.nk == 1 || (a.nk >= 4 && a.nk <= 6) || (int64_t)H * W >= (3 << 17)) &&
-             out_pitch <= ((int64_t)1 << 25);             // 32-bit byte offsets inside a group of 32 rows
-    a.step = a.lean && in_pitch % 2 ? 2 : 1;
-    const int rowsteps = a.step == 2 ? 2 * ceil_div(H, 32) : ceil_div(H, 16);
+    plan = fir_plan({H, W, in_pitch, out_pitch, in_pitch % 2 == 0 && aligned_to(in, 4), a.lines != 0, ntaps, anchor, num_cu()});
+    a.step = plan.step;
     a.nct = ceil_div(W, 16 * HB_FIR_TILES);
-    if ((int64_t)rowsteps * a.nct > 0x7fffffff / 2) return HB_ERR_UNSUPPORTED;
-    a.ntasks = rowsteps * a.nct;
-    // The walk of long filters: runs of an even number of tiles.  More waves have more bytes in flight and walk more windows ahead
-    // of their runs.  From four windows on one wave per SIMD in all (4096 x 4096, 256 / 200 taps 22.8 / 21.0 us, 25.1 / 23.8 with
-    // two; 1749 x 2603, 150 taps 12.7, 16.6; with three quarters of one 4096 x 4096 23.9 / 20.5, but 8192 x 4096, 256 taps 50.2
-    // against 38.4), but two where large outputs have rows that start inside lines and the input's do not start between
-    // dwords, whose shifting is work that one wave per SIMD already fills (2900 x 2900, 100 / 200 taps 15.7 / 17.9 us with one wave,
-    // 13.5 / 16.9 with two, 4500 x 4500 40.9 / 42.3 and 35.8 / 36.5, 2000 x 3000, 100 taps 12.1 and 11.2; 2401 x 2603, 14.1 and 15.8,
-    // 2000 x 3000, 200 taps 14.6 and 14.2, 5000 x 5000 44.1 and 47.2).
-    // Shorter filters two (4096 x 4096, 40 / 80 taps 17.3 / 18.6, with one 18.3 / 19.1), and four on
-    // large images of whole lines (8192 x 4096, 64 taps from memory 39.8 us, 45.8 with two).  Runs shorter than
-    // the windows ahead of them only where there are too few waves otherwise (1749 x 2603, 256 taps 25.9 with runs of 10
-    // tiles, 20.0 with 20).  Images of a few rows, most of whose lanes are idle, take two or three (8 x 500000, 34 taps 10.7 us with
-    // four, 9.5 so; 1 x 1000000, 100 taps 10.7, 13.4 with one) and longer runs (256 taps 24 -> 18).
-    a.ntiles = ceil_div(W, 16);
-    const int nk = a.nk;
-    const int64_t px = (int64_t)H * W;
-    int waves = 8;                                        // per compute unit
-    if (nk <= 3) waves = H < 16 ? 12 : a.lines && px > (24 << 20) ? 16 : 8;
-    else if (H >= 16) waves = !a.lines && even && (nk <= 6 ? px >= (4 << 20) : px >= (8 << 20) && px <= (20 << 20)) ? 8 : 4;
-    int runs = std::min(waves * num_cu() / rowsteps, a.ntiles / 4);
-    const int long_runs = a.ntiles / ((H < 16 ? 4 : 2) * nk);
-    if ((int64_t)rowsteps * long_runs >= 3 * num_cu()) runs = std::min(runs, long_runs);
-    runs = std::max(1, runs);
-    a.run_tiles = (ceil_div(a.ntiles, runs) + 1) & ~1;
-    a.nruns = ceil_div(a.ntiles, a.run_tiles);
-    const int64_t wtasks = (int64_t)rowsteps * a.nruns;
+    if ((int64_t)plan.rowsteps * a.nct > 0x7fffffff / 2) return HB_ERR_UNSUPPORTED;
+    a.ntasks = plan.rowsteps * a.nct;
+    a.ntiles = plan.ntiles;
+    a.run_tiles = plan.run_tiles;
+    a.nruns = plan.nruns;
+    const int64_t wtasks = (int64_t)plan.rowsteps * a.nruns;
     if (wtasks > 0x7fffffff / 4) return HB_ERR_UNSUPPORTED;
     a.wtasks = (int)wtasks;
     a.taps = pack_taps<HB_MAX_TAPS_FIR1D>(taps_host, ntaps);
@@ -393,15 +351,15 @@ static hb_status fir1d_prepare(FirArgs& a, const hb_half* in, float* out, int H,
 }
 
 template <bool LEAN>
-static hb_status fir1d_launch(const FirArgs& a, hipStream_t st) {
+static hb_status fir1d_launch(const FirArgs& a, const FirPlan& plan, hipStream_t st) {
 #define HB_FIR_WALK_AS(N, NO)                                                                     \
     hipLaunchKernelGGL((fir1d_walk_kernel<N, NO, LEAN>), dim3(ceil_div(a.wtasks, fir_walk_waves(N))), dim3(64 * fir_walk_waves(N)), 0, st, a)
 #define HB_FIR_WALK(N)                                                                            \
     case N:                                                                                       \
-        if (a.nko > N) HB_FIR_WALK_AS(N, N + 1);                                                  \
+        if (plan.nko > N) HB_FIR_WALK_AS(N, N + 1);                                                  \
         else HB_FIR_WALK_AS(N, N);                                                                \
         break;
-    switch (a.nk) {
+    switch (plan.nk) {
         // one window per tile: nothing to share between tiles, every wave takes one strip of tiles
         case 1: hipLaunchKernelGGL(fir1d_mfma_kernel<LEAN>, dim3(ceil_div(a.ntasks, 4)), dim3(256), 0, st, a); break;
         // long filters: the walk along the row, every window loaded once
@@ -425,11 +383,12 @@ extern "C" hb_status hb_fir1d(const hb_half* in, float* out, int H, int W,
                               const hb_half* taps_host, int ntaps, int anchor, hb_stream stream) {
     using namespace hb;
     FirArgs a;
-    hb_status s = fir1d_prepare(a, in, out, H, W, in_pitch, out_pitch, taps_host, ntaps, anchor);
+    FirPlan plan;
+    hb_status s = fir1d_prepare(a, plan, in, out, H, W, in_pitch, out_pitch, taps_host, ntaps, anchor);
     if (s != HB_OK) return s;
     // a 16-column tile reads the 16 + ntaps - 1 pixels from x0 - anchor on (one more when the
     // window is moved to an even pixel): NK windows of 32
-    const int nk = a.nk;
+    const int nk = plan.nk;
     // narrow images are one short run per row group, whose windows all reach over the row's ends: with rows inside lines
     // the vector ALU is the faster one (1000 x 100, 100 / 159 taps 5.4 / 6.7 us, walked 7.4 / 8.3, but 200 taps 8.3 and 7.8; 8192 x 65, 200 taps 8.7
     // and 9.3), with whole lines (1000 x 128, 100 / 200 taps 5.4 / 8.3, 4.9 / 5.3) and in tall images (20000 x 100, 159 taps 15, 11;
@@ -437,7 +396,7 @@ extern "C" hb_status hb_fir1d(const hb_half* in, float* out, int H, int W,
     if (W < kFirMinWidth || (nk >= 4 && W > 32 && W <= 128 && !a.lines && H <= 32 * num_cu()))
         return hb_fir1d_valu(in, out, H, W, in_pitch, out_pitch, taps_host, ntaps, anchor, stream);
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    return a.lean ? fir1d_launch<true>(a, st) : fir1d_launch<false>(a, st);
+    return plan.lean ? fir1d_launch<true>(a, plan, st) : fir1d_launch<false>(a, plan, st);
 }
 
 extern "C" hb_status hb_fir1d_valu(const hb_half* in, float* out, int H, int W,
@@ -445,7 +404,8 @@ extern "C" hb_status hb_fir1d_valu(const hb_half* in, float* out, int H, int W,
                                    const hb_half* taps_host, int ntaps, int anchor, hb_stream stream) {
     using namespace hb;
     FirArgs a;
-    hb_status s = fir1d_prepare(a, in, out, H, W, in_pitch, out_pitch, taps_host, ntaps, anchor);
+    FirPlan plan;
+    hb_status s = fir1d_prepare(a, plan, in, out, H, W, in_pitch, out_pitch, taps_host, ntaps, anchor);
     if (s != HB_OK) return s;
     const int64_t blocks = (int64_t)ceil_div(H, 16) * ceil_div(W, kValuTileW);
     if (blocks > 0x7fffffff) return HB_ERR_UNSUPPORTED;

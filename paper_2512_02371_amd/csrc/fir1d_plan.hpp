@@ -1,0 +1,90 @@
+// How hb_fir1d divides an image among waves.  Host arithmetic alone, so that a test can compile it with the host's compiler.
+#pragma once
+#include <stdint.h>
+
+#include <algorithm>
+
+#ifndef HB_FIR_TILES
+#define HB_FIR_TILES 4        // 16-column tiles per wave strip
+#endif
+
+namespace hb {
+
+constexpr int kFirApartRows = 17;             // of an image whose even and odd rows are taken apart
+constexpr int kFirMinWidth = 8;               // of an image
+
+// Waves per workgroup of the walk: long filters are best as single-wave workgroups, the shorter ones four to a workgroup (measured).
+constexpr int fir_walk_waves(int nk) { return nk >= 7 ? 1 : 4; }
+
+struct FirCall {
+    int H, W;
+    int64_t in_pitch, out_pitch;
+    bool even;             // the input starts on a whole dword, and so does every row
+    bool lines;            // every row of the output starts a 128-byte line
+    int ntaps, anchor;
+    int cu;                // compute units
+};
+struct FirPlan {
+    int nk, nko;           // windows of 32 pixels under a tile, under a pair of tiles
+    bool lean;             // windows start where their addresses are even
+    int step;              // rows of a group are this far apart
+    int rowsteps;          // groups of rows
+    int ntiles, run_tiles, nruns;   // the walk of long filters: tiles per row, per run, runs per group of rows
+};
+
+inline FirPlan fir_plan(const FirCall& c) {
+    const auto up = [](int64_t a, int64_t b) { return (int)((a + b - 1) / b); };
+    FirPlan p;
+    const int nk = p.nk = up(15 + c.ntaps + (c.anchor & 1), 32);
+    p.nko = up(31 + c.ntaps + (c.anchor & 1), 32);
+    p.ntiles = up(c.W, 16);
+    const int64_t px = (int64_t)c.H * c.W;
+
+    // The walk of long filters: runs of an even number of tiles.  More waves have more bytes in flight and walk more windows ahead
+    // of their runs.  From four windows on one wave per SIMD in all (4096 x 4096, 256 / 200 taps 22.8 / 21.0 us, 25.1 / 23.8 with
+    // two; 1749 x 2603, 150 taps 12.7, 16.6; with three quarters of one 4096 x 4096 23.9 / 20.5, but 8192 x 4096, 256 taps 50.2
+    // against 38.4), but two where large outputs have rows that start inside lines and the input's do not start between
+    // dwords, whose shifting is work that one wave per SIMD already fills (2900 x 2900, 100 / 200 taps 15.7 / 17.9 us with one wave,
+    // 13.5 / 16.9 with two, 4500 x 4500 40.9 / 42.3 and 35.8 / 36.5, 2000 x 3000, 100 taps 12.1 and 11.2; 2401 x 2603, 14.1 and 15.8,
+    // 2000 x 3000, 200 taps 14.6 and 14.2, 5000 x 5000 44.1 and 47.2).
+    // Shorter filters two (4096 x 4096, 40 / 80 taps 17.3 / 18.6, with one 18.3 / 19.1), and four on
+    // large images of whole lines (8192 x 4096, 64 taps from memory 39.8 us, 45.8 with two).  Runs shorter than
+    // the windows ahead of them only where there are too few waves otherwise (1749 x 2603, 256 taps 25.9 with runs of 10
+    // tiles, 20.0 with 20).  Images of a few rows, most of whose lanes are idle, take two or three (8 x 500000, 34 taps 10.7 us with
+    // four, 9.5 so; 1 x 1000000, 100 taps 10.7, 13.4 with one) and longer runs (256 taps 24 -> 18).
+    int waves = 8;                                        // per compute unit
+    if (nk <= 3) waves = c.H < 16 ? 12 : c.lines && px > (24 << 20) ? 16 : 8;
+    else if (c.H >= 16) waves = !c.lines && c.even && (nk <= 6 ? px >= (4 << 20) : px >= (8 << 20) && px <= (20 << 20)) ? 8 : 4;
+    const auto run_tiles = [&](int rowsteps) {
+        int runs = std::min(waves * c.cu / rowsteps, p.ntiles / 4);
+        const int long_runs = p.ntiles / ((c.H < 16 ? 4 : 2) * nk);
+        if ((int64_t)rowsteps * long_runs >= 3 * c.cu) runs = std::min(runs, long_runs);
+        return (up(p.ntiles, std::max(1, runs)) + 1) & ~1;
+    };
+    const auto rounds = [&](int rowsteps) {               // of four waves to every unit
+        const int64_t tasks = (int64_t)rowsteps * up(p.ntiles, run_tiles(rowsteps));
+        return (tasks + 4 * c.cu - 1) / (4 * c.cu);
+    };
+
+    // Odd starts are met where the windows have room for the pixel more (17, 33, 49, ... taps would take another window for every tile)
+    // and the rows fill more than one group.  The coefficients of a walk then wait for its place, which needs runs that hide it:
+    //  - no narrow images (one window 1000 x 32 5 % slower; 96 taps, 6752 x 32 4.7 us, 5.2 so; 24 taps, 2222 x 331 5.4, 5.8; 219 taps, 1459 x 497 7.9,
+    //    8.5; but 97 x 249, 96 taps 6.4, 6.6 against 23 x 517, 125 taps 7.1, 7.4 and a median gain of 3 % from 129 columns on with four to six windows);
+    //  - with two or three windows and seven to nine, which hide least, only from 384 K pixels on (200 x 501, 40 / 200 / 256 taps 5.48 / 7.05 / 7.58 us and
+    //    5.60 / 7.43 / 7.99 so, 300 x 3001 6.21 / 10.59 / 11.50 and 5.99 / 9.38 / 10.29);
+    //  - not where the groups, which are of 32 rows in pairs, become a round of waves more (167 x 11451, 50 taps 5.6, 6.8; 48 x 31892, 48 taps 6.1, 7.1), nor,
+    //    with seven to nine, more than an eighth more (34 x 11867, 205 taps 7.9, 8.6).
+    const int plain = up(c.H, 16), apart = c.in_pitch % 2 ? 2 * up(c.H, 32) : plain;
+    const bool room = up(16 + c.ntaps, 32) == nk && up(32 + c.ntaps, 32) == p.nko;
+    const int narrow = nk == 1 ? 32 : nk <= 3 ? 512 : nk <= 6 ? 128 : 1200;
+    p.lean = !c.even && room && c.H >= kFirApartRows && c.W > narrow && (nk == 1 || (nk >= 4 && nk <= 6) || px >= (3 << 17)) &&
+             (nk == 1 || rounds(apart) == rounds(plain)) && (nk < 7 || 7 * apart <= 8 * plain) &&
+             c.out_pitch <= ((int64_t)1 << 25);           // 32-bit byte offsets inside a group of 32 rows
+    p.step = p.lean && c.in_pitch % 2 ? 2 : 1;
+    p.rowsteps = p.lean ? apart : plain;
+    p.run_tiles = run_tiles(p.rowsteps);
+    p.nruns = up(p.ntiles, p.run_tiles);
+    return p;
+}
+
+}  // namespace hb

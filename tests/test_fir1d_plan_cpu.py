@@ -1,0 +1,68 @@
+"""Where hb_fir1d takes even and odd rows apart (csrc/fir1d_plan.hpp, host arithmetic, compiled here with the host's compiler)."""
+import os
+import random
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PROGRAM = r"""
+#include <stdio.h>
+#include "fir1d_plan.hpp"
+int main() {
+    hb::FirCall c;
+    long long ip, op;
+    int even;
+    c.cu = 256;
+    while (scanf("%d %d %lld %lld %d %d %d", &c.H, &c.W, &ip, &op, &even, &c.ntaps, &c.anchor) == 7) {
+        c.in_pitch = ip;
+        c.out_pitch = op;
+        c.even = even && ip % 2 == 0;
+        c.lines = op % 32 == 0;
+        const hb::FirPlan p = hb::fir_plan(c);
+        printf("%d %d %d %d %d %d %d %d\n", p.lean, p.step, p.nk, p.nko, p.rowsteps, p.ntiles, p.run_tiles, p.nruns);
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    src, exe = d / "plan.cpp", d / "plan"
+    src.write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2512_02371_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+
+    def ask(calls):
+        out = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, c)) for c in calls), capture_output=True, text=True, check=True).stdout
+        return [tuple(map(int, l.split())) for l in out.splitlines()]
+    return ask
+
+
+@pytest.mark.parametrize("H,W,pitch,even,taps,anchor,lean", [
+    (4095, 4095, 4095, 1, 8, 3, 1), (2047, 2047, 2047, 1, 40, 19, 1), (4095, 4095, 4095, 1, 256, 127, 1), (300, 8191, 8191, 1, 8, 3, 1), (17, 3001, 3001, 1, 100, 49, 1),
+    (4096, 4096, 4096, 1, 8, 3, 0), (4096, 4096, 4096, 0, 8, 3, 1),            # even rows that start on odd pixels, too
+    (6752, 32, 39, 1, 96, 0, 0), (1000, 32, 33, 1, 8, 0, 0), (2222, 331, 331, 1, 24, 11, 0), (1459, 497, 497, 1, 219, 109, 0), (64, 101, 101, 1, 130, 64, 0),     # narrow
+    (167, 11451, 11451, 1, 50, 6, 0), (48, 31892, 31899, 1, 48, 10, 0), (34, 11867, 11867, 1, 205, 0, 0),       # a round of waves more, a third more groups
+])
+def test_where_rows_are_taken_apart(plan, H, W, pitch, even, taps, anchor, lean):
+    assert plan([(H, W, pitch, W, even, taps, anchor)])[0][0] == lean
+
+
+def test_groups_and_runs_cover_the_image_once(plan):
+    rng = random.Random(4)
+    calls = []
+    for _ in range(3000):
+        H, W, taps = int(2 ** rng.uniform(0, 14)), int(2 ** rng.uniform(3, 15)), rng.randint(1, 256)
+        calls.append((H, W, W + rng.choice([0, 1, 2, 7]), W + rng.choice([0, -W % 32]), rng.choice([0, 1]), taps, rng.choice([0, taps - 1, (taps - 1) // 2])))
+    apart = 0
+    for c, (lean, step, nk, nko, rowsteps, ntiles, run_tiles, nruns) in zip(calls, plan(calls)):
+        H, W, pitch, _, _, taps, anchor = c
+        starts = [32 * (g >> 1) + (g & 1) if step == 2 else 16 * g for g in range(rowsteps)]
+        assert step == (2 if lean and pitch % 2 else 1)
+        rows = [y for s in starts for y in range(s, s + 16 * step, step) if y < H] if rowsteps < 40 else range(H)
+        assert sorted(rows) == list(range(H)), c
+        assert ntiles == -(-W // 16) and run_tiles % 2 == 0 and run_tiles * nruns >= ntiles > run_tiles * (nruns - 1), c
+        assert 32 * nk >= 15 + taps + (1 if lean else anchor & 1) and 32 * nko >= 31 + taps + (1 if lean else anchor & 1), c
+        apart += lean
+    assert apart > 100
