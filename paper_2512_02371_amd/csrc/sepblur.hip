@@ -25,11 +25,8 @@
 // independently.
 #include "hb_device.hpp"
 #include "hb_host.hpp"
+#include "sepblur_plan.hpp"
 #include <algorithm>
-
-#ifndef HB_SEP_TILES
-#define HB_SEP_TILES 2        // 16-column tiles per wave strip
-#endif
 
 namespace hb {
 
@@ -146,7 +143,6 @@ __global__ void __launch_bounds__(256) sepblur_mfma_kernel(SepArgs p) {
 // in registers; NT filtered ones are kept.  128 registers, four workgroups per compute unit (three: 29 us
 // instead of 19 at 4096 x 4096, 31 taps).  4096 x 4096 with 31 / 64 taps 28.2 / 41.7 -> 19.0 / 22.3 us, a copy of the
 // same bytes 18.3; all its pixels staged before the first product, four workgroups of 64 rows deep, 34.6 / 53.
-constexpr int kSepMarchCols = 4 * 16 * HB_SEP_TILES;
 constexpr int kSepAhead = 3;
 template <int NKX>
 struct SepMarch {
@@ -381,9 +377,8 @@ static hb_status sep_launch(K kernel, hipStream_t st, SepArgs& a, int ns, int co
     hipLaunchKernelGGL(kernel, dim3((unsigned)((tasks + per_wg - 1) / per_wg)), dim3(256), 0, st, a);
     return launch_status();
 }
-constexpr int sep_wide_rows(int nt) { return nt < 4 ? 48 : 80; }          // fewer are a shallow image where the row is long
-// One window per tile, for large and for shallow images: see sep_launch_nt.  4 steps per task, 8 where NT - 1 = 3 extra row tiles weigh
-// more (8192 x 8192, 16 taps down: 62 us with 4, 68 with 8), 2 where the rows end after two (16 x 300000, 16 / 64 taps 9.2 and 12.7 us with 4 and
+// One window per tile, where the march is slower: see sep_marches.  4 steps per task, 8 where NT - 1 = 3 extra row tiles weigh
+// more and its waves are not too few (8192 x 8192, 16 taps down: 62 us with 4, 68 with 8; 9036 x 9, 38 taps 7.2 with 4, 10.6 with 8), 2 where the rows end after two (16 x 300000, 16 / 64 taps 9.2 and 12.7 us with 4 and
 // 2 before, 8.3 and 12.7 with 2).
 template <int NT>
 static hb_status sep_launch_one_window(hipStream_t st, SepArgs& a) {
@@ -394,22 +389,10 @@ static hb_status sep_launch_one_window(hipStream_t st, SepArgs& a) {
     interior_range(nct, cols, xw, after > cols ? after : cols, a.W, a.c0, a.c1);
     if (a.H <= 32) return sep_launch(sepblur_mfma_kernel<NT, 2>, st, a, 2, cols, 4);
     if constexpr (NT == 4) {
-        if (a.H >= sep_wide_rows(NT)) return sep_launch(sepblur_mfma_kernel<NT, 8>, st, a, 8, cols, 4);
+        if (a.H >= sep_wide_rows(NT) && 2 * (int64_t)ceil_div(a.H, 128) * nct >= 15 * num_cu()) return sep_launch(sepblur_mfma_kernel<NT, 8>, st, a, 8, cols, 4);
     }
     return sep_launch(sepblur_mfma_kernel<NT, 4>, st, a, 4, cols, 4);
 }
-// The march also serves the filters of one window: its loads are whole rows of pixels, not 16 rows of 64 bytes, its coefficients arrive
-// while the first rows do, and the runs of its four strips meet in one L2 where rows of the output start inside 128-byte lines.  256 x 256,
-// 16 x 16 / 9 x 45 taps 5.2 / 6.1 -> 3.4 / 4.2 us, 1024 x 1024 5.9 / 7.0 -> 4.6 / 6.1, 2160 x 3840 11.4 / 13.1 -> 10.7 / 12.0, 4096 x 4096 19.1 / 20.9 -> 17.7 / 18.9,
-// 2047 x 2045, 9 x 45 taps 15.3 -> 10.4, 8191 x 8191 151 / 166 -> 120 / 102.  The kernel above is the faster one
-//  - in large images, where the march's lines are no longer put together in time or its requests no longer spread over the
-//    memory (8192 x 8192, 16 x 16 / 9 x 45 taps 62 / 66 us, the march 67 / 70, 8190 x 8190, 16 x 16 117 and 125), unless input rows start
-//    between dwords or there are many row tiles a step (8192 x 8192, 9 x 64 taps 75, 72; 8190 x 8190, 9 x 45 132, 125);
-//  - in images of a few rows, most of whose march is the row tiles ahead of the first (16 x 16, 64 taps down 3.7 us and 4.6, 16 x 300000, 9 x 30 taps
-//    9.6 and 10.0; 17 x 128 3.8 and 3.6), longer ones where the row is long (17 x 40000, 16 x 16 taps 3.9 and 5.1, 33 x 300000 12.6 and 15.7, 48 x 40000,
-//    9 x 64 taps 6.6 and 7.1; 16 x 16 5.5 and 5.1, 96 x 40000, 9 x 45 8.6 and 7.9);
-//  - with five row tiles a step, where the march's segments are two steps and two workgroups on every unit (1080 x 1920, 9 x 64 taps 7.5 and 7.8).
-constexpr int64_t kSepMarchShortMax = 24 << 20;           // outputs
 // Row tiles (steps) of a segment of the march.  Every segment requests and filters NT - 1 row tiles ahead of its own, so
 // long ones save work: as long as leaves two workgroups per compute unit (1079 x 1917, 31 / 60 taps 7.4 / 8.8 us, with
 // the four that are resident 8.7 / 11.3; 2048 x 2048, 31 / 64 taps 8.6 / 10.3 and 9.4 / 11.9; with one 9.1 / 10.5), of eight steps
@@ -446,15 +429,7 @@ static int sep_march_steps(const SepArgs& a, int nkx, int nt, bool lines) {
 template <int NT>
 static hb_status sep_launch_nt(int nkx, hipStream_t st, SepArgs& a) {
     const bool lines = a.out_pitch % 32 == 0 && aligned_to(a.out, 128);
-    if (nkx == 1) {
-        const bool even = a.in_pitch % 2 == 0 && aligned_to(a.in, 4);
-        const bool large = (int64_t)a.H * a.W > kSepMarchShortMax && even && NT <= (lines ? 4 : 3);
-        const int few = NT == 5 ? 32 : NT == 4 ? 24 : lines ? 16 : 0;
-        const bool wide = lines && a.H < sep_wide_rows(NT) && a.W > 64 * num_cu();
-        const int64_t all = (int64_t)ceil_div(a.H, 16) * ceil_div(a.W, kSepMarchCols);
-        const bool pairs = lines && NT == 5 && all > 3 * num_cu() && all <= 4 * num_cu();
-        if (large || wide || pairs || a.H <= few) return sep_launch_one_window<NT>(st, a);
-    }
+    if (nkx == 1 && !sep_marches({a.H, a.W, NT, a.in_pitch % 2 == 0 && aligned_to(a.in, 4), lines, num_cu()})) return sep_launch_one_window<NT>(st, a);
     const int steps = sep_march_steps(a, nkx, NT, lines);
     if (nkx == 1) return sep_launch(sepblur_march_mfma_kernel<1, NT>, st, a, steps, kSepMarchCols, 1);
     if (nkx == 2) return sep_launch(sepblur_march_mfma_kernel<2, NT>, st, a, steps, kSepMarchCols, 1);
