@@ -18,6 +18,7 @@
 
 #include "hb_device.hpp"
 #include "hb_host.hpp"
+#include "resize_route.hpp"
 
 namespace hb {
 
@@ -41,17 +42,6 @@ struct ResizeArgs {
     int64_t in_pitch, in_plane, out_pitch, out_plane;
     int ngx, ngy;                             // workgroups across and down
     int first_mask;                           // of a window's first column: ~7 where rows start on 16 bytes, else ~1
-};
-
-constexpr int kRzChunks = 12;                 // chunks of 32 columns whose coefficients are kept in LDS
-constexpr int kRzMinWidth = 8;                // of an image
-// A workgroup's waves own the same columns, either one below the other, each with its own T, or (SHARED, for
-// outputs too small to fill the chip that way) all the same 16 rows: the input rows are dealt among them.
-template <bool SHARED>
-struct RzGeom {
-    static constexpr int kWaves = SHARED ? 8 : 4;
-    static constexpr int kRows = SHARED ? 512 : 160;      // input rows whose horizontal results T holds at a time
-    static constexpr int kPitch = kRows + 40;             // halves per xo: 32 rows beyond, and an odd multiple of 16 bytes
 };
 
 // Coefficients t .. t + 7 of row o of an n x band matrix, zero outside [0, band).  The neighbouring rows' entries
@@ -638,36 +628,9 @@ static hb_status resize_run(bool valu, const hb_half* in, float* out, void* work
     if (!workspace || workspace_bytes < need || !aligned_to(workspace, 256)) return HB_ERR_WORKSPACE;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
 
-    // What a group of 16 outputs spans of an axis when its starts advance by the scale
-    auto span = [](int n_in, int n_out, int band) { return (double)(n_out < 16 ? n_out - 1 : 15) * n_in / n_out + band + 1; };
-    const double span_x = span(W, Wo, band_x), span_y = span(H, Ho, band_y);
-    const int groups = ceil_div(Ho, 16);
-    const int64_t waves = (int64_t)C * ceil_div(Wo, 16) * groups;         // of one group each
-    // The one-launch kernel keeps the coefficients of kRzChunks chunks; wider spans it takes chunk by chunk, each one a
-    // round trip, once for every group of rows that needs them.  That pays only while a group spans few rows and the
-    // waves are few (2048 x 2048 -> 1024 x 26 28 us, two launches 60; -> 26 x 26 460 against 99, 16 x 1024 x 1024 -> 500 x 40
-    // 63 against 37).
-    // Nor does it pay where the rows of a group are so many that few workgroups pass over most of the image (2832 x 3696
-    // -> 55 x 210, 370 x 1081 pixels a group: 84 us, two launches 64; 127 x 1655 47 against 77).
-    // Rows that start on odd samples are read at a fraction of the rate, and the one-launch kernel reads a row for every
-    // group of outputs that needs it.  Odd pitches: large images and many groups take the kernel that reads even and odd rows apart (8 planes
-    // of 2048 rows at a pitch of 2049, factors 4 / 9: 57 / two launches 55 -> 45 / 44 us; 1947 x 6281 -> 214 x 690 28.9 -> 18.9; 4095 x 4095 -> 900
-    // 45 -> 29; 901 x 1001 -> 800 x 900 6.0 -> 5.6; few groups of small images gain nothing: 2 x 600 x 603 -> 40 18.6, 19.2).  Other
-    // large images of such rows take two launches (874 x 3053 at 3117 -> 13 x 341 49 with one, 62 with two).
-    const bool apart = (in_pitch & 1) && (waves > num_cu() || (int64_t)C * H * W > (6 << 20));
-    const bool odd_rows = !apart && ((in_pitch & 1) || (C > 1 && (in_plane & 1)) || !aligned_to(in, 4));
-    // Large enlargements are bound by their stores, of 64-byte runs here and 256-byte runs there (3 x 2048 x 2048 to three
-    // times the size 222 us, two launches 170); where rows start inside 128-byte lines neither run is whole (227 against 246).
-    const bool line_stores = (double)Ho * Wo >= 2.0 * H * W && (int64_t)C * Ho * Wo > (16 << 20) && out_pitch % 32 == 0 &&
-                             out_plane % 32 == 0 && aligned_to(out, 128);
-    // One or two groups of rows as wide as the image leave a wave with a long walk and nothing to share (32 x 200 x 4096 -> 4
-    // x 4000 183 us, two launches 96; 8 x 514 x 8160 -> 30 x 4720 81 against 74); narrow results have fewer products in each
-    // row's pass (64 x 240 x 4096 -> 12 x 600 68 against 82, 12 x 1600 118 against 104).
-    const bool tall = span_y > RzGeom<false>::kRows;
-    const bool few_groups = tall && groups <= 2 && waves >= 8 * num_cu() && 4 * (int64_t)Wo >= W;
-    const bool one_launch = W >= kRzMinWidth && (span_x <= 32 * kRzChunks ? span_x * span_y <= 3.2e5 : span_y <= 128 && waves <= 2 * num_cu()) &&
-                            !line_stores && !few_groups && !(odd_rows && (int64_t)C * H * W > (6 << 20) && span_y > 120);
-    if (!valu && one_launch) {
+    const RzRoute route = rz_route({C, H, W, Ho, Wo, band_y, band_x, in_pitch, in_pitch % 2 == 0 && (C == 1 || in_plane % 2 == 0) && aligned_to(in, 4),
+                                    out_pitch % 32 == 0 && out_plane % 32 == 0 && aligned_to(out, 128), num_cu()});
+    if (!valu && route.one_launch) {
         ResizeArgs r;
         r.in = reinterpret_cast<const half_t*>(in);
         r.out = out;
@@ -688,15 +651,7 @@ static hb_status resize_run(bool valu, const hb_half* in, float* out, void* work
         r.out_plane = out_plane;
         r.ngx = ceil_div(Wo, 16);
         r.first_mask = in_pitch % 8 == 0 && (C == 1 || in_plane % 8 == 0) && aligned_to(in, 16) ? ~7 : ~1;
-        // Groups of 16 output rows per wave: more share more, while the rows they need fit the wave's LDS and the
-        // chip keeps two waves per SIMD (2048 x 2048 from 4096 x 4096: 34 / 29 / 27 us with 1 / 2 / 4; 450 x 450 x 3 from
-        // 2048 x 2048: 19 / 29 / 37).  Under one wave per SIMD the waves of a workgroup share one group (256 x 256 from
-        // 4096 x 4096: 20 us against 92), under two where its rows do not fit a wave's LDS at once (512 x 512 from
-        // 8192 x 8192: 56 against 96; at two 256 x 2048 from 4096 x 4096 33 with a group per wave, 41 shared), and
-        // where one group is all there is (64 x 240 x 4096 -> 12 x 600 68 against 121).
-        auto good = [&](int q) { return waves >= 8 * q * num_cu() && 16.0 * q * H / Ho + band_y <= RzGeom<false>::kRows; };
-        const bool shared = waves < (tall ? 8 : 4) * num_cu() || (tall && groups == 1);
-        const int gq = shared ? 0 : good(4) ? 4 : good(2) ? 2 : 1;
+        const int gq = route.groups, groups = ceil_div(Ho, 16);
         r.ngy = gq ? ceil_div(groups, gq * RzGeom<false>::kWaves) : groups;
         const int64_t blocks = (int64_t)C * r.ngx * r.ngy;
         if (blocks > 0x7fffffff) return HB_ERR_UNSUPPORTED;
@@ -708,7 +663,7 @@ static hb_status resize_run(bool valu, const hb_half* in, float* out, void* work
             else if (gq == 1) hipLaunchKernelGGL((resize_mfma_kernel<1, false, ODD>), grid, block, 0, st, r);
             else hipLaunchKernelGGL((resize_mfma_kernel<1, true, ODD>), grid, dim3(64 * RzGeom<true>::kWaves), 0, st, r);
         };
-        if (apart) launch(RzInt<1>{});
+        if (route.apart) launch(RzInt<1>{});
         else launch(RzInt<0>{});
         return launch_status();
     }

@@ -194,14 +194,24 @@ def test_resize_first_column_of_a_window(orc, band, pitch_extra):
             assert_close(got[c], orc.band_resize(img[c], sy, cy, sx, cx), f"offset {off} plane {c}")
 
 
+# calls of odd pitches, by what the library makes of them (tests/test_resize_route_cpu.py holds it to that)
+APART_SHARED = [                              # the waves of a workgroup share a group
+    (3, 700, 1003, 97, 700), (1, 1100, 1555, 400, 601), (1, 1400, 2001, 300, 444),               # windows of one to four chunks
+    (1, 1001, 3301, 181, 600), (1, 1600, 4601, 150, 307), (2, 1400, 2401, 100, 160),             # of more
+    (1, 190, 40001, 17, 5000), (1, 2500, 2601, 125, 700),                                        # few groups of rows; more rows than a wave's own T holds
+]
+APART_OWN = [                                 # a group, two or four per wave
+    (1, 300, 1201, 290, 1190), (2, 801, 1601, 700, 1400), (1, 2301, 2001, 2100, 1900),           # one chunk
+    (1, 1800, 2801, 1200, 700), (2, 900, 3001, 600, 560), (3, 800, 3201, 700, 400), (2, 1601, 1801, 1400, 700),    # three, four, six, two
+    (8, 1265, 2865, 221, 501),
+]
+NOT_APART = [(5, 500, 2101, 52, 1900), (8, 700, 2101, 73, 1900), (16, 300, 89, 180, 60), (1, 2701, 2601, 40, 40)]     # long groups in one launch and in two, narrow, a wide span
+
+
 @pytest.mark.parametrize("first", [0, 1])             # the image's first row starts on an even or an odd sample
-@pytest.mark.parametrize("C,H,W,Ho,Wo", [
-    (1, 300, 1201, 290, 1190), (3, 131, 1003, 97, 700), (1, 517, 1555, 300, 601), (1, 800, 2001, 300, 444),      # windows of one to four chunks
-    (1, 1001, 3301, 181, 600), (1, 1500, 4601, 150, 307), (2, 1400, 2401, 100, 160),                             # of more
-    (1, 190, 40001, 17, 5000), (1, 2701, 2601, 40, 40),                                                          # few rows of groups; shared by a workgroup's waves
-])
+@pytest.mark.parametrize("C,H,W,Ho,Wo", APART_SHARED + APART_OWN + NOT_APART)
 def test_resize_even_and_odd_rows_apart(orc, C, H, W, Ho, Wo, first):
-    """Odd pitches of large images and many groups: rows that start on even and on odd samples are read apart."""
+    """Odd pitches: rows that start on even and on odd samples are read apart, or not."""
     import torch
     from paper_2512_02371_amd import hb
     (sy, cy), (sx, cx) = lanczos(hb, H, Ho), lanczos(hb, W, Wo)
