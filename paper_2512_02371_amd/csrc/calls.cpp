@@ -8,7 +8,6 @@
 #include <pthread.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/jit/frontend/tracer.h>
-#include <torch/version.h>
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <c10/hip/HIPStream.h>
 
@@ -309,8 +308,8 @@ PyMODINIT_FUNC PyInit__calls() {
     PyObject* version = torch ? PyObject_GetAttrString(torch, "__version__") : nullptr;
     const char* v = version ? PyUnicode_AsUTF8(version) : nullptr;
     if (!v) return nullptr;
-    if (strncmp(v, TORCH_VERSION, strlen(TORCH_VERSION)) != 0) {
-        PyErr_Format(PyExc_ImportError, "built with torch " TORCH_VERSION ", this is %s", v);
+    if (strcmp(v, HB_TORCH_VERSION) != 0) {
+        PyErr_Format(PyExc_ImportError, "built with torch " HB_TORCH_VERSION ", this is %s", v);
         return nullptr;
     }
     PyObject* numpy = PyImport_ImportModule("numpy");

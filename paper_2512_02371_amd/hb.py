@@ -9,6 +9,7 @@ extension module ``_calls``, all others here.
 from __future__ import annotations
 
 import ctypes
+import logging
 import os
 
 import numpy as np
@@ -112,13 +113,13 @@ def load() -> ctypes.CDLL:
     L.hb_sat2d_workspace_size.argtypes = [I, I]
     L.hb_sat2d_workspace_size.restype = ctypes.c_size_t
     _lib = L
-    # built against one torch: with another it does not load, and ctypes makes every call
+    # built against one torch: with another, or not built at all, it does not load, and ctypes makes every call
     try:
         from . import _calls as native
         native.bind({name: ctypes.cast(getattr(L, name), vp).value for name in SYMBOLS[1:]}, HbError)
         _calls = native
-    except ImportError:
-        pass
+    except ImportError as e:
+        logging.getLogger(__name__).warning("short calls take 1 to 2 us more, the native marshalling did not load: %s", e)
     return L
 
 
