@@ -42,8 +42,16 @@ def test_usual_calls_are_taken_and_equal_ctypes(name, monkeypatch):
     args, o = usual(torch)[name]
     call = getattr(hb._calls, name)
     print(name, flush=True)
+    # On the current stream: its products take a millisecond each, and what the call reads is written behind them.  On the default
+    # stream it would read zeros.
+    image, busy = args[0].clone(), torch.zeros((2, 8192, 8192), dtype=torch.float16, device="cuda:0")
+    args[0].zero_()
     stream = torch.cuda.Stream()
-    with torch.cuda.stream(stream):                       # the current stream, not the default one
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        for _ in range(3):
+            torch.mm(busy[0], busy[0], out=busy[1])
+        args[0].copy_(image)
         assert call(*args) is True
     stream.synchronize()
     got = args[o].clone()
