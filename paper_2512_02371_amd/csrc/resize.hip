@@ -84,6 +84,29 @@ struct RzInt {
     static constexpr int value = I;
 };
 
+// The vertical pass over the rows that T holds from base on.  Text and not a lambda: as a lambda with two callers it has the compiler keep 10
+// registers fewer of loads in flight also where there is one (16 x 2946 x 322 -> 283 x 30 18.3 us, 20.9 so; 16 x 2001 x 125 -> 364 x 22 12.3, 14.3).
+#define HB_RZ_VERTICAL(base)                                                                                                                         \
+    _Pragma("unroll")                                                                                                                                \
+    for (int q = 0; q < GY; ++q) {                                                                                                                   \
+        const int vsy = __shfl(sy, 16 * q + c, 64), vo = min(yo0 + 16 * q + c, p.Ho - 1);                                                            \
+        const int first = ylo + ((__builtin_amdgcn_readlane(glo, 16 * q) - ylo) & ~7); /* 16-byte pieces of T */                                     \
+        const int hi = __builtin_amdgcn_readlane(ghi, 16 * q);                                                                                       \
+        /* chunks that start in this round, four coefficient loads at a time */                                                                      \
+        const int k_first = max(base - first + 31, 0) / 32, k_end = min(hi - first + 31, base + kRows - first + 31) / 32;                            \
+        _Pragma("unroll 1")                                                                                                                          \
+        for (int k0 = k_first; k0 < k_end; k0 += 4) {                                                                                                \
+            half8 f[4];                                                                                                                              \
+            _Pragma("unroll")                                                                                                                        \
+            for (int k = 0; k < 4; ++k)                                                                                                              \
+                if (k0 + k < k_end) f[k] = rz_coef8(p.coef_y, p.Ho, p.band_y, vo, first + 32 * (k0 + k) + 8 * g - vsy);                              \
+            _Pragma("unroll")                                                                                                                        \
+            for (int k = 0; k < 4; ++k)                                                                                                              \
+                if (k0 + k < k_end)                                                                                                                  \
+                    out[q] = mfma16x16x32(*reinterpret_cast<const half8*>(rows + c * kPitch + first + 32 * (k0 + k) - base + 8 * g), f[k], out[q]);  \
+        }                                                                                                                                            \
+    }
+
 // What bounds it: a wave's chain of dependent round trips (starts -> pixels and coefficients -> vertical products ->
 // stores) where waves are few, and its instructions (the geometry of a group is 600 of them) where they are many: GY
 // groups of rows per wave share them and the rows that neighbouring groups both need.  As two launches with T in
@@ -113,7 +136,6 @@ __global__ void __launch_bounds__(64 * RzGeom<SHARED>::kWaves, ODD && !SHARED ? 
     const int sy = clampi(p.start_y[min(yo0 + (lane & (16 * GY - 1)), p.Ho - 1)], -p.band_y, p.H - 1);
     int xlo = sx, xhi = sx + p.band_x;
     rz_extent(xlo, xhi);
-    const half_t* const px = p.in + (int64_t)plane * p.in_plane;
     // ODD: the rows that start on an odd sample are read from one sample further left
     xlo = (__builtin_amdgcn_readfirstlane(xlo) & ~1) - (ODD ? 1 : 0);
     xhi = __builtin_amdgcn_readfirstlane(xhi);
@@ -132,18 +154,20 @@ __global__ void __launch_bounds__(64 * RzGeom<SHARED>::kWaves, ODD && !SHARED ? 
 
     // coefficient blocks, B-operand layout: lane (c = o, g) holds coef[o][first + 32 kk + 8g + i - start[o]]
     const int x_even = xlo + (ODD ? 1 : 0);
-    auto frag_x = [&](int kk, int from) { return rz_coef8(p.coef_x, p.Wo, p.band_x, xo, from + 32 * kk + 8 * g - sx); };
-    for (int kk = wv; kk < min(nk, kRzChunks); kk += kWaves) s_frag[kk * 64 + lane] = frag_x(kk, x_even);
-    if (ODD)
-        for (int kk = kWaves - 1 - wv; kk < min(nk, kRzChunks); kk += kWaves) s_frag[(kRzChunks + kk) * 64 + lane] = frag_x(kk, xlo);
+    auto frag_x = [&](int kk) { return rz_coef8(p.coef_x, p.Wo, p.band_x, xo, x_even + 32 * kk + 8 * g - sx); };
+    for (int kk = wv; kk < min(nk, kRzChunks); kk += kWaves) s_frag[kk * 64 + lane] = frag_x(kk);
+    if constexpr (ODD)
+        for (int kk = kWaves - 1 - wv; kk < min(nk, kRzChunks); kk += kWaves)
+            s_frag[(kRzChunks + kk) * 64 + lane] = rz_coef8(p.coef_x, p.Wo, p.band_x, xo, xlo + 32 * kk + 8 * g - sx);
 
+    const half_t* const px = p.in + (int64_t)plane * p.in_plane;
     half_t* const rows = s_rows + (SHARED ? 0 : wv * 16 * kPitch);        // T
     floatx4 out[GY];
 #pragma unroll
     for (int q = 0; q < GY; ++q) out[q] = floatx4{0.f, 0.f, 0.f, 0.f};
-    auto load_from = [&](int y, int xs) {                 // 32 columns of row y from xs on
+    auto load = [&](int y, int kk) {                      // chunk kk of row y
         const uint32_t row = (uint32_t)clampi(y, 0, p.H - 1) * (uint32_t)p.in_pitch;
-        const int x = xs + 8 * g;
+        const int xs = x_even + 32 * kk, x = xs + 8 * g;
         if (xs >= 0 && xs + 32 <= p.W) return ldg8(px, 2u * (row + (uint32_t)x));     // uniform
         // Requested inside the row, then shifted into place.  The column is hidden from the compiler, which otherwise works
         // out the masks of all four chunks' shifts ahead of the loop, also for groups inside the image, and spills 40 scalar
@@ -153,7 +177,6 @@ __global__ void __launch_bounds__(64 * RzGeom<SHARED>::kWaves, ODD && !SHARED ? 
         const half8 v = ldg8(px, 2u * (row + (uint32_t)clampi(xe, 0, p.W - 8)));
         return shift_in_from_left(shift_in_from_right(v, max(xe - (p.W - 8), 0)), max(-xe, 0));
     };
-    auto load = [&](int y, int kk) { return load_from(y, x_even + 32 * kk); };
     auto rows_ready = [&]() {
         if (SHARED) __syncthreads();
         else wave_lds_fence();
@@ -162,27 +185,6 @@ __global__ void __launch_bounds__(64 * RzGeom<SHARED>::kWaves, ODD && !SHARED ? 
     __syncthreads();
     if (yo0 >= p.Ho) return;                              // SHARED: no such workgroup
 
-    auto vertical = [&](int base) {                       // with the rows that T holds from base on
-#pragma unroll
-        for (int q = 0; q < GY; ++q) {
-            const int vsy = __shfl(sy, 16 * q + c, 64), vo = min(yo0 + 16 * q + c, p.Ho - 1);
-            const int first = ylo + ((__builtin_amdgcn_readlane(glo, 16 * q) - ylo) & ~7);   // 16-byte pieces of T
-            const int hi = __builtin_amdgcn_readlane(ghi, 16 * q);
-            // chunks that start in this round, four coefficient loads at a time
-            const int k_first = max(base - first + 31, 0) / 32, k_end = min(hi - first + 31, base + kRows - first + 31) / 32;
-#pragma unroll 1
-            for (int k0 = k_first; k0 < k_end; k0 += 4) {
-                half8 f[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (k0 + k < k_end) f[k] = rz_coef8(p.coef_y, p.Ho, p.band_y, vo, first + 32 * (k0 + k) + 8 * g - vsy);
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (k0 + k < k_end)
-                        out[q] = mfma16x16x32(*reinterpret_cast<const half8*>(rows + c * kPitch + first + 32 * (k0 + k) - base + 8 * g), f[k], out[q]);
-            }
-        }
-    };
     // ODD: rows start on even and odd samples in turn, and of a row read from an odd one on every lane's 16 bytes are several cache
     // accesses.  Here the even and the odd rows of 32 are two operands, each of which is read from whole dwords with coefficients that
     // start where its window does; what they give is put together again on its way to T (3 x 1912 x 2923 -> 671 x 1025 39.3 -> 25.9 us).
@@ -297,6 +299,7 @@ __global__ void __launch_bounds__(64 * RzGeom<SHARED>::kWaves, ODD && !SHARED ? 
             use(tn, kn, d1);
         }
     };
+    int from = ylo;                                       // row
     const bool short_group = ODD && xlo >= 0 && x_even + 32 * nk <= p.W && yhi - ylo <= kRows && nk <= kRzChunks;    // uniform
     if constexpr (ODD) {
         if (short_group) {
@@ -308,11 +311,14 @@ __global__ void __launch_bounds__(64 * RzGeom<SHARED>::kWaves, ODD && !SHARED ? 
             else if (nk == 4) short_loop(RzInt<4>{}, base, tiles);
             else long_loop(base, tiles);
             rows_ready();
-            if (!SHARED || wv == 0) vertical(base);
+            if (!SHARED || wv == 0) {
+                HB_RZ_VERTICAL(base)
+            }
+            from = yhi;
         }
     }
 #pragma unroll 1
-    for (int base = ylo; !short_group && base < yhi; base += kRows) {
+    for (int base = from; base < yhi; base += kRows) {
         // T of rows base .. base + rows - 1; a chunk of the vertical pass that starts before base + kRows may reach
         // 32 rows further, real ones or, after the last, zeros
         const bool last = yhi - base <= kRows;
@@ -357,13 +363,13 @@ __global__ void __launch_bounds__(64 * RzGeom<SHARED>::kWaves, ODD && !SHARED ? 
             for (int t = t_first; t < tiles; t += t_step) {
                 floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-                for (int kk = 0; kk < nk; ++kk) acc = mfma16x16x32(load(base + 16 * t + c, kk), frag_x(kk, x_even), acc);
+                for (int kk = 0; kk < nk; ++kk) acc = mfma16x16x32(load(base + 16 * t + c, kk), frag_x(kk), acc);
                 keep(t, acc);
             }
         }
         rows_ready();
         if (SHARED && wv != 0) continue;
-        vertical(base);
+        HB_RZ_VERTICAL(base)
     }
     if (SHARED && wv != 0) return;
     // D[m = xo][n = yo]: lane (c = yo, g) holds columns 4g .. 4g + 3 of its row
@@ -374,6 +380,8 @@ __global__ void __launch_bounds__(64 * RzGeom<SHARED>::kWaves, ODD && !SHARED ? 
             store4_mask(p.out + (int64_t)plane * p.out_plane + (int64_t)yo * p.out_pitch, x, p.Wo, out[q]);
     }
 }
+
+#undef HB_RZ_VERTICAL
 
 // ---------------------------------------------------------------------------
 // The two-launch form for large factors: one kernel that contracts over the memory-contiguous index of its input and
