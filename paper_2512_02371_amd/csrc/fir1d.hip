@@ -84,6 +84,7 @@ __global__ void __launch_bounds__(256) fir1d_mfma_kernel(FirArgs p) {
     __shared__ __attribute__((aligned(16))) float s_patch[4][RowPatch<NW>::kFloats];
     const int lane = threadIdx.x & 63;
     const int c = lane & 15, g = lane >> 4;
+    int e = p.anchor & 1, aw = p.anchor + e;              // window start, left of the tile
     // (tasks in plain launch order: with one contiguous eighth of the tasks per XCD this kernel measured
     // 10 % slower on tall images, 100 against 89 us on 262144 x 256; groups of 2 to 8 neighbours per XCD
     // measured within 2 % of the plain order there)
@@ -92,7 +93,10 @@ __global__ void __launch_bounds__(256) fir1d_mfma_kernel(FirArgs p) {
     const int rg = task / p.nct, ct = task - rg * p.nct;
     const FirRows rows = fir_rows<LEAN>(p, rg);
     const int apart = LEAN ? p.step : 1;
-    const int e = rows.e, aw = p.anchor + e;              // window start, left of the tile
+    if constexpr (LEAN) {
+        e = rows.e;
+        aw = p.anchor + e;
+    }
     const int x0 = 16 * NW * ct, y0 = rows.y0;
     const bool inside = x0 >= aw && x0 + 16 * (NW - 1) - aw + 32 <= p.W && x0 + 16 * NW <= p.W;   // uniform
     const uint32_t rowoff = (uint32_t)min(y0 + apart * c, p.H - 1) * (uint32_t)p.in_pitch * 2u;
@@ -117,7 +121,7 @@ __global__ void __launch_bounds__(256) fir1d_mfma_kernel(FirArgs p) {
     float* const dst = p.out + (int64_t)y0 * p.out_pitch + x0;
     float* const patch = s_patch[threadIdx.x >> 6];
     const int64_t pitch = apart * p.out_pitch;
-    if (inside && y0 + 15 * apart < p.H) store_rows_via_lds<NW, true>(patch, dst, (uint32_t)pitch, acc, lane);
+    if (inside && y0 + 15 * apart + 1 <= p.H) store_rows_via_lds<NW, true>(patch, dst, (uint32_t)pitch, acc, lane);
     else store_rows_via_lds_masked<NW, true>(patch, dst, pitch, acc, lane, (p.H - y0 + apart - 1) / apart, p.W - x0);
 }
 
@@ -149,27 +153,36 @@ __global__ void __launch_bounds__(64 * fir_walk_waves(NK)) fir1d_walk_kernel(Fir
     const int lane = threadIdx.x & 63;
     const int c = lane & 15, g = lane >> 4;
     half8 even[NK], odd[NKO];
-    auto coefficients = [&](int e) {
+    // written out twice: in a function of e they cost the plain kernel address arithmetic and a later first load, 0.2 us of a small call (654 x 42,
+    // 20 taps 5.0, 5.2)
+    int e = p.anchor & 1;
+    if constexpr (!LEAN) {
 #pragma unroll
         for (int kk = 0; kk < NK; ++kk) even[kk] = tap_run(p.taps.tab, 32 * kk + 8 * g - c - e);
 #pragma unroll
         for (int kk = 0; kk < NKO; ++kk) odd[kk] = tap_run(p.taps.tab, 32 * kk - 16 + 8 * g - c - e);
-    };
-    if constexpr (!LEAN) coefficients(p.anchor & 1);
+    }
 
     const int wgpos = xcd_contiguous(blockIdx.x, gridDim.x);
     const int task = __builtin_amdgcn_readfirstlane(wgpos * WV + (threadIdx.x >> 6));
     if (task >= p.wtasks) return;
     const int rg = task / p.nruns, run = task - rg * p.nruns;
     const FirRows rows = fir_rows<LEAN>(p, rg);
-    const int y0 = rows.y0, aw = p.anchor + rows.e, apart = LEAN ? p.step : 1;
-    if constexpr (LEAN) coefficients(rows.e);
+    const int y0 = rows.y0, apart = LEAN ? p.step : 1;
+    if constexpr (LEAN) e = rows.e;
+    const int aw = p.anchor + e;
+    if constexpr (LEAN) {
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk) even[kk] = tap_run(p.taps.tab, 32 * kk + 8 * g - c - e);
+#pragma unroll
+        for (int kk = 0; kk < NKO; ++kk) odd[kk] = tap_run(p.taps.tab, 32 * kk - 16 + 8 * g - c - e);
+    }
     const int t0 = run * p.run_tiles;                     // first tile of the run
     const int L = min(p.run_tiles, p.ntiles - t0);        // its tiles
     const int npairs = (L + 1) / 2, nsteps = npairs + NKO - 1;        // pairs of tiles, windows
     const uint32_t rowoff = (uint32_t)min(y0 + apart * c, p.H - 1) * (uint32_t)p.in_pitch * 2u;
     float* patch = s_patch[threadIdx.x >> 6];
-    const bool rows16 = y0 + 15 * apart < p.H;
+    const bool rows16 = y0 + 15 * apart + 1 <= p.H;
 
     auto load_window = [&](int v) { return fir_request(p, rowoff, 16 * t0 + 32 * v - aw + 8 * g); };
     auto window_inside = [&](int v) {                     // uniform
