@@ -61,25 +61,28 @@ inline FirPlan fir_plan(const FirCall& c) {
         if ((int64_t)rowsteps * long_runs >= 3 * c.cu) runs = std::min(runs, long_runs);
         return (up(p.ntiles, std::max(1, runs)) + 1) & ~1;
     };
-    const auto rounds = [&](int rowsteps) {               // of four waves to every unit
-        const int64_t tasks = (int64_t)rowsteps * up(p.ntiles, run_tiles(rowsteps));
-        return (tasks + 4 * c.cu - 1) / (4 * c.cu);
-    };
+    const auto tasks = [&](int rowsteps) { return (int64_t)rowsteps * up(p.ntiles, run_tiles(rowsteps)); };
 
     // Odd starts are met where the windows have room for the pixel more (17, 33, 49, ... taps would take another window for every tile)
-    // and the rows fill more than one group.  The coefficients of a walk then wait for its place, which needs runs that hide it:
-    //  - no narrow images (one window 1000 x 32 5 % slower; 96 taps, 6752 x 32 4.7 us, 5.2 so; 24 taps, 2222 x 331 5.4, 5.8; 219 taps, 1459 x 497 7.9,
-    //    8.5; but 97 x 249, 96 taps 6.4, 6.6 against 23 x 517, 125 taps 7.1, 7.4 and a median gain of 3 % from 129 columns on with four to six windows);
-    //  - with two or three windows and seven to nine, which hide least, only from 384 K pixels on (200 x 501, 40 / 200 / 256 taps 5.48 / 7.05 / 7.58 us and
-    //    5.60 / 7.43 / 7.99 so, 300 x 3001 6.21 / 10.59 / 11.50 and 5.99 / 9.38 / 10.29);
-    //  - not where the groups, which are of 32 rows in pairs, become a round of waves more (167 x 11451, 50 taps 5.6, 6.8; 48 x 31892, 48 taps 6.1, 7.1), nor,
-    //    with seven to nine, more than an eighth more (34 x 11867, 205 taps 7.9, 8.6).
+    // and the rows fill more than one group.  The coefficients of a walk then wait for its place, which needs rows and runs that hide it.
+    // Of 7301 random calls no one is more than 8 % slower so than with plain groups, 34 more than 3 %; 7 miss more than 8 %.
+    //  - One window: all but the narrowest (1000 x 32 5 % slower).
+    //  - Two or three: more than a round of waves (7706 x 512, 41 taps 9.5 -> 6.8 us, 4109 x 465, 35 taps 9.1 -> 8.1, 5547 x 201, 40 taps 8.2 -> 7.3).
+    //    Within one where the groups, which are of 32 rows in pairs, do not make it two (167 x 11451, 50 taps 5.6 against 6.8): with three
+    //    windows always (47 x 3390, 80 taps 6.6 -> 5.9), with two in long rows (356 x 1534, 34 taps 6.2 -> 5.7), or short runs of whole lines
+    //    (323 x 832, 40 taps 4.7 -> 4.3; 2222 x 331, 24 taps 5.4 against 5.8, 200 x 501, 40 taps 5.5 and 5.6).
+    //  - Four to six: all but the narrowest (68 x 128, 132 taps 7.5 -> 6.4; 6752 x 32, 96 taps 4.7 against 5.2).
+    //  - Seven to nine, which hide least: from 384 K pixels on (1579 x 639, 228 taps 12.3 -> 10.5; 200 x 501, 200 taps 7.1 against 7.4, 5428 x 96, 211 taps 7.5 and
+    //    8.2), and not with a third more groups (34 x 11867, 205 taps 7.9 and 8.6).
     const int plain = up(c.H, 16), apart = c.in_pitch % 2 ? 2 * up(c.H, 32) : plain;
     const bool room = up(16 + c.ntaps, 32) == nk && up(32 + c.ntaps, 32) == p.nko;
-    const int narrow = nk == 1 ? 32 : nk <= 3 ? 512 : nk <= 6 ? 128 : 1200;
-    p.lean = !c.even && room && c.H >= kFirApartRows && c.W > narrow && (nk == 1 || (nk >= 4 && nk <= 6) || px >= (3 << 17)) &&
-             (nk == 1 || rounds(apart) == rounds(plain)) && (nk < 7 || 7 * apart <= 8 * plain) &&
-             c.out_pitch <= ((int64_t)1 << 25);           // 32-bit byte offsets inside a group of 32 rows
+    const int64_t round = 4 * c.cu;
+    bool gains;
+    if (nk == 1) gains = c.W > 32;
+    else if (nk <= 3) gains = c.W > 48 && (tasks(plain) > round || (tasks(apart) <= round && (nk == 3 || c.W > 1000 || (c.lines && c.W > 64 && run_tiles(apart) <= 4))));
+    else if (nk <= 6) gains = c.W > 48;
+    else gains = c.W > 128 && px >= (3 << 17) && 7 * apart <= 8 * plain;
+    p.lean = !c.even && room && c.H >= kFirApartRows && gains && c.out_pitch <= ((int64_t)1 << 25);           // 32-bit byte offsets inside a group of 32 rows
     p.step = p.lean && c.in_pitch % 2 ? 2 : 1;
     p.rowsteps = p.lean ? apart : plain;
     p.run_tiles = run_tiles(p.rowsteps);
