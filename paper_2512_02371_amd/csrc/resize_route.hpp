@@ -51,29 +51,32 @@ inline RzRoute rz_route(const RzCall& c) {
 
     // Rows that start on odd samples are read at a fraction of the rate.  Of an odd pitch that is every second row, and the one-launch
     // kernel can read even and odd rows apart (8 planes of 2048 rows at a pitch of 2049, factors 4 / 9: 57 / two launches 54 -> 44 / 40 us;
-    // 1947 x 6281 -> 214 x 690 28.9 -> 18.9; 4095 x 4095 -> 900 45 -> 29), but
+    // 1947 x 6281 -> 214 x 690 28.9 -> 18.9; 4095 x 4095 -> 900 45 -> 29; 8 x 787 x 5325 -> 164 x 7830 122 -> 82), but
     //  - only groups whose rows fit T and whose windows lie inside the row; the others take its general loop, with three waves
-    //    per SIMD instead of four (16 x 3012 x 89 -> 1799 x 60 11 -> 18, 8 x 5171 x 155 -> 1697 x 54 15 -> 19);
-    //  - a group per wave costs it a round of workgroups where three to a unit are one round more than four (1266 x 1483 -> 876 x 1026 7.3 -> 8.9),
-    //    which it is worth in larger images with more than one chunk a window (3 x 413 x 2815 -> 281 x 858 14.6 -> 11.0; 3 x 1635 x 1381 -> 1209 x
-    //    1021 16.7 -> 18.9) or where two launches are the other way (8 x 1265 x 5731 -> 221 x 1001 79 -> 45), for few columns more than
-    //    two workgroups to a unit (16 x 1277 x 1311 -> 180 x 86 43 -> 53);
-    //  - nor is it worth a second chunk for the sample further left (3 x 5998 x 439 -> 4068 x 297 18.7 -> 21.2);
-    //  - few waves, and shared groups of small images, gain nothing (2 x 600 x 603 -> 40 18.6, 19.2; 217 x 2189 -> 198 x 176 8.2 -> 9.9).
-    const bool large = pixels > (6 << 20);
-    const bool would_be_two = large && span_y > 120;      // of odd rows, see below
+    //    per SIMD instead of four (16 x 3012 x 89 -> 1799 x 60 11 -> 18, 8 x 5171 x 155 -> 1697 x 54 15 -> 19).  Beyond 12 M pixels the other windows are
+    //    worth it (3 x 5459 x 4520 -> 3329 x 5014);
+    //  - a group per wave costs it a round of workgroups where three to a unit are nearly twice as many as four (1266 x 1483 -> 876 x 1026 7.3 -> 8.9,
+    //    16 x 273 x 532 -> 42 x 823 13.0 -> 16), which it is worth with more than one chunk a window (1 x 1611 x 2997 -> 1803 x 1624 19.3 -> 16.0, 3 x 413 x
+    //    2815 -> 281 x 858 14.6 -> 11.0), if that is not for the sample further left alone, and in large images (16 x 473 x 4430 -> 60 x 4397 118 -> 88);
+    //  - few windows of many chunks, which the loop for more than four takes, are better off with two launches (16 x 1277 x 1311 -> 180 x 86 43 -> 53);
+    //  - of shared groups large images gain (8 x 3907 x 465 -> 659 x 78 25 -> 18), others with more than one to a unit (586 x 2559 -> 67 x 4036 16 -> 12),
+    //    few waves and small images do not (2 x 600 x 603 -> 40 18.6, 19.2; 217 x 2189 -> 198 x 176 8.2 -> 9.9), nor where half of the windows or more
+    //    reach over the row's ends (16 x 4295 x 284 -> 271 x 17 49 -> 55).
+    // Of 6215 random calls of odd pitches one in a hundred is more than 8 % slower so than the better way.
+    const bool would_be_two = pixels > (6 << 20) && span_y > 120;         // of odd rows, see below
     const double rows = span(16 * (r.groups > 1 ? r.groups : 1), c.H, c.Ho, c.band_y) - 1;
     const bool fits = rows <= (shared ? RzGeom<true>::kRows : RzGeom<false>::kRows) && span_x + 1 <= 32 * kRzChunks;
     const int nk = (int)(span_x + 32) / 32, nk_plain = (int)(span_x + 30.5) / 32;      // chunks of a window, with the sample further left and without
     const double step = 16.0 * c.W / c.Wo;                // columns from group to group
-    const double inside = floor((c.W - 32 * nk + c.band_x / 2.0 + 1) / step) - ceil((c.band_x / 2.0 + 1) / step) + 1;
+    const double inside = (floor((c.W - 32 * nk + c.band_x / 2.0 + 1) / step) - ceil((c.band_x / 2.0 + 1) / step) + 1) / ngx;
     const int64_t wgs = r.groups ? (int64_t)c.C * ngx * ((groups + 4 * r.groups - 1) / (4 * r.groups)) : waves;
     const auto rounds = [&](int per_cu) { return (wgs + per_cu * c.cu - 1) / (per_cu * c.cu); };
-    bool worth;
-    if (shared) worth = large || (pixels > (1 << 20) && waves > c.cu);
-    else worth = rounds(3) == rounds(4) || (nk > 1 && pixels > (5 << 19)) || would_be_two;
-    if (would_be_two ? !shared && ngx <= 12 && wgs < 2 * c.cu : nk == 2 && nk_plain == 1) worth = false;
-    r.apart = (c.in_pitch & 1) && fits && 2 * inside > ngx && worth;
+    bool gains;
+    if (shared) gains = inside > 0.54 && (pixels > (6 << 20) || (waves > c.cu && pixels > (1 << 19) && (inside > 0.8 || pixels > (2 << 20)) &&
+                                                                 (nk <= 5 || pixels > (1 << 20))));
+    else if (would_be_two && ngx <= 12 && nk > 8) gains = false;
+    else gains = pixels > (12 << 20) || (inside > 0.5 && (4 * rounds(3) < 7 * rounds(4) || (nk > 1 && nk == nk_plain)));
+    r.apart = (c.in_pitch & 1) && fits && gains;
 
     // The one-launch kernel keeps the coefficients of kRzChunks chunks; wider spans it takes chunk by chunk, each one a
     // round trip, once for every group of rows that needs them.  That pays only while a group spans few rows and the
@@ -83,8 +86,8 @@ inline RzRoute rz_route(const RzCall& c) {
     // -> 55 x 210, 370 x 1081 pixels a group: 84 us, two launches 64; 127 x 1655 47 against 77).
     // It reads a row for every group of outputs that needs it: large images of odd rows that are not taken apart take two launches
     // (16 planes of 2048 rows at a pitch of 2049 -> 228 x 228 97 us, in one 135 and, apart, 159; 3 x 4000 x 4001 -> 444 x 2667 126, 136, 140), but
-    // for odd pitches whose groups are shared, with windows of few chunks or few of them (16 x 5140 x 115 -> 506 x 8 29, 16).
-    const bool odd_rows = !r.apart && !c.even && !((c.in_pitch & 1) && shared && (nk <= 5 || waves <= 2 * c.cu));
+    // for odd pitches whose groups are shared (16 x 5140 x 115 -> 506 x 8 29, in one 16) or have windows of one chunk (16 x 473 x 4430 -> 60 x 4397 118, 88).
+    const bool odd_rows = !r.apart && !c.even && !((c.in_pitch & 1) && (shared || nk == 1));
     // Large enlargements are bound by their stores, of 64-byte runs here and 256-byte runs there (3 x 2048 x 2048 to three
     // times the size 222 us, two launches 170); where rows start inside 128-byte lines neither run is whole (227 against 246).
     const bool line_stores = (double)c.Ho * c.Wo >= 2.0 * c.H * c.W && (int64_t)c.C * c.Ho * c.Wo > (16 << 20) && c.lines;

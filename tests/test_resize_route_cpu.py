@@ -55,6 +55,9 @@ TWO, PLAIN, APART = "two launches", "one launch", "one launch, even and odd rows
     ((16, 3012, 89, 1799, 60, 89), PLAIN), ((16, 5140, 115, 506, 8, 115), PLAIN), ((1, 1266, 1483, 876, 1026, 1483), PLAIN),
     ((1, 8191, 1001, 120, 200, 1001), PLAIN), ((2, 217, 2189, 198, 176, 2189), PLAIN), ((3, 5998, 439, 4068, 297, 439), PLAIN),
     ((8, 2048, 2048, 227, 227, 2049), APART), ((8, 2048, 2048, 512, 512, 2049), APART), ((1, 4095, 4095, 900, 900, 4095), APART),
+    # a round more in large images or with several chunks a window; shared groups with more than one to a unit
+    ((8, 787, 5325, 164, 7830, 5389), APART), ((8, 3907, 465, 659, 78, 465), APART), ((16, 473, 4430, 60, 4397, 4495), PLAIN), ((1, 1611, 2997, 1803, 1624, 2997), APART),
+    ((1, 586, 2559, 67, 4036, 2559), APART), ((16, 4295, 284, 271, 17, 285), PLAIN),
     ((1, 1947, 6281, 214, 690, 6281), APART), ((3, 1912, 2923, 671, 1025, 2923), APART), ((8, 1265, 5731, 221, 1001, 5731), APART),
 ])
 def test_routes_of_odd_pitches(route, call, want):
