@@ -30,7 +30,7 @@ struct SepCall {
 //    memory (8192 x 8192, 16 x 16 / 9 x 45 taps 62 / 66 us, the march 67 / 70, 8190 x 8190, 16 x 16 117 and 125), unless input rows start
 //    between dwords or there are many row tiles a step (8192 x 8192, 9 x 64 taps 75, 72; 8190 x 8190, 9 x 45 132, 125);
 //  - in images of a few rows, most of whose march is the row tiles ahead of the first (16 x 16, 64 taps down 3.7 us and 4.6, 16 x 300000, 9 x 30 taps
-//    9.6 and 10.0; 17 x 128 3.8 and 3.6; 28 x 288, 44 taps 4.0 and 4.4), longer ones where the row is long (17 x 40000, 16 x 16 taps 3.9 and 5.1, 33 x 300000 12.6
+//    9.6 and 10.0; 17 x 128 3.8 and 3.6; 28 x 288, 44 taps 4.0 and 4.4; odd rows 29 x 24, 41 taps 4.0 and 4.6, but 32 x 100 5.5 and 4.8), longer ones where the row is long (17 x 40000, 16 x 16 taps 3.9 and 5.1, 33 x 300000 12.6
 //    and 15.7, 48 x 40000, 9 x 64 taps 6.6 and 7.1, 84 x 27920, 50 taps 7.1 and 8.3, 26 x 31499, 37 taps 5.8 and 7.2; 16 x 16 5.5 and 5.1, 96 x 40000, 9 x 45 8.6 and 7.9);
 //  - with five row tiles a step, where the march's segments are two steps and two workgroups on every unit (1080 x 1920, 9 x 64 taps 7.5 and 7.8);
 //  - in tall narrow images, whose columns leave much of the march's 128 idle, once there is more than a round of its workgroups (12872 x 159, 41 taps 8.1
@@ -38,7 +38,7 @@ struct SepCall {
 inline bool sep_marches(const SepCall& c) {
     const int64_t all = (int64_t)((c.H + 15) / 16) * ((c.W + kSepMarchCols - 1) / kSepMarchCols);
     const bool large = (int64_t)c.H * c.W > kSepMarchShortMax && c.even && c.nt <= (c.lines ? 4 : 3);
-    const int few = c.nt == 5 ? 32 : c.nt == 4 ? (c.even ? 32 : 24) : c.lines ? 16 : 0;
+    const int few = c.nt == 5 ? 32 : c.nt == 4 ? (c.even || c.W <= kSepStrip ? 32 : 24) : c.lines ? 16 : 0;
     const bool wide = c.lines && c.H < sep_wide_rows(c.nt) && c.W > 64 * c.cu;
     // with four or five row tiles a step from more than one round of workgroups on
     const int shallow = c.nt == 5 ? (c.even ? 112 : 56) : c.nt == 4 ? (c.even ? 48 : 32) : 0;
