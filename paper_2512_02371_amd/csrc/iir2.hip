@@ -21,6 +21,7 @@
 
 #include "hb_device.hpp"
 #include "hb_host.hpp"
+#include "iir2_plan.hpp"
 
 namespace hb {
 
@@ -120,7 +121,6 @@ struct IirRun {
     int64_t t0;
     int ch, index, n;
 };
-constexpr int kIirAhead = 4;
 // Runs of fewer than kIirAhead tiles (and single runs), of kIirAhead, of more: the kernels' forms.
 constexpr int kIirShort = 0, kIirEven = 1, kIirLong = 2;
 // The run of wave w and its first tiles.  SHORT: runs that may have fewer than kIirAhead tiles.  The tiles that follow are other
@@ -400,10 +400,9 @@ __global__ void __launch_bounds__(256) iir2_apply_mfma_kernel(IirArgs p) {
 }
 
 // Both in one launch for short signals: a workgroup takes a channel, a wave a run of tiles, and the end states pass through LDS.  One
-// compute unit does all of a channel's work, so this is the faster form only while that is little: see the rule at the
-// launch.  What bounds it: the vector instructions of its 16 waves.  KEPT: runs of up to four tiles keep their products and
+// compute unit does all of a channel's work, so this is the faster form only while that is little (iir_one_launch).
+// What bounds it: the vector instructions of its 16 waves.  KEPT: runs of up to four tiles keep their products and
 // the scans of their blocks in registers from the first pass to the second (1 x 32768 samples 8.5 us with both done twice).
-constexpr int kIirChannelWaves = 16;
 template <bool KEPT>
 __global__ void __launch_bounds__(64 * kIirChannelWaves) iir2_channel_mfma_kernel(IirArgs p) {
     __shared__ __attribute__((aligned(16))) float s_patch[kIirChannelWaves * RowPatch<2>::kFloats];
@@ -633,17 +632,7 @@ static hb_status iir2_run(bool valu, const hb_half* in, float* out, int C, int64
     a.run = a.ntiles <= kIirAhead ? kIirAhead : 1;
     auto round = [&]() { return (int64_t)(a.run < kIirAhead ? 8 : 16) * num_cu() * a.run; };
     while (a.ntiles > (int64_t)kIirMaxRuns * a.run || ((int64_t)C * a.ntiles > round() && a.run < a.ntiles)) a.run *= 2;
-    // A workgroup per channel in one launch, while each has a compute unit to itself: runs of up to four tiles, or eight where
-    // most units have one (T = 2500 .. 16384, 1 to 256 channels 10.2 us, 6.9 so; 32768, 1 / 64 / 256 channels 10.4 / 10.4 / 14.8, 8.4 / 9.0 /
-    // 12.4; 65536, 64 / 100 / 200 channels 10.7 / 14.0 / 21.9, 12.9 / 12.9 / 17.7; 400 x 8192 10.3, 11.9).  One to 16 channels owe
-    // this to the host, which takes 9.4 us for two launches: their kernels, replayed from a graph, take 6.5 us for 32768 samples, this one 7.9.
-    // Signals that start between dwords cost one compute unit more than they cost many: with few channels only up to 38 tiles
-    // (2 / 16 x 18433 8.3 / 8.6 us, two launches 8.6 / 8.8, 16387 7.9 / 8.2 and 8.4 / 8.6, 20001 9.1 / 9.5 and 8.6 / 8.9, 24575 10.6 / 11.0 and 8.6 / 8.8), up to three
-    // tiles a run from a tenth of the units on (31 x 20001 9.6 and 10.8; 24 x 9.6 and 8.6), four from an eighth (32 x 32767 12.0 and 11.4),
-    // and up to eight only from three channels to four units on (160 x 40001 / 50001 16.6 / 18.0 and 18.4 / 20.0, 200 x 18.2 / 21.8 and 18.8 / 20.1).
-    const bool even = aligned_to(in, 4) && (C == 1 || in_pitch % 2 == 0);
-    const int most = C > num_cu() || valu ? 0 : (even ? 2 * C >= num_cu() : 4 * C >= 3 * num_cu()) ? 8 : even || 8 * C >= num_cu() ? 4 : 3;
-    const bool channel = a.ntiles > kIirAhead && a.ntiles <= (most == 3 && 10 * C < num_cu() ? 38 : most * kIirChannelWaves);
+    const bool channel = !valu && iir_one_launch(C, a.ntiles, aligned_to(in, 4) && (C == 1 || in_pitch % 2 == 0), num_cu());
     if (channel) a.run = ceil_div(a.ntiles, kIirChannelWaves);
     a.nruns = (a.ntiles + a.run - 1) / a.run;
     for (int j = 0; j < 7; ++j) {
