@@ -28,7 +28,7 @@ def one_launch(tmp_path_factory):
 # channels, samples, signals that start on whole dwords
 @pytest.mark.parametrize("C,T,even,one", [
     (1, 2048, 1, 0), (1, 2049, 1, 1), (16, 32768, 1, 1), (16, 32769, 1, 0), (256, 65536, 1, 1), (257, 4096, 1, 0),
-    (2, 19456, 0, 1), (2, 19457, 0, 0), (23, 24000, 0, 0), (24, 20001, 0, 0), (24, 22100, 0, 1), (25, 22532, 0, 1), (25, 20480, 0, 0), (25, 24576, 0, 1), (25, 24577, 0, 0),
+    (2, 19456, 0, 1), (2, 19457, 0, 0), (23, 24000, 0, 0), (24, 20001, 0, 0), (24, 22528, 0, 0), (24, 22529, 0, 1), (25, 22532, 0, 1), (25, 21301, 0, 0), (25, 24576, 0, 1), (25, 24577, 0, 0),
     (26, 20001, 0, 1), (31, 24576, 0, 1), (31, 24577, 0, 0), (32, 32767, 0, 1), (191, 40001, 0, 0), (192, 40001, 0, 1),
 ])
 def test_one_launch_or_two(one_launch, C, T, even, one):
