@@ -58,7 +58,8 @@ inline RzRoute rz_route(const RzCall& c) {
     //  - a group per wave costs it a round of workgroups where three to a unit are nearly twice as many as four (1266 x 1483 -> 876 x 1026 7.3 -> 8.9,
     //    16 x 273 x 532 -> 42 x 823 13.0 -> 16), which it is worth with more than one chunk a window (1 x 1611 x 2997 -> 1803 x 1624 19.3 -> 16.0, 3 x 413 x
     //    2815 -> 281 x 858 14.6 -> 11.0), if that is not for the sample further left alone, and in large images (16 x 473 x 4430 -> 60 x 4397 118 -> 88);
-    //  - few windows of many chunks, which the loop for more than four takes, are better off with two launches (16 x 1277 x 1311 -> 180 x 86 43 -> 53);
+    //  - few windows of many chunks, which the loop for more than four takes, are better off with two launches (16 x 1277 x 1311 -> 180 x 86 43 -> 53,
+    //    3 x 3632 x 1409 -> 545 x 145 38 -> 55);
     //  - of shared groups large images gain (8 x 3907 x 465 -> 659 x 78 25 -> 18), others with more than one to a unit (586 x 2559 -> 67 x 4036 16 -> 12),
     //    few waves and small images do not (2 x 600 x 603 -> 40 18.6, 19.2; 217 x 2189 -> 198 x 176 8.2 -> 9.9), nor where half of the windows or more
     //    reach over the row's ends (16 x 4295 x 284 -> 271 x 17 49 -> 55).
@@ -74,7 +75,7 @@ inline RzRoute rz_route(const RzCall& c) {
     bool gains;
     if (shared) gains = inside > 0.54 && (pixels > (6 << 20) || (waves > c.cu && pixels > (1 << 19) && (inside > 0.8 || pixels > (2 << 20)) &&
                                                                  (nk <= 5 || pixels > (1 << 20))));
-    else if (would_be_two && ngx <= 12 && nk > 8) gains = false;
+    else if (would_be_two && ngx <= 12 && nk > 6) gains = false;
     else gains = pixels > (12 << 20) || (inside > 0.5 && (4 * rounds(3) < 7 * rounds(4) || (nk > 1 && nk == nk_plain)));
     r.apart = (c.in_pitch & 1) && fits && gains;
 
@@ -86,8 +87,9 @@ inline RzRoute rz_route(const RzCall& c) {
     // -> 55 x 210, 370 x 1081 pixels a group: 84 us, two launches 64; 127 x 1655 47 against 77).
     // It reads a row for every group of outputs that needs it: large images of odd rows that are not taken apart take two launches
     // (16 planes of 2048 rows at a pitch of 2049 -> 228 x 228 97 us, in one 135 and, apart, 159; 3 x 4000 x 4001 -> 444 x 2667 126, 136, 140), but
-    // for odd pitches whose groups are shared (16 x 5140 x 115 -> 506 x 8 29, in one 16) or have windows of one chunk (16 x 473 x 4430 -> 60 x 4397 118, 88).
-    const bool odd_rows = !r.apart && !c.even && !((c.in_pitch & 1) && (shared || nk == 1));
+    // for odd pitches whose groups are shared (16 x 5140 x 115 -> 506 x 8 29, in one 16) or have windows of one chunk (16 x 473 x 4430 -> 60 x 4397 118, 88, but
+    // 1 x 1101 x 5825 -> 70 x 6899 41, 50).
+    const bool odd_rows = !r.apart && !c.even && !((c.in_pitch & 1) && (shared || (nk == 1 && c.Wo <= c.W)));
     // Large enlargements are bound by their stores, of 64-byte runs here and 256-byte runs there (3 x 2048 x 2048 to three
     // times the size 222 us, two launches 170); where rows start inside 128-byte lines neither run is whole (227 against 246).
     const bool line_stores = (double)c.Ho * c.Wo >= 2.0 * c.H * c.W && (int64_t)c.C * c.Ho * c.Wo > (16 << 20) && c.lines;
