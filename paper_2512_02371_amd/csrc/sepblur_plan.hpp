@@ -34,7 +34,8 @@ struct SepCall {
 //    and 15.7, 48 x 40000, 9 x 64 taps 6.6 and 7.1, 84 x 27920, 50 taps 7.1 and 8.3, 26 x 31499, 37 taps 5.8 and 7.2; 16 x 16 5.5 and 5.1, 96 x 40000, 9 x 45 8.6 and 7.9);
 //  - with five row tiles a step, where the march's segments are two steps and two workgroups on every unit (1080 x 1920, 9 x 64 taps 7.5 and 7.8);
 //  - in tall narrow images, whose columns leave much of the march's 128 idle, once there is more than a round of its workgroups (12872 x 159, 41 taps 8.1
-//    and 10.6, 10773 x 32, 55 taps 5.9 and 7.1, 8629 x 192, 22 taps 6.0 and 6.9; 14921 x 149, 19 taps 8.9 and 10.2; below that 0.7 to 0.9 of the time everywhere).
+//    and 10.6, 10773 x 32, 55 taps 5.9 and 7.1, 8629 x 192, 22 taps 6.0 and 6.9; 14921 x 149, 19 taps 8.9 and 10.2; below that 0.7 to 0.9 of the time everywhere);
+//    beyond 3 M pixels, and in lower images of four row tiles that start inside lines, the march gains again (11097 x 444, 57 taps 14.2 and 11.2, 5177 x 129, 49 taps 8.7 and 7.7).
 inline bool sep_marches(const SepCall& c) {
     const int64_t all = (int64_t)((c.H + 15) / 16) * ((c.W + kSepMarchCols - 1) / kSepMarchCols);
     const bool large = (int64_t)c.H * c.W > kSepMarchShortMax && c.even && c.nt <= (c.lines ? 4 : 3);
@@ -45,7 +46,8 @@ inline bool sep_marches(const SepCall& c) {
     const bool long_rows = c.H <= shallow && 2 * all > (c.nt == 5 || c.even ? 3 : 2) * c.cu;
     const bool pairs = c.lines && c.nt == 5 && all > 3 * c.cu && all <= 4 * c.cu;
     const int64_t strips = (c.W + kSepStrip - 1) / kSepStrip, marched = 4 * ((strips + 3) / 4);
-    const bool idle = c.even && (c.lines || c.nt >= 4) && all > 2 * c.cu && all <= 12 * c.cu && 100 * marched >= (c.nt >= 4 ? 110 : 125) * strips;
+    const bool idle = c.even && (c.lines || c.nt == 5 || (c.nt == 4 && c.H > 6400)) && (int64_t)c.H * c.W <= (11 << 18) && all > (c.nt <= 2 ? 4 : 2) * c.cu &&
+                      all <= 12 * c.cu && 100 * marched >= (c.nt >= 4 ? 110 : 116) * strips;
     return !(large || wide || long_rows || pairs || idle || c.H <= few);
 }
 
