@@ -54,15 +54,16 @@ inline RzRoute rz_route(const RzCall& c) {
     // 1947 x 6281 -> 214 x 690 28.9 -> 18.9; 4095 x 4095 -> 900 45 -> 29; 8 x 787 x 5325 -> 164 x 7830 122 -> 82), but
     //  - only groups whose rows fit T and whose windows lie inside the row; the others take its general loop, with three waves
     //    per SIMD instead of four (16 x 3012 x 89 -> 1799 x 60 11 -> 18, 8 x 5171 x 155 -> 1697 x 54 15 -> 19).  Beyond 12 M pixels the other windows are
-    //    worth it (3 x 5459 x 4520 -> 3329 x 5014);
+    //    worth it (3 x 5459 x 4520 -> 3329 x 5014), if they cost no round as well (16 x 4166 x 311 -> 5190 x 35 30 -> 42);
     //  - a group per wave costs it a round of workgroups where three to a unit are nearly twice as many as four (1266 x 1483 -> 876 x 1026 7.3 -> 8.9,
     //    16 x 273 x 532 -> 42 x 823 13.0 -> 16), which it is worth with more than one chunk a window (1 x 1611 x 2997 -> 1803 x 1624 19.3 -> 16.0, 3 x 413 x
-    //    2815 -> 281 x 858 14.6 -> 11.0), if that is not for the sample further left alone, and in large images (16 x 473 x 4430 -> 60 x 4397 118 -> 88);
+    //    2815 -> 281 x 858 14.6 -> 11.0), if that is not for the sample further left alone, and in large images (1 x 4313 x 3334 -> 1434 x 1108 32 -> 23);
     //  - few windows of many chunks, which the loop for more than four takes, are better off with two launches (16 x 1277 x 1311 -> 180 x 86 43 -> 53,
     //    3 x 3632 x 1409 -> 545 x 145 38 -> 55);
     //  - of shared groups large images gain (8 x 3907 x 465 -> 659 x 78 25 -> 18), others with more than one to a unit (586 x 2559 -> 67 x 4036 16 -> 12),
     //    few waves and small images do not (2 x 600 x 603 -> 40 18.6, 19.2; 217 x 2189 -> 198 x 176 8.2 -> 9.9), nor where half of the windows or more
-    //    reach over the row's ends (16 x 4295 x 284 -> 271 x 17 49 -> 55).
+    //    reach over the row's ends (16 x 4295 x 284 -> 271 x 17 49 -> 55), or long windows have no more rows than the 32 that one wave takes at a time (603 x 5703 ->
+    //    425 x 448 12.5 -> 16).
     // Of 6215 random calls of odd pitches one in a hundred is more than 8 % slower so than the better way.
     const bool would_be_two = pixels > (6 << 20) && span_y > 120;         // of odd rows, see below
     const double rows = span(16 * (r.groups > 1 ? r.groups : 1), c.H, c.Ho, c.band_y) - 1;
@@ -73,10 +74,11 @@ inline RzRoute rz_route(const RzCall& c) {
     const int64_t wgs = r.groups ? (int64_t)c.C * ngx * ((groups + 4 * r.groups - 1) / (4 * r.groups)) : waves;
     const auto rounds = [&](int per_cu) { return (wgs + per_cu * c.cu - 1) / (per_cu * c.cu); };
     bool gains;
-    if (shared) gains = inside > 0.54 && (pixels > (6 << 20) || (waves > c.cu && pixels > (1 << 19) && (inside > 0.8 || pixels > (2 << 20)) &&
-                                                                 (nk <= 5 || pixels > (1 << 20))));
+    if (shared) gains = inside > 0.54 && (rows > 32 || nk <= 4) && (pixels > (6 << 20) || (waves > c.cu && pixels > (1 << 19) && (inside > 0.8 || pixels > (2 << 20)) &&
+                                                                                         (nk <= 5 || pixels > (1 << 20))));
     else if (would_be_two && ngx <= 12 && nk > 6) gains = false;
-    else gains = pixels > (12 << 20) || (inside > 0.5 && (4 * rounds(3) < 7 * rounds(4) || (nk > 1 && nk == nk_plain)));
+    else if (4 * rounds(3) < 7 * rounds(4)) gains = pixels > (12 << 20) || inside > 0.5;
+    else gains = inside > 0.5 && (pixels > (12 << 20) || (nk > 1 && nk == nk_plain));
     r.apart = (c.in_pitch & 1) && fits && gains;
 
     // The one-launch kernel keeps the coefficients of kRzChunks chunks; wider spans it takes chunk by chunk, each one a

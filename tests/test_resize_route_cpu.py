@@ -57,7 +57,7 @@ TWO, PLAIN, APART = "two launches", "one launch", "one launch, even and odd rows
     ((8, 2048, 2048, 227, 227, 2049), APART), ((8, 2048, 2048, 512, 512, 2049), APART), ((1, 4095, 4095, 900, 900, 4095), APART),
     # a round more in large images or with several chunks a window; shared groups with more than one to a unit
     ((8, 787, 5325, 164, 7830, 5389), APART), ((8, 3907, 465, 659, 78, 465), APART), ((16, 473, 4430, 60, 4397, 4495), PLAIN), ((1, 1611, 2997, 1803, 1624, 2997), APART),
-    ((1, 586, 2559, 67, 4036, 2559), APART), ((16, 4295, 284, 271, 17, 285), PLAIN), ((3, 3632, 1409, 545, 145, 1409), TWO), ((1, 1101, 5825, 70, 6899, 5825), TWO),
+    ((1, 586, 2559, 67, 4036, 2559), APART), ((16, 4295, 284, 271, 17, 285), PLAIN), ((1, 603, 5703, 425, 448, 5767), PLAIN), ((16, 4166, 311, 5190, 35, 311), PLAIN), ((3, 3632, 1409, 545, 145, 1409), TWO), ((1, 1101, 5825, 70, 6899, 5825), TWO),
     ((1, 1947, 6281, 214, 690, 6281), APART), ((3, 1912, 2923, 671, 1025, 2923), APART), ((8, 1265, 5731, 221, 1001, 5731), APART),
 ])
 def test_routes_of_odd_pitches(route, call, want):
