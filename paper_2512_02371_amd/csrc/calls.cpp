@@ -1,8 +1,8 @@
 // The usual call of each entry point, marshalled natively: exact torch.Tensor objects in, the library's C function out.
 //
 // On the host a small call costs its launch (3.4 us) and the marshalling: a tensor's strides, sizes, type and address asked for
-// through Python, and ctypes, which converts ten arguments in 1.1 us, took 2.4 us more: hb_fir1d of 256 x 256, 8 taps, call after
-// call 5.1 -> 3.3 us, other short kernels 6.1 .. 6.9 -> 4.7 .. 5.6; calls of more than 7 us have the time anyway.  hb.py comes here first.  A call that is
+// through Python, and ctypes, which converts ten arguments in 1.1 us, take 2 us more: hb_fir1d of 256 x 256, 8 taps, call after
+// call 5.7 -> 4.0 us, other short kernels 5.6 .. 6.0 -> 3.9 .. 4.2; kernels of 6 us and more leave the host the time anyway.  hb.py comes here first.  A call that is
 // anything but usual (another type of tensor, a mode that watches tensor functions, an array of another layout, a wrong shape) is
 // not taken: the function returns False before it has done anything, and hb.py marshals it, with the checks and errors it has.
 #include <pthread.h>

@@ -11,7 +11,8 @@
 //     r + 1 with 0: 48 products each, after which a finished row is rounded to fp16 (RNE) and leaves.  So a pixel is
 //     read from LDS once per horizontal tap, and no wave ever waits for another one.
 //   Image rows (34 pixels x 64 channels each, with the one-pixel halo) stream through a ring of eight rows in LDS that belongs
-//     to the wave: one is in use, seven are on their way.  They arrive by buffer loads that write LDS directly, in the image's
+//     to the wave: one is in use, up to seven are on their way (three to four beside the stores of finished rows, which the counted
+//     waits cannot tell from loads).  They arrive by buffer loads that write LDS directly, in the image's
 //     own order (pixel-major, 128 bytes per pixel) with the eight 16-byte channel pieces of a pixel permuted
 //     by an XOR with bits 1..3 of the pixel index: a row is a few contiguous 1 KB copies, and the
 //     16-byte reads of 16 consecutive pixels at one channel piece still fall into 64 different
@@ -60,7 +61,7 @@ __device__ __forceinline__ int cv_lds_index(int r, int kc, int half, int px) {
 // A strip's rows in LDS, a ring per wave: kCvRing rows of 34 pixels x 128 bytes; channel piece cp (16 bytes) of
 // pixel px sits in slot cp ^ ((px >> 1) & 7) of the pixel's eight.
 constexpr int kCvWaves = 4;
-constexpr int kCvRing = 8;                                // one in use, seven on their way
+constexpr int kCvRing = 8;                                // one in use, up to seven on their way
 constexpr int kCvRowBytes = kCvPx * 128;                  // 4352
 constexpr int kCvRowLoads = 5;                            // of 64 x 16 bytes per row, the last one of 16 lanes
 constexpr int kCvRingBytes = kCvRing * kCvRowBytes;       // 34816 per wave
@@ -99,8 +100,10 @@ template <int LANES>                                      // the first LANES < 3
 __device__ __forceinline__ void cv_dma16_part(u32x4 rsrc, uint32_t voff) {
     asm volatile("s_mov_b64 exec, %2\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds\n\ts_mov_b64 exec, -1" ::"v"(voff), "s"(rsrc), "n"((1 << LANES) - 1) : "memory");
 }
+// At most N memory instructions of this wave are outstanding afterwards, loads and stores together.  Loads are done in their order, so those
+// outstanding are at most the newest N loads, in whatever order the stores are done among them.
 template <int N>
-__device__ __forceinline__ void cv_wait_loads() {         // all but the newest N memory instructions of this wave are done
+__device__ __forceinline__ void cv_wait_loads() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 __device__ __forceinline__ void cv_pin() { __builtin_amdgcn_sched_barrier(0); }
@@ -274,7 +277,7 @@ __global__ void __launch_bounds__(64 * kCvWaves, 1) conv3x3_mfma_kernel(ConvArgs
             if constexpr (j == 14) request(CvInt<4>{});
             if constexpr (j == 16) next_request();
             if constexpr (j == 17) next_row();
-            if constexpr (j == 19) cv_wait_loads<kCvRowLoads * (kCvRing - 1)>();          // row r + 1 is there
+            if constexpr (j == 19) cv_wait_loads<kCvRowLoads * (kCvRing - 1)>();          // row r + 1 is there; with four stores a row, later ones may be waited for too
             if constexpr (j >= 24 && j < 36 && j % 2 == 0) load(0, (j - 24) / 2);
         });
     };
