@@ -5,6 +5,8 @@ import subprocess
 
 import pytest
 
+from test_gpu_fir1d import APART
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PROGRAM = r"""
 #include <stdio.h>
@@ -68,3 +70,10 @@ def test_groups_and_runs_cover_the_image_once(plan):
         assert 32 * nk >= 15 + taps + (1 if lean else anchor & 1) and 32 * nko >= 31 + taps + (1 if lean else anchor & 1), c
         apart += lean
     assert apart > 100
+
+
+def test_the_calls_taken_apart_on_the_gpu_are_of_every_length(plan):
+    every_second = plan([(H, W, W, W, 1, T, a) for H, W, T, a in APART])
+    from_odd = plan([(H, W, W + 3, W + 2, 0, T, a) for H, W, T, a in APART])
+    assert all(p[0] and p[1] == 2 for p in every_second) and all(p[0] and p[1] == 1 for p in from_odd)
+    assert [p[2] for p in every_second] == list(range(1, 10))

@@ -135,3 +135,15 @@ def test_fir1d_even_and_odd_rows_apart(orc, H, W, T, a, extra, offset):
     img, taps, got, obuf = run("hb_fir1d", H, W, T, a, pitch_extra=extra, offset=offset)
     assert_close(got, orc.fir1d(img, taps, a), f"{H}x{W} T={T} pitch+{extra} off {offset}")
     assert np.all(obuf[:, W:] == 7.0), "wrote past the row end"
+
+
+# calls whose odd rows are taken apart, one to nine windows (tests/test_fir1d_plan_cpu.py holds the library to that)
+APART = [(64, 33, 12, 5), (61, 1777, 36, 3), (161, 1055, 80, 19), (68, 113, 100, 50), (33, 49, 130, 64), (60, 333, 160, 80), (200, 1991, 200, 99), (300, 1401, 230, 100), (200, 1971, 256, 128)]
+
+
+@pytest.mark.parametrize("H,W,T,a", APART)
+@pytest.mark.parametrize("extra,offset", [(0, 0), (2, 1)])
+def test_fir1d_rows_apart_of_every_length(orc, H, W, T, a, extra, offset):
+    img, taps, got, obuf = run("hb_fir1d", H, W, T, a, pitch_extra=extra, offset=offset)
+    assert_close(got, orc.fir1d(img, taps, a), f"{H}x{W} T={T} pitch+{extra} off {offset}")
+    assert np.all(obuf[:, W:] == 7.0), "wrote past the row end"
