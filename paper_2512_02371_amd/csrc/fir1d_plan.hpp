@@ -67,7 +67,7 @@ inline FirPlan fir_plan(const FirCall& c) {
     // and the rows fill more than one group.  The coefficients of a walk then wait for its place, which needs rows and runs that hide it.
     // Of 7301 random calls no one is more than 8 % slower so than with plain groups, 34 more than 3 %; 7 miss more than 8 %.
     //  - One window: all but the narrowest (1000 x 32 5 % slower).
-    //  - Two or three: clearly more than a round of waves (1025 x 1012, 18 taps, 1.6 % more, 5.3 against 6.0; 7706 x 512, 41 taps 9.5 -> 6.8 us, 4109 x 465, 35 taps 9.1 -> 8.1, 5547 x 201, 40 taps 8.2 -> 7.3).
+    //  - Two or three: more than a round of waves, with runs of four tiles clearly more (1025 x 1012, 18 taps, 1.6 % more, 5.3 us against 6.0; 7706 x 512, 41 taps 9.5 -> 6.8 us, 4109 x 465, 35 taps 9.1 -> 8.1, 5547 x 201, 40 taps 8.2 -> 7.3).
     //    Within one where the groups, which are of 32 rows in pairs, do not make it two (167 x 11451, 50 taps 5.6 against 6.8): with three
     //    windows always (47 x 3390, 80 taps 6.6 -> 5.9), with two in long rows (356 x 1534, 34 taps 6.2 -> 5.7), or short runs of whole lines
     //    (323 x 832, 40 taps 4.7 -> 4.3; 2222 x 331, 24 taps 5.4 against 5.8, 200 x 501, 40 taps 5.5 and 5.6).
@@ -79,7 +79,7 @@ inline FirPlan fir_plan(const FirCall& c) {
     const int64_t round = 4 * c.cu;
     bool gains;
     if (nk == 1) gains = c.W > 32;
-    else if (nk <= 3) gains = c.W > 48 && (50 * tasks(plain) > 51 * round || (tasks(apart) <= round && (nk == 3 || c.W > 1000 || (c.lines && c.W > 64 && run_tiles(apart) <= 4))));
+    else if (nk <= 3) gains = c.W > 48 && (tasks(plain) > (run_tiles(plain) > 4 ? round : round + round / 50) || (tasks(apart) <= round && (nk == 3 || c.W > 1000 || (c.lines && c.W > 64 && run_tiles(apart) <= 4))));
     else if (nk <= 6) gains = c.W > 48;
     else gains = c.W > 128 && px >= (3 << 17) && 7 * apart <= 8 * plain;
     p.lean = !c.even && room && c.H >= kFirApartRows && gains && c.out_pitch <= ((int64_t)1 << 25);           // 32-bit byte offsets inside a group of 32 rows
