@@ -73,7 +73,7 @@ inline FirPlan fir_plan(const FirCall& c) {
     //    (323 x 832, 40 taps 4.7 -> 4.3; 2222 x 331, 24 taps 5.4 against 5.8, 200 x 501, 40 taps 5.5 and 5.6).
     //  - Four to six: all but the narrowest (68 x 128, 132 taps 7.5 -> 6.4; 6752 x 32, 96 taps 4.7 against 5.2), while the pair of groups that the last rows may
     //    begin leaves the runs about as long as they are (5453 x 3253, 157 taps, two runs a row instead of three 27.5 against 33.7).
-    //  - Seven to nine, which hide least: from 384 K pixels on (1579 x 639, 228 taps 12.3 -> 10.5; 200 x 501, 200 taps 7.1 against 7.4, 5428 x 96, 211 taps 7.5 and
+    //  - Seven to nine, which hide least: from 384 K pixels on (1579 x 639, 228 taps 12.3 -> 10.5, 142 x 7154, 215 taps with runs of six tiles for four 10.6 -> 9.0; 200 x 501, 200 taps 7.1 against 7.4, 5428 x 96, 211 taps 7.5 and
     //    8.2), and not with a third more groups (34 x 11867, 205 taps 7.9 and 8.6).
     const int plain = up(c.H, 16), apart = c.in_pitch % 2 ? 2 * up(c.H, 32) : plain;
     const bool room = up(16 + c.ntaps, 32) == nk && up(32 + c.ntaps, 32) == p.nko;
@@ -81,7 +81,8 @@ inline FirPlan fir_plan(const FirCall& c) {
     bool gains;
     if (nk == 1) gains = c.W > 32;
     else if (nk <= 3) gains = c.W > 48 && (tasks(plain) > (run_tiles(plain) > 4 ? round : round + round / 50) || (tasks(apart) <= round && (nk == 3 || c.W > 1000 || (c.lines && c.W > 64 && run_tiles(apart) <= 4))));
-    else gains = 5 * run_tiles(apart) < 7 * run_tiles(plain) && (nk <= 6 ? c.W > 48 : c.W > 128 && px >= (3 << 17) && 7 * apart <= 8 * plain);
+    else if (nk <= 6) gains = c.W > 48 && 5 * run_tiles(apart) < 7 * run_tiles(plain);
+    else gains = c.W > 128 && px >= (3 << 17) && 7 * apart <= 8 * plain;
     p.lean = !c.even && room && c.H >= kFirApartRows && gains && c.out_pitch <= ((int64_t)1 << 25);           // 32-bit byte offsets inside a group of 32 rows
     p.step = p.lean && c.in_pitch % 2 ? 2 : 1;
     p.rowsteps = p.lean ? apart : plain;

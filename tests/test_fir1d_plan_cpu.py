@@ -46,7 +46,7 @@ def plan(tmp_path_factory):
     (4096, 4096, 4096, 1, 8, 3, 0), (4096, 4096, 4096, 0, 8, 3, 1),            # even rows that start on odd pixels, too
     (6752, 32, 39, 1, 96, 0, 0), (1000, 32, 33, 1, 8, 0, 0), (2222, 331, 331, 1, 24, 11, 0), (5428, 96, 159, 1, 211, 105, 0), (200, 501, 501, 1, 200, 99, 0),     # narrow, small
     (1025, 1012, 1013, 1, 18, 8, 0), (5453, 3253, 3317, 1, 157, 78, 0), (5446, 2942, 2943, 1, 133, 66, 0), (167, 11451, 11451, 1, 50, 6, 0), (48, 31892, 31899, 1, 48, 10, 0), (34, 11867, 11867, 1, 205, 0, 0),       # a round of waves more, a third more groups
-    (7706, 512, 513, 1, 41, 20, 1), (4109, 465, 465, 1, 35, 17, 1), (5547, 201, 201, 1, 40, 19, 1), (6941, 256, 256, 0, 75, 37, 1), (2758, 768, 768, 0, 211, 105, 1),        # tall
+    (142, 7154, 7155, 1, 215, 107, 1), (7706, 512, 513, 1, 41, 20, 1), (4109, 465, 465, 1, 35, 17, 1), (5547, 201, 201, 1, 40, 19, 1), (6941, 256, 256, 0, 75, 37, 1), (2758, 768, 768, 0, 211, 105, 1),        # tall
     (1579, 639, 639, 1, 228, 113, 1), (68, 128, 129, 1, 132, 65, 1), (47, 3390, 3391, 1, 80, 39, 1), (323, 832, 832, 0, 40, 19, 1), (356, 1534, 1535, 1, 34, 16, 1),
 ])
 def test_where_rows_are_taken_apart(plan, H, W, pitch, even, taps, anchor, lean):
